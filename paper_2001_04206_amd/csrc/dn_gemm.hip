@@ -16,17 +16,16 @@
 // instructions pairing k = j (h = 0) with k = 4 + j (h = 1): a lane then needs
 // four consecutive k values of its row, one 128-bit LDS read when the tile is
 // stored k-contiguous.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
 #include "dn_internal.h"
 #include "dn_narrow.h"
+#include "dn_split.h"
 #include "dn_wave.h"
 
 namespace dn {
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float act_fn(int act, float z)
 {
@@ -50,6 +49,7 @@ __device__ __forceinline__ float act_deriv(int act, float a)
 
 template <int BM_, int BN_, int KT_, int WM_, int WN_, int WK_, int R_, int PC_ = 0, int OCC_ = 1, bool PV_ = true>
 struct Tile {
+    static constexpr bool SPLIT = false;
     static constexpr int BM = BM_, BN = BN_, KT = KT_, WM = WM_, WN = WN_, WK = WK_, R = R_;
     static constexpr int PC = PC_;    // peeled k steps that carry the epilogue-operand prefetch (update kernels)
     static constexpr int OCC = OCC_;  // waves per SIMD the register budget must allow
@@ -652,6 +652,378 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g0, float *smem, const
     }
 }
 
+// Work of one workgroup on the tile at (m0, n0) with the products on the f16 matrix instruction (dn_split.h).
+// What bounds it: power.  With both the matrix cores and the vector unit busy the chip lowers its clock to 1.5 - 2.0
+// GHz, so every operand byte moved to LDS and every instruction that splits counts, whether or not it is hidden: at 256
+// x 4096, k = 4096 the operand loads are worth 15 us of 56, the splitting 14, the matrix instructions 8.  Hence the
+// largest tile whose sums fit a wave's registers (64 x 64: 128 registers of sums), operands straight into LDS as fp32
+// (one write and one read of LDS per number) and the split in registers, once per number and tile.  Measured against
+// the fp32 instruction, us: forward 256 x 4096, k = 4096 76 -> 56; delta 80 -> 52; gradient + momentum update 4096 x
+// 4096, k = 256 104 -> 71; forward 2048 x 1024, k = 1024 40 -> 27; 301 x 777, k = 1021 (odd widths) 31 -> 11.
+// (Six bf16 products on three-way splits, which need no scales, were slower than the fp32 instruction: 82 us for the
+// first of these.)
+template <class T, bool A_KC, bool B_KC, int EPI, bool FAST>
+__device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, const int m0, const int n0, const int tile_id,
+                                           const int split)
+{
+    constexpr int BM = T::BM, BN = T::BN, KT = T::KT, NT = T::NT, WK = T::WK, TM = T::TM, TN = T::TN;
+    constexpr bool IS_GRAD = EPI >= EPI_GRAD_STORE;
+    GemmArgs g = g0;
+    if (g0.sk > 1) {
+        const int per = (((g0.K + KT - 1) / KT) + g0.sk - 1) / g0.sk * KT;
+        const int kb = split * per;
+        g.A = A_KC ? g0.A + kb : g0.A + (size_t)kb * g0.lda;
+        g.B = B_KC ? g0.B + kb : g0.B + (size_t)kb * g0.ldb;
+        g.K = min(per, g0.K - kb);
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int idx = lane & 31, h = lane >> 5;
+    const int wk = wave / (T::WM * T::WN);
+    const int wm = (wave % (T::WM * T::WN)) / T::WN, wn = wave % T::WN;
+    const int nk = (g.K + KT - 1) / KT;
+    const int rows_a = g.M - m0, rows_b = g.N - n0;
+    const float *tile_a = A_KC ? g.A + (size_t)m0 * g.lda : g.A + m0;
+    const float *tile_b = B_KC ? g.B + (size_t)n0 * g.ldb : g.B + n0;
+    const size_t kstep_a = A_KC ? (size_t)KT : (size_t)KT * g.lda, kstep_b = B_KC ? (size_t)KT : (size_t)KT * g.ldb;
+    char *lds_a = reinterpret_cast<char *>(smem);
+
+    v16f acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    float bs[TM];   // GRAD: this lane's part of the column sums of Delta
+#pragma unroll
+    for (int i = 0; i < TM; ++i) bs[i] = 0.f;
+    {
+        using SA = Slice<A_KC, BM>;
+        using SB = Slice<B_KC, BN>;
+        constexpr int LOADS = SA::Q + SB::Q;
+        char *own = lds_a + wave * 2 * T::STAGE;   // A's slice, then B's; twice
+        const unsigned own_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)own;
+        const int nsl = (g.K + 15) / 16, mine = nsl > wave ? (nsl - wave + WK - 1) / WK : 0;   // slices of this wave
+        unsigned at_a[TM][2], at_b[TN][2];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) SA::read_at(at_a[i], i, idx, h);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) SB::read_at(at_b[j], j, idx, h);
+        const float *sl_a = A_KC ? tile_a + 16 * wave : tile_a + (size_t)(16 * wave) * g.lda;
+        const float *sl_b = B_KC ? tile_b + 16 * wave : tile_b + (size_t)(16 * wave) * g.ldb;
+        v4f xa[TM][2], xb[TN][2];        // a slice in fp32
+        // Row r's numbers enter as 2^e x; a lane holds the exponent of its row (column) of every block, as the factor and
+        // as the largest number that still fits.
+        float scale_a[TM], scale_b[TN], room_a[TM], room_b[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) scale_a[i] = 1.f, room_a[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) scale_b[j] = 1.f, room_b[j] = 0.f;
+        v16f small[TM][TN];   // the sum of h l' + l h', 2^11 times its share
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) small[i][j][r] = 0.f;
+        auto read_slice = [&](int buf) {
+            const unsigned base = own_at + buf * T::STAGE;
+            read_blocks<A_KC, BM>(xa, base, at_a);
+            read_blocks<B_KC, BN>(xb, base + BM * 64, at_b);
+        };
+        auto contract = [&] {
+            v8h fa[TM][2], fb[TN][2];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) split_eight(xa[i][0], xa[i][1], scale_a[i], fa[i]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) split_eight(xb[j][0], xb[j][1], scale_b[j], fb[j]);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i][0], fb[j][1], small[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i][1], fb[j][0], small[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
+            if (IS_GRAD) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    bs[i] += ((xa[i][0][0] + xa[i][0][1]) + (xa[i][0][2] + xa[i][0][3])) + ((xa[i][1][0] + xa[i][1][1]) + (xa[i][1][2] + xa[i][1][3]));
+            }
+        };
+        auto outgrown = [&] {
+            bool out = false;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) out |= largest(xa[i][0], xa[i][1]) > room_a[i];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) out |= largest(xb[j][0], xb[j][1]) > room_b[j];
+            return __any(out);
+        };
+        // sums 2^shift, the shift of an element being that of its row plus that of its column
+        auto shift_sums = [&](const int (&da)[TM], const int (&db)[TN]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int d = __shfl(da[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        acc[i][j][r] = __builtin_ldexpf(acc[i][j][r], d + db[j]);
+                        small[i][j][r] = __builtin_ldexpf(small[i][j][r], d + db[j]);
+                    }
+                }
+        };
+        // scales that fit the slice in xa, xb; what has been summed so far follows
+        auto rescale = [&] {
+            auto fit = [&](const v4f (&x)[2], float &scale, float &room) {
+                float m = largest(x[0], x[1]);
+                m = fmaxf(m, __shfl_xor(m, 32, 64));   // the other lane of the row
+                if (!(m > room && m < INFINITY)) return 0;
+                const int e = 12 - max(__builtin_amdgcn_frexp_expf(m), -100);   // scale m is in [2^11, 2^12)
+                const int d = room > 0.f ? e - (__builtin_amdgcn_frexp_expf(scale) - 1) : 0;
+                scale = __builtin_ldexpf(1.f, e);
+                room = __builtin_ldexpf(1.f, 15 - e);
+                return d;
+            };
+            int da[TM], db[TN];
+            bool moved = false;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) da[i] = fit(xa[i], scale_a[i], room_a[i]), moved |= da[i] != 0;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) db[j] = fit(xb[j], scale_b[j], room_b[j]), moved |= db[j] != 0;
+            if (__any(moved)) shift_sums(da, db);
+        };
+        // pieces of four from aligned addresses, slices wholly inside k: straight into LDS
+        int it = 0;
+        const int whole = !g.vec ? 0 : (g.K / 16) > wave ? (g.K / 16 - wave + WK - 1) / WK : 0;
+        if (whole > 0) {
+            unsigned off_a[SA::Q], off_b[SB::Q];
+            SA::offsets(off_a, g.lda, rows_a, lane);
+            SB::offsets(off_b, g.ldb, rows_b, lane);
+            auto fetch = [&](int t, int buf) {
+                SA::fetch(sl_a + (size_t)t * kstep_a, off_a, own + buf * T::STAGE);
+                SB::fetch(sl_b + (size_t)t * kstep_b, off_b, own + buf * T::STAGE + BM * 64);
+            };
+            // wait for slice t (the one behind it may still travel), read it, and send for the one two behind
+            auto take = [&](int t, int buf) {
+                if (t + 1 < whole) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                read_slice(buf);
+                if (t + 2 < whole) fetch(t + 2, buf);
+            };
+            fetch(0, 0);
+            if (whole > 1) fetch(1, 1);
+            for (; it < whole; ++it) {
+                take(it, it & 1);
+                if (outgrown()) rescale();
+                contract();
+            }
+        }
+        if (it < mine) {   // through registers: odd widths, and the last k
+            v4f va[SA::Q], vb[SB::Q];
+            auto load = [&](int t) {
+                SA::load(va, sl_a + (size_t)t * kstep_a, g.lda, rows_a, g.K - 16 * (wave + t * WK), lane);
+                SB::load(vb, sl_b + (size_t)t * kstep_b, g.ldb, rows_b, g.K - 16 * (wave + t * WK), lane);
+            };
+            constexpr bool AHEAD = TM * TN < 4;   // the large tile has no registers to spare
+            if (AHEAD) load(it);
+            for (; it < mine; ++it) {
+                if (!AHEAD) load(it);
+                SA::put(own, va, lane);
+                SB::put(own + BM * 64, vb, lane);
+                read_slice(0);
+                if (AHEAD && it + 1 < mine) load(it + 1);
+                if (outgrown()) rescale();
+                contract();
+            }
+        }
+        int back_a[TM], back_b[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) back_a[i] = 1 - __builtin_amdgcn_frexp_expf(scale_a[i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) back_b[j] = 1 - __builtin_amdgcn_frexp_expf(scale_b[j]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int d = __shfl(back_a[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j][r] = __builtin_ldexpf(__builtin_fmaf(small[i][j][r], 0x1p-11f, acc[i][j][r]), d + back_b[j]);
+            }
+        __syncthreads();
+    }
+
+    // An infinite operand has no finite rest: h l' + ... is then NaN where the fp32 product may be infinite.  A wave that finds such a sum contracts its blocks again on the fp32 matrix
+    // instruction, straight from memory.
+    float probe = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
+    if (__any(probe != 0.f)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int t = 0; t < nk; ++t)
+            for (int kk = wk; kk < KT / 16; kk += WK)
+                for (int c = 0; c < 16; c += 2) {
+                    const int k = t * KT + kk * 16 + c + h;
+                    float a[TM], b[TN];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int r = m0 + wm * T::WTM + i * 32 + idx;
+                        a[i] = (r < g.M && k < g.K) ? (A_KC ? g.A[(size_t)r * g.lda + k] : g.A[(size_t)k * g.lda + r]) : 0.f;
+                    }
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int r = n0 + wn * T::WTN + j * 32 + idx;
+                        b[j] = (r < g.N && k < g.K) ? (B_KC ? g.B[(size_t)r * g.ldb + k] : g.B[(size_t)k * g.ldb + r]) : 0.f;
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+                }
+    }
+
+    if constexpr (IS_GRAD) {
+        if (n0 == 0) {   // bias gradient: the threads' sums over their k values, in a fixed order
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                bs[i] += __shfl_xor(bs[i], 32, 64);
+                if (h == 0) smem[wave * BM + i * 32 + idx] = bs[i];
+            }
+            __syncthreads();
+            if (tid < BM && tid < rows_a) {
+                float bsum = 0.f;
+#pragma unroll
+                for (int w = 0; w < WK; ++w) bsum += smem[w * BM + tid];
+                narrow_apply(g.mode, g.scale, g.mu, bsum, g.gb + m0 + tid, g.vb + m0 + tid);
+            }
+            __syncthreads();
+        }
+    }
+
+    // The wave groups' partial tiles meet in LDS, [wk][row][BN]; every thread then holds E quads of four adjacent
+    // columns and finishes them with 16-byte accesses.
+    constexpr int QUADS = BM * BN / 4, E = (QUADS + NT - 1) / NT;
+    auto spare = [&](int f) { return QUADS % NT != 0 && f >= QUADS; };   // more threads than quads
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                smem[(wk * BM + wm * T::WTM + i * 32 + 8 * (r / 4) + 4 * h + (r % 4)) * BN + wn * T::WTN + j * 32 + idx] = acc[i][j][r];
+    __syncthreads();
+    v4f sum[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int f = tid + e * NT, rl = f / (BN / 4), cl = (f % (BN / 4)) * 4;
+        if (spare(f)) { sum[e] = (v4f){0.f, 0.f, 0.f, 0.f}; continue; }
+        sum[e] = *reinterpret_cast<const v4f *>(smem + rl * BN + cl);
+#pragma unroll
+        for (int w = 1; w < WK; ++w) sum[e] += *reinterpret_cast<const v4f *>(smem + (w * BM + rl) * BN + cl);
+    }
+    if (g0.sk > 1) {   // k split across workgroups: as in gemm_tile
+        constexpr int WS = E * 4 * NT;   // floats of a partial tile in the workspace
+        float *mine = g0.ws + ((size_t)tile_id * g0.sk + split) * WS;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                __hip_atomic_store(&mine[(e * 4 + q) * NT + tid], sum[e][q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drain_device_scope_stores();
+        __syncthreads();
+        int *s_last = reinterpret_cast<int *>(smem);
+        if (tid == 0) {
+            const unsigned old = __hip_atomic_fetch_add(&g0.counters[tile_id], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *s_last = (old == (unsigned)(g0.sk - 1)) ? 1 : 0;
+        }
+        __syncthreads();
+        if (*s_last == 0) return;
+        if (tid == 0) __hip_atomic_store(&g0.counters[tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int e = 0; e < E; ++e) sum[e] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int sp = 0; sp < g0.sk; ++sp) {
+            const float *src = g0.ws + ((size_t)tile_id * g0.sk + sp) * WS;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    sum[e][q] += __hip_atomic_load(&src[(e * 4 + q) * NT + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    constexpr bool IN_PLACE = EPI == EPI_DELTA || EPI >= EPI_GRAD_SGD, VEL = EPI == EPI_GRAD_MOMENTUM;
+    constexpr int CH = E < 4 ? E : 4;
+    const float *src_w = EPI == EPI_DELTA ? g.aux : g.C;
+#pragma unroll
+    for (int e0 = 0; e0 < E; e0 += CH) {
+        v4f w[CH], v[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int f = tid + (e0 + c) * NT, row = m0 + f / (BN / 4), col = n0 + (f % (BN / 4)) * 4;
+            const size_t o = (size_t)row * g.ldc + col;
+            if (spare(f) || (!FAST && (row >= g.M || col >= g.N))) continue;
+            if (FAST || col + 4 <= g.N) {
+                if (IN_PLACE) w[c] = *reinterpret_cast<const v4f_a4 *>(src_w + o);
+                if (VEL) v[c] = *reinterpret_cast<const v4f_a4 *>(g.V + o);
+                if (EPI == EPI_FWD) w[c] = *reinterpret_cast<const v4f_a4 *>(g.bias + col);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (IN_PLACE) w[c][q] = col + q < g.N ? src_w[o + q] : 0.f;
+                    if (VEL) v[c][q] = col + q < g.N ? g.V[o + q] : 0.f;
+                    if (EPI == EPI_FWD) w[c][q] = col + q < g.N ? g.bias[col + q] : 0.f;
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int f = tid + (e0 + c) * NT, row = m0 + f / (BN / 4), col = n0 + (f % (BN / 4)) * 4;
+            const size_t o = (size_t)row * g.ldc + col;
+            if (spare(f) || (!FAST && (row >= g.M || col >= g.N))) continue;
+            v4f out, vel;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float s = sum[e0 + c][q];
+                if (EPI == EPI_FWD) out[q] = act_fn(g.act, s + w[c][q]);
+                else if (EPI == EPI_DELTA) out[q] = s * act_deriv(g.act, w[c][q]);
+                else if (EPI == EPI_GRAD_STORE) out[q] = s * g.scale;
+                else {
+                    vel[q] = (VEL ? g.mu * v[c][q] : 0.f) - g.scale * s;
+                    out[q] = w[c][q] + vel[q];
+                }
+            }
+            constexpr bool KEEP = EPI == EPI_GRAD_SGD_KEEPV || VEL;
+            if (FAST || col + 4 <= g.N) {
+                *reinterpret_cast<v4f_a4 *>(g.C + o) = out;
+                if (KEEP) *reinterpret_cast<v4f_a4 *>(g.V + o) = vel;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (col + q < g.N) {
+                        g.C[o + q] = out[q];
+                        if (KEEP) g.V[o + q] = vel[q];
+                    }
+            }
+        }
+    }
+}
+
 // The tile (and k split) a workgroup takes, and its work.  `block` counts the workgroups of this
 // product from zero.  Workgroups are dealt round-robin to the 8 XCDs; each XCD gets a contiguous
 // run of tiles so that tiles sharing operand panels meet in one L2.  Tiles are ordered in groups of
@@ -675,7 +1047,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, float *smem, int t
     const int gn = min(GN, tiles_n - group * GN);
     const int tm = r / gn, tn = group * GN + (r - tm * gn);
     const int m0 = tm * T::BM, n0 = tn * T::BN;
-    if (VEC && m0 + T::BM <= g.M && n0 + T::BN <= g.N)
+    if constexpr (T::SPLIT) {
+        if (m0 + T::BM <= g.M && n0 + T::BN <= g.N)
+            split_tile<T, A_KC, B_KC, EPI, true>(g, smem, m0, n0, v, split);
+        else
+            split_tile<T, A_KC, B_KC, EPI, false>(g, smem, m0, n0, v, split);
+    } else if (VEC && m0 + T::BM <= g.M && n0 + T::BN <= g.N)
         gemm_tile<T, A_KC, B_KC, EPI, VEC, VEC>(g, smem, m0, n0, v, split);
     else
         gemm_tile<T, A_KC, B_KC, EPI, VEC, false>(g, smem, m0, n0, v, split);
@@ -747,9 +1124,24 @@ __global__ __launch_bounds__(T::NT, T::OCC) void gemm_multi_grad_kernel(MultiGra
 template <class T, bool A_KC, bool B_KC>
 constexpr size_t smem_bytes()
 {
+    if constexpr (T::SPLIT) {
+        constexpr size_t out = sizeof(float) * (size_t)T::WK * T::BM * T::BN;
+        return T::BYTES > out ? T::BYTES : out;
+    } else {
     constexpr int stage = Lds<A_KC, T::BM, T::KT>::FLOATS + Lds<B_KC, T::BN, T::KT>::FLOATS;
     constexpr int red = (T::WK > 1) ? (T::WK / 2) * T::BM * T::BN : 0;
     return sizeof(float) * (size_t)((2 * stage > red) ? 2 * stage : red);
+    }
+}
+
+// Both operands in 16-byte pieces: contiguous extent and leading dimension multiples of 4, 16-byte aligned (and rows
+// short enough for 32-bit byte offsets inside a tile).
+template <bool A_KC, bool B_KC>
+static bool vec_pieces(const GemmArgs &a)
+{
+    const bool a_vec = (a.lda % 4 == 0) && ((A_KC ? a.K : a.M) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0);
+    const bool b_vec = (a.ldb % 4 == 0) && ((B_KC ? a.K : a.N) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0);
+    return a_vec && b_vec && a.lda <= 1 << 23 && a.ldb <= 1 << 23;
 }
 
 template <class T, bool A_KC, bool B_KC, int EPI, bool VEC>
@@ -760,12 +1152,13 @@ static hipError_t launch_vec(const GemmArgs &a, hipStream_t stream)
     // Few output tiles and a long k: split k across workgroups until about two per CU are busy.
     GemmArgs b = a;
     b.sk = 1;
+    b.vec = vec_pieces<A_KC, B_KC>(a);
     if (EPI <= EPI_DELTA && a.ws && a.counters && nt < 256 && nt <= a.n_counters) {
         const int nk = (a.K + T::KT - 1) / T::KT;
         int sk = (int)(256 / nt);
         if (sk > 16) sk = 16;
         if (sk > nk / 2) sk = nk / 2;          // at least two k steps each
-        while (sk > 1 && (size_t)nt * sk * T::BM * T::BN > a.ws_floats) --sk;
+        while (sk > 1 && (size_t)nt * sk * std::max(T::BM * T::BN, 4 * T::NT) > a.ws_floats) --sk;
         if (sk > 1) {
             const int per = (nk + sk - 1) / sk;
             sk = (nk + per - 1) / per;         // no empty splits
@@ -804,23 +1197,32 @@ using V10 = Tile<64, 64, 32, 2, 2, 2, 2, 0, 2>;   // weight gradients over long 
 using V11 = Tile<64, 64, 16, 2, 2, 1, 2, 8, 3>;   // as V9 with three workgroups per CU: the momentum update then needs no register spills
 using V12 = Tile<32, 32, 64, 1, 1, 4, 2, 0, 3>;   // batch x width products beside a weight gradient in one launch: 256 threads like V11
 
+//                 BM  BN WK OCC
+using S0 = SliceTile<64, 64, 4, 2>;   // two workgroups on a compute unit
+using S1 = SliceTile<32, 64, 8, 2>;
+using S2 = SliceTile<32, 32, 8, 4>;
+using S3 = SliceTile<64, 64, 2, 2>;   // large weight gradients over a short k: fewer partial tiles to add
+using S4 = SliceTile<32, 32, 4, 4>;   // as S2 with 256 threads: beside a narrow layer's gradient in one launch
+
 static const char *kVariantNames[] = {"128x128x16_r1",  "128x64x16_r2",   "64x64x64_k4_r2", "64x64x32_k4_r2",
                                       "32x64x32_k4_r2", "32x64x64_k8_r2", "32x32x64_k8_r2", "128x128x16_r2_pc16",
                                       "128x64x16_r2_pc16_o2", "64x64x16_r2_pc8_o4", "64x64x32_k2_r2_o2", "64x64x16_r2_pc8_o3",
-                                      "32x32x64_k4_r2_o3"};
-constexpr int kVariants = 13;
+                                      "32x32x64_k4_r2_o3", "slice_64x64_k4", "slice_32x64_k8",
+                                      "slice_32x32_k8", "slice_64x64_k2"};
+constexpr int kVariants = 17;
 int gemm_variant_count() { return kVariants; }
 const char *gemm_variant_name(int v) { return (v >= 0 && v < kVariants) ? kVariantNames[v] : "?"; }
 
 template <class T, bool A_KC, bool B_KC, int EPI>
 static hipError_t launch_one(const GemmArgs &a, hipStream_t stream)
 {
-    const bool a_vec = (a.lda % 4 == 0) && ((A_KC ? a.K : a.M) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0);
-    const bool b_vec = (a.ldb % 4 == 0) && ((B_KC ? a.K : a.N) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0);
-    if (a_vec && b_vec) return launch_vec<T, A_KC, B_KC, EPI, true>(a, stream);
+    if constexpr (T::SPLIT) return launch_vec<T, A_KC, B_KC, EPI, true>(a, stream);
+    else {
+    if (vec_pieces<A_KC, B_KC>(a)) return launch_vec<T, A_KC, B_KC, EPI, true>(a, stream);
     // operands that cannot be loaded as float4 (widths not a multiple of 4) are small in
     // practice: one tile shape serves them all
     return launch_vec<V4, A_KC, B_KC, EPI, false>(a, stream);
+    }
 }
 
 template <class T>
@@ -841,42 +1243,45 @@ static hipError_t launch_kind(GemmKind kind, const GemmArgs &a, hipStream_t stre
     }
 }
 
-// Tile shape from the problem shape: prefer the largest tile that still gives every CU
-// (256 of them) at least one workgroup; outputs with few tiles use small tiles whose waves
-// split k among themselves.
+static bool vec_ok(GemmKind kind, const GemmArgs &a)
+{
+    return kind == GEMM_FWD ? vec_pieces<true, true>(a) : kind == GEMM_DELTA ? vec_pieces<true, false>(a) : vec_pieces<false, false>(a);
+}
+
+// Sums of fewer terms than this stay on the fp32 instruction: an operand of the split kernels keeps 22 to 23 bits, which
+// only counts while the sum itself is rounded a few times (error against 64 bits, split / fp32: k = 37 9.4e-8 /
+// 7.0e-8, k = 77 9.8e-8 / 9.0e-8, k = 128 1.0e-7 / 2.0e-7, k = 1024 1.2e-7 / 2.9e-7, k = 4096 2.2e-7 / 8.1e-7).
+constexpr int kSplitMinK = 96;
+
+// A large weight gradient over a short k: few slices a wave, so the partial tiles of two waves instead of four
+// (4096 x 4096, k = 256 with momentum: 71 us against 83; 1024 x 1024, k = 512, which has 256 tiles: 16.6 against 11.8).
+static bool large_short_grad(long tiles64, int k) { return tiles64 >= 1024 && k <= 384; }
+
+// Tile shape from the problem shape.
+// Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
+// compute units have one, or, for a long k, once k split across workgroups gives them one; below that smaller tiles
+// keep more units busy.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 56 / 62 / 76; 2048 x
+// 1024, k 1024: 27 / 39 / 41; 256 x 1000, k 4096: 21.0 / 21.0 / 20.4; 512 x 1024, k 1024: 13.8 / 10.9 / 12.5; 128 x
+// 1024, k 1024: 12.4 / 8.9 / 7.7; gradients 1024 x 1024, k 512: 11.8 / 14.7 / 14.3; k 128: 7.2 / 9.5 / 9.4.  Operands
+// read through registers (odd widths) do without the middle shape: 301 x 777, k 1021: 16.8 / 14.7 / 10.8.
+// fp32 instruction: 64x64 tiles at several workgroups per CU let one workgroup's prologue / epilogue traffic run under
+// another's matrix work; outputs with few tiles use small tiles whose waves split k among themselves.
 static int pick_variant(GemmKind kind, const GemmArgs &a)
 {
     auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    // 64x64 tiles at several workgroups per CU let one workgroup's prologue / epilogue traffic run
-    // under another's matrix work.  Weight gradients (read-modify-write epilogue): the k = batch
-    // loop is short, so the epilogue operands are prefetched in chunks (variant 11: three
-    // workgroups per CU, whose register budget holds the prefetched W and velocity without
-    // spills; variant 9, four per CU, spills and is ~6 % slower); over a long k (large batches)
-    // two wave groups split each k step instead (variant 10).  Forward and delta products always
-    // have a long k.
-    if (kind == GEMM_GRAD && tiles(64, 64) >= 256) return a.K > 512 ? 10 : 11;
-    if (kind != GEMM_GRAD && tiles(64, 64) >= 256) return 10;
-    // fewer tiles over a long k: the same tile with k split across workgroups (256 x 1000 x 4096:
-    // 31 us against 38 us for 32x32 tiles whose eight waves split k)
-    if (kind != GEMM_GRAD && a.ws && tiles(64, 64) >= 64 && a.K >= 2048) return 10;
-    if (a.K <= 512 && tiles(128, 128) >= 256) return a.K >= 192 ? 7 : 0;
-    if (tiles(128, 64) >= 256) return 1;
+    const long t64 = tiles(64, 64);
+    if (a.K >= kSplitMinK) {
+        if (kind == GEMM_GRAD && large_short_grad(t64, a.K)) return 16;
+        if (t64 >= (kind == GEMM_GRAD ? 128 : 192)) return 13;
+        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 13;
+        return tiles(32, 64) >= 192 && vec_ok(kind, a) ? 14 : 15;
+    }
+    if (t64 >= 256) return kind == GEMM_GRAD ? 11 : 10;
     if (tiles(32, 64) > 256) return 4;
-    // few output tiles: 32 x 32 tiles whose waves split k.  Four waves at up to three workgroups per
-    // CU (variant 12) measured 3-5 % faster than eight waves at one (variant 6) on batch x 1024 x 1024
-    // forward / delta products for batches of 32 to 512; weight gradients keep the older choice
     return kind != GEMM_GRAD ? 12 : 6;
 }
 
 // ---- a delta product and a narrow layer's gradient in one launch ---------------------------
-static bool vec_ok(GemmKind kind, const GemmArgs &a)
-{
-    const bool a_kc = kind != GEMM_GRAD, b_kc = kind == GEMM_FWD;
-    const bool a_vec = (a.lda % 4 == 0) && ((a_kc ? a.K : a.M) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0);
-    const bool b_vec = (a.ldb % 4 == 0) && ((b_kc ? a.K : a.N) % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0);
-    return a_vec && b_vec;
-}
-
 // Whether launch_delta_with_narrow_grad takes this pair: a narrow layer's gradient (dense operands,
 // 16-byte pieces) beside a moderate batch x width delta product through another layer's weights.
 bool delta_narrow_grad_fits(const GemmArgs &delta, const GemmArgs &grad, int variant)
@@ -888,33 +1293,46 @@ bool delta_narrow_grad_fits(const GemmArgs &delta, const GemmArgs &grad, int var
            delta.M <= 512 && delta.K <= 2048;
 }
 
-// The delta product `delta` (through W_{l-1}) and the gradient / update `grad` of a narrow layer l in
-// one launch (they do not depend on each other); call only if delta_narrow_grad_fits.
-hipError_t launch_delta_with_narrow_grad(const GemmArgs &delta, const GemmArgs &grad, hipStream_t stream)
+template <class T>
+static hipError_t launch_delta_narrow_as(const GemmArgs &delta, const GemmArgs &grad, hipStream_t stream)
 {
-    using P0 = Product<V12, true, false, EPI_DELTA>;
+    using P0 = Product<T, true, false, EPI_DELTA>;
     GemmArgs d = delta;
     d.sk = 1;   // the launch has enough workgroups as it is
-    const int tm = (d.M + V12::BM - 1) / V12::BM, tn = (d.N + V12::BN - 1) / V12::BN;
+    d.vec = 1;
+    const int tm = (d.M + T::BM - 1) / T::BM, tn = (d.N + T::BN - 1) / T::BN;
     const long g0 = 8 * (((long)tm * tn + 7) / 8);
     const int nb = grad.N / 4 + 1;
     NarrowGradArgs ng{grad.A, grad.B, grad.C, grad.V, grad.gb, grad.vb, grad.K, grad.M, grad.N, grad.mode, grad.scale, grad.mu};
-    constexpr size_t lds = smem_bytes<V12, true, false>();
+    constexpr size_t lds = smem_bytes<T, true, false>();
     launch_kernel(gemm_narrow_grad_kernel<P0>, dim3((unsigned)(g0 + nb)), dim3(256), lds, stream, d, tm, tn, (int)g0, ng, nb);
     return hipGetLastError();
 }
 
-// ---- the gradients of several layers in one launch ---------------------------------------
-// The shared launch uses one tile shape: the 64 x 64, three-per-CU gradient tile for short
-// contractions (batches up to 512), the 64 x 64 tile whose two wave groups split k for longer ones --
-// the choices pick_variant makes for large weight matrices.
-static bool long_k(const GemmArgs &a) { return a.K > 512; }
-
-static bool multi_grad_layer_fits(const GemmArgs &a, bool family_long_k)
+// The delta product `delta` (through W_{l-1}) and the gradient / update `grad` of a narrow layer l in
+// one launch (they do not depend on each other); call only if delta_narrow_grad_fits.
+hipError_t launch_delta_with_narrow_grad(const GemmArgs &delta, const GemmArgs &grad, hipStream_t stream)
 {
-    // a matrix of at least 64 tiles of 64 x 64, contraction length in the family's range
-    return !narrow_layer(a.M) && vec_ok(GEMM_GRAD, a) && long_k(a) == family_long_k &&
+    return delta.K >= kSplitMinK ? launch_delta_narrow_as<S4>(delta, grad, stream) : launch_delta_narrow_as<V12>(delta, grad, stream);
+}
+
+// ---- the gradients of several layers in one launch ---------------------------------------
+// One tile shape for all layers of the launch (they contract over the same batch): the shape pick_variant takes for
+// large matrices.
+static bool multi_grad_layer_fits(const GemmArgs &a)
+{
+    // a matrix of at least 64 tiles of 64 x 64; the fp32 tile reads it in 16-byte pieces
+    return !narrow_layer(a.M) && (a.K >= kSplitMinK || vec_ok(GEMM_GRAD, a)) &&
            (long)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 64;
+}
+
+static long multi_grad_tiles(const GemmArgs *grads, int n)
+{
+    long tiles = 0;
+    for (int i = 0; i < n; ++i)
+        if (grads[i].mode == grads[0].mode && multi_grad_layer_fits(grads[i]))
+            tiles += (long)((grads[i].M + 63) / 64) * ((grads[i].N + 63) / 64);
+    return tiles;
 }
 
 static bool multi_grad_narrow_fits(const GemmArgs &a)
@@ -953,13 +1371,14 @@ void gemm_grads_plan(const GemmArgs *grads, int n, int variant, bool merge, bool
     int wide = 0, narrow = 0;
     for (int i = 0; i < n; ++i) in_shared[i] = false;
     if (merge && variant < 0) {
-        const bool family = long_k(grads[0]);   // every layer of a backward pass contracts over the same batch
+        // (the narrow layer's gradient needs workgroups of 256 threads)
+        const bool room = grads[0].K <= 512 && !(grads[0].K >= kSplitMinK && large_short_grad(multi_grad_tiles(grads, n), grads[0].K));
         for (int i = 0; i < n; ++i) {
             if (grads[i].mode != grads[0].mode) continue;
-            if (wide < MG_MAX && multi_grad_layer_fits(grads[i], family)) {
+            if (wide < MG_MAX && multi_grad_layer_fits(grads[i])) {
                 in_shared[i] = true;
                 ++wide;
-            } else if (narrow < 1 && !family && multi_grad_narrow_fits(grads[i])) {
+            } else if (narrow < 1 && room && multi_grad_narrow_fits(grads[i])) {
                 in_shared[i] = true;
                 ++narrow;
             }
@@ -991,15 +1410,15 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
             } else {
                 m.g[m.n] = grads[i];
                 m.g[m.n].sk = 1;
+                m.g[m.n].vec = vec_ok(GEMM_GRAD, grads[i]);
                 ++m.n;
             }
         }
-        static_assert(V10::BM == V11::BM && V10::BN == V11::BN, "both families tile the matrices alike");
         long at = 0;
         for (int p = 0; p < m.n; ++p) {
             m.first[p] = (int)at;
-            m.tiles_m[p] = (m.g[p].M + V11::BM - 1) / V11::BM;
-            m.tiles_n[p] = (m.g[p].N + V11::BN - 1) / V11::BN;
+            m.tiles_m[p] = (m.g[p].M + 63) / 64;
+            m.tiles_n[p] = (m.g[p].N + 63) / 64;
             at += 8 * (((long)m.tiles_m[p] * m.tiles_n[p] + 7) / 8);
         }
         m.first[m.n] = (int)at;
@@ -1010,8 +1429,11 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
             at += m.narrow_blocks;
         }
         if (at > 0x7fffffffL) return hipErrorInvalidValue;
-        const hipError_t e = long_k(m.g[0]) ? launch_multi_mode<V10>(m, grads[0].mode, (unsigned)at, stream)
-                                            : launch_multi_mode<V11>(m, grads[0].mode, (unsigned)at, stream);
+        const int k = m.g[0].K;
+        const hipError_t e = k < kSplitMinK ? launch_multi_mode<V11>(m, grads[0].mode, (unsigned)at, stream)
+                             : large_short_grad(multi_grad_tiles(grads, n), k)
+                                 ? launch_multi_mode<S3>(m, grads[0].mode, (unsigned)at, stream)
+                                 : launch_multi_mode<S0>(m, grads[0].mode, (unsigned)at, stream);
         if (e != hipSuccess) return e;
     }
     for (int i = 0; i < n; ++i) {
@@ -1047,6 +1469,10 @@ hipError_t launch_gemm(GemmKind kind, const GemmArgs &a, int variant, hipStream_
     case 10: return launch_kind<V10>(kind, a, stream);
     case 11: return launch_kind<V11>(kind, a, stream);
     case 12: return launch_kind<V12>(kind, a, stream);
+    case 13: return launch_kind<S0>(kind, a, stream);
+    case 14: return launch_kind<S1>(kind, a, stream);
+    case 15: return launch_kind<S2>(kind, a, stream);
+    case 16: return launch_kind<S3>(kind, a, stream);
     default: return hipErrorInvalidValue;
     }
 }

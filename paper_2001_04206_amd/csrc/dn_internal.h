@@ -77,6 +77,7 @@ struct GemmArgs {
     size_t ws_floats;  // capacity of ws
     int n_counters;    // capacity of counters
     int sk;
+    int vec;           // set by the launchers: operands can be read in 16-byte pieces
 };
 
 constexpr size_t GEMM_WS_FLOATS = (size_t)2 << 20;  // 8 MB of partial tiles

@@ -1,0 +1,112 @@
+"""The contraction kernels that split fp32 operands into pairs of f16 numbers (tile shapes 13 to 16): edges of tiles
+and slices, alignment, magnitudes far from one, operands whose magnitude grows along k, infinities and NaN.  Reference:
+the same products in 64 bits; the bound on every element follows from the number of fp32 roundings of its sum, the bits
+an operand keeps, and what rounds away below an operand's largest number."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LINEAR, MSE = 0, 0
+
+
+@pytest.fixture(scope="module")
+def dnlib():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2001_04206_amd import dn
+    return dn
+
+
+def products(dn, X, W, variant):
+    """One linear layer: its outputs X W^T, gradient Delta^T X / B and input gradient Delta W, with the Delta they belong to."""
+    import torch
+    B, K = X.shape
+    N = W.shape[0]
+    net = dn.Net([K, N], [LINEAR], MSE, B)
+    net.dn_set_params(1, W, np.zeros(N, np.float32))
+    net.dn_set_option("gemm_variant", variant)
+    Xd, y = torch.from_numpy(X).cuda(), torch.zeros(B, dtype=torch.int32, device="cuda")
+    out, dX = torch.empty((B, N), device="cuda"), torch.empty((B, K), device="cuda")
+    net.dn_forward(Xd, out)
+    net.dn_backward(y)
+    net.dn_input_gradient(dX)
+    G, g = net.dn_get_grads(1)
+    delta = out.cpu().numpy().copy()
+    delta[:, 0] -= 1.0
+    return out.cpu().numpy(), G, g, dX.cpu().numpy(), delta
+
+
+def close(got, A, B, scale, what):
+    """got against scale * A B in 64 bits.  Three or four roundings of the sum per sixteen terms and one per addition of
+    at most 32 partial sums; 2^-22 per operand; 2^-36 of the largest number of either operand."""
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    k = A.shape[1]
+    big = np.abs(A).max() * np.abs(B).max()
+    bound = ((4 * (k / 16 + 1) + 40) * 2.0 ** -24 + 2.0 ** -21) * (np.abs(A) @ np.abs(B)) + 2.0 ** -36 * k * big
+    err = np.abs(got - scale * (A @ B))
+    assert np.all(err <= abs(scale) * bound + 1e-44), "%s: %g times the bound" % (what, np.max(err / (abs(scale) * bound + 1e-44)))
+
+
+def check(dn, X, W, variant):
+    out, G, g, dX, delta = products(dn, X, W, variant)
+    close(out, X, W.T, 1.0, "forward")
+    close(G, delta.T, X, 1.0 / X.shape[0], "gradient")
+    close(g[:, None], delta.T, np.ones((X.shape[0], 1), np.float32), 1.0 / X.shape[0], "bias gradient")
+    close(dX, delta, W, 1.0, "input gradient")
+
+
+# batch, inputs, outputs: whole tiles; one past and one short of tiles and slices; less than one slice; a long sum that
+# workgroups share; 16-byte pieces that end inside a slice
+SHAPES = [(64, 128, 64), (65, 129, 33), (63, 127, 95), (3, 5, 17), (1, 40, 32), (128, 2064, 96), (70, 2051, 130), (36, 20, 68)]
+
+
+@pytest.mark.parametrize("variant", [13, 14, 15, 16])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_products_match_64_bits(dnlib, shape, variant):
+    B, K, N = shape
+    rng = np.random.default_rng(B * 1000 + K)
+    check(dnlib, rng.standard_normal((B, K), dtype=np.float32), rng.standard_normal((N, K), dtype=np.float32), variant)
+
+
+@pytest.mark.parametrize("variant", [13, 15])
+@pytest.mark.parametrize("sx,sw", [(1e-30, 1e25), (1e30, 1e-30), (1e-20, 1e-10), (3e4, 7e4), (1e-7, 1.0)])
+def test_magnitudes(dnlib, sx, sw, variant):
+    rng = np.random.default_rng(5)
+    X = (rng.standard_normal((66, 260)) * sx).astype(np.float32)
+    W = (rng.standard_normal((70, 260)) * sw).astype(np.float32)
+    check(dnlib, X, W, variant)
+
+
+@pytest.mark.parametrize("variant", [13, 14, 15, 16])
+@pytest.mark.parametrize("order", ["zeros first", "growing", "shrinking", "one large row"])
+def test_magnitude_changes_along_k(dnlib, order, variant):
+    rng = np.random.default_rng(6)
+    X = rng.standard_normal((40, 600)).astype(np.float32)
+    W = rng.standard_normal((72, 600)).astype(np.float32)
+    if order == "zeros first":
+        X[:, :300] = 0.0
+        X[:, 300:] *= np.float32(1e-6)
+    elif order == "one large row":
+        X[7] *= np.float32(1e6)
+    else:
+        steps = np.exp2(np.linspace(-40, 40, 600)).astype(np.float32)
+        X *= steps if order == "growing" else steps[::-1]
+    check(dnlib, X, W, variant)
+
+
+@pytest.mark.parametrize("variant", [13, 14, 15, 16])
+def test_infinities_and_nan(dnlib, variant):
+    rng = np.random.default_rng(7)
+    X = rng.standard_normal((70, 100)).astype(np.float32)
+    W = rng.standard_normal((40, 100)).astype(np.float32)
+    X[3, 10], X[65, 99], X[20, 0], X[5, 50] = np.inf, -np.inf, np.nan, np.float32(3.4e38)
+    W[:, 50] = np.sign(W[:, 50]) * np.float32(0.5)
+    out, G, _, _, _ = products(dnlib, X, W, variant)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = X.astype(np.float64) @ W.astype(np.float64).T
+    assert np.array_equal(np.isnan(out), np.isnan(want)) and np.array_equal(np.isinf(out), np.isinf(want))
+    assert np.array_equal(np.sign(out[[3, 65]]), np.sign(want[[3, 65]]))
+    rows = [r for r in range(70) if r not in (3, 65, 20, 5)]
+    assert np.allclose(out[rows], want[rows], rtol=0, atol=2e-4) and np.allclose(out[5] / want[5], 1.0, rtol=1e-5)
