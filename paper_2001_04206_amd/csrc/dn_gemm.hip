@@ -1255,7 +1255,9 @@ constexpr int kSplitMinK = 96;
 
 // A large weight gradient over a short k: few slices a wave, so the partial tiles of two waves instead of four
 // (4096 x 4096, k = 256 with momentum: 71 us against 83; 1024 x 1024, k = 512, which has 256 tiles: 16.6 against 11.8).
-static bool large_short_grad(long tiles64, int k) { return tiles64 >= 1024 && k <= 384; }
+// Between 640 and 1024 tiles also for a k up to 512: 768 tiles are one and a half rounds of the four-wave tile's 512
+// places but fit the two-wave tile's 1024 at once (three 1024 x 1024 layers at batch 512: a step 103.7 -> 101 us).
+static bool large_short_grad(long tiles64, int k) { return (tiles64 >= 1024 && k <= 384) || (tiles64 >= 640 && k <= 512); }
 
 // Tile shape from the problem shape.
 // Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
