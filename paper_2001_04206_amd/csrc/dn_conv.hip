@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "dn_internal.h"
+#include "dn_split.h"
 #include "dn_wave.h"
 
 namespace dn {
@@ -393,6 +394,240 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
     }
 }
 
+// 3 x 3 filters: the same correlation on the f16 matrix instruction (how a number is split: dn_split.h).  A k slice of an
+// instruction is sixteen input channels at one tap, so a staged number is split once and serves nine taps; that keeps the
+// splitting, which bounds the fully connected products, to a tenth of the work here.  Sixteen channels are staged at a
+// time, both operands as pieces of eight channels (16 bytes, one per plane): the input as [half of the channels][pixel
+// of the patch], the filters as [half, tap][output channel]; every operand of an instruction is then one conflict-free
+// 16-byte LDS read per lane.  One scale for the workgroup's patch and one for its filters, from their largest numbers.
+// Where most numbers of a stage are too small beside its largest one to keep their bits, or a sum is not finite, the
+// outputs are summed again in fp32.
+// Bound: half matrix instructions (384 cycles a tap and compute unit), half LDS reads (256), staging between two
+// workgroups.  128 x 32 x 32 x 32 -> 64 channels, us (fp32 instruction / this): forward and
+// input gradient together 125 / 86.
+template <int OT, int RW, int TW>
+__global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const float *__restrict__ In,
+                                                             const float *__restrict__ Wt, const float *__restrict__ bias,
+                                                             float *__restrict__ Out)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    constexpr int OC = 32 * OT, RPT = 32 / TW, ROWS = 4 * RW * RPT, PROW = ROWS + 2, PCOL = TW + 2, NPIX = PROW * PCOL;
+    constexpr int PPLANE = 2 * NPIX * 16, WPITCH = OC * 16 + 16, WPLANE = 18 * WPITCH;
+    char *pl = reinterpret_cast<char *>(lds), *wl = pl + 2 * PPLANE;
+    float *red = reinterpret_cast<float *>(wl + 2 * WPLANE);   // [0]: stage that needs new scales; then per-wave values
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int idx = lane & 31, h = lane >> 5;
+    const int col_tiles = (s.Wo + TW - 1) / TW;
+    const int i0 = (blockIdx.x / col_tiles) * ROWS, j0 = (blockIdx.x % col_tiles) * TW;
+    const int oc0 = blockIdx.y * OC, b = blockIdx.z;
+    const int r_in0 = i0 - s.pad_h, c_in0 = j0 - s.pad_w;
+    const int plane = s.H * s.W;
+    const float *image = In + (size_t)b * s.Cin * plane;
+    constexpr int XU = (2 * NPIX + 255) / 256, WU = (18 * OC + 255) / 256;   // staged pieces per thread
+    v4f xr[XU][2], wr[WU][2];
+    // (a uniform base per channel and one 32-bit byte offset per piece: the sizes that reach this kernel keep it in range)
+    auto request = [&](int ic0) {
+        const char *xbase = reinterpret_cast<const char *>(image + (size_t)ic0 * plane);
+        const char *wbase = reinterpret_cast<const char *>(Wt + (size_t)ic0 * 9);
+#pragma unroll
+        for (int m = 0; m < XU; ++m) {
+            const int e = tid + 256 * m, half = e >= NPIX ? 1 : 0, pix = e - half * NPIX;
+            const int r = r_in0 + pix / PCOL, c = c_in0 + pix % PCOL, left = s.Cin - ic0 - 8 * half;
+            const bool ok = e < 2 * NPIX && r >= 0 && r < s.H && c >= 0 && c < s.W;
+            const unsigned off = 4u * (unsigned)(8 * half * plane + r * s.W + c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                xr[m][j / 4][j % 4] = (ok && j < left) ? *reinterpret_cast<const float *>(xbase + (size_t)j * plane * 4 + off) : 0.f;
+        }
+#pragma unroll
+        for (int m = 0; m < WU; ++m) {
+            const int e = tid + 256 * m, tap = e % 9, half = (e / 9) & 1, oc = e / 18, left = s.Cin - ic0 - 8 * half;
+            const bool ok = e < 18 * OC && oc0 + oc < s.Cout;
+            const unsigned off = 4u * (unsigned)((oc0 + oc) * s.w_out_stride + 72 * half + tap);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                wr[m][j / 4][j % 4] = (ok && j < left) ? *reinterpret_cast<const float *>(wbase + j * 36 + off) : 0.f;
+        }
+    };
+    v16f acc[OT][RW], small[OT][RW];
+#pragma unroll
+    for (int t = 0; t < OT; ++t)
+#pragma unroll
+        for (int q = 0; q < RW; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][q][r] = small[t][q][r] = 0.f;
+    int exp_x = 0, exp_w = 0;              // operands enter as 2^exp x
+    float room_x = 0.f, room_w = 0.f;      // largest number that fits
+    bool again = false;                    // sum the outputs once more in fp32
+    request(0);
+    for (int ic0 = 0, stage = 1; ic0 < s.Cin; ic0 += 16, ++stage) {
+        float mx = 0.f, mw = 0.f;
+#pragma unroll
+        for (int m = 0; m < XU; ++m) mx = fmaxf(mx, largest(xr[m][0], xr[m][1]));
+#pragma unroll
+        for (int m = 0; m < WU; ++m) mw = fmaxf(mw, largest(wr[m][0], wr[m][1]));
+        if (__any(mx > room_x || mw > room_w) && lane == 0) red[0] = (float)stage;
+        __syncthreads();   // the previous stage has been used; red[0] is set if any thread's numbers have outgrown a scale
+        if (red[0] == (float)stage) {
+            const float wx = wave_max(mx), ww = wave_max(mw);
+            if (lane == 0) { red[4 + wave] = wx; red[8 + wave] = ww; }
+            __syncthreads();
+            const float gx = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7])), gw = fmaxf(fmaxf(red[8], red[9]), fmaxf(red[10], red[11]));
+            int shift = 0;
+            auto fit = [&](float g, int &e, float &room) {
+                if (!(g > room && g < INFINITY)) return;
+                const int fresh = 12 - max(__builtin_amdgcn_frexp_expf(g), -100);   // 2^fresh g is in [2^11, 2^12)
+                if (stage > 1) shift += fresh - e;
+                e = fresh;
+                room = __builtin_ldexpf(1.f, 15 - e);
+            };
+            fit(gx, exp_x, room_x);
+            fit(gw, exp_w, room_w);
+            // numbers of this stage, and those that keep all their bits (down to 2^-25 of the largest)
+            float some_x = 0.f, good_x = 0.f, some_w = 0.f, good_w = 0.f;
+            const float least_x = __builtin_ldexpf(1.f, -14 - exp_x), least_w = __builtin_ldexpf(1.f, -14 - exp_w);
+#pragma unroll
+            for (int m = 0; m < XU; ++m)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float a = fabsf(xr[m][j / 4][j % 4]);
+                    some_x += a > 0.f ? 1.f : 0.f;
+                    good_x += a >= least_x ? 1.f : 0.f;
+                }
+#pragma unroll
+            for (int m = 0; m < WU; ++m)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float a = fabsf(wr[m][j / 4][j % 4]);
+                    some_w += a > 0.f ? 1.f : 0.f;
+                    good_w += a >= least_w ? 1.f : 0.f;
+                }
+            some_x = wave_sum(some_x), good_x = wave_sum(good_x), some_w = wave_sum(some_w), good_w = wave_sum(good_w);
+            if (lane == 0) { red[12 + wave] = 2.f * good_x - some_x; red[16 + wave] = 2.f * good_w - some_w; }
+            __syncthreads();
+            again |= !(gx < INFINITY && gw < INFINITY) || red[12] + red[13] + red[14] + red[15] < 0.f || red[16] + red[17] + red[18] + red[19] < 0.f;
+            if (shift != 0) {
+#pragma unroll
+                for (int t = 0; t < OT; ++t)
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            acc[t][q][r] = __builtin_ldexpf(acc[t][q][r], shift);
+                            small[t][q][r] = __builtin_ldexpf(small[t][q][r], shift);
+                        }
+            }
+        }
+        const float scale_x = __builtin_ldexpf(1.f, exp_x), scale_w = __builtin_ldexpf(1.f, exp_w);
+#pragma unroll
+        for (int m = 0; m < XU; ++m) {
+            const int e = tid + 256 * m;
+            v8h f[2];
+            split_eight(xr[m][0], xr[m][1], scale_x, f);
+            if (e < 2 * NPIX) {
+                *reinterpret_cast<v8h *>(pl + e * 16) = f[0];
+                *reinterpret_cast<v8h *>(pl + PPLANE + e * 16) = f[1];
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < WU; ++m) {
+            const int e = tid + 256 * m, tap = e % 9, half = (e / 9) & 1, oc = e / 18;
+            v8h f[2];
+            split_eight(wr[m][0], wr[m][1], scale_w, f);
+            if (e < 18 * OC) {
+                char *dst = wl + (half * 9 + tap) * WPITCH + oc * 16;
+                *reinterpret_cast<v8h *>(dst) = f[0];
+                *reinterpret_cast<v8h *>(dst + WPLANE) = f[1];
+            }
+        }
+        __syncthreads();
+        if (ic0 + 16 < s.Cin) request(ic0 + 16);
+        __builtin_amdgcn_sched_barrier(0);
+        const char *wa = wl + h * 9 * WPITCH + idx * 16;
+        const char *pb = pl + (h * NPIX + (RW * wave * RPT + idx / TW) * PCOL + idx % TW) * 16;
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int v = 0; v < 3; ++v) {
+                v8h fw[OT][2], fx[RW][2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                    for (int t = 0; t < OT; ++t)
+                        fw[t][p] = *reinterpret_cast<const v8h *>(wa + p * WPLANE + (u * 3 + v) * WPITCH + t * 512);
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+                        fx[q][p] = *reinterpret_cast<const v8h *>(pb + p * PPLANE + ((q * RPT + u) * PCOL + v) * 16);
+                }
+#pragma unroll
+                for (int t = 0; t < OT; ++t)
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+                        small[t][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[t][0], fx[q][1], small[t][q], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < OT; ++t)
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+                        small[t][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[t][1], fx[q][0], small[t][q], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < OT; ++t)
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+                        acc[t][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[t][0], fx[q][0], acc[t][q], 0, 0, 0);
+            }
+    }
+    float probe = 0.f;
+#pragma unroll
+    for (int t = 0; t < OT; ++t)
+#pragma unroll
+        for (int q = 0; q < RW; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[t][q][r] = __builtin_ldexpf(__builtin_fmaf(small[t][q][r], 0x1p-11f, acc[t][q][r]), -exp_x - exp_w);
+                probe = __builtin_fmaf(acc[t][q][r], 0.f, probe);
+            }
+    again |= __any(probe != 0.f) != 0;
+    const int j = j0 + idx % TW;
+    if (j >= s.Wo) return;
+#pragma unroll
+    for (int q = 0; q < RW; ++q) {
+        const int i = i0 + (RW * wave + q) * RPT + idx / TW;
+        if (i >= s.Ho) continue;
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int oc = oc0 + 32 * t + 8 * (r >> 2) + 4 * h + (r & 3);
+                if (oc >= s.Cout) continue;
+                float sum = acc[t][q][r];
+                if (again) {
+                    sum = 0.f;
+                    for (int ic = 0; ic < s.Cin; ++ic)
+                        for (int u = 0; u < 3; ++u)
+                            for (int v = 0; v < 3; ++v) {
+                                const int y = i + u - s.pad_h, x = j + v - s.pad_w;
+                                if (y >= 0 && y < s.H && x >= 0 && x < s.W)
+                                    sum = fmaf(Wt[(size_t)oc * s.w_out_stride + (size_t)(ic * 9 + u * 3 + v)],
+                                               image[(size_t)ic * plane + (unsigned)(y * s.W + x)], sum);
+                            }
+                }
+                Out[(((size_t)b * s.Cout + oc) * s.Ho + i) * s.Wo + j] = conv_act(s.act, sum + (bias ? bias[oc] : 0.f));
+            }
+    }
+}
+
+template <int OT, int RW, int TW>
+hipError_t launch_corr3_split(const CorrShape &s, const float *In, const float *Wt, const float *bias, float *Out, hipStream_t stream)
+{
+    constexpr int rows = 4 * RW * (32 / TW);
+    constexpr size_t lds = 2 * (2 * (rows + 2) * (TW + 2) * 16) + 2 * 18 * (32 * OT * 16 + 16) + 20 * sizeof(float);
+    static_assert(lds <= 64 * 1024, "more dynamic LDS than a launch may ask for without an attribute");
+    const dim3 grid((unsigned)(((s.Ho + rows - 1) / rows) * ((s.Wo + TW - 1) / TW)),
+                    (unsigned)((s.Cout + 32 * OT - 1) / (32 * OT)), (unsigned)s.B);
+    hipLaunchKernelGGL((corr3_split_kernel<OT, RW, TW>), grid, dim3(256), lds, stream, s, In, Wt, bias, Out);
+    return hipGetLastError();
+}
+
 // Wide enough for the matrix-core form?  (Narrow layers would mostly multiply padding.)
 bool corr_mfma_fits(const CorrShape &s)
 {
@@ -427,26 +662,25 @@ hipError_t launch_corr_mfma_as(const CorrShape &s, const float *In, const float 
 hipError_t launch_corr_mfma(const CorrShape &s, const float *In, const float *Wt, const float *bias, float *Out,
                             hipStream_t stream)
 {
-    const bool k3 = s.KH == 3 && s.KW == 3, k5 = s.KH == 5 && s.KW == 5;
-    // 3 x 3: pixel tiles of 16 rows x 16 columns instead of 8 x 32 where they cover the image with less padding
+    const bool k5 = s.KH == 5 && s.KW == 5;
+    // 3 x 3, planes and filter tensors within the split kernel's 32-bit byte offsets
+    const bool split = s.KH == 3 && s.KW == 3 && (long)s.H * s.W <= 1 << 25 && (long)s.Cout * s.w_out_stride <= 1 << 29;
+    // its pixel tiles: 16 rows x 16 columns instead of 8 x 32 where they cover the image with less padding
     const auto padded = [&](int rows, int cols) {
         return (long)((s.Ho + rows - 1) / rows * rows) * ((s.Wo + cols - 1) / cols * cols);
     };
-    const bool narrow = k3 && padded(16, 16) < padded(8, 32);
+    const bool narrow = padded(16, 16) < padded(8, 32);
     // ... and of half the rows when the full tiles would leave CUs without a workgroup
-    const long wg16 = (long)((s.Ho + 15) / 16) * ((s.Wo + 15) / 16) * s.B * ((s.Cout + 63) / 64);
-    const bool small = narrow && wg16 < 512;
-    if (s.Cout > 32) {
-        if (small) return launch_corr_mfma_as<2, 1, 3, 16>(s, In, Wt, bias, Out, stream);
-        if (narrow) return launch_corr_mfma_as<2, 2, 3, 16>(s, In, Wt, bias, Out, stream);
-        if (k5) return launch_corr_mfma_as<2, 2, 5>(s, In, Wt, bias, Out, stream);
-        return k3 ? launch_corr_mfma_as<2, 2, 3>(s, In, Wt, bias, Out, stream)
-                  : launch_corr_mfma_as<2, 2, 0>(s, In, Wt, bias, Out, stream);
+    const bool small = narrow && (long)((s.Ho + 15) / 16) * ((s.Wo + 15) / 16) * s.B * ((s.Cout + 31) / 32) < 256;
+    if (split) {
+        if (small) return launch_corr3_split<1, 1, 16>(s, In, Wt, bias, Out, stream);
+        return narrow ? launch_corr3_split<1, 2, 16>(s, In, Wt, bias, Out, stream)
+                      : launch_corr3_split<1, 2, 32>(s, In, Wt, bias, Out, stream);
     }
-    if (small) return launch_corr_mfma_as<1, 1, 3, 16>(s, In, Wt, bias, Out, stream);
-    if (narrow) return launch_corr_mfma_as<1, 2, 3, 16>(s, In, Wt, bias, Out, stream);
-    if (k5) return launch_corr_mfma_as<1, 2, 5>(s, In, Wt, bias, Out, stream);
-    return k3 ? launch_corr_mfma_as<1, 2, 3>(s, In, Wt, bias, Out, stream)
+    if (s.Cout > 32)
+        return k5 ? launch_corr_mfma_as<2, 2, 5>(s, In, Wt, bias, Out, stream)
+                  : launch_corr_mfma_as<2, 2, 0>(s, In, Wt, bias, Out, stream);
+    return k5 ? launch_corr_mfma_as<1, 2, 5>(s, In, Wt, bias, Out, stream)
               : launch_corr_mfma_as<1, 2, 0>(s, In, Wt, bias, Out, stream);
 }
 
