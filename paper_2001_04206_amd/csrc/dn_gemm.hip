@@ -719,7 +719,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
         for (int i = 0; i < TM; ++i) scale_a[i] = 1.f, room_a[i] = 0.f;
 #pragma unroll
         for (int j = 0; j < TN; ++j) scale_b[j] = 1.f, room_b[j] = 0.f;
-        v16f small[TM][TN];   // the sum of h l' + l h', 2^11 times its share
+        v16f small[TM][TN];   // the sum of h l' + l h', 2^11 times its share (F32: a second sum of the products)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -732,6 +732,23 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
             read_blocks<B_KC, BN>(xb, base + BM * 64, at_b);
         };
         auto contract = [&] {
+            if constexpr (IS_GRAD) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    bs[i] += ((xa[i][0][0] + xa[i][0][1]) + (xa[i][0][2] + xa[i][0][3])) + ((xa[i][1][0] + xa[i][1][1]) + (xa[i][1][2] + xa[i][1][3]));
+            }
+            if constexpr (T::F32) {   // k = q of one half of the lanes with k = 8 + q of the other
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) {
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][0][q], xb[j][0][q], acc[i][j], 0, 0, 0);
+                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][1][q], xb[j][1][q], small[i][j], 0, 0, 0);
+                        }
+                return;
+            }
             v8h fa[TM][2], fb[TN][2];
 #pragma unroll
             for (int i = 0; i < TM; ++i) split_eight(xa[i][0], xa[i][1], scale_a[i], fa[i]);
@@ -752,11 +769,6 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
-            if (IS_GRAD) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    bs[i] += ((xa[i][0][0] + xa[i][0][1]) + (xa[i][0][2] + xa[i][0][3])) + ((xa[i][1][0] + xa[i][1][1]) + (xa[i][1][2] + xa[i][1][3]));
-            }
         };
         auto outgrown = [&] {
             bool out = false;
@@ -822,7 +834,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
             if (whole > 1) fetch(1, 1);
             for (; it < whole; ++it) {
                 take(it, it & 1);
-                if (outgrown()) rescale();
+                if (!T::F32 && outgrown()) rescale();
                 contract();
             }
         }
@@ -840,24 +852,31 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
                 SB::put(own + BM * 64, vb, lane);
                 read_slice(0);
                 if (AHEAD && it + 1 < mine) load(it + 1);
-                if (outgrown()) rescale();
+                if (!T::F32 && outgrown()) rescale();
                 contract();
             }
         }
-        int back_a[TM], back_b[TN];
+        if constexpr (T::F32) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) back_a[i] = 1 - __builtin_amdgcn_frexp_expf(scale_a[i]);
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) back_b[j] = 1 - __builtin_amdgcn_frexp_expf(scale_b[j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
+        } else {
+            int back_a[TM], back_b[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i) back_a[i] = 1 - __builtin_amdgcn_frexp_expf(scale_a[i]);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int d = __shfl(back_a[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
+            for (int j = 0; j < TN; ++j) back_b[j] = 1 - __builtin_amdgcn_frexp_expf(scale_b[j]);
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j][r] = __builtin_ldexpf(__builtin_fmaf(small[i][j][r], 0x1p-11f, acc[i][j][r]), d + back_b[j]);
-            }
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int d = __shfl(back_a[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j][r] = __builtin_ldexpf(__builtin_fmaf(small[i][j][r], 0x1p-11f, acc[i][j][r]), d + back_b[j]);
+                }
+        }
         __syncthreads();
     }
 
@@ -870,7 +889,7 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
-    if (__any(probe != 0.f)) {
+    if (!T::F32 && __any(probe != 0.f)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1203,13 +1222,16 @@ using S1 = SliceTile<32, 64, 8, 2>;
 using S2 = SliceTile<32, 32, 8, 4>;
 using S3 = SliceTile<64, 64, 2, 2>;   // large weight gradients over a short k: fewer partial tiles to add
 using S4 = SliceTile<32, 32, 4, 4>;   // as S2 with 256 threads: beside a narrow layer's gradient in one launch
+using S5 = SliceTile<32, 32, 4, 4, true>;   // short sums, on the fp32 instruction
+using S6 = SliceTile<32, 32, 2, 4, true>;   // ... large weight gradients
 
 static const char *kVariantNames[] = {"128x128x16_r1",  "128x64x16_r2",   "64x64x64_k4_r2", "64x64x32_k4_r2",
                                       "32x64x32_k4_r2", "32x64x64_k8_r2", "32x32x64_k8_r2", "128x128x16_r2_pc16",
                                       "128x64x16_r2_pc16_o2", "64x64x16_r2_pc8_o4", "64x64x32_k2_r2_o2", "64x64x16_r2_pc8_o3",
                                       "32x32x64_k4_r2_o3", "slice_64x64_k4", "slice_32x64_k8",
-                                      "slice_32x32_k8", "slice_64x64_k2"};
-constexpr int kVariants = 17;
+                                      "slice_32x32_k8", "slice_64x64_k2", "slice_32x32_k4_f32",
+                                      "slice_32x32_k2_f32"};
+constexpr int kVariants = 19;
 int gemm_variant_count() { return kVariants; }
 const char *gemm_variant_name(int v) { return (v >= 0 && v < kVariants) ? kVariantNames[v] : "?"; }
 
@@ -1266,8 +1288,10 @@ static bool large_short_grad(long tiles64, int k) { return (tiles64 >= 1024 && k
 // 1024, k 1024: 27 / 39 / 41; 256 x 1000, k 4096: 21.0 / 21.0 / 20.4; 512 x 1024, k 1024: 13.8 / 10.9 / 12.5; 128 x
 // 1024, k 1024: 12.4 / 8.9 / 7.7; gradients 1024 x 1024, k 512: 11.8 / 14.7 / 14.3; k 128: 7.2 / 9.5 / 9.4.  Operands
 // read through registers (odd widths) do without the middle shape: 301 x 777, k 1021: 16.8 / 14.7 / 10.8.
-// fp32 instruction: 64x64 tiles at several workgroups per CU let one workgroup's prologue / epilogue traffic run under
-// another's matrix work; outputs with few tiles use small tiles whose waves split k among themselves.
+// Short sums are bound by launch, loads and stores; 32 x 32 tiles in slices take them all.  Measured against the best of
+// the LDS-tiled fp32 shapes, us (those / these): gradient + momentum 4096 x 4096, k = 32 59 / 40, k = 64 62 / 43 (HBM
+// floor 56; the last-level cache helps); 2017 x 1023, k = 37 24.2 / 12.2; gradient 301 x 777, k = 18 7.0 / 3.6;
+// forward 64 x 2048, k = 49 6.6 / 3.6; 2048 x 512, k = 64 5.0 / 5.1.
 static int pick_variant(GemmKind kind, const GemmArgs &a)
 {
     auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
@@ -1278,9 +1302,7 @@ static int pick_variant(GemmKind kind, const GemmArgs &a)
         if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 13;
         return tiles(32, 64) >= 192 && vec_ok(kind, a) ? 14 : 15;
     }
-    if (t64 >= 256) return kind == GEMM_GRAD ? 11 : 10;
-    if (tiles(32, 64) > 256) return 4;
-    return kind != GEMM_GRAD ? 12 : 6;
+    return kind == GEMM_GRAD && large_short_grad(t64, a.K) ? 18 : 17;
 }
 
 // ---- a delta product and a narrow layer's gradient in one launch ---------------------------
@@ -1315,7 +1337,7 @@ static hipError_t launch_delta_narrow_as(const GemmArgs &delta, const GemmArgs &
 // one launch (they do not depend on each other); call only if delta_narrow_grad_fits.
 hipError_t launch_delta_with_narrow_grad(const GemmArgs &delta, const GemmArgs &grad, hipStream_t stream)
 {
-    return delta.K >= kSplitMinK ? launch_delta_narrow_as<S4>(delta, grad, stream) : launch_delta_narrow_as<V12>(delta, grad, stream);
+    return delta.K >= kSplitMinK ? launch_delta_narrow_as<S4>(delta, grad, stream) : launch_delta_narrow_as<S5>(delta, grad, stream);
 }
 
 // ---- the gradients of several layers in one launch ---------------------------------------
@@ -1323,9 +1345,8 @@ hipError_t launch_delta_with_narrow_grad(const GemmArgs &delta, const GemmArgs &
 // large matrices.
 static bool multi_grad_layer_fits(const GemmArgs &a)
 {
-    // a matrix of at least 64 tiles of 64 x 64; the fp32 tile reads it in 16-byte pieces
-    return !narrow_layer(a.M) && (a.K >= kSplitMinK || vec_ok(GEMM_GRAD, a)) &&
-           (long)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 64;
+    // a matrix of at least 64 tiles of 64 x 64
+    return !narrow_layer(a.M) && (long)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 64;
 }
 
 static long multi_grad_tiles(const GemmArgs *grads, int n)
@@ -1374,7 +1395,7 @@ void gemm_grads_plan(const GemmArgs *grads, int n, int variant, bool merge, bool
     for (int i = 0; i < n; ++i) in_shared[i] = false;
     if (merge && variant < 0) {
         // (the narrow layer's gradient needs workgroups of 256 threads)
-        const bool room = grads[0].K <= 512 && !(grads[0].K >= kSplitMinK && large_short_grad(multi_grad_tiles(grads, n), grads[0].K));
+        const bool room = grads[0].K <= 512 && !large_short_grad(multi_grad_tiles(grads, n), grads[0].K);
         for (int i = 0; i < n; ++i) {
             if (grads[i].mode != grads[0].mode) continue;
             if (wide < MG_MAX && multi_grad_layer_fits(grads[i])) {
@@ -1416,11 +1437,13 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
                 ++m.n;
             }
         }
+        const int k = m.g[0].K, edge = k < kSplitMinK ? S5::BM : S0::BM;
+        static_assert(S0::BM == S3::BM && S0::BN == S3::BN && S0::BM == S0::BN && S5::BM == S5::BN, "square tiles of one size");
         long at = 0;
         for (int p = 0; p < m.n; ++p) {
             m.first[p] = (int)at;
-            m.tiles_m[p] = (m.g[p].M + 63) / 64;
-            m.tiles_n[p] = (m.g[p].N + 63) / 64;
+            m.tiles_m[p] = (m.g[p].M + edge - 1) / edge;
+            m.tiles_n[p] = (m.g[p].N + edge - 1) / edge;
             at += 8 * (((long)m.tiles_m[p] * m.tiles_n[p] + 7) / 8);
         }
         m.first[m.n] = (int)at;
@@ -1431,11 +1454,10 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
             at += m.narrow_blocks;
         }
         if (at > 0x7fffffffL) return hipErrorInvalidValue;
-        const int k = m.g[0].K;
-        const hipError_t e = k < kSplitMinK ? launch_multi_mode<V11>(m, grads[0].mode, (unsigned)at, stream)
-                             : large_short_grad(multi_grad_tiles(grads, n), k)
-                                 ? launch_multi_mode<S3>(m, grads[0].mode, (unsigned)at, stream)
-                                 : launch_multi_mode<S0>(m, grads[0].mode, (unsigned)at, stream);
+        const bool large = large_short_grad(multi_grad_tiles(grads, n), k);
+        const int mode = grads[0].mode;
+        const hipError_t e = k < kSplitMinK ? (large ? launch_multi_mode<S6>(m, mode, (unsigned)at, stream) : launch_multi_mode<S5>(m, mode, (unsigned)at, stream))
+                                            : (large ? launch_multi_mode<S3>(m, mode, (unsigned)at, stream) : launch_multi_mode<S0>(m, mode, (unsigned)at, stream));
         if (e != hipSuccess) return e;
     }
     for (int i = 0; i < n; ++i) {
@@ -1475,6 +1497,8 @@ hipError_t launch_gemm(GemmKind kind, const GemmArgs &a, int variant, hipStream_
     case 14: return launch_kind<S1>(kind, a, stream);
     case 15: return launch_kind<S2>(kind, a, stream);
     case 16: return launch_kind<S3>(kind, a, stream);
+    case 17: return launch_kind<S5>(kind, a, stream);
+    case 18: return launch_kind<S6>(kind, a, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -31,9 +31,10 @@ typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 // tile.  Nothing is shared between waves before the partial tiles are added, so the k loop has no barrier: a wave
 // keeps two slices of fp32 operands in LDS of its own, filled straight from memory, reads the one that has
 // arrived into registers, splits it there and multiplies while the other travels.
-template <int BM_, int BN_, int WK_, int OCC_>
+// F32: no splitting, the slices go to the fp32 instruction as they are.
+template <int BM_, int BN_, int WK_, int OCC_, bool F32_ = false>
 struct SliceTile {
-    static constexpr bool SPLIT = true;
+    static constexpr bool SPLIT = true, F32 = F32_;
     static constexpr int BM = BM_, BN = BN_, WM = 1, WN = 1, WK = WK_, OCC = OCC_;
     static constexpr int KT = 16 * WK, NT = 64 * WK;
     static constexpr int WTM = BM, WTN = BN, TM = BM / 32, TN = BN / 32;
