@@ -5,8 +5,9 @@
 // of an epoch without returning to the host between steps.
 //
 // Nothing is computed here: every step is one of the library's own entry points (dn_conv_*,
-// dn_maxpool_*, dn_forward / dn_backward / dn_input_gradient / dn_update, dn_sgd_step) enqueued
-// on one stream in the order of the chain rule.  This file owns the layout of the arena (filters,
+// dn_maxpool_*, dn_forward / dn_backward / dn_input_gradient / dn_update), or two of them in one
+// (pooling and convolution backward; the filters' and biases' updates), enqueued on one stream in
+// the order of the chain rule.  This file owns the layout of the arena (filters,
 // their velocities and gradients, the activations and gradients between the blocks, the
 // convolution workspaces, the fully connected net's own arena) and the epoch loop.
 #include <hip/hip_runtime.h>
@@ -15,7 +16,7 @@
 #include <new>
 #include <vector>
 
-#include "../../include/dn.h"
+#include "dn_internal.h"
 
 namespace {
 
@@ -291,15 +292,20 @@ dn_status dn_cnn_train_epoch(dn_cnn *net, const float *X_dev, const int32_t *lab
             Block &bk = net->lo.blocks[i];
             const dn_conv_block &s = bk.spec;
             const float *dA = net->at(bk.dOut);
+            const float *in = i == 0 ? Xb : (net->lo.blocks[i - 1].pooled() ? net->at(net->lo.blocks[i - 1].P)
+                                                                             : net->at(net->lo.blocks[i - 1].Y));
+            float *dX = i == 0 ? nullptr : net->at(net->lo.blocks[i - 1].dOut);
             if (bk.pooled()) {
+                st = dn::conv_backward_pooled(in, net->at(bk.W), net->at(bk.Y), dA, net->at(bk.delta), dX, net->at(bk.dW),
+                                          net->at(bk.db), net->arena + bk.ws, bk.ws_bytes, B, bk.c_in, bk.h, bk.w, s.c_out, s.k,
+                                          s.stride, s.pad, s.act, s.pool_k, s.pool_stride, net->stream);
+                if (st == DN_OK) continue;
+                if (st != DN_ERR_UNSUPPORTED) return st;
                 st = dn_maxpool_backward(net->at(bk.Y), net->at(bk.dOut), net->at(bk.dY), B, s.c_out, bk.ho, bk.wo, s.pool_k,
                                          s.pool_stride, net->stream);
                 if (st != DN_OK) return st;
                 dA = net->at(bk.dY);
             }
-            const float *in = i == 0 ? Xb : (net->lo.blocks[i - 1].pooled() ? net->at(net->lo.blocks[i - 1].P)
-                                                                             : net->at(net->lo.blocks[i - 1].Y));
-            float *dX = i == 0 ? nullptr : net->at(net->lo.blocks[i - 1].dOut);
             st = dn_conv_backward(in, net->at(bk.W), net->at(bk.Y), dA, net->at(bk.delta), dX, net->at(bk.dW), net->at(bk.db),
                                   net->arena + bk.ws, bk.ws_bytes, B, bk.c_in, bk.h, bk.w, s.c_out, s.k, s.k, s.stride, s.pad,
                                   (dn_act)s.act, net->stream);
@@ -307,12 +313,16 @@ dn_status dn_cnn_train_epoch(dn_cnn *net, const float *X_dev, const int32_t *lab
         }
         // the update, every layer by the same rule
         if ((st = dn_update(net->dense, lr, momentum)) != DN_OK) return st;
+        dn::UpdateVector vectors[dn::UPDATE_MAX];
+        int n = 0;
         for (Block &bk : net->lo.blocks) {
-            float *vW = momentum != 0.f ? net->at(bk.vW) : nullptr, *vb = momentum != 0.f ? net->at(bk.vb) : nullptr;
-            if ((st = dn_sgd_step(net->at(bk.W), net->at(bk.dW), vW, (int64_t)bk.filt, lr, momentum, net->stream)) != DN_OK)
-                return st;
-            if ((st = dn_sgd_step(net->at(bk.b), net->at(bk.db), vb, bk.spec.c_out, lr, momentum, net->stream)) != DN_OK)
-                return st;
+            const bool v = momentum != 0.f;
+            vectors[n++] = {net->at(bk.W), v ? net->at(bk.vW) : nullptr, net->at(bk.dW), bk.filt};
+            vectors[n++] = {net->at(bk.b), v ? net->at(bk.vb) : nullptr, net->at(bk.db), (size_t)bk.spec.c_out};
+            if (n == dn::UPDATE_MAX || &bk == &net->lo.blocks.back()) {
+                if (dn::launch_updates(vectors, n, lr, momentum, net->stream) != hipSuccess) return DN_ERR_DEVICE;
+                n = 0;
+            }
         }
         if ((int)step_size.size() == kLossSlots && (st = drain()) != DN_OK) return st;
     }

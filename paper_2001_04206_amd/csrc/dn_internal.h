@@ -137,10 +137,27 @@ hipError_t launch_narrow_output(const float *Aprev, const float *W, const float 
 // Elementwise update of a parameter vector from a stored gradient (dn_update).
 hipError_t launch_update(float *p, float *v, const float *g, size_t count, float lr, float mu,
                          hipStream_t stream);
+// The same for several vectors in one launch; v may be null (plain gradient descent).
+struct UpdateVector {
+    float *p, *v;
+    const float *g;
+    size_t count;
+};
+constexpr int UPDATE_MAX = 16;
+hipError_t launch_updates(const UpdateVector *vectors, int n, float lr, float mu, hipStream_t stream);
 hipError_t launch_copy(float *dst, const float *src, size_t count, hipStream_t stream);
 // One sample's backward outputs of one layer (gradients, lr-scaled weight and bias deltas).
 hipError_t launch_layer_backward(const float *deltas, const float *inputs, float lr, int cols_out, int cols_in,
                                  float *G, float *dW, float *dB, hipStream_t stream);
+
+// The backward step of a convolution whose output Y is max-pooled, from dP, the derivative with respect to the POOLED
+// output: dn_maxpool_backward and dn_conv_backward with the gradient between them kept out of memory.
+// DN_ERR_UNSUPPORTED (nothing launched) unless the pooling windows tile Y.
+dn_status conv_backward_pooled(const float *X_dev, const float *W_dev, const float *Y_dev, const float *dP_dev,
+                               float *delta_dev, float *dX_dev, float *dW_dev, float *dbias_dev, void *workspace_dev,
+                               size_t workspace_bytes, int32_t batch, int32_t c_in, int32_t h, int32_t w, int32_t c_out,
+                               int32_t k, int32_t stride, int32_t pad, int32_t act, int32_t pool_k, int32_t pool_stride,
+                               hipStream_t stream);
 
 // ---- persistent batch-1 epoch kernel (dn_online.hip) ----------------------------
 constexpr int ON_MAX_L = 8;         // layers
