@@ -4,7 +4,7 @@
 // in include/dn.h).  Gather form throughout: every output element is owned by one thread, wave or
 // workgroup, so nothing is accumulated with atomics and every sum has a fixed order.  Stride-1
 // layers wide enough for 32 x 32 tiles run their forward product and input gradient on the matrix
-// cores (corr_mfma_kernel), with square filters of odd edge the filter gradient too (conv_dw_mfma_kernel);
+// cores (corr3_split_kernel and corr_mfma_kernel), with square filters of odd edge the filter gradient too (conv_dw_mfma_kernel);
 // everything else uses register-tiled vector kernels.
 #include <atomic>
 #include <mutex>
@@ -217,24 +217,23 @@ hipError_t launch_corr_rows(const CorrShape &s, const float *In, const float *Wt
 constexpr int MC_IC = 8, MC_WSTRIDE = 80;
 typedef float v16f_t __attribute__((ext_vector_type(16)));
 
-// KS: filter edge known at compile time (3: the tap loop is unrolled), 0: any.  TW: columns of the
-// workgroup's pixel tile, 32 (a 32-pixel accumulator tile is one output row) or 16 (two rows of 16:
-// images of at most 16 columns would leave half of every 32-column tile empty).
-template <int OT, int RW, int KS, int TW = 32>
+// KS: filter edge known at compile time (5: the tap loop is unrolled), 0: any; 3 x 3 filters run in
+// corr3_split_kernel below.
+template <int OT, int RW, int KS>
 __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float *__restrict__ In,
                                                         const float *__restrict__ Wt, const float *__restrict__ bias,
                                                         float *__restrict__ Out)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    constexpr int OC = 32 * OT, RPT = 32 / TW, MC_ROWS = 4 * RW * RPT;   // RPT: output rows per accumulator tile
+    constexpr int OC = 32 * OT, MC_ROWS = 4 * RW;
     const int taps = s.KH * s.KW, kstage = MC_IC * taps;
-    const int prow = MC_ROWS + s.KH - 1, pcol = TW + s.KW - 1;   // staged input patch per channel
+    const int prow = MC_ROWS + s.KH - 1, pcol = 32 + s.KW - 1;   // staged input patch per channel
     float *wl = lds;                                   // [kstage][MC_WSTRIDE]
     float *pl = lds + (size_t)kstage * MC_WSTRIDE;     // [MC_IC][prow][pcol]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int idx = lane & 31, h = lane >> 5;
-    const int col_tiles = (s.Wo + TW - 1) / TW;
-    const int i0 = (blockIdx.x / col_tiles) * MC_ROWS, j0 = (blockIdx.x % col_tiles) * TW;
+    const int col_tiles = (s.Wo + 31) / 32;
+    const int i0 = (blockIdx.x / col_tiles) * MC_ROWS, j0 = (blockIdx.x % col_tiles) * 32;
     const int oc0 = blockIdx.y * OC, b = blockIdx.z;
     v16f_t acc[OT][RW];
 #pragma unroll
@@ -250,31 +249,31 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
     const bool w_on = w_ocl < OC;
     const int w_oc = min(oc0 + w_ocl, s.Cout - 1);
     const bool w_real = oc0 + w_ocl < s.Cout;
-    // Filter edge known (3 x 3, 5 x 5): every load of a stage is requested at once, into registers, before the
+    // Filter edge known (5 x 5): every load of a stage is requested at once, into registers, before the
     // first value is stored; the staging indices are recomputed from the thread
     // index every time rather than kept in registers across the product loop (the empty asm hides
     // that they repeat)
-    constexpr int TAPS3 = KS * KS, PROW3 = MC_ROWS + KS - 1, PCOL3 = TW + KS - 1, NP3 = MC_IC * PROW3 * PCOL3;
-    constexpr int XP3 = KS > 0 ? (NP3 + 255) / 256 : 1, WP3 = KS > 0 ? MC_IC * TAPS3 / 4 : 1;
-    [[maybe_unused]] float wreg[WP3], xreg[XP3];
+    constexpr int TAPS_K = KS * KS, PROW_K = MC_ROWS + KS - 1, PCOL_K = 32 + KS - 1, NP_K = MC_IC * PROW_K * PCOL_K;
+    constexpr int XP_K = KS > 0 ? (NP_K + 255) / 256 : 1, WP_K = KS > 0 ? MC_IC * TAPS_K / 4 : 1;
+    [[maybe_unused]] float wreg[WP_K], xreg[XP_K];
     [[maybe_unused]] auto stage_request = [&](int ic0) {
         const int st = tid;
-        const int kvalid = min(MC_IC, s.Cin - ic0) * TAPS3;
+        const int kvalid = min(MC_IC, s.Cin - ic0) * TAPS_K;
         const int ocl = st >> 2, kq = st & 3;
         const bool real = ocl < OC && oc0 + ocl < s.Cout;
-        const float *src = Wt + (size_t)min(oc0 + ocl, s.Cout - 1) * s.w_out_stride + (size_t)ic0 * TAPS3;
+        const float *src = Wt + (size_t)min(oc0 + ocl, s.Cout - 1) * s.w_out_stride + (size_t)ic0 * TAPS_K;
 #pragma unroll
-        for (int m = 0; m < WP3; ++m) {
+        for (int m = 0; m < WP_K; ++m) {
             const int kl = kq + 4 * m;
             wreg[m] = (real && kl < kvalid) ? src[kl] : 0.f;
         }
         const float *img = In + ((size_t)b * s.Cin + ic0) * s.H * s.W;
 #pragma unroll
-        for (int m = 0; m < XP3; ++m) {
+        for (int m = 0; m < XP_K; ++m) {
             const int e = st + 256 * m;
-            const int c = e % PCOL3, pr = (e / PCOL3) % PROW3, icl = e / (PCOL3 * PROW3);
+            const int c = e % PCOL_K, pr = (e / PCOL_K) % PROW_K, icl = e / (PCOL_K * PROW_K);
             const int r_img = r_in0 + pr, c_img = c_in0 + c;
-            const bool ok = e < NP3 && ic0 + icl < s.Cin && r_img >= 0 && r_img < s.H && c_img >= 0 && c_img < s.W;
+            const bool ok = e < NP_K && ic0 + icl < s.Cin && r_img >= 0 && r_img < s.H && c_img >= 0 && c_img < s.W;
             xreg[m] = ok ? img[(unsigned)((icl * s.H + r_img) * s.W + c_img)] : 0.f;
         }
     };
@@ -283,12 +282,12 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
         const int ocl = st >> 2, kq = st & 3;
         if (ocl < OC) {
 #pragma unroll
-            for (int m = 0; m < WP3; ++m) wl[(kq + 4 * m) * MC_WSTRIDE + ocl] = wreg[m];
+            for (int m = 0; m < WP_K; ++m) wl[(kq + 4 * m) * MC_WSTRIDE + ocl] = wreg[m];
         }
 #pragma unroll
-        for (int m = 0; m < XP3; ++m) {
+        for (int m = 0; m < XP_K; ++m) {
             const int e = st + 256 * m;
-            if (e < NP3) pl[e] = xreg[m];
+            if (e < NP_K) pl[e] = xreg[m];
         }
     };
     if constexpr (KS > 0) stage_request(0);
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
         }
         // k slot h of every instruction: input channel 2 * pair + h at one tap
         const float *wa = wl + (size_t)(h * taps) * MC_WSTRIDE + idx;
-        const float *pb = pl + (size_t)h * prow * pcol + (RW * wave * RPT + idx / TW) * pcol + idx % TW;
+        const float *pb = pl + (size_t)h * prow * pcol + (RW * wave) * pcol + idx;
 #pragma unroll
         for (int pair = 0; pair < MC_IC / 2; ++pair) {
             const float *wp = wa + (size_t)(2 * pair * taps) * MC_WSTRIDE;
@@ -347,7 +346,7 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
             auto one_tap = [&](int tap, int po) {   // po: patch offset u * pcol + v of the tap
                 float xv[RW];
 #pragma unroll
-                for (int q = 0; q < RW; ++q) xv[q] = pp[po + q * RPT * pcol];
+                for (int q = 0; q < RW; ++q) xv[q] = pp[po + q * pcol];
                 const float *wq = wp + tap * MC_WSTRIDE;
 #pragma unroll
                 for (int t = 0; t < OT; ++t) {
@@ -375,12 +374,12 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
         if (tid < OC) wl[tid] = oc0 + tid < s.Cout ? bias[oc0 + tid] : 0.f;
         __syncthreads();
     }
-    // register r of lane (idx, h): output channel 8 (r / 4) + 4 h + r % 4 of the tile, pixel idx of the tile's row(s)
-    const int j = j0 + idx % TW;
+    // register r of lane (idx, h): output channel 8 (r / 4) + 4 h + r % 4 of the tile, pixel idx of the tile's row
+    const int j = j0 + idx;
     if (j >= s.Wo) return;
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
-        const int i = i0 + (RW * wave + q) * RPT + idx / TW;
+        const int i = i0 + RW * wave + q;
         if (i >= s.Ho) continue;
 #pragma unroll
         for (int t = 0; t < OT; ++t)
@@ -636,26 +635,26 @@ bool corr_mfma_fits(const CorrShape &s)
     return s.Cout >= 32 && s.Cin >= 8 && s.Wo >= min_w && s.w_in_stride == s.KH * s.KW && !s.flip;
 }
 
-template <int OT, int RW, int KS, int TW = 32>
+template <int OT, int RW, int KS>
 hipError_t launch_corr_mfma_as(const CorrShape &s, const float *In, const float *Wt, const float *bias, float *Out,
                                hipStream_t stream)
 {
-    constexpr int rows = 4 * RW * (32 / TW);
+    constexpr int rows = 4 * RW;
     const int taps = s.KH * s.KW;
     const size_t lds = sizeof(float) * ((size_t)MC_IC * taps * MC_WSTRIDE +
-                                        (size_t)MC_IC * (rows + s.KH - 1) * (TW + s.KW - 1));
+                                        (size_t)MC_IC * (rows + s.KH - 1) * (32 + s.KW - 1));
     // 7 x 7 filters need up to 146 KB, more than the default limit of dynamic LDS (the calls are stateless and
     // may come from several threads: setting the limit twice is harmless, the flag is read and written atomically)
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&corr_mfma_kernel<OT, RW, KS, TW>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&corr_mfma_kernel<OT, RW, KS>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    const dim3 grid((unsigned)(((s.Ho + rows - 1) / rows) * ((s.Wo + TW - 1) / TW)),
+    const dim3 grid((unsigned)(((s.Ho + rows - 1) / rows) * ((s.Wo + 31) / 32)),
                     (unsigned)((s.Cout + 32 * OT - 1) / (32 * OT)), (unsigned)s.B);
-    hipLaunchKernelGGL((corr_mfma_kernel<OT, RW, KS, TW>), grid, dim3(256), lds, stream, s, In, Wt, bias, Out);
+    hipLaunchKernelGGL((corr_mfma_kernel<OT, RW, KS>), grid, dim3(256), lds, stream, s, In, Wt, bias, Out);
     return hipGetLastError();
 }
 
