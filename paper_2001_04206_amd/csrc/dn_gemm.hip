@@ -18,6 +18,7 @@
 // stored k-contiguous.
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <type_traits>
 
 #include "dn_internal.h"
@@ -680,7 +681,6 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
     const int idx = lane & 31, h = lane >> 5;
     const int wk = wave / (T::WM * T::WN);
     const int wm = (wave % (T::WM * T::WN)) / T::WN, wn = wave % T::WN;
-    const int nk = (g.K + KT - 1) / KT;
     const int rows_a = g.M - m0, rows_b = g.N - n0;
     const float *tile_a = A_KC ? g.A + (size_t)m0 * g.lda : g.A + m0;
     const float *tile_b = B_KC ? g.B + (size_t)n0 * g.ldb : g.B + n0;
@@ -713,12 +713,25 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
         const float *sl_b = B_KC ? tile_b + 16 * wave : tile_b + (size_t)(16 * wave) * g.ldb;
         v4f xa[TM][2], xb[TN][2];        // a slice in fp32
         // Row r's numbers enter as 2^e x; a lane holds the exponent of its row (column) of every block, as the factor and
-        // as the largest number that still fits.
-        float scale_a[TM], scale_b[TN], room_a[TM], room_b[TN];
+        // as the largest number that fits and the smallest that keeps its bits.  A zero is no such number: activations
+        // and deltas, which have zeros everywhere, are tested by keys (1.5 instructions a number), weights by their
+        // smallest number first (half an instruction).  The vector unit is the busy one here, so the tests show: forward 256
+        // x 4096, k = 4096 47.6 -> 52.8 us.  A range wider by one or two bits, with less room above, was slower (54.1
+        // us): rows outgrow their scale more often.
+        constexpr bool KEYS_B = IS_GRAD;
+        float scale_a[TM], scale_b[TN], room_a[TM], room_b[TN], low_b[TN], first_a[TM], first_b[TN];
+        unsigned key_a[TM], key_b[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) scale_a[i] = 1.f, room_a[i] = 0.f;
+        for (int i = 0; i < TM; ++i) scale_a[i] = 1.f, room_a[i] = first_a[i] = 0.f, key_a[i] = 0;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) scale_b[j] = 1.f, room_b[j] = 0.f;
+        for (int j = 0; j < TN; ++j) scale_b[j] = 1.f, room_b[j] = low_b[j] = first_b[j] = 0.f, key_b[j] = 0;
+        // Slices left for the fp32 instruction: this wave's slices in 64 groups, lane g holds the first slice of group g
+        // that is left (the rest of the group is left with it).  Once a quarter is left, so are all further ones: the
+        // product 256 x 4096, k = 4096 then takes 125 us where tiles made for the fp32 instruction take 83, with a NaN or an
+        // infinity 147.  One number in 40 million is that small in normal data.
+        const int group = (mine + 63) / 64;
+        int left = INT_MAX, left_until = 0, left_sum = 0;
+        bool again = false;   // every slice
         v16f small[TM][TN];   // the sum of h l' + l h', 2^11 times its share (F32: a second sum of the products)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -731,24 +744,121 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
             read_blocks<A_KC, BM>(xa, base, at_a);
             read_blocks<B_KC, BN>(xb, base + BM * 64, at_b);
         };
-        auto contract = [&] {
+        // sums 2^shift, the shift of an element being that of its row plus that of its column
+        auto shift_sums = [&](const int (&da)[TM], const int (&db)[TN]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int d = __shfl(da[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        acc[i][j][r] = __builtin_ldexpf(acc[i][j][r], d + db[j]);
+                        small[i][j][r] = __builtin_ldexpf(small[i][j][r], d + db[j]);
+                    }
+                }
+        };
+        // the smallest number of a row that would keep its bits with a scale that fits the row's part of the slice
+        auto fit = [&](const v4f (&x)[2], float room, float low) {
+            float m = largest(x[0], x[1]);
+            m = fmaxf(m, __shfl_xor(m, 32, 64));   // the other lane of the row
+            if (!(m > room && m < INFINITY)) return low;
+            return __builtin_ldexpf(1.f, max(__builtin_amdgcn_frexp_expf(m), -100) - 26);   // scale m will be in [2^11, 2^12)
+        };
+        auto key_of = [](float low) { return low > 0.f ? magnitude_key(low) : 0u; };
+        auto low_of = [](unsigned key) { return __uint_as_float((key + 1) >> 1); };
+        // A slice that does not fit the scales.  Either there are new ones and what has been summed so far follows (after 2^45
+        // on either side its smallest products, 2^-14 by 2^-14 at first, could leave fp32's range), or the slice is left and
+        // the scales stay: a few large numbers do not take the other slices' bits.
+        auto fits = [&](int it) {
+            float la[TM], lb[TN], was_a[TM], was_b[TN];
+            bool below = false;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                was_a[i] = low_of(key_a[i]);
+                la[i] = fit(xa[i], room_a[i], was_a[i]);
+                below |= least_key(xa[i][0], xa[i][1]) < key_of(la[i]);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                was_b[j] = KEYS_B ? low_of(key_b[j]) : low_b[j];
+                lb[j] = fit(xb[j], room_b[j], was_b[j]);
+                below |= least_key(xb[j][0], xb[j][1]) < key_of(lb[j]);
+            }
+            if (__builtin_amdgcn_ballot_w64(below) != 0) {
+                const int g = it / group;
+                if (lane == g) left = it;
+                left_until = min((g + 1) * group, mine);
+                left_sum += left_until - it;
+                if (left_sum > mine / 4) {   // these operands are not for splitting
+                    if (lane > g) left = lane * group;
+                    left_until = mine;
+                }
+                return false;
+            }
+            bool moved = false;
+            auto take_over = [&](float low, float was, float &scale, float &room, float &first) {
+                const int e = __builtin_amdgcn_frexp_expf(low), d = was > 0.f ? __builtin_amdgcn_frexp_expf(was) - e : 0;
+                if (low > 0.f) scale = __builtin_ldexpf(1.f, -13 - e);
+                room = low * 0x1p29f;
+                if (first == 0.f) first = low;
+                again |= low > first * 0x1p45f;
+                moved |= d != 0;
+                return d;
+            };
+            int da[TM], db[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                da[i] = take_over(la[i], was_a[i], scale_a[i], room_a[i], first_a[i]);
+                key_a[i] = key_of(la[i]);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                db[j] = take_over(lb[j], was_b[j], scale_b[j], room_b[j], first_b[j]);
+                if (KEYS_B) key_b[j] = key_of(lb[j]);
+                else low_b[j] = lb[j];
+            }
+            if (__any(moved)) shift_sums(da, db);
+            return true;
+        };
+        auto add_bias = [&] {
             if constexpr (IS_GRAD) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
                     bs[i] += ((xa[i][0][0] + xa[i][0][1]) + (xa[i][0][2] + xa[i][0][3])) + ((xa[i][1][0] + xa[i][1][1]) + (xa[i][1][2] + xa[i][1][3]));
             }
-            if constexpr (T::F32) {   // k = q of one half of the lanes with k = 8 + q of the other
+        };
+        // on the fp32 instruction: k = q of one half of the lanes with k = 8 + q of the other
+        auto contract_fp32 = [&](v16f (&even)[TM][TN], v16f (&odd)[TM][TN]) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j) {
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][0][q], xb[j][0][q], acc[i][j], 0, 0, 0);
-                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][1][q], xb[j][1][q], small[i][j], 0, 0, 0);
-                        }
+                    for (int j = 0; j < TN; ++j) {
+                        even[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][0][q], xb[j][0][q], even[i][j], 0, 0, 0);
+                        odd[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][1][q], xb[j][1][q], odd[i][j], 0, 0, 0);
+                    }
+        };
+        auto contract = [&](int it) {
+            add_bias();
+            if constexpr (T::F32) {
+                contract_fp32(acc, small);
                 return;
             }
+            if (it < left_until) return;
+            bool odd = false;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                odd |= largest(xa[i][0], xa[i][1]) > room_a[i];
+                odd |= least_key(xa[i][0], xa[i][1]) < key_a[i];
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                odd |= largest(xb[j][0], xb[j][1]) > room_b[j];
+                odd |= KEYS_B ? least_key(xb[j][0], xb[j][1]) < key_b[j] : smallest(xb[j][0], xb[j][1]) < low_b[j];
+            }
+            if (__builtin_amdgcn_ballot_w64(odd) != 0 && !fits(it)) return;
             v8h fa[TM][2], fb[TN][2];
 #pragma unroll
             for (int i = 0; i < TM; ++i) split_eight(xa[i][0], xa[i][1], scale_a[i], fa[i]);
@@ -769,48 +879,6 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
-        };
-        auto outgrown = [&] {
-            bool out = false;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) out |= largest(xa[i][0], xa[i][1]) > room_a[i];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) out |= largest(xb[j][0], xb[j][1]) > room_b[j];
-            return __any(out);
-        };
-        // sums 2^shift, the shift of an element being that of its row plus that of its column
-        auto shift_sums = [&](const int (&da)[TM], const int (&db)[TN]) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int d = __shfl(da[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        acc[i][j][r] = __builtin_ldexpf(acc[i][j][r], d + db[j]);
-                        small[i][j][r] = __builtin_ldexpf(small[i][j][r], d + db[j]);
-                    }
-                }
-        };
-        // scales that fit the slice in xa, xb; what has been summed so far follows
-        auto rescale = [&] {
-            auto fit = [&](const v4f (&x)[2], float &scale, float &room) {
-                float m = largest(x[0], x[1]);
-                m = fmaxf(m, __shfl_xor(m, 32, 64));   // the other lane of the row
-                if (!(m > room && m < INFINITY)) return 0;
-                const int e = 12 - max(__builtin_amdgcn_frexp_expf(m), -100);   // scale m is in [2^11, 2^12)
-                const int d = room > 0.f ? e - (__builtin_amdgcn_frexp_expf(scale) - 1) : 0;
-                scale = __builtin_ldexpf(1.f, e);
-                room = __builtin_ldexpf(1.f, 15 - e);
-                return d;
-            };
-            int da[TM], db[TN];
-            bool moved = false;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) da[i] = fit(xa[i], scale_a[i], room_a[i]), moved |= da[i] != 0;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) db[j] = fit(xb[j], scale_b[j], room_b[j]), moved |= db[j] != 0;
-            if (__any(moved)) shift_sums(da, db);
         };
         // pieces of four from aligned addresses, slices wholly inside k: straight into LDS
         int it = 0;
@@ -834,26 +902,32 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
             if (whole > 1) fetch(1, 1);
             for (; it < whole; ++it) {
                 take(it, it & 1);
-                if (!T::F32 && outgrown()) rescale();
-                contract();
+                contract(it);
+                if (!T::F32 && left_until == mine) break;   // (all further slices are left)
             }
+            if (!T::F32) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
+        v4f va[SA::Q], vb[SB::Q];
+        auto load = [&](int t) {
+            SA::load(va, sl_a + (size_t)t * kstep_a, g.lda, rows_a, g.K - 16 * (wave + t * WK), lane);
+            SB::load(vb, sl_b + (size_t)t * kstep_b, g.ldb, rows_b, g.K - 16 * (wave + t * WK), lane);
+        };
+        auto put = [&] {
+            SA::put(own, va, lane);
+            SB::put(own + BM * 64, vb, lane);
+            read_slice(0);
+        };
+        const bool rest_left = !T::F32 && it < mine && left_until == mine;
+        const int seen = rest_left ? it + 1 : mine;   // slices whose part of the bias gradient is in bs
+        if (rest_left) it = mine;
         if (it < mine) {   // through registers: odd widths, and the last k
-            v4f va[SA::Q], vb[SB::Q];
-            auto load = [&](int t) {
-                SA::load(va, sl_a + (size_t)t * kstep_a, g.lda, rows_a, g.K - 16 * (wave + t * WK), lane);
-                SB::load(vb, sl_b + (size_t)t * kstep_b, g.ldb, rows_b, g.K - 16 * (wave + t * WK), lane);
-            };
             constexpr bool AHEAD = TM * TN < 4;   // the large tile has no registers to spare
             if (AHEAD) load(it);
             for (; it < mine; ++it) {
                 if (!AHEAD) load(it);
-                SA::put(own, va, lane);
-                SB::put(own + BM * 64, vb, lane);
-                read_slice(0);
+                put();
                 if (AHEAD && it + 1 < mine) load(it + 1);
-                if (!T::F32 && outgrown()) rescale();
-                contract();
+                contract(it);
             }
         }
         if constexpr (T::F32) {
@@ -867,55 +941,46 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
             for (int i = 0; i < TM; ++i) back_a[i] = 1 - __builtin_amdgcn_frexp_expf(scale_a[i]);
 #pragma unroll
             for (int j = 0; j < TN; ++j) back_b[j] = 1 - __builtin_amdgcn_frexp_expf(scale_b[j]);
+            float probe = 0.f;   // an infinite operand has no finite rest: its sums are NaN here and may be infinite in fp32
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int d = __shfl(back_a[i], 8 * (r / 4) + 4 * h + (r % 4), 64);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                    for (int j = 0; j < TN; ++j) {
                         acc[i][j][r] = __builtin_ldexpf(__builtin_fmaf(small[i][j][r], 0x1p-11f, acc[i][j][r]), d + back_b[j]);
+                        probe = fmaf(acc[i][j][r], 0.f, probe);
+                    }
                 }
+            if (__any(again || probe != 0.f)) {
+                left = lane * group;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            }
+            // the slices that were left, as they are
+            unsigned long long groups = __ballot(left < mine);
+            if (groups != 0) {
+                auto first_left = [&] { return __builtin_amdgcn_readlane(left, __builtin_ctzll(groups)); };
+                int t = first_left();
+                load(t);
+                while (groups != 0) {
+                    put();
+                    if (IS_GRAD && t >= seen) add_bias();
+                    if (++t >= min((__builtin_ctzll(groups) + 1) * group, mine)) {
+                        groups &= groups - 1;
+                        if (groups != 0) t = first_left();
+                    }
+                    if (groups != 0) load(t);
+                    contract_fp32(acc, acc);
+                }
+            }
         }
         __syncthreads();
-    }
-
-    // An infinite operand has no finite rest: h l' + ... is then NaN where the fp32 product may be infinite.  A wave that finds such a sum contracts its blocks again on the fp32 matrix
-    // instruction, straight from memory.
-    float probe = 0.f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) probe = fmaf(acc[i][j][r], 0.f, probe);
-    if (!T::F32 && __any(probe != 0.f)) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-        for (int t = 0; t < nk; ++t)
-            for (int kk = wk; kk < KT / 16; kk += WK)
-                for (int c = 0; c < 16; c += 2) {
-                    const int k = t * KT + kk * 16 + c + h;
-                    float a[TM], b[TN];
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        const int r = m0 + wm * T::WTM + i * 32 + idx;
-                        a[i] = (r < g.M && k < g.K) ? (A_KC ? g.A[(size_t)r * g.lda + k] : g.A[(size_t)k * g.lda + r]) : 0.f;
-                    }
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int r = n0 + wn * T::WTN + j * 32 + idx;
-                        b[j] = (r < g.N && k < g.K) ? (B_KC ? g.B[(size_t)r * g.ldb + k] : g.B[(size_t)k * g.ldb + r]) : 0.f;
-                    }
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-                }
     }
 
     if constexpr (IS_GRAD) {

@@ -6,11 +6,15 @@
 // another.  Three of those instructions cover sixteen k values in 96 cycles where v_mfma_f32_32x32x2_f32 needs 512,
 // and the sum is rounded once per sixteen k instead of eight times.
 //
+// (Single precision from half precision products, the rest scaled up and summed apart: Ootomo and Yokota, "Recovering
+// single precision accuracy from Tensor Cores while surpassing the FP32 theoretical peak performance", 2022.)
+//
 // f16 has three fewer bits of exponent than fp32, hence the scales: a power of two for every row of either operand, which
 // each wave chooses from the numbers it meets (the row's largest so far lies in [2^11, 2^15], and the accumulators
-// follow when a number no longer fits).  Nothing overflows; numbers down to 2^-25 of their row's largest keep all their
-// bits and smaller ones are off by 2^-48 of the largest.  Infinities and NaN are contracted again on the fp32
-// instruction (split_tile).
+// follow when a number no longer fits).  Nothing overflows.  A scaled number keeps its 22 to 23 bits down to 2^-14, which is
+// 2^-25 of the row's largest or less; a slice that holds a smaller one, other than zero, is left out and contracted on
+// the fp32 instruction afterwards, as all of them are where a sum is infinite or NaN (split_tile).  So a result is as good
+// as its own terms, whatever larger numbers of its row or column meet zeros.
 //
 // Lane layout of v_mfma_f32_32x32x16_f16 (lane = 32*h + i): A row i, k = 8*h .. 8*h+7; B column i, the same k; D as
 // v_mfma_f32_32x32x2_f32: register r is row 8*(r/4) + 4*h + (r%4), column i.
@@ -180,11 +184,36 @@ __device__ __forceinline__ void split_eight(const v4f &lo, const v4f &hi, float 
     }
 }
 
+// Largest and smallest magnitude of eight numbers.  (fmaxf and fminf would each quiet their operands first.)
+__device__ __forceinline__ float max3_magnitude(float a, float b, float c)
+{
+    float m;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
+__device__ __forceinline__ float min3_magnitude(float a, float b, float c)
+{
+    float m;
+    asm("v_min3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
 __device__ __forceinline__ float largest(const v4f &lo, const v4f &hi)
 {
-    float m = fabsf(lo[0]);
+    return max3_magnitude(max3_magnitude(lo[0], lo[1], lo[2]), max3_magnitude(lo[3], hi[0], hi[1]), max3_magnitude(hi[2], hi[3], hi[3]));
+}
+__device__ __forceinline__ float smallest(const v4f &lo, const v4f &hi)
+{
+    return min3_magnitude(min3_magnitude(lo[0], lo[1], lo[2]), min3_magnitude(lo[3], hi[0], hi[1]), min3_magnitude(hi[2], hi[3], hi[3]));
+}
+
+// The smallest magnitude among eight numbers that are not zero, as twice its bits less one.  (Shifted left the sign is
+// gone, and less one a zero is the largest of unsigned numbers.)
+__device__ __forceinline__ unsigned magnitude_key(float x) { return (__float_as_uint(x) << 1) - 1u; }
+__device__ __forceinline__ unsigned least_key(const v4f &lo, const v4f &hi)
+{
+    unsigned m = ~0u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) m = fmaxf(fmaxf(m, fabsf(lo[q])), fabsf(hi[q]));
+    for (int q = 0; q < 4; ++q) m = min(min(m, magnitude_key(lo[q])), magnitude_key(hi[q]));
     return m;
 }
 

@@ -110,3 +110,72 @@ def test_infinities_and_nan(dnlib, variant):
     assert np.array_equal(np.sign(out[[3, 65]]), np.sign(want[[3, 65]]))
     rows = [r for r in range(70) if r not in (3, 65, 20, 5)]
     assert np.allclose(out[rows], want[rows], rtol=0, atol=2e-4) and np.allclose(out[5] / want[5], 1.0, rtol=1e-5)
+
+
+def wide_products(dn, big, variant):
+    """Numbers `big` that meet only zeros, so no result holds them: feature 9 has zero weights, sample 4 has feature 30 large
+    and a delta of zero in every output but one, output 70 has zero weights and a large bias."""
+    import torch
+    B, K, N = 130, 200, 110
+    rng = np.random.default_rng(11)
+    X, W = rng.standard_normal((B, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    bias = np.zeros(N, np.float32)
+    W[:, 9] = 0.0
+    X[:, 9] = big
+    X[4] = 0.0
+    X[4, 30] = big
+    W[:, 30] = 0.0
+    W[70] = 0.0
+    bias[70] = big
+    net = dn.Net([K, N], [LINEAR], MSE, B)
+    net.dn_set_params(1, W, bias)
+    net.dn_set_option("gemm_variant", variant)
+    Xd, y = torch.from_numpy(X).cuda(), torch.zeros(B, dtype=torch.int32, device="cuda")
+    out, dX = torch.empty((B, N), device="cuda"), torch.empty((B, K), device="cuda")
+    net.dn_forward(Xd, out)
+    net.dn_backward(y)
+    net.dn_input_gradient(dX)
+    G, _ = net.dn_get_grads(1)
+    out, dX = out.cpu().numpy(), dX.cpu().numpy()
+    delta = out.copy()
+    delta[:, 0] -= 1.0
+    return X, W, bias, out, G, dX, delta
+
+
+def close_to_terms(got, A, B, scale, what):
+    """got against scale * A B in 64 bits, every element within the roundings of its own terms: nothing is allowed for the
+    largest numbers of its row or column."""
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    bound = abs(scale) * ((A.shape[1] / 2 + 44) * 2.0 ** -24 + 2.0 ** -21) * (np.abs(A) @ np.abs(B))
+    err = np.abs(got - scale * (A @ B))
+    assert np.all(err <= bound + 1e-44), "%s: %g times the bound" % (what, np.max(err / (bound + 1e-44)))
+
+
+@pytest.mark.parametrize("variant", [-1, 13, 14, 15, 16, 17])
+@pytest.mark.parametrize("big", [1e9, 1e12, 1e15, 1e22, 1e30])
+def test_large_numbers_against_zeros(dnlib, big, variant):
+    X, W, bias, out, G, dX, delta = wide_products(dnlib, np.float32(big), variant)
+    others = np.arange(110) != 70
+    close_to_terms(out[:, others], X, W[others].T, 1.0, "forward")
+    assert np.all(out[:, 70] == bias[70])
+    close_to_terms(G[others], delta[:, others].T, X, 1.0 / X.shape[0], "gradient")   # (row 70 overflows)
+    close_to_terms(dX, delta, W, 1.0, "input gradient")
+
+
+@pytest.mark.parametrize("variant", [13, 14, 15, 16])
+@pytest.mark.parametrize("shape", [(130, 200, 110), (129, 203, 111), (1300, 64, 40), (2100, 131, 33)])
+def test_slices_left_for_fp32(dnlib, shape, variant):
+    """Numbers of very different size along k: some slices, a run of them, or from one on all go to the fp32 instruction;
+    more slices than a wave counts one by one."""
+    B, K, N = shape
+    rng = np.random.default_rng(B)
+    for part in ("one sample in forty", "a tenth", "the second half", "all"):
+        X, W = rng.standard_normal((B, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+        rows = {"one sample in forty": slice(5, None, 40), "a tenth": slice(B // 3, B // 3 + B // 10),
+                "the second half": slice(B // 2, None), "all": slice(None)}[part]
+        X[rows] *= (10.0 ** rng.uniform(-14, 0, X[rows].shape)).astype(np.float32)
+        out, G, g, dX, delta = products(dnlib, X, W, variant)
+        close_to_terms(out, X, W.T, 1.0, part + ": forward")
+        close_to_terms(G, delta.T, X, 1.0 / B, part + ": gradient")
+        close_to_terms(g[:, None], delta.T, np.ones((B, 1), np.float32), 1.0 / B, part + ": bias gradient")
+        close_to_terms(dX, delta, W, 1.0, part + ": input gradient")
