@@ -7,6 +7,7 @@
 // cores (corr3_split_kernel and corr_mfma_kernel), with square filters of odd edge the filter gradient too (conv_dw_mfma_kernel);
 // everything else uses register-tiled vector kernels.
 #include <atomic>
+#include <climits>
 #include <mutex>
 
 #include "dn_internal.h"
@@ -393,17 +394,21 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
     }
 }
 
+__device__ __forceinline__ float uniform(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
 // 3 x 3 filters: the same correlation on the f16 matrix instruction (how a number is split: dn_split.h).  A k slice of an
 // instruction is sixteen input channels at one tap, so a staged number is split once and serves nine taps; that keeps the
 // splitting, which bounds the fully connected products, to a tenth of the work here.  Sixteen channels are staged at a
 // time, both operands as pieces of eight channels (16 bytes, one per plane): the input as [half of the channels][pixel
 // of the patch], the filters as [half, tap][output channel]; every operand of an instruction is then one conflict-free
 // 16-byte LDS read per lane.  One scale for the workgroup's patch and one for its filters, from their largest numbers.
-// Where most numbers of a stage are too small beside its largest one to keep their bits, or a sum is not finite, the
-// outputs are summed again in fp32.
+// A stage with a number, other than zero, too small beside them to keep its bits (2^-25) is left out; so are all stages
+// where a sum is not finite.  What was left is staged afterwards as it is, in fp32 in the place of the two planes (four
+// channels of a piece in either), and multiplied by the fp32 instruction.
 // Bound: half matrix instructions (384 cycles a tap and compute unit), half LDS reads (256), staging between two
-// workgroups.  128 x 32 x 32 x 32 -> 64 channels, us (fp32 instruction / this): forward and
-// input gradient together 125 / 86.
+// workgroups.  128 x 32 x 32 x 32 -> 64 channels, forward, us (fp32 instruction / this): 71 / 54; with numbers of twelve
+// decades everywhere, or an output channel far below the others, so that all stages are left: 67 / 88 to 94; with a NaN in
+// every image 70 / 97.
 template <int OT, int RW, int TW>
 __global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const float *__restrict__ In,
                                                              const float *__restrict__ Wt, const float *__restrict__ bias,
@@ -425,7 +430,15 @@ __global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const 
     constexpr int XU = (2 * NPIX + 255) / 256, WU = (18 * OC + 255) / 256;   // staged pieces per thread
     v4f xr[XU][2], wr[WU][2];
     // (a uniform base per channel and one 32-bit byte offset per piece: the sizes that reach this kernel keep it in range)
+    // (the staging indices are recomputed from the thread index every time rather than kept in registers: the empty asm hides
+    // that they repeat)
+    auto thread = [] {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
     auto request = [&](int ic0) {
+        const int tid = thread();
         const char *xbase = reinterpret_cast<const char *>(image + (size_t)ic0 * plane);
         const char *wbase = reinterpret_cast<const char *>(Wt + (size_t)ic0 * 9);
 #pragma unroll
@@ -457,94 +470,121 @@ __global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const 
             for (int r = 0; r < 16; ++r) acc[t][q][r] = small[t][q][r] = 0.f;
     int exp_x = 0, exp_w = 0;              // operands enter as 2^exp x
     float room_x = 0.f, room_w = 0.f;      // largest number that fits
-    bool again = false;                    // sum the outputs once more in fp32
+    unsigned key_x = 0, key_w = 0;         // smallest number that keeps its bits, by its key ...
+    float low_w = 0.f;                     // ... and the number
+    int first_x = 0, first_w = 0;          // the first exponents
+    // stages left for the fp32 instruction, in 64 groups: lane g holds the first one of group g that is left (the rest of
+    // the group is left with it); once a quarter and two are left, so are all further ones
+    const int stages = (s.Cin + 15) / 16, group = (stages + 63) / 64;
+    int left = INT_MAX, left_until = 0, left_sum = 0;
     request(0);
-    for (int ic0 = 0, stage = 1; ic0 < s.Cin; ic0 += 16, ++stage) {
-        float mx = 0.f, mw = 0.f;
+    for (int stage = 0; stage < stages; ++stage) {
+        const float mark = (float)(stage + 1);
+        float mx = 0.f, mw = 0.f, lw = INFINITY;
+        unsigned kx = ~0u, kw = ~0u;
 #pragma unroll
-        for (int m = 0; m < XU; ++m) mx = fmaxf(mx, largest(xr[m][0], xr[m][1]));
+        for (int m = 0; m < XU; ++m) mx = fmaxf(mx, largest(xr[m][0], xr[m][1])), kx = min(kx, least_key(xr[m][0], xr[m][1]));
 #pragma unroll
-        for (int m = 0; m < WU; ++m) mw = fmaxf(mw, largest(wr[m][0], wr[m][1]));
-        if (__any(mx > room_x || mw > room_w) && lane == 0) red[0] = (float)stage;
-        __syncthreads();   // the previous stage has been used; red[0] is set if any thread's numbers have outgrown a scale
-        if (red[0] == (float)stage) {
+        for (int m = 0; m < WU; ++m) mw = fmaxf(mw, largest(wr[m][0], wr[m][1])), lw = fminf(lw, smallest(wr[m][0], wr[m][1]));
+        auto filter_key = [&] {
+#pragma unroll
+            for (int m = 0; m < WU; ++m) kw = min(kw, least_key(wr[m][0], wr[m][1]));
+        };
+        bool odd = mx > room_x;
+        odd |= kx < key_x;
+        odd |= mw > room_w;
+        if (__any(lw < low_w)) {   // (the filters of a ragged tile have zeros)
+            filter_key();
+            odd |= kw < key_w;
+        }
+        if (__any(odd) && lane == 0) red[0] = mark;
+        __syncthreads();   // the previous stage has been used; red[0] is set if any thread's numbers do not fit
+        bool leave = stage < left_until;
+        if (!leave && uniform(red[0]) == mark) {
+            filter_key();
             const float wx = wave_max(mx), ww = wave_max(mw);
             if (lane == 0) { red[4 + wave] = wx; red[8 + wave] = ww; }
             __syncthreads();
-            const float gx = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7])), gw = fmaxf(fmaxf(red[8], red[9]), fmaxf(red[10], red[11]));
-            int shift = 0;
-            auto fit = [&](float g, int &e, float &room) {
-                if (!(g > room && g < INFINITY)) return;
-                const int fresh = 12 - max(__builtin_amdgcn_frexp_expf(g), -100);   // 2^fresh g is in [2^11, 2^12)
-                if (stage > 1) shift += fresh - e;
-                e = fresh;
-                room = __builtin_ldexpf(1.f, 15 - e);
+            const float gx = uniform(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7])));
+            const float gw = uniform(fmaxf(fmaxf(red[8], red[9]), fmaxf(red[10], red[11])));
+            auto fit = [](float g, float room, int e) {   // 2^e g is in [2^13, 2^14)
+                return g > room && g < INFINITY ? 14 - max(__builtin_amdgcn_frexp_expf(g), -98) : e;
             };
-            fit(gx, exp_x, room_x);
-            fit(gw, exp_w, room_w);
-            // numbers of this stage, and those that keep all their bits (down to 2^-25 of the largest)
-            float some_x = 0.f, good_x = 0.f, some_w = 0.f, good_w = 0.f;
-            const float least_x = __builtin_ldexpf(1.f, -14 - exp_x), least_w = __builtin_ldexpf(1.f, -14 - exp_w);
-#pragma unroll
-            for (int m = 0; m < XU; ++m)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float a = fabsf(xr[m][j / 4][j % 4]);
-                    some_x += a > 0.f ? 1.f : 0.f;
-                    good_x += a >= least_x ? 1.f : 0.f;
-                }
-#pragma unroll
-            for (int m = 0; m < WU; ++m)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float a = fabsf(wr[m][j / 4][j % 4]);
-                    some_w += a > 0.f ? 1.f : 0.f;
-                    good_w += a >= least_w ? 1.f : 0.f;
-                }
-            some_x = wave_sum(some_x), good_x = wave_sum(good_x), some_w = wave_sum(some_w), good_w = wave_sum(good_w);
-            if (lane == 0) { red[12 + wave] = 2.f * good_x - some_x; red[16 + wave] = 2.f * good_w - some_w; }
+            const int ex = __builtin_amdgcn_readfirstlane(fit(gx, room_x, exp_x)), ew = __builtin_amdgcn_readfirstlane(fit(gw, room_w, exp_w));
+            auto power = [](int e) { return (unsigned)min(e + 127, 255) << 23; };   // 2^e (or infinity) in bits
+            auto key_of = [&](int e) { return 2 * power(-14 - e) - 1; };
+            const bool has_x = room_x > 0.f || gx > 0.f, has_w = room_w > 0.f || gw > 0.f;
+            if (__any((has_x && kx < key_of(ex)) || (has_w && kw < key_of(ew))) && lane == 0) red[2] = mark;
             __syncthreads();
-            again |= !(gx < INFINITY && gw < INFINITY) || red[12] + red[13] + red[14] + red[15] < 0.f || red[16] + red[17] + red[18] + red[19] < 0.f;
-            if (shift != 0) {
+            if (uniform(red[2]) == mark) {
+                leave = true;
+                const int g = stage / group;
+                if (lane == g) left = stage;
+                left_until = min((g + 1) * group, stages);
+                left_sum += left_until - stage;
+                if (left_sum > 2 + stages / 4) {
+                    if (lane > g) left = lane * group;
+                    left_until = stages;
+                }
+            } else {
+                int shift = 0;
+                if (has_x) {
+                    if (room_x > 0.f) shift += ex - exp_x;
+                    else first_x = ex;
+                    exp_x = ex, room_x = __uint_as_float(power(15 - ex)), key_x = key_of(ex);
+                }
+                if (has_w) {
+                    if (room_w > 0.f) shift += ew - exp_w;
+                    else first_w = ew;
+                    exp_w = ew, room_w = __uint_as_float(power(15 - ew)), key_w = key_of(ew), low_w = __uint_as_float(power(-14 - ew));
+                }
+                if (shift != 0) {
+                    const float factor = shift > -126 ? __uint_as_float(power(shift)) : 0.f;
 #pragma unroll
-                for (int t = 0; t < OT; ++t)
+                    for (int t = 0; t < OT; ++t)
 #pragma unroll
-                    for (int q = 0; q < RW; ++q)
+                        for (int q = 0; q < RW; ++q)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            acc[t][q][r] = __builtin_ldexpf(acc[t][q][r], shift);
-                            small[t][q][r] = __builtin_ldexpf(small[t][q][r], shift);
-                        }
+                            for (int r = 0; r < 16; ++r) {
+                                acc[t][q][r] *= factor;
+                                small[t][q][r] *= factor;
+                            }
+                }
             }
         }
-        const float scale_x = __builtin_ldexpf(1.f, exp_x), scale_w = __builtin_ldexpf(1.f, exp_w);
+        if (leave && left_until == stages) break;
+        if (!leave) {
+            const int tid = thread();
+            const float scale_x = __builtin_ldexpf(1.f, exp_x), scale_w = __builtin_ldexpf(1.f, exp_w);
 #pragma unroll
-        for (int m = 0; m < XU; ++m) {
-            const int e = tid + 256 * m;
-            v8h f[2];
-            split_eight(xr[m][0], xr[m][1], scale_x, f);
-            if (e < 2 * NPIX) {
-                *reinterpret_cast<v8h *>(pl + e * 16) = f[0];
-                *reinterpret_cast<v8h *>(pl + PPLANE + e * 16) = f[1];
+            for (int m = 0; m < XU; ++m) {
+                const int e = tid + 256 * m;
+                v8h f[2];
+                split_eight(xr[m][0], xr[m][1], scale_x, f);
+                if (e < 2 * NPIX) {
+                    *reinterpret_cast<v8h *>(pl + e * 16) = f[0];
+                    *reinterpret_cast<v8h *>(pl + PPLANE + e * 16) = f[1];
+                }
             }
-        }
 #pragma unroll
-        for (int m = 0; m < WU; ++m) {
-            const int e = tid + 256 * m, tap = e % 9, half = (e / 9) & 1, oc = e / 18;
-            v8h f[2];
-            split_eight(wr[m][0], wr[m][1], scale_w, f);
-            if (e < 18 * OC) {
-                char *dst = wl + (half * 9 + tap) * WPITCH + oc * 16;
-                *reinterpret_cast<v8h *>(dst) = f[0];
-                *reinterpret_cast<v8h *>(dst + WPLANE) = f[1];
+            for (int m = 0; m < WU; ++m) {
+                const int e = tid + 256 * m, tap = e % 9, half = (e / 9) & 1, oc = e / 18;
+                v8h f[2];
+                split_eight(wr[m][0], wr[m][1], scale_w, f);
+                if (e < 18 * OC) {
+                    char *dst = wl + (half * 9 + tap) * WPITCH + oc * 16;
+                    *reinterpret_cast<v8h *>(dst) = f[0];
+                    *reinterpret_cast<v8h *>(dst + WPLANE) = f[1];
+                }
             }
+            __syncthreads();
         }
-        __syncthreads();
-        if (ic0 + 16 < s.Cin) request(ic0 + 16);
+        if (stage + 1 < stages) request(16 * stage + 16);
+        if (leave) continue;
         __builtin_amdgcn_sched_barrier(0);
         const char *wa = wl + h * 9 * WPITCH + idx * 16;
         const char *pb = pl + (h * NPIX + (RW * wave * RPT + idx / TW) * PCOL + idx % TW) * 16;
-#pragma unroll
+#pragma unroll 1   // (unrolled, the loop takes more registers than there are)
         for (int u = 0; u < 3; ++u)
 #pragma unroll
             for (int v = 0; v < 3; ++v) {
@@ -585,7 +625,72 @@ __global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const 
                 acc[t][q][r] = __builtin_ldexpf(__builtin_fmaf(small[t][q][r], 0x1p-11f, acc[t][q][r]), -exp_x - exp_w);
                 probe = __builtin_fmaf(acc[t][q][r], 0.f, probe);
             }
-    again |= __any(probe != 0.f) != 0;
+    // not finite, or a scale that has moved so far that the smallest products could leave fp32's range
+    if (__any(probe != 0.f || first_x - exp_x > 45 || first_w - exp_w > 45) && lane == 0) red[1] = (float)(stages + 1);
+    __syncthreads();
+    if (uniform(red[1]) == (float)(stages + 1)) {
+        left = lane * group;
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int q = 0; q < RW; ++q)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][q][r] = 0.f;
+    }
+    // the stages that were left: channel c of one half of the lanes with channel c of the other
+    unsigned long long groups = __ballot(left < stages);
+    if (groups != 0) {
+        auto first_left = [&] { return __builtin_amdgcn_readlane(left, __builtin_ctzll(groups)); };
+        int stage = first_left();
+        request(16 * stage);
+        while (groups != 0) {
+            const int tid = thread();
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < XU; ++m) {
+                const int e = tid + 256 * m;
+                if (e < 2 * NPIX) {
+                    *reinterpret_cast<v4f *>(pl + e * 16) = xr[m][0];
+                    *reinterpret_cast<v4f *>(pl + PPLANE + e * 16) = xr[m][1];
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < WU; ++m) {
+                const int e = tid + 256 * m, tap = e % 9, half = (e / 9) & 1, oc = e / 18;
+                if (e < 18 * OC) {
+                    char *dst = wl + (half * 9 + tap) * WPITCH + oc * 16;
+                    *reinterpret_cast<v4f *>(dst) = wr[m][0];
+                    *reinterpret_cast<v4f *>(dst + WPLANE) = wr[m][1];
+                }
+            }
+            __syncthreads();
+            if (++stage >= min((__builtin_ctzll(groups) + 1) * group, stages)) {
+                groups &= groups - 1;
+                if (groups != 0) stage = first_left();
+            }
+            if (groups != 0) request(16 * stage);
+#pragma unroll 1
+            for (int tap = 0; tap < 9; ++tap) {
+                const int u = tap / 3, v = tap % 3;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    v4f fw[OT], fx[RW];
+#pragma unroll
+                    for (int t = 0; t < OT; ++t) fw[t] = *reinterpret_cast<const v4f *>(wl + (h * 9 + tap) * WPITCH + idx * 16 + p * WPLANE + t * 512);
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+                        fx[q] = *reinterpret_cast<const v4f *>(pl + (h * NPIX + ((RW * wave + q) * RPT + idx / TW + u) * PCOL + idx % TW + v) * 16 + p * PPLANE);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int t = 0; t < OT; ++t)
+#pragma unroll
+                            for (int q = 0; q < RW; ++q)
+                                acc[t][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[t][c], fx[q][c], acc[t][q], 0, 0, 0);
+                }
+            }
+        }
+    }
     const int j = j0 + idx % TW;
     if (j >= s.Wo) return;
 #pragma unroll
@@ -598,19 +703,7 @@ __global__ __launch_bounds__(256, 2) void corr3_split_kernel(CorrShape s, const 
             for (int r = 0; r < 16; ++r) {
                 const int oc = oc0 + 32 * t + 8 * (r >> 2) + 4 * h + (r & 3);
                 if (oc >= s.Cout) continue;
-                float sum = acc[t][q][r];
-                if (again) {
-                    sum = 0.f;
-                    for (int ic = 0; ic < s.Cin; ++ic)
-                        for (int u = 0; u < 3; ++u)
-                            for (int v = 0; v < 3; ++v) {
-                                const int y = i + u - s.pad_h, x = j + v - s.pad_w;
-                                if (y >= 0 && y < s.H && x >= 0 && x < s.W)
-                                    sum = fmaf(Wt[(size_t)oc * s.w_out_stride + (size_t)(ic * 9 + u * 3 + v)],
-                                               image[(size_t)ic * plane + (unsigned)(y * s.W + x)], sum);
-                            }
-                }
-                Out[(((size_t)b * s.Cout + oc) * s.Ho + i) * s.Wo + j] = conv_act(s.act, sum + (bias ? bias[oc] : 0.f));
+                Out[(((size_t)b * s.Cout + oc) * s.Ho + i) * s.Wo + j] = conv_act(s.act, acc[t][q][r] + (bias ? bias[oc] : 0.f));
             }
     }
 }

@@ -91,3 +91,40 @@ def test_infinities_and_nan(dnlib):
     assert np.array_equal(np.isnan(Y), np.isnan(want)) and np.array_equal(np.isposinf(Y), np.isposinf(want))
     fine = np.isfinite(want)
     assert np.array_equal(np.isfinite(Y), fine) and np.allclose(Y[fine], want[fine], rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("small", [1e-8, 1e-11, 1e-13, 1e-16, 1e-30])
+@pytest.mark.parametrize("case", ["later channels", "part of an image", "one output channel", "one input channel's filters",
+                                  "beside one weight", "beside one pixel"])
+def test_small_numbers_beside_large_ones(dnlib, case, small):
+    """Every output is within the roundings of its own terms, however small they are beside other numbers of the tile."""
+    X, W, dA = draw(2, 64, 18, 34, 40, 1)
+    small = np.float32(small)
+    if case == "later channels":          # the large channels meet zero weights, the first one's weights meet zeros
+        X[:, 16:] *= small
+        X[:, 0] = 0.0
+        W[:, 1:16] = 0.0
+        dA[:, 16:] *= small
+        dA[:, 0] = 0.0
+        W[1:16] = 0.0
+    elif case == "part of an image":
+        X[:, :, :, :12] *= small
+        dA[:, :, :, :12] *= small
+    elif case == "one output channel":    # and, in the input gradient, its part of every sum alone
+        W[7] *= small
+        dA[0] = 0.0
+        dA[0, 7] = draw(1, 64, 18, 34, 40, 1, seed=4)[2][0, 7]
+    elif case == "beside one weight":     # of a later stage, which meets zeros
+        W[37, 20], X[:, 20], dA[:, 37] = 1.0 / small, 0.0, 0.0
+    elif case == "beside one pixel":
+        X[0, 20, 9, 9], W[:, 20] = 1.0 / small, 0.0
+        dA[1, 18, 3, 30], W[18] = 1.0 / small, 0.0
+    else:
+        W[:, 9] *= small
+        X[1] = 0.0
+        X[1, 9] = draw(1, 64, 18, 34, 40, 1, seed=4)[0][0, 9]
+    Y, dX = run(dnlib, X, W, dA, 1)
+    wantY, wantdX = reference(X, W, dA, 1)
+    magY, magdX = reference(np.abs(X), np.abs(W), np.abs(dA), 1)
+    close(Y, wantY, magY, 9 * 64 * 16, 1e-44, "forward")
+    close(dX, wantdX, magdX, 9 * 40 * 16, 1e-44, "input gradient")
