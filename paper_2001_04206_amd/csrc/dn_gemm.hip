@@ -1340,12 +1340,12 @@ static bool vec_ok(GemmKind kind, const GemmArgs &a)
 // 7.0e-8, k = 77 9.8e-8 / 9.0e-8, k = 128 1.0e-7 / 2.0e-7, k = 1024 1.2e-7 / 2.9e-7, k = 4096 2.2e-7 / 8.1e-7).
 constexpr int kSplitMinK = 96;
 
-// A large weight gradient over a short k: few slices a wave, so the partial tiles of two waves instead of four
-// (4096 x 4096, k = 256 with momentum: 71 us against 83; 1024 x 1024, k = 512, which has 256 tiles: 16.6 against 11.8).
-// Between 640 and 1024 tiles also for a k up to 512: 768 tiles are one and a half rounds of the four-wave tile's 512
-// places but fit the two-wave tile's 1024 at once (three 1024 x 1024 layers at batch 512: a step 103.7 -> 101 us).
-static bool large_short_grad(long tiles64, int k) { return (tiles64 >= 1024 && k <= 384) || (tiles64 >= 640 && k <= 512); }
-
+// A large weight gradient over a short k: few slices a wave, so the partial tiles of two waves instead of four.  Measured on
+// whole training steps, two waves against four, single launches and several layers in one: at 640, 704, 768, 896, 1024,
+// 4096 and 8192 tiles faster for every k from 64 to 512 (1 to 18 %; 640 tiles at k = 512 64.8 -> 63.1 us, 1024 at 384
+// 72.9 -> 71.8, at 512 82.1 -> 81.2), at 2048 tiles up to k = 384 (13 to 0 %; at 512 from 1.5 % faster to 2.5 %
+// slower); at 512 tiles slower from k = 128 on (36.6 -> 38.7 us at 256: they fit the four-wave tile's 512 places at once).
+// At k = 640 the two differ by 4 % either way.
 // Tile shape from the problem shape.
 // Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
 // compute units have one, or, for a long k, once k split across workgroups gives them one; below that smaller tiles
