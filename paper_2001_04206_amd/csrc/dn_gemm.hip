@@ -1346,6 +1346,8 @@ constexpr int kSplitMinK = 96;
 // 72.9 -> 71.8, at 512 82.1 -> 81.2), at 2048 tiles up to k = 384 (13 to 0 %; at 512 from 1.5 % faster to 2.5 %
 // slower); at 512 tiles slower from k = 128 on (36.6 -> 38.7 us at 256: they fit the four-wave tile's 512 places at once).
 // At k = 640 the two differ by 4 % either way.
+static bool large_short_grad(long tiles64, int k) { return tiles64 >= 640 && k <= 512; }
+
 // Tile shape from the problem shape.
 // Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
 // compute units have one, or, for a long k, once k split across workgroups gives them one; below that smaller tiles
