@@ -1228,27 +1228,33 @@ static bool vec_pieces(const GemmArgs &a)
     return a_vec && b_vec && a.lda <= 1 << 23 && a.ldb <= 1 << 23;
 }
 
+// Forward and delta products with few output tiles and a long k: k is split across workgroups until about two per CU are
+// busy.
+template <class T>
+static int k_splits(const GemmArgs &a)
+{
+    const long nt = (long)((a.M + T::BM - 1) / T::BM) * ((a.N + T::BN - 1) / T::BN);
+    if (!a.ws || !a.counters || nt >= 256 || nt > a.n_counters) return 1;
+    const int nk = (a.K + T::KT - 1) / T::KT;
+    int sk = (int)(256 / nt);
+    if (sk > 16) sk = 16;
+    if (sk > nk / 2) sk = nk / 2;          // at least two k steps each
+    while (sk > 1 && (size_t)nt * sk * std::max(T::BM * T::BN, 4 * T::NT) > a.ws_floats) --sk;
+    if (sk > 1) {
+        const int per = (nk + sk - 1) / sk;
+        sk = (nk + per - 1) / per;         // no empty splits
+    }
+    return sk > 1 ? sk : 1;
+}
+
 template <class T, bool A_KC, bool B_KC, int EPI, bool VEC>
 static hipError_t launch_vec(const GemmArgs &a, hipStream_t stream)
 {
     const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
     const long nt = (long)tiles_m * tiles_n;
-    // Few output tiles and a long k: split k across workgroups until about two per CU are busy.
     GemmArgs b = a;
-    b.sk = 1;
+    b.sk = EPI <= EPI_DELTA ? k_splits<T>(a) : 1;
     b.vec = vec_pieces<A_KC, B_KC>(a);
-    if (EPI <= EPI_DELTA && a.ws && a.counters && nt < 256 && nt <= a.n_counters) {
-        const int nk = (a.K + T::KT - 1) / T::KT;
-        int sk = (int)(256 / nt);
-        if (sk > 16) sk = 16;
-        if (sk > nk / 2) sk = nk / 2;          // at least two k steps each
-        while (sk > 1 && (size_t)nt * sk * std::max(T::BM * T::BN, 4 * T::NT) > a.ws_floats) --sk;
-        if (sk > 1) {
-            const int per = (nk + sk - 1) / sk;
-            sk = (nk + per - 1) / per;         // no empty splits
-        }
-        b.sk = sk > 1 ? sk : 1;
-    }
     const long grid = 8 * ((nt * b.sk + 7) / 8);
     if (grid <= 0 || grid > 0x7fffffffL) return hipErrorInvalidValue;
     constexpr size_t lds = smem_bytes<T, A_KC, B_KC>();
@@ -1335,11 +1341,6 @@ static bool vec_ok(GemmKind kind, const GemmArgs &a)
     return kind == GEMM_FWD ? vec_pieces<true, true>(a) : kind == GEMM_DELTA ? vec_pieces<true, false>(a) : vec_pieces<false, false>(a);
 }
 
-// Sums of fewer terms than this stay on the fp32 instruction: an operand of the split kernels keeps 22 to 23 bits, which
-// only counts while the sum itself is rounded a few times (error against 64 bits, split / fp32: k = 37 9.4e-8 /
-// 7.0e-8, k = 77 9.8e-8 / 9.0e-8, k = 128 1.0e-7 / 2.0e-7, k = 1024 1.2e-7 / 2.9e-7, k = 4096 2.2e-7 / 8.1e-7).
-constexpr int kSplitMinK = 96;
-
 // A large weight gradient over a short k: few slices a wave, so the partial tiles of two waves instead of four.  Measured on
 // whole training steps, two waves against four, single launches and several layers in one: at 640, 704, 768, 896, 1024,
 // 4096 and 8192 tiles faster for every k from 64 to 512 (1 to 18 %; 640 tiles at k = 512 64.8 -> 63.1 us, 1024 at 384
@@ -1347,6 +1348,24 @@ constexpr int kSplitMinK = 96;
 // slower); at 512 tiles slower from k = 128 on (36.6 -> 38.7 us at 256: they fit the four-wave tile's 512 places at once).
 // At k = 640 the two differ by 4 % either way.
 static bool large_short_grad(long tiles64, int k) { return tiles64 >= 640 && k <= 512; }
+
+// Which sums go to the fp32 instruction: those whose waves add at most 23 terms in a row there (two accumulators in each of
+// four waves, or two for large gradients, and the k split among workgroups make so many runs of a sum), and of large forward
+// and delta products those of fewer than 96 terms.  An operand in pairs keeps 22 to 23 bits, which only counts while the
+// sum itself is rounded a few times, and a slice in pairs costs tests and splitting.  Error against 64 bits, 1e-8 of the
+// 2-norm, operands N(0,1) / one of them through ReLU, pairs against fp32: forward 128 x 1024, k = 128 (8 in a row) 10.5 /
+// 10.4 against 8.9 / 7.4, k = 256 10.7 / 10.5 against 9.3 / 7.9, k = 512 (32) 11.0 / 11.0 against 11.7 / 9.4; 512 x 1024,
+// k = 512 (64) 11.0 / 10.9 against 15.2 / 11.4; gradient 1024 x 1024, k = 192 (24) 10.1 / 6.1 against 10.3 / 6.0, k = 512
+// 9.8 / 5.2 against 12.9 / 5.2.  Time, us: forward 32 x 1024, k = 512 7.4 against 6.5; 128 x 256, k = 784 8.8 against 7.2;
+// 512 x 1024, k = 128 7.2 against 4.9; gradient 512 x 512, k = 128 5.7 against 4.6; forward 2048 x 1024 (large), k = 128
+// 12.3 against 12.9, k = 256 13.3 against 16.4.
+constexpr int kFp32Run = 23, kPairsMinK = 96;
+
+static bool in_pairs(GemmKind kind, const GemmArgs &a, long tiles64)
+{
+    if (kind == GEMM_GRAD) return a.K > kFp32Run * (large_short_grad(tiles64, a.K) ? 4 : 8);
+    return tiles64 >= 192 ? a.K >= kPairsMinK : a.K > kFp32Run * 8 * k_splits<S5>(a);
+}
 
 // Tile shape from the problem shape.
 // Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
@@ -1363,7 +1382,7 @@ static int pick_variant(GemmKind kind, const GemmArgs &a)
 {
     auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     const long t64 = tiles(64, 64);
-    if (a.K >= kSplitMinK) {
+    if (in_pairs(kind, a, t64)) {
         if (kind == GEMM_GRAD && large_short_grad(t64, a.K)) return 16;
         if (t64 >= (kind == GEMM_GRAD ? 128 : 192)) return 13;
         if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 13;
@@ -1404,7 +1423,10 @@ static hipError_t launch_delta_narrow_as(const GemmArgs &delta, const GemmArgs &
 // one launch (they do not depend on each other); call only if delta_narrow_grad_fits.
 hipError_t launch_delta_with_narrow_grad(const GemmArgs &delta, const GemmArgs &grad, hipStream_t stream)
 {
-    return delta.K >= kSplitMinK ? launch_delta_narrow_as<S4>(delta, grad, stream) : launch_delta_narrow_as<S5>(delta, grad, stream);
+    GemmArgs d = delta;
+    d.ws = nullptr;   // (this launch does not split k)
+    return in_pairs(GEMM_DELTA, d, (long)((d.M + 63) / 64) * ((d.N + 63) / 64)) ? launch_delta_narrow_as<S4>(delta, grad, stream)
+                                                                               : launch_delta_narrow_as<S5>(delta, grad, stream);
 }
 
 // ---- the gradients of several layers in one launch ---------------------------------------
@@ -1504,7 +1526,10 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
                 ++m.n;
             }
         }
-        const int k = m.g[0].K, edge = k < kSplitMinK ? S5::BM : S0::BM;
+        const int k = m.g[0].K;
+        const long tiles64 = multi_grad_tiles(grads, n);
+        const bool large = large_short_grad(tiles64, k), pairs = in_pairs(GEMM_GRAD, m.g[0], tiles64);
+        const int edge = pairs ? S0::BM : S5::BM;
         static_assert(S0::BM == S3::BM && S0::BN == S3::BN && S0::BM == S0::BN && S5::BM == S5::BN, "square tiles of one size");
         long at = 0;
         for (int p = 0; p < m.n; ++p) {
@@ -1521,9 +1546,8 @@ hipError_t launch_gemm_grads(const GemmArgs *grads, int n, int variant, bool mer
             at += m.narrow_blocks;
         }
         if (at > 0x7fffffffL) return hipErrorInvalidValue;
-        const bool large = large_short_grad(multi_grad_tiles(grads, n), k);
         const int mode = grads[0].mode;
-        const hipError_t e = k < kSplitMinK ? (large ? launch_multi_mode<S6>(m, mode, (unsigned)at, stream) : launch_multi_mode<S5>(m, mode, (unsigned)at, stream))
+        const hipError_t e = !pairs ? (large ? launch_multi_mode<S6>(m, mode, (unsigned)at, stream) : launch_multi_mode<S5>(m, mode, (unsigned)at, stream))
                                             : (large ? launch_multi_mode<S3>(m, mode, (unsigned)at, stream) : launch_multi_mode<S0>(m, mode, (unsigned)at, stream));
         if (e != hipSuccess) return e;
     }

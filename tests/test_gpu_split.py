@@ -213,3 +213,30 @@ def test_updates_in_the_epilogue(dnlib, mu, variant):
 @pytest.mark.parametrize("B,mu", [(101, 0.9), (101, 0.0), (41, 0.9)])
 def test_merged_gradients_of_odd_widths(dnlib, widths, B, mu):
     parity.test_merged_backward_launches(dnlib, widths, [parity.TANH, parity.TANH, parity.SOFTMAX], parity.CE, B, mu, 1)
+
+
+# either side of the line between the fp32 instruction and pairs, as the library picks: one k split and several, gradients
+# small and large, the launches that join a narrow layer's gradient with a delta product and several gradients
+@pytest.mark.parametrize("B,K,N", [(100, 184, 300), (100, 185, 300), (40, 1288, 520), (40, 1289, 520), (184, 96, 300), (185, 97, 300),
+                                   (92, 2560, 1024), (93, 2560, 1024), (2048, 96, 384), (2048, 95, 384)])
+def test_either_side_of_the_line(dnlib, B, K, N):
+    rng = np.random.default_rng(B + K)
+    check(dnlib, rng.standard_normal((B, K), dtype=np.float32), rng.standard_normal((N, K), dtype=np.float32), -1)
+
+
+@pytest.mark.parametrize("widths,B", [([516, 1040, 184, 12], 184), ([516, 1040, 188, 12], 188), ([1028, 1040, 1100, 24], 184), ([1028, 1040, 1100, 24], 188)])
+def test_joined_launches_either_side_of_the_line(dnlib, widths, B):
+    parity.test_merged_backward_launches(dnlib, widths, [parity.TANH, parity.RELU, parity.SOFTMAX], parity.CE, B, 0.9, 1)
+
+
+def test_short_sums_lose_nothing(dnlib):
+    """Fewer than 184 terms a run of one tile: no further from 64 bits than fp32 sums in 8 runs of 23 terms (pairs are: 1.0e-7)."""
+    import torch
+    torch.manual_seed(0)
+    X, W = torch.randn(512, 128, device="cuda").relu_(), torch.randn(1024, 128) * 0.125
+    net = dnlib.Net([128, 1024], [LINEAR], MSE, 512)
+    net.dn_set_params(1, W.numpy(), np.zeros(1024, np.float32))
+    out = torch.empty(512, 1024, device="cuda")
+    net.dn_forward(X, out)
+    want = X.double() @ W.cuda().double().t()
+    assert ((out.double() - want).norm() / want.norm()).item() < 8.5e-8
