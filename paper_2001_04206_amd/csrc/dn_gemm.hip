@@ -654,13 +654,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g0, float *smem, const
 }
 
 // Work of one workgroup on the tile at (m0, n0) with the products on the f16 matrix instruction (dn_split.h).
-// What bounds it: power.  With both the matrix cores and the vector unit busy the chip lowers its clock to 1.5 - 2.0
-// GHz, so every operand byte moved to LDS and every instruction that splits counts, whether or not it is hidden: at 256
-// x 4096, k = 4096 the operand loads are worth 15 us of 56, the splitting 14, the matrix instructions 8.  Hence the
-// largest tile whose sums fit a wave's registers (64 x 64: 128 registers of sums), operands straight into LDS as fp32
-// (one write and one read of LDS per number) and the split in registers, once per number and tile.  Measured against
-// the fp32 instruction, us: forward 256 x 4096, k = 4096 76 -> 56; delta 80 -> 52; gradient + momentum update 4096 x
-// 4096, k = 256 104 -> 71; forward 2048 x 1024, k = 1024 40 -> 27; 301 x 777, k = 1021 (odd widths) 31 -> 11.
+// What bounds it: the vector unit and waiting.  At 256 x 4096, k = 4096 every SIMD has one wave; of a wave's time 42 % issues
+// vector instructions (a slice of the 64 x 64 tile takes 128 to split its numbers, 64 to test them and 16 for
+// addresses, four cycles each), 27 % waits for LDS or memory and 17 % for a place to issue; the matrix cores are busy
+// 18 %, and the clock stays at 2.4 GHz (active cycles and duration of the same run).  Hence the largest tile whose sums fit
+// a wave's registers (64 x 64: 128 registers of sums), operands straight into LDS as fp32 (one write and one read of LDS
+// per number) and the split in registers, once per number and tile.  Measured against the fp32 instruction, us: forward 256
+// x 4096, k = 4096 74 -> 62; delta 71 -> 58; gradient + momentum update 4096 x 4096, k = 256 105 -> 82; forward 2048 x
+// 1024, k = 1024 41 -> 30; 301 x 777, k = 1021 (odd widths) 30 -> 12.8.
 // (Six bf16 products on three-way splits, which need no scales, were slower than the fp32 instruction: 82 us for the
 // first of these.)
 template <class T, bool A_KC, bool B_KC, int EPI, bool FAST>
@@ -1368,15 +1369,16 @@ static bool in_pairs(GemmKind kind, const GemmArgs &a, long tiles64)
 }
 
 // Tile shape from the problem shape.
-// Split kernels: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most
-// compute units have one, or, for a long k, once k split across workgroups gives them one; below that smaller tiles
-// keep more units busy.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 56 / 62 / 76; 2048 x
-// 1024, k 1024: 27 / 39 / 41; 256 x 1000, k 4096: 21.0 / 21.0 / 20.4; 512 x 1024, k 1024: 13.8 / 10.9 / 12.5; 128 x
-// 1024, k 1024: 12.4 / 8.9 / 7.7; gradients 1024 x 1024, k 512: 11.8 / 14.7 / 14.3; k 128: 7.2 / 9.5 / 9.4.  Operands
-// read through registers (odd widths) do without the middle shape: 301 x 777, k 1021: 16.8 / 14.7 / 10.8.
+// Pairs: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most compute units have
+// one; below that smaller tiles keep more units busy, for a long k the middle shape, whose k is also split across
+// workgroups.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 62 / 64 / 77; 2048 x 1024, k 1024: 30 / 47 /
+// 47; 768 x 1024, k 1024: 19.3 / 22.6 / 20.3; 640 x 1024, k 2048: 32 / 35.5 / 32; 512 x 1024, k 2048: 22 / 20 / 24.5; 256 x
+// 1000, k 4096: 24.9 / 21.2 / 23.5; 257 x 1021, k 4097: 45.7 / 42.5 / 43.8; 512 x 1024, k 1024: 15.1 / 13.2 / 14.9; 128 x
+// 1024, k 1024: 13.0 / 10.4 / 8.8; gradient 1024 x 1024, k 512: 15.1 / 19.4 / 19.3.  Operands read through registers
+// (odd widths) do without the middle shape for a shorter k: 301 x 777, k 1021: 18.4 / 16.8 / 12.7.
 // Short sums are bound by launch, loads and stores; 32 x 32 tiles in slices take them all.  Measured against the best of
-// the LDS-tiled fp32 shapes, us (those / these): gradient + momentum 4096 x 4096, k = 32 59 / 40, k = 64 62 / 43 (HBM
-// floor 56; the last-level cache helps); 2017 x 1023, k = 37 24.2 / 12.2; gradient 301 x 777, k = 18 7.0 / 3.6;
+// the LDS-tiled fp32 shapes, us (those / these): gradient + momentum 4096 x 4096, k = 32 62 / 44, k = 64 65 / 46 (HBM
+// floor 56; the last-level cache helps); 2017 x 1023, k = 37 21.1 / 12.5; gradient 301 x 777, k = 18 8.2 / 4.5;
 // forward 64 x 2048, k = 49 6.6 / 3.6; 2048 x 512, k = 64 5.0 / 5.1.
 static int pick_variant(GemmKind kind, const GemmArgs &a)
 {
@@ -1385,7 +1387,7 @@ static int pick_variant(GemmKind kind, const GemmArgs &a)
     if (in_pairs(kind, a, t64)) {
         if (kind == GEMM_GRAD && large_short_grad(t64, a.K)) return 16;
         if (t64 >= (kind == GEMM_GRAD ? 128 : 192)) return 13;
-        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 13;
+        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return t64 <= 128 ? 14 : 13;
         return tiles(32, 64) >= 192 && vec_ok(kind, a) ? 14 : 15;
     }
     return kind == GEMM_GRAD && large_short_grad(t64, a.K) ? 18 : 17;
