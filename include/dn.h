@@ -423,7 +423,13 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  * Tuning and diagnostics switches (all default 0):
  *   "time_kernels"   1: collect per-launch times in dn_train_epoch (see above)
  *   "gemm_variant"   -1 (default): pick the tile configuration of each
- *                    contraction from its shape; >= 0: force that configuration
+ *                    contraction from its shape; >= 0: force that configuration.  By itself the library
+ *                    forms long sums from operands held as pairs of f16 numbers (22 to 23 of an fp32
+ *                    number's 24 bits, products summed in fp32; numbers that a pair cannot hold beside
+ *                    others of their row are multiplied in fp32) and short ones from the fp32 numbers
+ *                    themselves; 17 and 18 take the fp32 numbers for every sum.  The 3 x 3, stride 1
+ *                    convolutions of 32 and more output and 8 and more input channels use the same pairs
+ *                    and have no such switch
  *   "split_k"        1 (default): forward / delta products with few output tiles split k across
  *                    workgroups (partials summed in a fixed order); 0: never
  *   "merge_launches" 1 (default): the gradient / update products of a backward pass, independent of one

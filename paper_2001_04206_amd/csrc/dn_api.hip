@@ -585,7 +585,11 @@ dn_status run_online_shared(dn_net *net, const float *X, const int32_t *labels, 
 
 // Automatic choice between the persistent minibatch kernel and one launch per product: the
 // persistent kernel does its products on the vector units, so it only pays while a step is
-// launch bound, i.e. while the step's contraction work is small.
+// launch bound, i.e. while the step's contraction work is small.  us/step with momentum, persistent against launches:
+// 784-128-10 batch 32 11.9 / 25.4, batch 128 19.5 / 27.7, batch 256 30.7 / 28.8; 784-256-10 batch 128 22.4 / 28.2, batch 256
+// 32.9 / 29.5; 1024-512-10 batch 64 21.3 / 24.5, batch 128 (above the line) 29.8 / 25.9; 2048-1024-10 batch 16 24.6 / 34.5,
+// batch 32 28.7 / 34.7, batch 64 (above) 42.0 / 35.3; 784-1024-10 batch 64 27.7 / 27.8.  The line is where it was set before
+// the launches became faster; at batch 256 they are now up to a tenth faster below it.
 bool batch_pays(const dn_net *net, int batch)
 {
     double flop = 0.0;
@@ -598,8 +602,9 @@ bool batch_pays(const dn_net *net, int batch)
 bool deep_pays(const dn_net *net, int batch)
 {
     (void)net;
-    // 1024-1024-1024-1024-10, us/step persistent against one launch per product (7 launches): batch 4: 37 / 76,
-    // batch 8: 38 / 76, batch 16: 43 / 77, batch 24: 57 / 77, batch 32: 58 / 75, batch 48: 77 / 72, batch 64: 85 / 71
+    // 1024-1024-1024-1024-10, us/step persistent against one launch per product (7 launches): batch 4: 38 / 66,
+    // batch 8: 38 / 66, batch 16: 44 / 65, batch 24: 58 / 66, batch 32: 60 / 65, batch 48: 79 / 70, batch 64: 87 / 71;
+    // 512-512-512-10: batch 8: 24 / 34, batch 16: 27 / 34, batch 32: 30 / 34, batch 48: 37 / 35
     return batch <= 32;
 }
 

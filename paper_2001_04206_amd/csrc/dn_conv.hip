@@ -251,9 +251,7 @@ __global__ __launch_bounds__(256) void corr_mfma_kernel(CorrShape s, const float
     const int w_oc = min(oc0 + w_ocl, s.Cout - 1);
     const bool w_real = oc0 + w_ocl < s.Cout;
     // Filter edge known (5 x 5): every load of a stage is requested at once, into registers, before the
-    // first value is stored; the staging indices are recomputed from the thread
-    // index every time rather than kept in registers across the product loop (the empty asm hides
-    // that they repeat)
+    // first value is stored
     constexpr int TAPS_K = KS * KS, PROW_K = MC_ROWS + KS - 1, PCOL_K = 32 + KS - 1, NP_K = MC_IC * PROW_K * PCOL_K;
     constexpr int XP_K = KS > 0 ? (NP_K + 255) / 256 : 1, WP_K = KS > 0 ? MC_IC * TAPS_K / 4 : 1;
     [[maybe_unused]] float wreg[WP_K], xreg[XP_K];
