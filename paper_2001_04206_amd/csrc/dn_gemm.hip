@@ -654,10 +654,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g0, float *smem, const
 }
 
 // Work of one workgroup on the tile at (m0, n0) with the products on the f16 matrix instruction (dn_split.h).
-// What bounds it: the vector unit and waiting.  At 256 x 4096, k = 4096 every SIMD has one wave; of a wave's time 42 % issues
+// What bounds it: the vector unit and waiting.  At 256 x 4096, k = 4096 every SIMD has one wave; of a wave's time 44 % issues
 // vector instructions (a slice of the 64 x 64 tile takes 128 to split its numbers, 64 to test them and 16 for
-// addresses, four cycles each), 27 % waits for LDS or memory and 17 % for a place to issue; the matrix cores are busy
-// 18 %, and the clock stays at 2.4 GHz (active cycles and duration of the same run).  Hence the largest tile whose sums fit
+// addresses, four cycles each), 26 % waits for LDS or memory and 17 % for a place to issue; the matrix cores are busy
+// 16 %, and the clock stays at 2.4 GHz (active cycles and duration of the same run).  Hence the largest tile whose sums fit
 // a wave's registers (64 x 64: 128 registers of sums), operands straight into LDS as fp32 (one write and one read of LDS
 // per number) and the split in registers, once per number and tile.  Measured against the fp32 instruction, us: forward 256
 // x 4096, k = 4096 74 -> 62; delta 71 -> 58; gradient + momentum update 4096 x 4096, k = 256 105 -> 82; forward 2048 x
@@ -717,8 +717,8 @@ __device__ __forceinline__ void split_tile(const GemmArgs &g0, float *smem, cons
         // as the largest number that fits and the smallest that keeps its bits.  A zero is no such number: activations
         // and deltas, which have zeros everywhere, are tested by keys (1.5 instructions a number), weights by their
         // smallest number first (half an instruction).  The vector unit is the busy one here, so the tests show: forward 256
-        // x 4096, k = 4096 47.6 -> 52.8 us.  A range wider by one or two bits, with less room above, was slower (54.1
-        // us): rows outgrow their scale more often.
+        // x 4096, k = 4096 57 -> 62 us.  A range wider by a bit, with less room above, was 2 % slower: rows outgrow their
+        // scale more often.
         constexpr bool KEYS_B = IS_GRAD;
         float scale_a[TM], scale_b[TN], room_a[TM], room_b[TN], low_b[TN], first_a[TM], first_b[TN];
         unsigned key_a[TM], key_b[TN];
