@@ -127,3 +127,20 @@ def test_small_numbers_beside_large_ones(dnlib, case, small):
     magY, magdX = reference(np.abs(X), np.abs(W), np.abs(dA), 1)
     close(Y, wantY, magY, 9 * 64 * 16, 1e-44, "forward")
     close(dX, wantdX, magdX, 9 * 40 * 16, 1e-44, "input gradient")
+
+
+def test_more_stages_than_are_counted_one_by_one(dnlib):
+    """1040 and 1060 channels are 65 and 67 stages, counted in pairs: some are left alone, some with the one after them, and
+    from the last quarter on all of them."""
+    X, W, dA = draw(1, 1040, 9, 14, 1060, 1)
+    for c in (20, 320, 336, 700):
+        X[:, c] *= np.float32(1e-12)
+        dA[:, c] *= np.float32(1e-12)
+    check(dnlib, X, W, dA, 1)
+    X[:, 100::16] *= np.float32(1e-12)
+    dA[:, 100::16] *= np.float32(1e-12)
+    Y, dX = run(dnlib, X, W, dA, 1)
+    wantY, wantdX = reference(X, W, dA, 1)
+    magY, magdX = reference(np.abs(X), np.abs(W), np.abs(dA), 1)
+    close(Y, wantY, magY, 9 * 1040 * 16, 0.0, "forward")
+    close(dX, wantdX, magdX, 9 * 1060 * 16, 0.0, "input gradient")
