@@ -409,8 +409,9 @@ enum {
     DN_SCHED_ONE_WAVE = 6,        /* batch 1, every layer at most 64 wide: one wavefront runs the epoch */
     DN_SCHED_WIDE_HIDDEN = 7,     /* batch 1, two layers, a hidden layer too wide for LDS: rows in LDS, registers and memory */
     DN_SCHED_ONE_WAVE_REGISTERS = 8, /* batch 1, two layers at most 64 wide, no momentum: one wavefront, the net in its registers */
-    DN_SCHED_ONE_WORKGROUP = 9     /* batch 1, two layers, no momentum, W_1 within one compute unit's registers: one workgroup
+    DN_SCHED_ONE_WORKGROUP = 9,    /* batch 1, two layers, no momentum, W_1 within one compute unit's registers: one workgroup
                                       (the last few samples of a call may run on another batch-1 schedule) */
+    DN_SCHED_SAMPLE_BLOCKS = 10    /* batch 1, two layers, no momentum, enough samples: W_1 read and written once per 32 samples */
 };
 dn_status dn_last_schedule(dn_net *net, int32_t *schedule);
 dn_status dn_kernel_time(dn_net *net, int32_t kernel_class, float *ms_total, int64_t *launches);
@@ -464,6 +465,11 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    at most 16 outputs and at most 1568 / 784 / 392 inputs (for up to 64 / 128 / 256
  *                    hidden units) runs on ONE workgroup that keeps W_1 in its registers and reads the
  *                    samples through scalar loads; 0: such nets take the other batch-1 schedules
+ *   "online_blocks"  1 (default): a pass of at least 64 samples at batch 1 without momentum over a two-layer net with
+ *                    4 to 1024 inputs, at most 1004 hidden units (512 with more than 16 outputs), at most 64
+ *                    outputs and some layer wider than 64 forms the first layer's products of 32 samples at a time
+ *                    and corrects them step by step through the samples' inner products; 0: such passes take the
+ *                    other batch-1 schedules
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose
  *                    parameters fit in LDS, twice with momentum) runs on a single wavefront that keeps
  *                    the whole net in LDS -- in its registers, for two layers and momentum 0; 2: the

@@ -70,7 +70,7 @@ bool compute_layout(const int32_t *widths, int32_t n_widths, int32_t max_batch, 
     lo.off_loss_sums = o; o += align_up((size_t)max_batch * sizeof(double));
     lo.off_scalars = o; o += kAlign;
     lo.online_bytes = std::max({online_exchange_bytes_bound(widths, L), twin_exchange_bytes_bound(widths, L),
-                                wide_exchange_bytes_bound(widths, L)});
+                                wide_exchange_bytes_bound(widths, L), block_exchange_bytes(widths, L)});
     lo.off_online = o; o += align_up(lo.online_bytes);
     lo.off_gemm_ws = o; o += align_up(GEMM_WS_FLOATS * sizeof(float));
     lo.off_gemm_counters = o; o += align_up(GEMM_COUNTERS * sizeof(unsigned));
@@ -106,7 +106,7 @@ struct dn_net {
     bool w1_as_in_bwd = false;   // W_1 is still the matrix the last dn_backward propagated through
     // options
     int time_kernels = 0, gemm_variant = -1, online_mode = 0, online_min_tile = ON_DEFAULT_MIN_TILE,
-        online_resident = 1, online_twin = 1, online_tiny = 1, online_solo = 1, online_wide = 1, split_k_on = 1, merge_launches = 1;
+        online_resident = 1, online_twin = 1, online_tiny = 1, online_solo = 1, online_wide = 1, online_blocks = 1, split_k_on = 1, merge_launches = 1;
     // persistent batch-1 kernel
     OnlineGeom geom{};
     bool online_ok = false;
@@ -115,6 +115,7 @@ struct dn_net {
     bool tiny_ready = false;   // the one-wave batch-1 kernel's LDS limit is raised
     bool wide_ready = false;   // the wide-hidden-layer batch-1 kernel's LDS limit is raised
     bool wide_ok = false;      // ... and the net suits it
+    bool block_ready = false;  // the sample-block batch-1 kernel's LDS limit is raised and the net suits it
     int last_schedule = DN_SCHED_NONE;   // how the last dn_train_epoch ran
     uint32_t online_seq = 0;   // last step number stamped into the exchange buffers
     // persistent minibatch kernel (one- and two-layer nets)
@@ -420,6 +421,8 @@ dn_status run_twin(dn_net *net, const TwinGeom &g, const float *X, const int32_t
     return DN_OK;
 }
 
+constexpr int64_t kBlocksMinSamples = 64;   // of a pass, for the samples to be taken in blocks
+
 // Batch-1 epochs of a two-layer net with a wide hidden layer: most of W_1 stays in LDS and registers.
 dn_status run_wide(dn_net *net, const WideGeom &g, const float *X, const int32_t *labels, int64_t n_samples, float lr,
                    float mu, bool timing)
@@ -483,6 +486,37 @@ dn_status run_solo(dn_net *net, const SoloGeom &g, const float *X, const int32_t
 dn_status run_online_shared(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
                             bool timing);
 
+// Batch-1 steps of a two-layer net with the samples in blocks of 32 (plain gradient descent).
+dn_status run_blocks(dn_net *net, const BlockGeom &g, const float *X, const int32_t *labels, int64_t n_samples, float lr,
+                     bool timing)
+{
+    BlockPlan p{};
+    p.W1 = net->W(1); p.b1 = net->b(1); p.VW1 = net->VW(1); p.Vb1 = net->Vb(1);
+    p.W2 = net->W(2); p.b2 = net->b(2); p.VW2 = net->VW(2); p.Vb2 = net->Vb(2);
+    p.n0 = net->n[0]; p.n1 = net->n[1]; p.n2 = net->n[2];
+    p.abort_flag = net->abort_flag();
+    p.loss_acc = net->epoch_acc();
+    p.act1 = net->act[1]; p.act2 = net->act[2]; p.loss = net->loss;
+    p.lr = lr;
+    for (int64_t s0 = 0; s0 < n_samples; s0 += BLOCK_LAUNCH_SAMPLES) {
+        const int64_t n = std::min<int64_t>(n_samples - s0, BLOCK_LAUNCH_SAMPLES);
+        if ((uint64_t)net->online_seq + (uint64_t)n + 2 > 0xffffffffull) {   // step numbers would wrap
+            DN_HIP(hipMemsetAsync(net->exchange(), 0, net->lo.online_bytes, net->stream));
+            net->online_seq = 0;
+        }
+        p.X = X + (size_t)s0 * p.n0;
+        p.labels = labels + s0;
+        p.vec = p.n0 % 4 == 0 && (reinterpret_cast<uintptr_t>(p.X) & 15) == 0;
+        p.n_samples = n;
+        p.keep_v = (s0 + n >= n_samples) ? 1 : 0;
+        p.seq0 = net->online_seq;
+        ScopedTimer st(net, DN_K_ONLINE, timing);
+        DN_HIP(launch_block_epoch(g, p, net->exchange(), net->stream));
+        net->online_seq += (uint32_t)n;
+    }
+    return DN_OK;
+}
+
 // A whole batch-1 epoch on the persistent kernel that suits the net.
 dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
                      bool timing)
@@ -492,6 +526,13 @@ dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t
         TinyPlan tp;   // every layer at most 64 wide: one wavefront runs the epoch
         if (tiny_plan(net->n.data(), L, mu != 0.f, tp)) {
             return run_tiny(net, tp, X, labels, n_samples, lr, mu, timing);
+        }
+    }
+    if (mu == 0.f && net->online_blocks && net->block_ready && n_samples >= kBlocksMinSamples) {
+        BlockGeom bg;
+        if (block_geometry(net->n.data(), L, bg) && bg.grid <= net->device_cus) {
+            net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
+            return run_blocks(net, bg, X, labels, n_samples, lr, timing);
         }
     }
     bool solo_ran = false;
@@ -796,6 +837,7 @@ dn_status dn_net_create(const int32_t *widths, int32_t n_widths, const dn_act *a
         net->twin_ready = lo.online_bytes > 0 && twin_exchange_bytes_bound(net->n.data(), L) > 0 && twin_prepare() == hipSuccess;
         net->tiny_ready = tiny_prepare() == hipSuccess;
         net->wide_ready = lo.online_bytes > 0 && wide_exchange_bytes_bound(net->n.data(), L) > 0 && wide_prepare() == hipSuccess;
+        net->block_ready = block_exchange_bytes(net->n.data(), L) > 0 && block_prepare(net->n.data(), net->act[1]) == hipSuccess;
         net->batch_prepared = lo.batch_bytes > 0 && batch_prepare() == hipSuccess;
         net->deep_prepared = lo.deep_bytes > 0 && deep_prepare() == hipSuccess;
         (void)hipGetLastError();
@@ -972,7 +1014,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         wide_fit = wide_geometry(net->n.data(), net->L, net->device_cus, momentum != 0.f, wg);
     }
     const bool online_fit = net->online_ok || wide_fit;
-    bool persistent = batch == 1 && net->online_mode != 1 && online_fit;
+    bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || net->block_ready);
     if (batch == 1 && net->online_mode == 2 && !online_fit) return DN_ERR_UNSUPPORTED;
     const bool pbatch = batch > 1 && net->batch_mode != 1 && net->batch_ok &&
                         (net->batch_mode == 2 || batch_pays(net, batch));
@@ -1218,6 +1260,9 @@ dn_status dn_set_option(dn_net *net, const char *name, int64_t value)
     } else if (!strcmp(name, "online_twin")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->online_twin = (int)value;
+    } else if (!strcmp(name, "online_blocks")) {
+        if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
+        net->online_blocks = (int)value;
     } else if (!strcmp(name, "online_wide")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->online_wide = (int)value;

@@ -448,6 +448,39 @@ struct SoloPlan {
 bool solo_geometry(const int32_t *n, int L, SoloGeom &g);
 hipError_t launch_solo_epoch(const SoloGeom &g, const SoloPlan &plan, hipStream_t stream);
 
+// ---- two-layer nets, the samples in blocks (dn_block.hip) ----
+constexpr int BLOCK_SAMPLES = 32;            // samples whose first-layer products are formed together
+constexpr int BLOCK_GRAM_GROUPS = 4;         // workgroups that form the samples' inner products
+constexpr int BLOCK_LAUNCH_SAMPLES = 4096;   // samples of one launch (their inner products are kept for its duration)
+
+struct BlockGeom {
+    int units_per_lane, chain_waves;   // the workgroup that runs the steps
+    int grid;
+};
+
+struct BlockPlan {
+    float *W1, *b1, *W2, *b2, *VW1, *Vb1, *VW2, *Vb2;
+    unsigned long long *z_x;      // [2][32][n1] net inputs of a block's samples, rows to steps
+    unsigned long long *d_x;      // [2][32][d_stride] -lr delta, steps to rows
+    unsigned long long *gram_x;   // [blocks][2][32][32] inner products of a block's samples among themselves and with the next block's;
+                                  // word 31: whether they are usable
+    int *abort_flag;
+    double *loss_acc;
+    const float *X;
+    const int32_t *labels;
+    int64_t n_samples;
+    int n0, n1, n2, act1, act2, loss, keep_v, vec, chain_waves, d_stride;
+    float lr;
+    uint32_t seq0;
+};
+
+// False unless the net has two layers of 4 to 1024 inputs, at most 1004 hidden units (512 with more than 16 outputs) and
+// at most 64 outputs.
+bool block_geometry(const int32_t *n, int L, BlockGeom &g);
+size_t block_exchange_bytes(const int32_t *n, int L);
+hipError_t block_prepare(const int32_t *n, int act);
+hipError_t launch_block_epoch(const BlockGeom &g, BlockPlan plan, unsigned long long *exchange, hipStream_t stream);
+
 // Slices and buffer offsets for widths n[0..L]; false if the net does not fit the kernel
 // (too many layers, output layer too wide, LDS).  want_v: velocity slices are read every step
 // (momentum), so they must fit in LDS next to the weights for the slices to be resident.

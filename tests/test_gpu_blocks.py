@@ -1,0 +1,132 @@
+"""Per-sample training of two-layer nets with the samples in blocks of 32 (W_1 read and written once per block), against the
+CPU checker (fp32 storage, fp64 sums) on the same seeded inputs.
+
+Tolerance 2e-5 (2-norm, per tensor): a pass of n steps rounds a weight n / 32 times and every step's change a few times, each
+by 6e-8 of itself, and what a step's error does to the later ones stays of that size at these rates; 200 steps of random
+signs come to about 1e-6."""
+import numpy as np
+import pytest
+
+from oracle.dn_oracle import Oracle
+from paper_2001_04206_amd import synth
+from parity_util import announce, assert_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+LIN, SIG, TANH, RELU, SOFTMAX = 0, 1, 2, 3, 4
+MSE, CE = 0, 1
+TOL = 2e-5
+
+
+@pytest.fixture(scope="module")
+def dnlib():
+    from paper_2001_04206_amd import dn
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    dn.lib()
+    return dn
+
+
+def run(dn, w, passes=(0.0,), shift=0, blocks=True):
+    rng = np.random.default_rng(11)
+    w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
+    net = dn.Net(w.widths, w.acts, w.loss, 1)
+    net.set_all(w.W, w.b)
+    net.dn_set_option("online_tiny", 0)
+    o = Oracle("o32", w.widths, w.acts, w.loss)
+    o.set_params(w.W, w.b)
+    X = torch.zeros(w.X.size + shift, device="cuda:0")[shift:].view(w.X.shape)
+    X.copy_(torch.from_numpy(w.X))
+    y = torch.from_numpy(w.labels).to("cuda:0")
+    for mu in passes:
+        got = net.dn_train_epoch(X, y, 1, w.lr, mu)
+        assert (net.dn_last_schedule() == dn.DN_SCHED_SAMPLE_BLOCKS) == (blocks and mu == 0.0)
+        ref, _ = o.train_epoch(w.X, w.labels, 1, w.lr, mu)
+        assert abs(got - ref) <= TOL * max(abs(ref), 1e-6), (got, ref)
+    W, b = net.get_all()
+    Wr, br = o.get_params()
+    for l in range(2):
+        assert_close(W[l], Wr[l], TOL, "W_%d" % (l + 1))
+        assert_close(b[l], br[l], TOL, "b_%d" % (l + 1))
+    net.close()
+
+
+def make(widths, acts, loss, n, lr=0.003):
+    return synth.make("blocks", widths, acts, loss, n_samples=n, features="normal", init="xavier_uniform", batch=1, lr=lr,
+                      momentum=0.0, seed=6)
+
+
+SHAPES = [
+    # hidden units around one, two and more units a lane and one, two and four waves; outputs around the compiled widths;
+    # inputs around the waves' column groups and off the 16-byte path; samples around blocks
+    ([784, 128, 10], [RELU, SOFTMAX], CE, 96),
+    ([4, 1, 1], [TANH, LIN], MSE, 64),
+    ([5, 64, 3], [SIG, SIG], MSE, 65),
+    ([63, 65, 4], [TANH, SOFTMAX], CE, 97),
+    ([64, 127, 5], [LIN, SOFTMAX], CE, 127),
+    ([65, 128, 10], [SIG, SOFTMAX], CE, 128),
+    ([255, 129, 11], [TANH, SOFTMAX], CE, 129),
+    ([256, 256, 16], [RELU, SOFTMAX], CE, 95),
+    ([257, 257, 2], [TANH, SIG], MSE, 100),
+    ([511, 64, 17], [TANH, SOFTMAX], CE, 96),
+    ([512, 63, 32], [SIG, SOFTMAX], CE, 70),
+    ([513, 200, 33], [TANH, SOFTMAX], CE, 96),
+    ([1023, 256, 64], [SIG, SOFTMAX], CE, 66),
+    ([1024, 257, 20], [TANH, SOFTMAX], CE, 96),
+    ([30, 512, 64], [TANH, SOFTMAX], CE, 80),
+    ([100, 512, 10], [RELU, SOFTMAX], CE, 96),
+    ([1000, 513, 10], [TANH, SOFTMAX], CE, 96),
+    ([12, 1004, 3], [SIG, SIG], MSE, 96),
+    ([37, 770, 16], [TANH, SOFTMAX], CE, 96),
+]
+
+
+@pytest.mark.parametrize("widths,acts,loss,n", SHAPES)
+def test_sample_block_epochs_match_checker(dnlib, widths, acts, loss, n):
+    """A plain pass (its last step leaves the applied change as velocity), a momentum pass that starts from it (another
+    kernel), a plain pass again."""
+    announce("sample blocks widths=%s n=%d" % (widths, n))
+    run(dnlib, make(widths, acts, loss, n), (0.0, 0.5, 0.0))
+
+
+def test_sample_blocks_over_several_launches(dnlib):
+    announce("sample blocks: 4096 + 37 samples (two launches)")
+    run(dnlib, make([5, 65, 2], [TANH, SOFTMAX], CE, 4096 + 37, lr=0.001))
+
+
+def test_sample_blocks_from_an_odd_address(dnlib):
+    announce("sample blocks: features 4 bytes off a 16-byte address")
+    run(dnlib, make([128, 70, 10], [TANH, SOFTMAX], CE, 96), shift=1)
+
+
+@pytest.mark.parametrize("large", [[40, 45], [10, 40], [31, 32], [63, 64, 65, 95, 96], [0, 1], list(range(32, 64))])
+def test_sample_blocks_with_inner_products_beyond_fp32(dnlib, large):
+    """Samples whose inner products overflow (their net inputs do not): within a block, between adjacent blocks, whole
+    blocks.  Hidden units are saturated there and W_1 stays as it is for these steps."""
+    announce("sample blocks: inner products beyond fp32, samples %s" % (large,))
+    w = make([40, 70, 5], [TANH, SOFTMAX], CE, 130)
+    w.X[large] *= np.float32(3e19)
+    assert np.isfinite(w.X).all() and not np.isfinite(w.X[large] @ w.X[large].T).all()
+    run(dnlib, w, (0.0, 0.5))
+
+
+def test_sample_blocks_left_to_other_kernels(dnlib):
+    announce("sample blocks: nets and passes left to other kernels")
+    for widths, acts, n in (([64, 128, 10], [RELU, SOFTMAX], 63), ([3, 70, 4], [TANH, SOFTMAX], 96), ([1028, 70, 4], [TANH, SOFTMAX], 96),
+                            ([16, 1008, 4], [TANH, SOFTMAX], 96), ([16, 516, 20], [TANH, SOFTMAX], 96), ([16, 70, 65], [TANH, SOFTMAX], 96)):
+        run(dnlib, make(widths, acts, CE, n), blocks=False)
+
+
+def test_sample_blocks_are_bitwise_reproducible(dnlib):
+    announce("sample blocks: determinism")
+    w = make([300, 200, 10], [TANH, SOFTMAX], CE, 500)
+    outs = []
+    for _ in range(2):
+        net = dnlib.Net(w.widths, w.acts, w.loss, 1)
+        net.set_all(w.W, w.b)
+        loss = net.dn_train_epoch(torch.from_numpy(w.X).to("cuda:0"), torch.from_numpy(w.labels).to("cuda:0"), 1, w.lr, 0.0)
+        outs.append((loss, net.get_all()))
+        net.close()
+    assert outs[0][0] == outs[1][0]
+    for a, b in zip(outs[0][1][0] + outs[0][1][1], outs[1][1][0] + outs[1][1][1]):
+        assert np.array_equal(a, b)
