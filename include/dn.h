@@ -468,8 +468,8 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *   "online_blocks"  1 (default): a pass of at least 64 samples at batch 1 without momentum over a two-layer net with
  *                    4 to 1024 inputs, at most 1004 hidden units (512 with more than 16 outputs), at most 64
  *                    outputs and some layer wider than 64 forms the first layer's products of 32 samples at a time
- *                    and corrects them step by step through the samples' inner products; 0: such passes take the
- *                    other batch-1 schedules
+ *                    and corrects them step by step through the samples' inner products, and so does one over a net that
+ *                    "online_wide" takes (of at most 131072 hidden units); 0: such passes take the other batch-1 schedules
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose
  *                    parameters fit in LDS, twice with momentum) runs on a single wavefront that keeps
  *                    the whole net in LDS -- in its registers, for two layers and momentum 0; 2: the

@@ -70,7 +70,8 @@ bool compute_layout(const int32_t *widths, int32_t n_widths, int32_t max_batch, 
     lo.off_loss_sums = o; o += align_up((size_t)max_batch * sizeof(double));
     lo.off_scalars = o; o += kAlign;
     lo.online_bytes = std::max({online_exchange_bytes_bound(widths, L), twin_exchange_bytes_bound(widths, L),
-                                wide_exchange_bytes_bound(widths, L), block_exchange_bytes(widths, L)});
+                                wide_exchange_bytes_bound(widths, L), block_exchange_bytes(widths, L),
+                                wide_exchange_bytes_bound(widths, L) > 0 ? wide_block_exchange_bytes() : 0});
     lo.off_online = o; o += align_up(lo.online_bytes);
     lo.off_gemm_ws = o; o += align_up(GEMM_WS_FLOATS * sizeof(float));
     lo.off_gemm_counters = o; o += align_up(GEMM_COUNTERS * sizeof(unsigned));
@@ -115,6 +116,7 @@ struct dn_net {
     bool tiny_ready = false;   // the one-wave batch-1 kernel's LDS limit is raised
     bool wide_ready = false;   // the wide-hidden-layer batch-1 kernel's LDS limit is raised
     bool wide_ok = false;      // ... and the net suits it
+    bool wide_block_ready = false;   // ... and the sample-block form of the wide-hidden-layer kernel
     bool block_ready = false;  // the sample-block batch-1 kernel's LDS limit is raised and the net suits it
     int last_schedule = DN_SCHED_NONE;   // how the last dn_train_epoch ran
     uint32_t online_seq = 0;   // last step number stamped into the exchange buffers
@@ -440,10 +442,15 @@ dn_status run_wide(dn_net *net, const WideGeom &g, const float *X, const int32_t
     p.lds_x = g.lds_x; p.lds_a = g.lds_a; p.lds_d = g.lds_d; p.lds_b = g.lds_b; p.lds_z = g.lds_z; p.lds_w2 = g.lds_w2;
     p.lds_vb = g.lds_vb; p.lds_vw2 = g.lds_vw2;
     p.lds_zall = g.lds_zall; p.lds_out = g.lds_out; p.lds_w1 = g.lds_w1;
-    const int64_t chunk = (int64_t)1 << 30;
+    // Without momentum the samples go in blocks, W_1 read and written once per block; the kernel that sweeps it every step is
+    // launched behind and ends at once unless a block's inner products left fp32.
+    const bool blocks = mu == 0.f && net->online_blocks && net->wide_block_ready && n_samples >= kBlocksMinSamples &&
+                        (reinterpret_cast<uintptr_t>(X) & 15) == 0;   // (it reads the samples in sixteen-byte pieces)
+    if (blocks) net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
+    const int64_t chunk = blocks ? BLOCK_LAUNCH_SAMPLES : (int64_t)1 << 30;
     for (int64_t s0 = 0; s0 < n_samples; s0 += chunk) {
         const int64_t n = (n_samples - s0) < chunk ? (n_samples - s0) : chunk;
-        if ((uint64_t)net->online_seq + (uint64_t)n + 2 > 0xffffffffull) {   // step numbers would wrap
+        if ((uint64_t)net->online_seq + 2 * (uint64_t)n + 2 > 0xffffffffull) {   // step numbers would wrap
             DN_HIP(hipMemsetAsync(net->exchange(), 0, net->lo.online_bytes, net->stream));
             net->online_seq = 0;
         }
@@ -451,8 +458,21 @@ dn_status run_wide(dn_net *net, const WideGeom &g, const float *X, const int32_t
         p.labels = labels + s0;
         p.n_samples = n;
         p.keep_v = (s0 + n >= n_samples) ? 1 : 0;
-        p.seq0 = net->online_seq;
         ScopedTimer st(net, DN_K_ONLINE, timing);
+        if (blocks) {
+            BlockPlan b{};
+            b.W1 = p.W1; b.b1 = p.b1; b.VW1 = p.VW1; b.Vb1 = p.Vb1; b.W2 = p.W2; b.b2 = p.b2; b.VW2 = p.VW2; b.Vb2 = p.Vb2;
+            b.abort_flag = p.abort_flag; b.loss_acc = p.loss_acc;
+            b.X = p.X; b.labels = p.labels; b.n_samples = n; b.keep_v = p.keep_v;
+            b.n0 = p.n0; b.n1 = p.n1; b.n2 = p.nL; b.act1 = p.act1; b.act2 = p.actL; b.loss = p.loss;
+            b.per = g.per; b.lr = lr;
+            b.vec = (reinterpret_cast<uintptr_t>(p.X) & 15) == 0;
+            b.seq0 = net->online_seq;
+            DN_HIP(launch_wide_block_epoch(b, g.grid, net->exchange(), &p.gram, net->stream));
+            p.gram_blocks = (int)((n + BLOCK_SAMPLES - 1) / BLOCK_SAMPLES);
+            net->online_seq += (uint32_t)n;
+        }
+        p.seq0 = net->online_seq;
         DN_HIP(launch_wide_epoch(g, p, net->stream));
         net->online_seq += (uint32_t)n;
     }
@@ -837,6 +857,9 @@ dn_status dn_net_create(const int32_t *widths, int32_t n_widths, const dn_act *a
         net->twin_ready = lo.online_bytes > 0 && twin_exchange_bytes_bound(net->n.data(), L) > 0 && twin_prepare() == hipSuccess;
         net->tiny_ready = tiny_prepare() == hipSuccess;
         net->wide_ready = lo.online_bytes > 0 && wide_exchange_bytes_bound(net->n.data(), L) > 0 && wide_prepare() == hipSuccess;
+        WideGeom wg;
+        net->wide_block_ready = net->wide_ready && wide_geometry(net->n.data(), L, net->device_cus, false, wg) &&
+                                wide_block_fits(net->n[1], wg.per) && wide_block_prepare(net->n[2], net->act[1]) == hipSuccess;
         net->block_ready = block_exchange_bytes(net->n.data(), L) > 0 && block_prepare(net->n.data(), net->act[1]) == hipSuccess;
         net->batch_prepared = lo.batch_bytes > 0 && batch_prepare() == hipSuccess;
         net->deep_prepared = lo.deep_bytes > 0 && deep_prepare() == hipSuccess;

@@ -39,7 +39,9 @@
 #include <algorithm>
 #include <cfloat>
 
+#ifndef DN_PERSIST_THREADS
 #define DN_PERSIST_THREADS 256   // one wave per SIMD: a lane may hold 512 registers
+#endif
 #include "dn_internal.h"
 #include "dn_persist.h"
 #include "dn_wave.h"
@@ -175,23 +177,6 @@ __device__ __forceinline__ float over_groups(float v, Op op)
     return op(bits_to_float(h[0]), bits_to_float(h[1]));
 }
 
-// e^x for x <= 0 (NaN stays): 2^n 2^r with x log2 e = n + r, |r| <= 1/2; log2 e in two parts.
-__device__ __forceinline__ float exp_below_zero(float x)
-{
-    x = x < -150.f ? -150.f : x;   // 0 in fp32
-    const float n = __builtin_rintf(x * 1.44269502f);
-    float r = __builtin_fmaf(x, 1.44269502f, -n);
-    r = __builtin_fmaf(x, 1.92596299e-8f, r);
-    return __builtin_ldexpf(__builtin_amdgcn_exp2f(r), (int)n);
-}
-
-// 1 / x of a normal number: the hardware's estimate and one Newton step.
-__device__ __forceinline__ float inverse(float x)
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r);
-}
-
 template <int ACT>
 __device__ __forceinline__ float activation(float z) { return act_fn(ACT, z); }
 template <int ACT>
@@ -258,6 +243,7 @@ __device__ __forceinline__ float gather(const u64 *parts, int nw, uint32_t stamp
         for (int w = 0; w < N; ++w) v[w] = __hip_atomic_load(parts + min(w, nw - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
         for (int w = 0; w < N; ++w) wait = wait || (uint32_t)(v[w] >> 32) != stamp;
+        if (N == 1 && __any(wait)) __builtin_amdgcn_s_sleep(1);
     } while (__any(wait));
     float sum = 0.f;
 #pragma unroll
@@ -266,11 +252,19 @@ __device__ __forceinline__ float gather(const u64 *parts, int nw, uint32_t stamp
 }
 
 // ---- the steps' workgroup ----
+struct ChainLds;
+template <int NK>
+__device__ __forceinline__ float over_workgroups(const BlockPlan &p, const ChainLds &l, float z2, uint32_t stamp, int par, bool first, int group, int my_k);
+
 struct ChainLds {
     float *gs;   // [2][32][32]: row j: inner products of sample j with samples j0, j0 + 1, .. (j0 = j rounded down to 4)
     float *gx;   // [2][32][32]: row j: inner products of sample j with the next block's samples
     u64 *zp;     // [2][64][4]: the waves' parts of the output layer's sums, stamped
-    float *zc;   // [32][d_stride]: net inputs of the next block as they came from the rows
+    float *zc;   // [32][d_stride]: net inputs of the next block as they came from the rows.  WIDE: [2][32][d_stride], by block
+                 // parity: a block's net inputs, then -lr delta in their place
+    u64 *zq;     // WIDE: [2][16]: the sums over all workgroups, stamped
+    float *parts;   // WIDE: [4][32][32]: four parts of the net inputs of units shared_from .. shared_from + 31
+    int shared_from;
     lds_int *abort;
     lds_int *flags;   // [2]: the blocks' flags
 };
@@ -345,35 +339,85 @@ __device__ __forceinline__ void run_fetcher(const BlockPlan &p, const ChainLds &
     }
 }
 
-template <int U, int NK, int ACT>
+// The output layer's sums over the units of all workgroups, in two levels of sixteen: the four waves' parts meet in LDS, the
+// workgroup's go out as words, one workgroup of every sixteen adds those of its sixteen and sends the sums on, and every
+// workgroup adds the sixteen sums.  (Two short hops: with everybody reading everybody's words, 5 MB a look, a step waited 6 us.)
+// Words: [2][16 groups][16 outputs][16 members], then [2][8 copies][16 outputs][16 groups] (a word that all workgroups ask for
+// keeps its writer waiting).  Every sum is formed in the same order.
+__device__ __forceinline__ int reader_of_group(int g, int grid) { return min(16 * g + g, grid - 1); }
+
+template <int NK>
+__device__ __forceinline__ float over_workgroups(const BlockPlan &p, const ChainLds &l, float z2, uint32_t stamp, int par, bool first, int group, int my_k)
+{
+    static_assert(NK <= 16, "a workgroup's words");
+    constexpr int R = (NK + 3) / 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), grid = (int)gridDim.x, w = (int)blockIdx.x;
+    u64 *mine = l.zp + (par * 64 + group) * 4, *sums = l.zq + par * 16;
+    if (first) __hip_atomic_store(mine + wave, ((u64)stamp << 32) | float_to_bits(z2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (wave == 0) {
+        u64 *words = p.all_x + par * 4096, *tops = p.all_x + 2 * 4096 + par * 8 * 256;
+        const float own = gather<4>(mine, 4, stamp);
+        if (first && my_k >= 0) ll_store(words + (w >> 4) * 256 + my_k * 16 + (w & 15), own, stamp);
+        const int member = lane & 15, kq = lane >> 4;   // lane's word of round r: output 4 r + kq
+        bool ok = true;
+        u64 v[R];
+        if (w == reader_of_group(w >> 4, grid)) {
+            const int there = min(16, grid - (w & ~15));
+            const u64 *from = words + (w >> 4) * 256 + min(member, there - 1);
+            ok = wave_poll(v, stamp, [&](int r, int) { return from + min(4 * r + kq, NK - 1) * 16; }, [](int) { return true; }, p.abort_flag);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float sum = row16_sum(member < there ? bits_to_float((uint32_t)v[r]) : 0.f);
+                if (member < 8 && 4 * r + kq < NK) ll_store(tops + member * 256 + (4 * r + kq) * 16 + (w >> 4), sum, stamp);
+            }
+        }
+        const int groups = (grid + 15) / 16;
+        const u64 *from = tops + (w & 7) * 256 + min(member, groups - 1);
+        ok = wave_poll(v, stamp, [&](int r, int) { return from + min(4 * r + kq, NK - 1) * 16; }, [](int) { return true; }, p.abort_flag) && ok;
+        if (!ok) *l.abort = 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float sum = row16_sum(member < groups ? bits_to_float((uint32_t)v[r]) : 0.f);
+            if (member == 0) __hip_atomic_store(sums + 4 * r + kq, ((u64)stamp << 32) | float_to_bits(sum), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    } else {
+        __builtin_amdgcn_s_sleep(32);   // (nothing to find before the words have travelled; the sweep has the SIMD meanwhile)
+    }
+    return gather<1>(sums + max(my_k, 0), 1, stamp);
+}
+
+// WIDE: the hidden layer is spread over the workgroups of the launch (dn_wide_block.hip), p.per units each; the output
+// layer's sums meet in exchanged words once a step, and the rows are updated by other waves of this workgroup, through LDS.
+template <int U, int NK, int ACT, bool WIDE = false>
 __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
 {
     constexpr int LEVELS = log2_up(NK), SH = 6 - LEVELS;
+    if (WIDE) __builtin_amdgcn_s_setprio(3);   // before the waves that sweep: every workgroup waits for the slowest step
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n1 = p.n1, n2 = p.n2, nw = p.chain_waves, stride = p.d_stride;
+    const int base = WIDE ? (int)blockIdx.x * p.per : 0, count = WIDE ? min(p.per, n1 - base) : n1;
     const int my_k = sum_of_lane(NK, lane), group = lane >> SH;
     const int lane_first = group << SH;   // of the lanes with the same sum
     const bool outl = my_k >= 0 && my_k < n2, first = lane == lane_first;
     const float lr = p.lr;
 
-    float w2[U][NK], b1[U], lr_u[U];
+    float w2[U][NK], b1[U];
     int unit[U];
     bool hid[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         unit[u] = (wave * U + u) * 64 + lane;
-        hid[u] = unit[u] < n1;
-        b1[u] = hid[u] ? p.b1[unit[u]] : 0.f;
-        lr_u[u] = hid[u] ? lr : 0.f;   // (lanes past the layer's end keep zeros)
+        hid[u] = unit[u] < count;
+        b1[u] = hid[u] ? p.b1[base + unit[u]] : 0.f;
 #pragma unroll
-        for (int k = 0; k < NK; ++k) w2[u][k] = (hid[u] && k < n2) ? p.W2[(size_t)k * n1 + unit[u]] : 0.f;
+        for (int k = 0; k < NK; ++k) w2[u][k] = (hid[u] && k < n2) ? p.W2[(size_t)k * n1 + base + unit[u]] : 0.f;
     }
     float b2 = outl ? p.b2[my_k] : 0.f;
     double loss_acc = 0.0;
     float loss_sum = 1.f, loss_z = 0.f;   // lane j: softmax sum of step j and its label's distance from the maximum
 
     const int64_t n = p.n_samples;
-    if (!fetch_beside(p)) fetch_piece(p, l, 0, true, wave, kWaves);
+    if (!WIDE && !fetch_beside(p)) fetch_piece(p, l, 0, true, wave, kWaves);
 
     v16f ahead[U][2];   // corrections of the next block's net inputs: units 0 .. 31 and 32 .. 63 of the wave's 64
 #pragma unroll
@@ -385,16 +429,45 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
         const int64_t block = s0 / TB;
         __syncthreads();
         if (*l.abort) break;
-        const int flags = __builtin_amdgcn_readfirstlane(l.flags[block & 1]);
+        const int flags = WIDE ? 0 : __builtin_amdgcn_readfirstlane(l.flags[block & 1]);
         const bool serial = (flags & OWN_BAD) != 0;
         const int at = (int)(s0 - block * TB);            // the piece's first sample within its block
         const int m = serial ? 1 : (int)min((int64_t)TB, n - s0);
         const uint32_t seq = p.seq0 + 1u + (uint32_t)(block * TB);
         float z[U][TB];
+        float *zd = l.zc + (size_t)(WIDE ? block & 1 : 0) * TB * stride;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int i = 0; i < TB; ++i) z[u][i] = l.zc[i * stride + unit[u]] + b1[u];
+            for (int i = 0; i < TB; ++i) {
+                if constexpr (WIDE) z[u][i] = zd[i * stride + min(unit[u], stride - 1)];
+                else z[u][i] = l.zc[i * stride + unit[u]];
+            }
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = unit[u] - l.shared_from;
+                if (c < 0 || c >= 32) continue;
+#pragma unroll
+                for (int i = 0; i < TB; ++i)
+                    z[u][i] = (l.parts[i * 32 + c] + l.parts[(TB + i) * 32 + c]) + (l.parts[(2 * TB + i) * 32 + c] + l.parts[(3 * TB + i) * 32 + c]);
+            }
+            // the block's inner products
+            const u64 *rec = p.gram_x + (size_t)block * kRecord;
+            const int mx = (int)min((int64_t)TB, n - s0 - m);
+#pragma unroll
+            for (int i = 0; i < kRecord / 256; ++i) {
+                const int q = (i * 256 + tid) % (TB * TB), j = q / TB, t = q % TB;
+                const bool own = i < kRecord / 512, inside = own ? j + t + 1 < m : (j < m && t < mx);
+                const float v = inside ? bits_to_float((uint32_t)rec[i * 256 + tid]) : 0.f;
+                if (own) l.gs[j * TB + (t + 1 + j % 4) % TB] = v;
+                else l.gx[j * TB + t] = v;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < TB; ++i) z[u][i] = !WIDE || hid[u] ? z[u][i] + b1[u] : 0.f;   // (WIDE: the rows past a workgroup's last repeat it)
         if (next_is_ahead(before, flags)) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -413,7 +486,7 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
         label = lane_of_sum(NK, label < 0 ? 0 : (label >= n2 ? n2 - 1 : label));
         __syncthreads();   // zc is free
         const int64_t next = s0 + m;
-        const float *gsb = l.gs + (block & 1) * TB * TB, *gxb = l.gx + (block & 1) * TB * TB;
+        const float *gsb = l.gs + (WIDE ? 0 : block & 1) * TB * TB, *gxb = l.gx + (WIDE ? 0 : block & 1) * TB * TB;
         u64 *out = p.d_x + (size_t)((block & 1) * TB + at) * stride;
         const int last = p.keep_v && next == n ? m - 1 : -1;   // the pass's last step also leaves the applied change as velocity
         // steps j0 .. j0 + 3 use net inputs 0 .. 3 of the registers, which then move up
@@ -434,7 +507,9 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
                     for (int u = 1; u < U; ++u) part[k] = __builtin_fmaf(w2[u][k], a[u], part[k]);
                 }
                 float z2 = sums_over_lanes<NK>(part, lane);
-                if (nw > 1) {   // the waves' parts, added in wave order
+                if constexpr (WIDE) {
+                    z2 = over_workgroups<NK>(p, l, z2, seq + (uint32_t)j, j & 1, first, group, my_k);
+                } else if (nw > 1) {   // the waves' parts, added in wave order
                     const uint32_t stamp = seq + (uint32_t)(at + j);
                     u64 *zq = l.zp + ((q & 1) * 64 + group) * 4;
                     if (first) __hip_atomic_store(zq + wave, ((u64)stamp << 32) | float_to_bits(z2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -465,23 +540,30 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
 #pragma unroll
                 for (int i = 0; i < TB / 4; ++i) g[i] = *(const v4f *)(gsb + j * TB + 4 * i);
                 // ---- deltas of the own units through W_2 as it was, W_2's update ----
-                float d1[U], d1b[U], nla[U];
+                // (both take -lr delta_2, rounded anew every step.  Rounding lr a instead leaves the same error in a weight step
+                // after step where a unit's activation hardly changes: W_2 of the wide net 4.4e-7 off instead of 3.9e-7.)
+                const float nld2 = -(lr * d2);
+                float d1[U], d1b[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) d1[u] = d1b[u] = 0.f, nla[u] = -(lr_u[u] * a[u]);
+                for (int u = 0; u < U; ++u) {
+                    d1[u] = d1b[u] = 0.f;
+                    if (ACT == DN_ACT_SIGMOID) a[u] = hid[u] ? a[u] : 0.f;   // (lanes past the layer's end keep zeros; f(0) = 0 elsewhere)
+                }
 #pragma unroll
                 for (int k = 0; k < NK; ++k) {
-                    const float dk = lane_value(d2, lane_of_sum(NK, k));
+                    const float dk = lane_value(nld2, lane_of_sum(NK, k));
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         (k & 1 ? d1b[u] : d1[u]) = __builtin_fmaf(w2[u][k], dk, k & 1 ? d1b[u] : d1[u]);
-                        w2[u][k] = __builtin_fmaf(dk, nla[u], w2[u][k]);
+                        w2[u][k] = __builtin_fmaf(dk, a[u], w2[u][k]);
                     }
                 }
                 // ---- -lr delta to the rows, into the net inputs of the samples to come, and the biases ----
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const float v = -(lr * ((d1[u] + d1b[u]) * activation_slope<ACT>(a[u])));
-                    ll_store(out + (uint32_t)(j * stride + unit[u]), v, seq);
+                    const float v = (d1[u] + d1b[u]) * activation_slope<ACT>(a[u]);
+                    if constexpr (!WIDE) ll_store(out + (uint32_t)(j * stride + unit[u]), v, seq);
+                    else if (unit[u] < stride) zd[j * stride + unit[u]] = v;
                     b1[u] += v;
                     nld[u][q] = v;
                 }
@@ -494,7 +576,7 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
                         for (int i = 8 * c; i < 8 * c + 8; ++i)
                             if (i > q) z[u][i] = __builtin_fmaf(g[i / 4][i % 4], nld[u][q], z[u][i]);
                 }
-                b2 -= lr * d2;
+                b2 += nld2;
                 if (q % 2 == 1) {   // two steps' part of the next block's corrections: k = 0 and 1 of the product
                     const float gk = gxb[(j - 1 + (lane >> 5)) * TB + (lane & 31)];
 #pragma unroll
@@ -510,12 +592,12 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         if (!hid[u]) continue;
-                        p.Vb1[unit[u]] = nld[u][q];
+                        p.Vb1[base + unit[u]] = nld[u][q];
 #pragma unroll
                         for (int k = 0; k < NK; ++k)
-                            if (k < n2v) p.VW2[(size_t)k * n1 + unit[u]] = nla[u] * lane_value(d2, lane_of_sum(NK, k));
+                            if (k < n2v) p.VW2[(size_t)k * n1 + base + unit[u]] = a[u] * lane_value(nld2, lane_of_sum(NK, k));
                     }
-                    if (wave == 0 && outl && first) p.Vb2[my_k] = -(lr * d2);
+                    if (wave == 0 && (!WIDE || blockIdx.x == 0) && outl && first) p.Vb2[my_k] = nld2;
                 }
             }
 #pragma unroll
@@ -524,10 +606,16 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
                 for (int i = 0; i + 4 < TB; ++i) z[u][i] = z[u][i + 4];
         }
         if (p.loss == DN_LOSS_CROSS_ENTROPY && lane < m) loss_acc += (double)(logf(loss_sum) - loss_z);
-        if (next < n && !fetch_beside(p)) fetch_piece(p, l, next, next / TB != block, wave, kWaves);
+        if constexpr (WIDE) {   // a short last block: no deltas in the rest of it
+            for (int j = m; j < TB; ++j)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (unit[u] < stride) zd[j * stride + unit[u]] = 0.f;
+        } else if (next < n && !fetch_beside(p)) fetch_piece(p, l, next, next / TB != block, wave, kWaves);
         if (next / TB != block) before = flags;
         s0 = next;
     }
+    if constexpr (WIDE) __syncthreads();   // the last block's deltas
 
     // ---- epilogue ----
     int n2e = n2;
@@ -535,12 +623,12 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if (!hid[u]) continue;
-        p.b1[unit[u]] = b1[u];
+        p.b1[base + unit[u]] = b1[u];
 #pragma unroll
         for (int k = 0; k < NK; ++k)
-            if (k < n2e) p.W2[(size_t)k * n1 + unit[u]] = w2[u][k];
+            if (k < n2e) p.W2[(size_t)k * n1 + base + unit[u]] = w2[u][k];
     }
-    if (wave != 0) return;
+    if (wave != 0 || (WIDE && blockIdx.x != 0)) return;
     if (outl && first) p.b2[my_k] = b2;
     if (p.loss != DN_LOSS_CROSS_ENTROPY && !(outl && first)) loss_acc = 0.0;
     for (int off = 32; off > 0; off >>= 1) loss_acc += __shfl_xor(loss_acc, off, 64);
@@ -598,8 +686,8 @@ __device__ __forceinline__ void run_gram(const BlockPlan &p, float *lds, int fir
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r = wave + 4 * q, j = 8 * (r / 4) + 4 * h + (r % 4);
+            for (int q = 0; q < 16 / kWaves; ++q) {
+                const int r = wave + kWaves * q, j = 8 * (r / 4) + 4 * h + (r % 4);
                 float v = c == 0 ? 1.0f : 0.f;   // within a block the bias moves too, an input of one
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) v += lds[((c * kWaves + w) * 16 + r) * 64 + lane];

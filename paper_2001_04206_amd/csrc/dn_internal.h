@@ -384,6 +384,8 @@ struct WidePlan {
     float lr, mu;
     uint32_t seq0;
     int lds_x, lds_a, lds_d, lds_b, lds_z, lds_w2, lds_vb, lds_vw2, lds_zall, lds_out, lds_w1;
+    const unsigned long long *gram;   // not null: the launch is only for the case that a block's inner products are not usable (their
+    int gram_blocks;                  // records' flags), which the kernel launched before it leaves to this one
 };
 
 // false if the net does not suit the kernel (not two layers, inputs not a multiple of 4 or above 384,
@@ -470,6 +472,8 @@ struct BlockPlan {
     const int32_t *labels;
     int64_t n_samples;
     int n0, n1, n2, act1, act2, loss, keep_v, vec, chain_waves, d_stride;
+    int per;                      // wide hidden layers: units of a workgroup
+    unsigned long long *all_x;    // wide hidden layers: parts of the output layer's net inputs
     float lr;
     uint32_t seq0;
 };
@@ -479,6 +483,11 @@ struct BlockPlan {
 bool block_geometry(const int32_t *n, int L, BlockGeom &g);
 size_t block_exchange_bytes(const int32_t *n, int L);
 hipError_t block_prepare(const int32_t *n, int act);
+// ... with the hidden layer over all workgroups (dn_wide_block.hip), for nets that wide_geometry takes
+bool wide_block_fits(int n1, int per);
+size_t wide_block_exchange_bytes();
+hipError_t wide_block_prepare(int n2, int act);
+hipError_t launch_wide_block_epoch(BlockPlan plan, int grid, unsigned long long *exchange, const unsigned long long **gram, hipStream_t stream);
 hipError_t launch_block_epoch(const BlockGeom &g, BlockPlan plan, unsigned long long *exchange, hipStream_t stream);
 
 // Slices and buffer offsets for widths n[0..L]; false if the net does not fit the kernel

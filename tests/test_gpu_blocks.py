@@ -110,6 +110,33 @@ def test_sample_blocks_with_inner_products_beyond_fp32(dnlib, large):
     run(dnlib, w, (0.0, 0.5))
 
 
+WIDE = [
+    # a hidden layer over all workgroups: 13, 8, 5, 6 and 7 groups of 32 units (one left over is shared by the waves), short last
+    # workgroups and blocks, rows that end within a tile
+    ([340, 100000, 10], [TANH, SOFTMAX], CE, 65),
+    ([384, 60001, 16], [SIG, SIG], MSE, 64),
+    # (no ReLU at these widths: among millions of net inputs one lies within rounding of zero, and whichever side it falls on moves
+    # its row by a step's whole change, 1e-3 of the weights against a bound of 2e-5)
+    ([340, 38000, 3], [TANH, SOFTMAX], CE, 97),
+    ([260, 45003, 11], [TANH, SOFTMAX], CE, 70),
+    ([336, 56000, 10], [LIN, SOFTMAX], CE, 96),
+]
+
+
+@pytest.mark.parametrize("widths,acts,loss,n", WIDE)
+def test_sample_blocks_of_wide_hidden_layers_match_checker(dnlib, widths, acts, loss, n):
+    announce("sample blocks, wide hidden layer widths=%s n=%d" % (widths, n))
+    run(dnlib, make(widths, acts, loss, n, lr=0.0003), (0.0, 0.5, 0.0))
+
+
+def test_sample_blocks_of_wide_hidden_layers_beyond_fp32(dnlib):
+    """Inner products that overflow: the kernel that sweeps W_1 every step takes the pass."""
+    announce("sample blocks, wide hidden layer: inner products beyond fp32")
+    w = make([340, 38000, 10], [TANH, SOFTMAX], CE, 70, lr=0.0003)
+    w.X[[3, 20, 66]] *= np.float32(3e18)
+    run(dnlib, w)
+
+
 def test_sample_blocks_left_to_other_kernels(dnlib):
     announce("sample blocks: nets and passes left to other kernels")
     for widths, acts, n in (([64, 128, 10], [RELU, SOFTMAX], 63), ([3, 70, 4], [TANH, SOFTMAX], 96), ([1028, 70, 4], [TANH, SOFTMAX], 96),
