@@ -1296,14 +1296,15 @@ using S3 = SliceTile<64, 64, 2, 2>;   // large weight gradients over a short k: 
 using S4 = SliceTile<32, 32, 4, 4>;   // as S2 with 256 threads: beside a narrow layer's gradient in one launch
 using S5 = SliceTile<32, 32, 4, 4, true>;   // short sums, on the fp32 instruction
 using S6 = SliceTile<32, 32, 2, 4, true>;   // ... large weight gradients
+using S7 = SliceTile<64, 64, 8, 2>;   // a tile or less per compute unit: two waves on a SIMD
 
 static const char *kVariantNames[] = {"128x128x16_r1",  "128x64x16_r2",   "64x64x64_k4_r2", "64x64x32_k4_r2",
                                       "32x64x32_k4_r2", "32x64x64_k8_r2", "32x32x64_k8_r2", "128x128x16_r2_pc16",
                                       "128x64x16_r2_pc16_o2", "64x64x16_r2_pc8_o4", "64x64x32_k2_r2_o2", "64x64x16_r2_pc8_o3",
                                       "32x32x64_k4_r2_o3", "slice_64x64_k4", "slice_32x64_k8",
                                       "slice_32x32_k8", "slice_64x64_k2", "slice_32x32_k4_f32",
-                                      "slice_32x32_k2_f32"};
-constexpr int kVariants = 19;
+                                      "slice_32x32_k2_f32", "slice_64x64_k8"};
+constexpr int kVariants = 20;
 int gemm_variant_count() { return kVariants; }
 const char *gemm_variant_name(int v) { return (v >= 0 && v < kVariants) ? kVariantNames[v] : "?"; }
 
@@ -1371,7 +1372,15 @@ static bool in_pairs(GemmKind kind, const GemmArgs &a, long tiles64)
 // Tile shape from the problem shape.
 // Pairs: 64 x 64 tiles need the fewest operand reads and splits per product and are the choice once most compute units have
 // one; below that smaller tiles keep more units busy, for a long k the middle shape, whose k is also split across
-// workgroups.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 62 / 64 / 77; 2048 x 1024, k 1024: 30 / 47 /
+// workgroups.  With 256 tiles or fewer a compute unit has one of them, four waves of it one on each SIMD, and half of such a
+// wave's time is waiting: eight waves (two on a SIMD, half the k each) are faster wherever 64 x 64 was the choice, and for forward
+// and delta products from 129 tiles on and over a long k from 65.  us (eight waves / four / the choice before): forward 256 x
+// 4096, k 4096 52 / 60 / 60, k 1024 19.4 / 22.2, k 512 13.8 / 15.3; 768 x 1024, k 1024 17.6 / 21.5; 576 x 1024, k 1024 16.9 / 20.8 /
+// 22.3; 700 x 900, k 300 11.3 / 14.2 / 15.0; 250 x 4001, k 4003 62 / 103; 512 x 1024, k 4096 33.1 / 37.7 / 36.5, k 3072 28.5 / 31.1 /
+// 28.8, k 2048 22.0 / 24.0 / 21.1; 257 x 1021, k 4097 30 / 45 / 42; 384 x 1024, k 4096 30.8 / 35.4 / 32.8; but 256 x 1024 (64 tiles),
+// k 4096 23.8 / 25.3 / 23.0 and 1500 x 1024 (384 tiles), k 1024 33.3 / 28.1.  Gradient (with the launch that forms the output
+// delta) 1024 x 1024, k 2048 37 / 44, k 512 17.8 / 18.4, k 256 13.8 / 13.4; 777 x 1021, k 301 15.1 / 17.1; 1500 x 1500 (576
+// tiles), k 512 41 / 34.5.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 62 / 64 / 77; 2048 x 1024, k 1024: 30 / 47 /
 // 47; 768 x 1024, k 1024: 19.3 / 22.6 / 20.3; 640 x 1024, k 2048: 32 / 35.5 / 32; 512 x 1024, k 2048: 22 / 20 / 24.5; 256 x
 // 1000, k 4096: 24.9 / 21.2 / 23.5; 257 x 1021, k 4097: 45.7 / 42.5 / 43.8; 512 x 1024, k 1024: 15.1 / 13.2 / 14.9; 128 x
 // 1024, k 1024: 13.0 / 10.4 / 8.8; gradient 1024 x 1024, k 512: 15.1 / 19.4 / 19.3.  Operands read through registers
@@ -1386,8 +1395,9 @@ static int pick_variant(GemmKind kind, const GemmArgs &a)
     const long t64 = tiles(64, 64);
     if (in_pairs(kind, a, t64)) {
         if (kind == GEMM_GRAD && large_short_grad(t64, a.K)) return 16;
-        if (t64 >= (kind == GEMM_GRAD ? 128 : 192)) return 13;
-        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return t64 <= 128 ? 14 : 13;
+        if (t64 <= 256 && (kind == GEMM_GRAD ? t64 >= 128 && a.K > 256 : t64 > 128 || (t64 > 64 && a.K >= 3072))) return 19;
+        if (kind == GEMM_GRAD ? t64 >= 128 : t64 > 256) return 13;
+        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 14;
         return tiles(32, 64) >= 192 && vec_ok(kind, a) ? 14 : 15;
     }
     return kind == GEMM_GRAD && large_short_grad(t64, a.K) ? 18 : 17;
@@ -1592,6 +1602,7 @@ hipError_t launch_gemm(GemmKind kind, const GemmArgs &a, int variant, hipStream_
     case 16: return launch_kind<S3>(kind, a, stream);
     case 17: return launch_kind<S5>(kind, a, stream);
     case 18: return launch_kind<S6>(kind, a, stream);
+    case 19: return launch_kind<S7>(kind, a, stream);
     default: return hipErrorInvalidValue;
     }
 }
