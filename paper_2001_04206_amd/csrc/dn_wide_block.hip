@@ -11,10 +11,12 @@
 //
 // What bounds it: the exchange.  340-100000-10, 256 samples, workgroup 0, cycles per step: activations and own sums 980, exchange
 // 10700 (two hops of 3900 and waiting for the slowest of sixteen workgroups), output layer 690, deltas and corrections 590;
-// a block's sweep is 30 us of matrix instructions beside 200 us of steps.  us per step 20.2 -> 5.7 (a pass 5310 -> 1480),
-// 340-60001-10 15.7 -> 6.3 and 384-40000-3 14.3 -> 5.8 in passes of 130 and 96 samples.  Exchanges tried: every workgroup reads
+// a block's sweep is 30 us of matrix instructions beside 180 us of steps.  us per step, a pass with it divided by its samples:
+// 340-100000-10, 256 samples 20.8 -> 5.5 (a pass 5335 -> 1410); 340-60001-10 15.6 -> 6.3 and 384-40000-3 14.3 -> 6.0 in passes of
+// 130 and 96 samples.  Exchanges tried: every workgroup reads
 // all 2560 words, by workgroup 12.3 us a step, by output (whole lines) 9.0; two levels 7.7, with three looks on their way at a
-// time 8.7 (the looks hold up the words), with eight copies of the upper level 6.9; steps before the sweep (s_setprio) 6.8.
+// time 8.7 (the looks hold up the words), with eight copies of the upper level 6.9; steps before the sweep (s_setprio) 6.8; the
+// sweep's products with a sum per tile 5.7 (one sum 5.8 to 6.5; four side by side 6.2, their registers spill).
 #define DN_PERSIST_THREADS 512   // four waves for the steps, four for the sweep
 #include "dn_block.h"
 
@@ -63,9 +65,9 @@ __device__ __forceinline__ void sweep(const BlockPlan &p, const ChainLds &l, int
         float nld[16];
 #pragma unroll
         for (int s = 0; s < 16; ++s) nld[s] = update >= 0 ? deltas[(2 * s + h) * stride + unit] : 0.f;
-        v16f acc;
+        v16f total;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int r = 0; r < 16; ++r) total[r] = 0.f;
         auto load = [&](TileOperands &t, int tile) {
             const int f0 = 32 * tile;
 #pragma unroll
@@ -106,6 +108,11 @@ __device__ __forceinline__ void sweep(const BlockPlan &p, const ChainLds &l, int
                 }
             }
             if (products >= 0) {
+                // (a sum per tile: one of 340 terms in a row left the net inputs, and W_2 with them, 11 % further from 64 bits than
+                // the sixteen short ones of the kernel that sweeps every step)
+                v16f acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const bool in = f0 + 8 * q + 4 * h < n0;
@@ -113,6 +120,8 @@ __device__ __forceinline__ void sweep(const BlockPlan &p, const ChainLds &l, int
                     for (int e = 0; e < 4; ++e)
                         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? t.xf[q][e] : 0.f, in ? w[4 * q + e] : 0.f, acc, 0, 0, 0);
                 }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) total[r] += acc[r];
             }
         };
         const int step = shared ? 4 : 1;
@@ -130,8 +139,8 @@ __device__ __forceinline__ void sweep(const BlockPlan &p, const ChainLds &l, int
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int sample = 8 * (r / 4) + 4 * h + r % 4;
-                if (shared) l.parts[(sweeper * TB + sample) * 32 + c] = acc[r];
-                else to[sample * stride + unit] = acc[r];
+                if (shared) l.parts[(sweeper * TB + sample) * 32 + c] = total[r];
+                else to[sample * stride + unit] = total[r];
             }
         }
     }
