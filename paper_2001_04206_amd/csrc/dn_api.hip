@@ -949,13 +949,21 @@ dn_status dn_forward(dn_net *net, const float *X_dev, int32_t batch, float *out_
     net->have_fwd = false;
     net->have_bwd = false;
     net->w1_as_in_bwd = false;
-    dn_status st = run_forward(net, X_dev, batch, false);
-    if (st != DN_OK) return st;
+    // A narrow last layer's product, softmax and the copy to the caller are one launch, other softmax layers' last two.  (Not the
+    // copy of a single layer's narrow outputs: the product reads X, which a caller may ask to be overwritten.)
     const int L = net->L;
-    if (net->loss == DN_LOSS_CROSS_ENTROPY)
+    const bool narrow = net->gemm_variant < 0 && narrow_layer(net->n[L]);
+    dn_status st = run_forward(net, X_dev, batch, false, narrow ? L - 1 : L);
+    if (st != DN_OK) return st;
+    if (narrow)
+        DN_HIP(launch_narrow_output(L == 1 ? X_dev : net->A(L - 1), net->W(L), net->b(L), nullptr, net->A(L), nullptr, nullptr,
+                                    nullptr, batch, net->n[L], net->n[L - 1], net->act[L], net->loss, net->stream, nullptr, 0,
+                                    L > 1 ? out_dev : nullptr));
+    else if (net->loss == DN_LOSS_CROSS_ENTROPY)
         DN_HIP(launch_output_delta(net->A(L), net->D(L), nullptr, net->loss_rows(), batch, net->n[L],
-                                   net->act[L], net->loss, OUT_SOFTMAX_ONLY, net->stream));
-    if (out_dev) DN_HIP(launch_copy(out_dev, net->A(L), (size_t)batch * net->n[L], net->stream));
+                                   net->act[L], net->loss, OUT_SOFTMAX_ONLY, net->stream, nullptr, nullptr, out_dev));
+    if (out_dev && (narrow ? L == 1 : net->loss != DN_LOSS_CROSS_ENTROPY))
+        DN_HIP(launch_copy(out_dev, net->A(L), (size_t)batch * net->n[L], net->stream));
     net->X = X_dev;
     net->fwd_batch = batch;
     net->have_fwd = true;

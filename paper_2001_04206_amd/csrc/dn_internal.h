@@ -109,10 +109,11 @@ enum OutPhase : int {
     OUT_EVAL = 3           // z (cross-entropy) or a (squared error) -> loss and hit flag, rows untouched (dn_evaluate)
 };
 // hit_rows (OUT_EVAL only): 1.0 where the row's largest output is at the label, else 0.0.
-// loss_sums (optional, phases that produce a loss): loss_sums[row] += the row's loss.
+// loss_sums (optional, phases that produce a loss): loss_sums[row] += the row's loss.  copy (optional, phases that write p):
+// a second place for it.
 hipError_t launch_output_delta(float *AL, float *DL, const int32_t *labels, float *loss_rows,
                                int B, int nL, int act, int loss, int phase, hipStream_t stream,
-                               float *hit_rows = nullptr, double *loss_sums = nullptr);
+                               float *hit_rows = nullptr, double *loss_sums = nullptr, float *copy = nullptr);
 // Sum loss_rows[0..B): *loss_mean_out = sum / B (if non-null); *epoch_acc += sum (if non-null).
 hipError_t launch_loss_reduce(const float *loss_rows, int B, float *loss_mean_out,
                               double *epoch_acc, hipStream_t stream);
@@ -128,12 +129,13 @@ hipError_t launch_narrow_delta(const float *D, const float *W, const float *Apre
 hipError_t launch_narrow_grad(const float *D, const float *Aprev, float *C, float *V, float *gb, float *vb, int B,
                               int nl, int nin, int mode, float scale, float mu, hipStream_t stream);
 // Last layer with at most 16 outputs, training step: forward product, then softmax / loss / Delta_L as
-// launch_output_delta's phase OUT_FUSED, in one launch.  Aprev [B][nin], W [nl][nin], AL and DL [B][nl].
+// launch_output_delta's phase OUT_FUSED, in one launch.  Aprev [B][nin], W [nl][nin], AL and DL [B][nl].  Without labels the
+// outputs only.  copy: a second place for them.
 // Dprev (optional, [B][nin]): also receives Delta_{L-1} = (Delta_L W_L) * f'_{act_prev}(Aprev), as
 // launch_narrow_delta would compute it.
 hipError_t launch_narrow_output(const float *Aprev, const float *W, const float *bias, const int32_t *labels,
                                 float *AL, float *DL, float *loss_rows, double *loss_sums, int B, int nl, int nin,
-                                int act, int loss, hipStream_t stream, float *Dprev = nullptr, int act_prev = 0);
+                                int act, int loss, hipStream_t stream, float *Dprev = nullptr, int act_prev = 0, float *copy = nullptr);
 // Elementwise update of a parameter vector from a stored gradient (dn_update).
 hipError_t launch_update(float *p, float *v, const float *g, size_t count, float lr, float mu,
                          hipStream_t stream);
