@@ -411,7 +411,7 @@ struct TinyPlan {
     int L;
     TinyLayer layer[ON_MAX_L + 1];                   // 1..L
     int lds_act[ON_MAX_L + 1], lds_dl[ON_MAX_L + 1]; // activations (0: the features, two buffers) and deltas
-    double *loss_acc;
+    double *loss_acc;                                // set to the summed loss
     const float *X;
     const int32_t *labels;
     int64_t n_samples;

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(64) void tiny_epoch_kernel(TinyPlan p)
             if (with_v) ly.Vb[lane] = lds[ly.lds_vb + lane];
         }
     }
-    if (lane == 0) *p.loss_acc += loss_acc;
+    if (lane == 0) *p.loss_acc = loss_acc;
 }
 
 // ---- two-layer nets, plain gradient descent: the whole net in the wave's registers ----
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(64) void tiny_regs_epoch_kernel(TinyPlan p)
         const unsigned hi = __builtin_amdgcn_readlane((int)(__builtin_bit_cast(unsigned long long, loss_acc) >> 32), l);
         total += __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
     }
-    if (lane == 0) *p.loss_acc += total;
+    if (lane == 0) *p.loss_acc = total;
 }
 
 }  // namespace

@@ -1,4 +1,6 @@
-
+"""What used to be several small operations around a call: the last layer of a forward pass whose outputs are few is one launch
+(product, softmax or activation, the copy to the caller), and the kernels of one wavefront hand a pass's loss to the host
+themselves."""
 import numpy as np
 import pytest
 
@@ -51,3 +53,19 @@ def test_forward_tail(dnlib, widths, batch, loss, in_place):
     err = np.abs(out.cpu().numpy() - want)
     assert np.all(err <= bound), float((err / bound).max())
     net.close()
+
+
+# (more nets at once than there are places for their results; both forms of the kernel; after passes of another schedule)
+def test_losses_of_many_small_nets(dnlib):
+    nets = [build(dnlib, [4, 10, 3], [TANH, SOFTMAX], CE, 150, 5) for _ in range(70)]
+    X = torch.from_numpy(nets[0][3]).cuda()
+    y = torch.from_numpy((np.arange(150) % 3).astype(np.int32)).cuda()
+    for lr, mu in ((0.05, 0.0), (0.05, 0.9)):
+        losses = {(n[0].dn_train_epoch(X, y, 1, lr, mu), n[0].dn_train_epoch(X, y, 32, lr, mu), n[0].dn_evaluate(X, y, 50)[0])
+                  for n in nets}
+        assert len(losses) == 1
+    assert len({n[0].dn_train_epoch(X, y, 1, 0.05, 0.0) for n in nets}) == 1
+    for n in nets:
+        n[0].close()
+    again = [build(dnlib, [4, 10, 3], [TANH, SOFTMAX], CE, 150, 5)[0] for _ in range(2)]
+    assert len({n.dn_train_epoch(X, y, 1, 0.05, 0.0) for n in again}) == 1
