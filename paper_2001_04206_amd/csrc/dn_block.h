@@ -6,9 +6,9 @@
 // so a step needs the products W x_i (one 32-column product per block), the inner products x_j . x_i of the block's samples
 // and, of every step before it, one multiply-add per hidden unit; W_1 itself takes the block's 32 rank-1 updates as one
 // product.  (The bias of layer 1 is a further input of 1: x_j . x_i + 1.)  The arithmetic per weight is the same; what is
-// gone is the sweep over W_1 inside every step, and with it every wait but those of a block's end.  Weights are rounded
-// once where they were rounded once a step: the error against 64 bits after 4000 steps of 784-128-10 is 1.1e-7 of W_1's
-// norm where step by step it is 2.5e-7.
+// gone is the sweep over W_1 inside every step, and with it every wait but those of a block's end.  Errors against 64 bits
+// are those of the kernels that sweep every step: 4000 steps of 784-128-10, mean of twelve seeds, before and now, W_1 2.49e-7 and
+// 2.49e-7 of its norm, b_1 2.49e-7 and 2.49e-7, W_2 2.33e-7 and 2.37e-7, b_2 7.9e-7 and 8.2e-7 (2e-7 either way from seed to seed).
 //
 // Roles, one workgroup each, 256 threads (one wave per SIMD: a lane may hold 512 registers):
 //   chain   (workgroup 0) runs the steps.  A lane of the first NW waves keeps U hidden units: their net inputs for the
