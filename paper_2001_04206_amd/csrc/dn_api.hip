@@ -583,6 +583,14 @@ dn_status run_blocks(dn_net *net, const BlockGeom &g, const float *X, const int3
     return DN_OK;
 }
 
+// Whether a pass of a two-layer net takes its samples in blocks, on workgroups that the device can hold all at once.  (One wavefront
+// goes first.)
+bool takes_blocks(const dn_net *net, int64_t n_samples, float mu, BlockGeom &g)
+{
+    return net->block_ready && net->online_blocks && mu == 0.f && n_samples >= kBlocksMinSamples &&
+           block_geometry(net->n.data(), net->L, g) && g.grid <= net->device_cus;
+}
+
 // A whole batch-1 epoch on the persistent kernel that suits the net.
 dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
                      bool timing)
@@ -590,12 +598,10 @@ dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t
     const int L = net->L;
     TinyPlan tp;
     if (one_wave(net, mu, tp)) return run_tiny(net, tp, X, labels, n_samples, lr, mu, timing);
-    if (mu == 0.f && net->online_blocks && net->block_ready && n_samples >= kBlocksMinSamples) {
-        BlockGeom bg;
-        if (block_geometry(net->n.data(), L, bg) && bg.grid <= net->device_cus) {
-            net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
-            return run_blocks(net, bg, X, labels, n_samples, lr, timing);
-        }
+    BlockGeom bg;
+    if (takes_blocks(net, n_samples, mu, bg)) {
+        net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
+        return run_blocks(net, bg, X, labels, n_samples, lr, timing);
     }
     bool solo_ran = false;
     if (mu == 0.f && net->online_solo) {
@@ -642,7 +648,7 @@ dn_status run_online_shared(dn_net *net, const float *X, const int32_t *labels, 
         }
     }
     OnlineGeom g;   // same slices as net->geom; LDS residency depends on whether velocities are read
-    if (!online_geometry(net->n.data(), L, net->online_min_tile, mu != 0.f, g)) return DN_ERR_UNSUPPORTED;
+    if (!online_geometry(net->n.data(), L, net->online_min_tile, mu != 0.f, g) || g.grid > net->device_cus) return DN_ERR_UNSUPPORTED;
     OnlinePlan p{};
     p.L = L;
     for (int l = 1; l <= L; ++l) {
@@ -1090,7 +1096,8 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         wide_fit = wide_geometry(net->n.data(), net->L, net->device_cus, momentum != 0.f, wg);
     }
     const bool online_fit = net->online_ok || wide_fit;
-    bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || net->block_ready);
+    BlockGeom bg;
+    bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || takes_blocks(net, n_samples, momentum, bg));
     if (batch == 1 && net->online_mode == 2 && !online_fit) return DN_ERR_UNSUPPORTED;
     const bool pbatch = batch > 1 && net->batch_mode != 1 && net->batch_ok &&
                         (net->batch_mode == 2 || batch_pays(net, batch));

@@ -1,0 +1,65 @@
+"""Which kernels the library launches, on devices of made-up sizes: tests/fake_device.cpp stands in for the HIP runtime, so the
+library's own host code decides and nothing runs.  No launch of workgroups that wait for one another may be larger than the
+device, and a pass that no such kernel can take runs launch by launch."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2001_04206_amd import dn
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def device(tmp_path_factory):
+    if not os.path.exists(dn.LIB_PATH):
+        from paper_2001_04206_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("fake_device") / "fake_device")
+    lib = os.path.dirname(dn.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "fake_device.cpp"), "-o", exe,
+                    "-L" + lib, "-l:libdn.so", "-Wl,--export-dynamic,--allow-shlib-undefined,--disable-new-dtags,-rpath," + lib +
+                    ",-rpath,/opt/rocm/lib"], check=True)
+
+    def run(units, *commands):
+        """One (status, schedule, [(kernel, workgroups)]) per command."""
+        out = subprocess.run([exe, str(units), *commands], check=True, capture_output=True, text=True, timeout=120).stdout
+        rows = []
+        for line in out.splitlines():
+            status, schedule, *launches = line.split()
+            launches = [l.rsplit("/", 1) for l in launches]
+            rows.append((int(status), int(schedule),
+                         [(re.search(r"\d([a-z][a-z0-9_]*_kernel)", name).group(1), int(grid)) for name, grid in launches]))
+        assert len(rows) == len(commands), out
+        return rows
+
+    return run
+
+
+WAITING = ("online_epoch_kernel", "twin_epoch_kernel", "wide_epoch_kernel", "wide_block_epoch_kernel", "block_epoch_kernel", "batch_epoch_kernel",
+           "deep_batch_epoch_kernel")
+NETS = ["784-128-10:ce", "256-256-10:ce", "1024-1000-16:ce", "64-512-64:ce", "5-999-2:mse", "340-100000-10:ce", "340-38000-3:mse", "4-16-3:ce"]
+
+
+@pytest.mark.parametrize("units", [256, 128, 36, 21, 8, 2, 1])
+@pytest.mark.parametrize("net", NETS)
+def test_batch_1_passes_on_devices_of_any_size(device, net, units):
+    passes = ["train:96:1:0", "train:96:1:0.9", "train:63:1:0", "train:63:1:0.9", "option:online_blocks=0", "train:96:1:0"]
+    for command, (status, schedule, launches) in zip(passes, device(units, "net:%s:1" % net, *passes)[1:]):
+        assert status == dn.DN_OK, command
+        for kernel, grid in launches:
+            if kernel in WAITING:
+                assert grid <= units, (command, kernel, grid)
+        if command.startswith("train"):
+            assert launches and schedule != dn.DN_SCHED_NONE
+
+
+def test_digits_take_blocks_only_when_they_fit(device):
+    for units, blocks in ((256, True), (37, True), (36, False)):
+        rows = device(units, "net:784-128-10:ce:1", "train:64:1:0", "train:63:1:0", "train:64:1:0.5", "option:online_blocks=0", "train:64:1:0")
+        assert [r[1] == dn.DN_SCHED_SAMPLE_BLOCKS for r in rows[1:]] == [blocks, False, False, False, False]
+        if blocks:
+            assert rows[1][2] == [("block_epoch_kernel", 37)]
