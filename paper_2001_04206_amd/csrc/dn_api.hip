@@ -239,6 +239,24 @@ void refresh_persistent(dn_net *net)
     }
 }
 
+// Whether dn_forward takes a narrow last layer in one launch (product, softmax or activation, copy to the caller) or as a product and
+// what follows it.  A workgroup of the one launch reads all of W_L for one row (four beyond 1024 rows), so it loses where W_L is
+// large or the rows are many, and without a softmax there is less to save.  us for a whole dn_forward of 16-n-m, product and the
+// rest / one launch -- softmax: 64-16, 1 row 10.0 / 8.0; 4096-3, 64 and 512 rows 16.3 / 10.3, 26.9 / 17.4; 2048-16 (32768 weights),
+// 1 and 768 rows 14.3 / 10.7, 21.6 / 18.1; beyond it 4096-16, 1 and 1024 rows 16.1 / 14.7, 33.8 / 40.9, 8192-10, 1 row 17.1 / 18.2,
+// 16384-16, 1 row 19.2 / 38.4, 100000-10, 1 and 1024 rows 45.7 / 289, 389 / 983; 1025 to 2048 rows: 1024-10 22.3 / 20.0, 2048-6 34.1 /
+// 28.6, 512-10 16.1 / 15.3, but 256-16 12.7 / 14.4, 2048-16 1025 rows 24.5 / 24.2, 4096-10 44.6 / 47.3; 4096 rows: 256-10 15.4 /
+// 22.8, 1024-10 31.8 / 35.6.  Squared error, no copy: 1024-10, 1 and 768 rows 10.2 / 8.1, 13.6 / 11.4; 4096-3 14.1 / 9.4; but 64-16
+// 6.9 / 8.8, 256-16, 768 rows 9.0 / 10.5, 1536-16, 768 rows 16.6 / 17.1, 1024-16, 1025 rows 14.9 / 18.5.
+bool one_launch_forward(const dn_net *net, int rows)
+{
+    const int n_out = net->n[net->L], n_in = net->n[net->L - 1];
+    if (net->gemm_variant >= 0 || !narrow_layer(n_out)) return false;
+    const size_t weights = (size_t)n_out * n_in;
+    if (net->loss != DN_LOSS_CROSS_ENTROPY) return rows <= 768 && n_in >= 1024 && weights <= 16384;
+    return rows <= 768 ? weights <= 32768 : rows <= 2048 && n_in >= 512 && weights <= 16384;
+}
+
 double product_flop(const GemmArgs &g) { return 2.0 * (double)g.M * (double)g.N * (double)g.K; }
 
 bool rate_ok(float lr, float mu)
@@ -1003,7 +1021,7 @@ dn_status dn_forward(dn_net *net, const float *X_dev, int32_t batch, float *out_
     // A narrow last layer's product, softmax and the copy to the caller are one launch, other softmax layers' last two.  (Not the
     // copy of a single layer's narrow outputs: the product reads X, which a caller may ask to be overwritten.)
     const int L = net->L;
-    const bool narrow = net->gemm_variant < 0 && narrow_layer(net->n[L]);
+    const bool narrow = one_launch_forward(net, batch);
     dn_status st = run_forward(net, X_dev, batch, false, narrow ? L - 1 : L);
     if (st != DN_OK) return st;
     if (narrow)

@@ -8,7 +8,7 @@
 //     option:online_mode=2
 //     train:96:1:0.9          one epoch: samples, batch, momentum
 //     forward:64              rows
-// One line per command: its status, the schedule of the last epoch and the launches it made (mangled name/workgroups).
+// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups).
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include <cxxabi.h>
 #include <unistd.h>
 
 #include "dn.h"
@@ -37,7 +38,13 @@ std::map<const void *, std::string> &names()   // (the library registers its ker
 
 int log_launch(const void *f, Dim3 grid)
 {
-    launches += " " + names()[f] + "/" + std::to_string(grid.x * grid.y * grid.z);
+    int status;
+    char *full = abi::__cxa_demangle(names()[f].c_str(), nullptr, nullptr, &status);
+    std::string name = full ? full : names()[f];
+    free(full);
+    const size_t end = name.find("_kernel"), begin = name.find_last_of(": ", end);   // without namespaces, template arguments and parameters
+    name = end == std::string::npos ? name : name.substr(begin + 1, end + 7 - begin - 1);
+    launches += " " + name + "/" + std::to_string(grid.x * grid.y * grid.z);
     return 0;
 }
 

@@ -55,6 +55,15 @@ def test_forward_tail(dnlib, widths, batch, loss, in_place):
     net.close()
 
 
+# either side of the lines between one launch and several: four rows a workgroup (whole and ragged groups, rows of odd length, one
+# layer), the largest last layers of one row a workgroup, squared error
+@pytest.mark.parametrize("widths,batch,loss", [([24, 512, 10], 1025, CE), ([20, 1021, 16], 1030, CE), ([20, 1024, 16], 2048, CE), ([520, 7], 1101, CE),
+                                               ([24, 511, 10], 1025, CE), ([12, 2048, 16], 768, CE), ([12, 2049, 16], 5, CE), ([8, 10923, 3], 3, CE),
+                                               ([9, 1025, 3], 767, MSE), ([9, 1024, 16], 769, MSE)])
+def test_forward_tail_lines(dnlib, widths, batch, loss):
+    test_forward_tail(dnlib, widths, batch, loss, False)
+
+
 # (more nets at once than there are places for their results; both forms of the kernel; after passes of another schedule)
 def test_losses_of_many_small_nets(dnlib):
     nets = [build(dnlib, [4, 10, 3], [TANH, SOFTMAX], CE, 150, 5) for _ in range(70)]

@@ -2,7 +2,6 @@
 library's own host code decides and nothing runs.  No launch of workgroups that wait for one another may be larger than the
 device, and a pass that no such kernel can take runs launch by launch."""
 import os
-import re
 import subprocess
 
 import pytest
@@ -30,9 +29,7 @@ def device(tmp_path_factory):
         rows = []
         for line in out.splitlines():
             status, schedule, *launches = line.split()
-            launches = [l.rsplit("/", 1) for l in launches]
-            rows.append((int(status), int(schedule),
-                         [(re.search(r"\d([a-z][a-z0-9_]*_kernel)", name).group(1), int(grid)) for name, grid in launches]))
+            rows.append((int(status), int(schedule), [(l.split("/")[0], int(l.split("/")[1])) for l in launches]))
         assert len(rows) == len(commands), out
         return rows
 
@@ -63,3 +60,15 @@ def test_digits_take_blocks_only_when_they_fit(device):
         assert [r[1] == dn.DN_SCHED_SAMPLE_BLOCKS for r in rows[1:]] == [blocks, False, False, False, False]
         if blocks:
             assert rows[1][2] == [("block_epoch_kernel", 37)]
+
+
+# net, rows: whether dn_forward takes the last layer in one launch
+@pytest.mark.parametrize("net,rows,one", [
+    ("16-100000-10:ce", 1, False), ("16-100000-10:ce", 1024, False), ("16-16384-16:ce", 64, False), ("16-8193-4:ce", 1, False), ("16-8192-4:ce", 768, True),
+    ("16-8192-4:ce", 769, False), ("1024-1024-10:ce", 2048, True), ("1024-1024-10:ce", 2049, False), ("16-1024-16:ce", 2048, True),
+    ("16-1025-16:ce", 769, False), ("16-512-16:ce", 769, True), ("16-511-16:ce", 769, False), ("64-96-10:ce", 128, True), ("64-96-17:ce", 128, False),
+    ("16-100000-10:mse", 1, False), ("16-1024-16:mse", 768, True), ("16-1024-16:mse", 769, False), ("16-1023-16:mse", 1, False),
+    ("16-1025-16:mse", 1, False), ("16-64-16:mse", 1, False)])
+def test_narrow_last_layers_of_predictions(device, net, rows, one):
+    status, _, launches = device(256, "net:%s:%d" % (net, rows), "forward:%d" % rows)[1]
+    assert status == dn.DN_OK and ("narrow_output_kernel" in [k for k, _ in launches]) == one, launches
