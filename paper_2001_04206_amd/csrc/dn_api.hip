@@ -72,7 +72,7 @@ bool compute_layout(const int32_t *widths, int32_t n_widths, int32_t max_batch, 
     lo.off_scalars = o; o += kAlign;
     lo.online_bytes = std::max({online_exchange_bytes_bound(widths, L), twin_exchange_bytes_bound(widths, L),
                                 wide_exchange_bytes_bound(widths, L), block_exchange_bytes(widths, L),
-                                wide_exchange_bytes_bound(widths, L) > 0 ? wide_block_exchange_bytes() : 0});
+                                wide_block_exchange_bytes(widths, L)});
     lo.off_online = o; o += align_up(lo.online_bytes);
     lo.off_gemm_ws = o; o += align_up(GEMM_WS_FLOATS * sizeof(float));
     lo.off_gemm_counters = o; o += align_up(GEMM_COUNTERS * sizeof(unsigned));

@@ -20,7 +20,9 @@ static hipError_t block_act(int units, int n2, int act, const BlockGeom *g, cons
 bool block_geometry(const int32_t *n, int L, BlockGeom &g)
 {
     g = BlockGeom{};
-    if (L != 2 || n[0] < 4 || n[0] > 1024 || n[1] < 1 || n[2] < 1 || n[2] > 64) return false;
+    // (layers of at most 64: one wavefront's, whose arena need not hold the blocks' inner products)
+    if (L != 2 || (n[0] <= 64 && n[1] <= 64 && n[2] <= 64)) return false;
+    if (n[0] < 4 || n[0] > 1024 || n[1] < 1 || n[2] < 1 || n[2] > 64) return false;
     g.units_per_lane = n[2] <= 16 ? (n[1] <= 64 ? 1 : (n[1] <= 512 ? 2 : 4)) : (n[1] <= 256 ? 1 : 2);
     g.chain_waves = (n[1] + 64 * g.units_per_lane - 1) / (64 * g.units_per_lane);
     if (g.chain_waves > 4) return false;

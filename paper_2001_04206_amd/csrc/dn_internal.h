@@ -481,13 +481,13 @@ struct BlockPlan {
 };
 
 // False unless the net has two layers of 4 to 1024 inputs, at most 1004 hidden units (512 with more than 16 outputs) and
-// at most 64 outputs.
+// at most 64 outputs, some width above 64.
 bool block_geometry(const int32_t *n, int L, BlockGeom &g);
 size_t block_exchange_bytes(const int32_t *n, int L);
 hipError_t block_prepare(const int32_t *n, int act);
 // ... with the hidden layer over all workgroups (dn_wide_block.hip), for nets that wide_geometry takes
 bool wide_block_fits(int n1, int per);
-size_t wide_block_exchange_bytes();
+size_t wide_block_exchange_bytes(const int32_t *n, int L);
 hipError_t wide_block_prepare(int n2, int act);
 hipError_t launch_wide_block_epoch(BlockPlan plan, int grid, unsigned long long *exchange, const unsigned long long **gram, hipStream_t stream);
 hipError_t launch_block_epoch(const BlockGeom &g, BlockPlan plan, unsigned long long *exchange, hipStream_t stream);

@@ -241,9 +241,12 @@ bool wide_block_fits(int n1, int per)
 constexpr size_t kAllWords = 2 * 4096 + 2 * 8 * 256;
 static_assert(ON_MAX_WG <= 256, "sixteen groups of sixteen workgroups");
 
-size_t wide_block_exchange_bytes()
+size_t wide_block_exchange_bytes(const int32_t *n, int L)
 {
-    return (kAllWords + (size_t)(BLOCK_LAUNCH_SAMPLES / TB) * kRecord) * sizeof(u64);
+    bool fits = false;   // on a device of some size
+    WideGeom g;
+    for (int units = ON_MAX_WG; units > 0 && !fits; --units) fits = wide_geometry(n, L, units, false, g) && wide_block_fits(n[1], g.per);
+    return !fits ? 0 : (kAllWords + (size_t)(BLOCK_LAUNCH_SAMPLES / TB) * kRecord) * sizeof(u64);
 }
 
 hipError_t wide_block_prepare(int n2, int act)

@@ -60,8 +60,9 @@ SHAPES = [
     # hidden units around one, two and more units a lane and one, two and four waves; outputs around the compiled widths;
     # inputs around the waves' column groups and off the 16-byte path; samples around blocks
     ([784, 128, 10], [RELU, SOFTMAX], CE, 96),
-    ([4, 1, 1], [TANH, LIN], MSE, 64),
-    ([5, 64, 3], [SIG, SIG], MSE, 65),
+    ([65, 1, 1], [TANH, LIN], MSE, 64),
+    ([4, 65, 1], [TANH, LIN], MSE, 64),
+    ([66, 64, 3], [SIG, SIG], MSE, 65),
     ([63, 65, 4], [TANH, SOFTMAX], CE, 97),
     ([64, 127, 5], [LIN, SOFTMAX], CE, 127),
     ([65, 128, 10], [SIG, SOFTMAX], CE, 128),
@@ -140,7 +141,7 @@ def test_sample_blocks_of_wide_hidden_layers_beyond_fp32(dnlib):
 def test_sample_blocks_left_to_other_kernels(dnlib):
     announce("sample blocks: nets and passes left to other kernels")
     for widths, acts, n in (([64, 128, 10], [RELU, SOFTMAX], 63), ([3, 70, 4], [TANH, SOFTMAX], 96), ([1028, 70, 4], [TANH, SOFTMAX], 96),
-                            ([16, 1008, 4], [TANH, SOFTMAX], 96), ([16, 516, 20], [TANH, SOFTMAX], 96), ([16, 70, 65], [TANH, SOFTMAX], 96)):
+                            ([16, 1008, 4], [TANH, SOFTMAX], 96), ([16, 516, 20], [TANH, SOFTMAX], 96), ([16, 70, 65], [TANH, SOFTMAX], 96), ([64, 64, 64], [TANH, SOFTMAX], 96), ([4, 16, 3], [SIG, SOFTMAX], 96)):
         run(dnlib, make(widths, acts, CE, n), blocks=False)
 
 

@@ -62,6 +62,15 @@ def test_digits_take_blocks_only_when_they_fit(device):
             assert rows[1][2] == [("block_epoch_kernel", 37)]
 
 
+def test_nets_of_one_wavefront_hold_no_blocks(device):
+    """Every layer at most 64 wide: no room in the arena for inner products that nothing forms, whatever runs the passes."""
+    products = 4096 // 32 * 2 * 32 * 32 * 8
+    for widths in ([4, 16, 3], [64, 64, 64]):
+        assert dn.dn_net_arena_bytes(widths, 1) < dn.dn_net_arena_bytes([65, 64, 64], 1) - products // 2
+        rows = device(256, "net:%s:ce:1" % "-".join(map(str, widths)), "train:96:1:0", "option:online_tiny=0", "train:96:1:0")
+        assert rows[1][1] == dn.DN_SCHED_ONE_WAVE_REGISTERS and rows[3][1] in (dn.DN_SCHED_ONE_WORKGROUP, dn.DN_SCHED_TWO_COPY), rows
+
+
 # net, rows: whether dn_forward takes the last layer in one launch
 @pytest.mark.parametrize("net,rows,one", [
     ("16-100000-10:ce", 1, False), ("16-100000-10:ce", 1024, False), ("16-16384-16:ce", 64, False), ("16-8193-4:ce", 1, False), ("16-8192-4:ce", 768, True),
