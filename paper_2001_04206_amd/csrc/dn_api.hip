@@ -188,6 +188,8 @@ struct dn_net {
     double *hit_acc() const { return (double *)(arena + lo.off_scalars + 16); }   // after epoch_acc and the abort flag
     double *epoch_acc() const { return (double *)(arena + lo.off_scalars); }
     int *abort_flag() const { return (int *)(arena + lo.off_scalars + sizeof(double)); }
+    unsigned *arrived() const { return (unsigned *)(arena + lo.off_scalars + 24); }   // launches of sample blocks: see BlockPlan
+    int *settled() const { return (int *)(arena + lo.off_scalars + 28); }
     unsigned long long *exchange() const { return (unsigned long long *)(arena + lo.off_online); }
     unsigned long long *batch_exchange() const { return (unsigned long long *)(arena + lo.off_batch); }
     char *deep_exchange() const { return arena + lo.off_deep; }
@@ -582,7 +584,11 @@ dn_status run_blocks(dn_net *net, const BlockGeom &g, const float *X, const int3
     p.loss_acc = net->epoch_acc();
     p.act1 = net->act[1]; p.act2 = net->act[2]; p.loss = net->loss;
     p.lr = lr;
-    for (int64_t s0 = 0; s0 < n_samples; s0 += BLOCK_LAUNCH_SAMPLES) {
+    p.arrived = net->arrived();
+    p.settled = net->settled();
+    for (int64_t s0 = 0; s0 < n_samples; s0 += BLOCK_LAUNCH_SAMPLES, ++p.launch) {
+        p.expected = (unsigned)(p.launch + 1) * (unsigned)g.grid;
+        if (net->online_blocks >= 2 && p.launch == net->online_blocks - 2) ++p.expected;   // (one more than will come)
         const int64_t n = std::min<int64_t>(n_samples - s0, BLOCK_LAUNCH_SAMPLES);
         if ((uint64_t)net->online_seq + (uint64_t)n + 2 > 0xffffffffull) {   // step numbers would wrap
             DN_HIP(hipMemsetAsync(net->exchange(), 0, net->lo.online_bytes, net->stream));
@@ -611,13 +617,13 @@ bool takes_blocks(const dn_net *net, int64_t n_samples, float mu, BlockGeom &g)
 
 // A whole batch-1 epoch on the persistent kernel that suits the net.
 dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
-                     bool timing)
+                     bool blocks, bool timing)
 {
     const int L = net->L;
     TinyPlan tp;
     if (one_wave(net, mu, tp)) return run_tiny(net, tp, X, labels, n_samples, lr, mu, timing);
     BlockGeom bg;
-    if (takes_blocks(net, n_samples, mu, bg)) {
+    if (blocks && takes_blocks(net, n_samples, mu, bg)) {
         net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
         return run_blocks(net, bg, X, labels, n_samples, lr, timing);
     }
@@ -827,6 +833,44 @@ dn_status run_deep_persistent(dn_net *net, const float *X, const int32_t *labels
         DN_HIP(launch_deep_epoch(g, p, net->stream));
         net->deep_seq += (uint32_t)nt;
     }
+    return DN_OK;
+}
+
+// Launch-per-product path: every step enqueued on the net's stream.
+dn_status run_launches(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, int32_t batch, float lr, float momentum,
+                       bool timing)
+{
+    const int L = net->L;
+    // The epoch's loss is kept as one running sum per batch row, added
+    // to by the output kernel of each step, and reduced once after the last step.
+    const int rows_used = (int)(n_samples < batch ? n_samples : batch);
+    DN_HIP(hipMemsetAsync(net->loss_sums(), 0, (size_t)rows_used * sizeof(double), net->stream));
+    for (int64_t s0 = 0; s0 < n_samples; s0 += batch) {
+        const int B = (int)((n_samples - s0) < batch ? (n_samples - s0) : batch);
+        const float *Xb = X + (size_t)s0 * net->n[0];
+        const bool last = s0 + batch >= n_samples;
+        const int mode = (momentum != 0.f) ? GRAD_MOMENTUM : (last ? GRAD_SGD_KEEPV : GRAD_SGD);
+        // a last layer of at most 16 outputs: its forward product and the output error in one launch
+        const bool fused_out = net->gemm_variant < 0 && narrow_layer(net->n[L]);
+        dn_status st = run_forward(net, Xb, B, timing, fused_out ? L - 1 : L);
+        if (st != DN_OK) return st;
+        {
+            // with a narrow last layer the launch also holds that layer's forward product and its delta product
+            const double out_flop = fused_out ? 2.0 * B * (double)net->n[L] * net->n[L - 1] * (L > 1 ? 2.0 : 1.0) : 0.0;
+            ScopedTimer t(net, DN_K_OUTPUT, timing, out_flop, true);
+            if (fused_out)
+                DN_HIP(launch_narrow_output(L == 1 ? Xb : net->A(L - 1), net->W(L), net->b(L), labels + s0, net->A(L),
+                                            net->D(L), net->loss_rows(), net->loss_sums(), B, net->n[L], net->n[L - 1],
+                                            net->act[L], net->loss, net->stream, L > 1 ? net->D(L - 1) : nullptr,
+                                            L > 1 ? net->act[L - 1] : 0));
+            else
+                DN_HIP(launch_output_delta(net->A(L), net->D(L), labels + s0, net->loss_rows(), B, net->n[L],
+                                           net->act[L], net->loss, OUT_FUSED, net->stream, nullptr, net->loss_sums()));
+        }
+        st = run_backward(net, Xb, B, mode, lr, momentum, timing, fused_out && L > 1);
+        if (st != DN_OK) return st;
+    }
+    DN_HIP(launch_loss_sums_reduce(net->loss_sums(), rows_used, net->epoch_acc(), net->stream));
     return DN_OK;
 }
 
@@ -1106,7 +1150,6 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     net->have_fwd = net->have_bwd = net->w1_as_in_bwd = false;  // activations / gradients of the split API are overwritten
     const bool timing = net->time_kernels != 0;
     net->timed = 0;
-    const int L = net->L;
     // (a two-layer net with a very wide hidden layer may suit only the kernel for such nets)
     bool wide_fit = false;
     if (net->online_wide && net->wide_ok) {
@@ -1114,8 +1157,6 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         wide_fit = wide_geometry(net->n.data(), net->L, net->device_cus, momentum != 0.f, wg);
     }
     const bool online_fit = net->online_ok || wide_fit;
-    BlockGeom bg;
-    bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || takes_blocks(net, n_samples, momentum, bg));
     if (batch == 1 && net->online_mode == 2 && !online_fit) return DN_ERR_UNSUPPORTED;
     const bool pbatch = batch > 1 && net->batch_mode != 1 && net->batch_ok &&
                         (net->batch_mode == 2 || batch_pays(net, batch));
@@ -1124,66 +1165,57 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     if (batch > 1 && net->batch_mode == 2 && !pbatch && !pdeep) return DN_ERR_UNSUPPORTED;
     // One wavefront runs the whole pass and hands the loss over itself: no memset before it and no copy after it (iris 4-16-3,
     // 150 samples, us a pass: 119.3 with both, 102.8 without).
+    BlockGeom bg;
     TinyPlan tiny;
-    const bool direct = persistent && net->result && one_wave(net, momentum, tiny);
-    if (!direct) DN_HIP(hipMemsetAsync(net->epoch_acc(), 0, sizeof(double) + sizeof(int), net->stream));
+    bool blocks = true;   // samples may be taken in blocks
+    int64_t first = 0;    // samples that are done
+    const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && one_wave(net, momentum, tiny);
+    // what the kernels of a whole pass leave beside the parameters: off_scalars
+    struct { double acc; int aborted, pad; double hits; unsigned arrived; int settled; } res{};
+    static_assert(sizeof(res) == 32, "the scalars of the arena");
+    if (!direct) DN_HIP(hipMemsetAsync(net->epoch_acc(), 0, sizeof(res), net->stream));
     DN_HIP(hipEventRecord(net->ev_epoch0, net->stream));
-    // A persistent path that turns out not to fit (its geometry is recomputed for this call's momentum
-    // and the current tile option) reports DN_ERR_UNSUPPORTED before it launches anything: in automatic
-    // mode the epoch then runs with one launch per product instead.
-    net->last_schedule = DN_SCHED_LAUNCHES;
-    if (persistent) {
-        net->last_schedule = DN_SCHED_PER_SAMPLE;   // run_online changes it if the two-copy kernel takes the pass
-        dn_status st = run_online(net, X_dev, labels_dev, n_samples, lr, momentum, timing);
-        if (st == DN_ERR_UNSUPPORTED && net->online_mode == 0) persistent = false;
-        else if (st != DN_OK) return st;
-    } else if (pbatch) {
-        net->last_schedule = DN_SCHED_MINIBATCH;
-        dn_status st = run_batch_persistent(net, X_dev, labels_dev, n_samples, batch, lr, momentum, timing);
-        if (st == DN_OK) persistent = true;
-        else if (st != DN_ERR_UNSUPPORTED || net->batch_mode != 0) return st;
-    } else if (pdeep) {
-        net->last_schedule = DN_SCHED_MINIBATCH_DEEP;
-        dn_status st = run_deep_persistent(net, X_dev, labels_dev, n_samples, batch, lr, timing);
-        if (st == DN_OK) persistent = true;
-        else if (st != DN_ERR_UNSUPPORTED || net->batch_mode != 0) return st;
-    }
-    if (!persistent) net->last_schedule = DN_SCHED_LAUNCHES;
-    // Launch-per-product path.  The epoch's loss is kept as one running sum per batch row, added
-    // to by the output kernel of each step, and reduced once after the last step.
-    const int rows_used = (int)(n_samples < batch ? n_samples : batch);
-    if (!persistent) DN_HIP(hipMemsetAsync(net->loss_sums(), 0, (size_t)rows_used * sizeof(double), net->stream));
-    for (int64_t s0 = persistent ? n_samples : 0; s0 < n_samples; s0 += batch) {
-        const int B = (int)((n_samples - s0) < batch ? (n_samples - s0) : batch);
-        const float *Xb = X_dev + (size_t)s0 * net->n[0];
-        const bool last = s0 + batch >= n_samples;
-        const int mode = (momentum != 0.f) ? GRAD_MOMENTUM : (last ? GRAD_SGD_KEEPV : GRAD_SGD);
-        // a last layer of at most 16 outputs: its forward product and the output error in one launch
-        const bool fused_out = net->gemm_variant < 0 && narrow_layer(net->n[L]);
-        dn_status st = run_forward(net, Xb, B, timing, fused_out ? L - 1 : L);
-        if (st != DN_OK) return st;
-        {
-            // with a narrow last layer the launch also holds that layer's forward product and its delta product
-            const double out_flop = fused_out ? 2.0 * B * (double)net->n[L] * net->n[L - 1] * (L > 1 ? 2.0 : 1.0) : 0.0;
-            ScopedTimer t(net, DN_K_OUTPUT, timing, out_flop, true);
-            if (fused_out)
-                DN_HIP(launch_narrow_output(L == 1 ? Xb : net->A(L - 1), net->W(L), net->b(L), labels_dev + s0, net->A(L),
-                                            net->D(L), net->loss_rows(), net->loss_sums(), B, net->n[L], net->n[L - 1],
-                                            net->act[L], net->loss, net->stream, L > 1 ? net->D(L - 1) : nullptr,
-                                            L > 1 ? net->act[L - 1] : 0));
-            else
-                DN_HIP(launch_output_delta(net->A(L), net->D(L), labels_dev + s0, net->loss_rows(), B, net->n[L],
-                                           net->act[L], net->loss, OUT_FUSED, net->stream, nullptr, net->loss_sums()));
+    for (;;) {
+        const float *X = X_dev + (size_t)first * net->n[0];
+        const int32_t *labels = labels_dev + first;
+        const int64_t n = n_samples - first;
+        bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || (blocks && takes_blocks(net, n, momentum, bg)));
+        // A persistent path that turns out not to fit (its geometry is recomputed for this call's momentum
+        // and the current tile option) reports DN_ERR_UNSUPPORTED before it launches anything: in automatic
+        // mode the epoch then runs with one launch per product instead.
+        net->last_schedule = DN_SCHED_LAUNCHES;
+        if (persistent) {
+            net->last_schedule = DN_SCHED_PER_SAMPLE;   // run_online changes it if another kernel takes the pass
+            dn_status st = run_online(net, X, labels, n, lr, momentum, blocks, timing);
+            if (st == DN_ERR_UNSUPPORTED && net->online_mode == 0) persistent = false;
+            else if (st != DN_OK) return st;
+        } else if (pbatch) {
+            net->last_schedule = DN_SCHED_MINIBATCH;
+            dn_status st = run_batch_persistent(net, X, labels, n, batch, lr, momentum, timing);
+            if (st == DN_OK) persistent = true;
+            else if (st != DN_ERR_UNSUPPORTED || net->batch_mode != 0) return st;
+        } else if (pdeep) {
+            net->last_schedule = DN_SCHED_MINIBATCH_DEEP;
+            dn_status st = run_deep_persistent(net, X, labels, n, batch, lr, timing);
+            if (st == DN_OK) persistent = true;
+            else if (st != DN_ERR_UNSUPPORTED || net->batch_mode != 0) return st;
         }
-        st = run_backward(net, Xb, B, mode, lr, momentum, timing, fused_out && L > 1);
-        if (st != DN_OK) return st;
+        if (!persistent) {
+            net->last_schedule = DN_SCHED_LAUNCHES;
+            dn_status st = run_launches(net, X, labels, n, batch, lr, momentum, timing);
+            if (st != DN_OK) return st;
+        }
+        DN_HIP(hipEventRecord(net->ev_epoch1, net->stream));
+        if (!direct) DN_HIP(hipMemcpyAsync(&res, net->epoch_acc(), sizeof(res), hipMemcpyDeviceToHost, net->stream));
+        DN_HIP(hipStreamSynchronize(net->stream));
+        if (direct) res.acc = *(volatile double *)net->result;
+        if (res.settled >= 0) break;
+        // A launch of sample blocks whose workgroups did not all find room has changed nothing, nor have those behind it: the
+        // samples from its first on go to another kernel.
+        first += (int64_t)(-1 - res.settled) * BLOCK_LAUNCH_SAMPLES;
+        blocks = false;
+        DN_HIP(hipMemsetAsync(net->abort_flag(), 0, sizeof(res) - sizeof(double), net->stream));
     }
-    if (!persistent) DN_HIP(launch_loss_sums_reduce(net->loss_sums(), rows_used, net->epoch_acc(), net->stream));
-    DN_HIP(hipEventRecord(net->ev_epoch1, net->stream));
-    struct { double acc; int aborted; int pad; } res = {0.0, 0, 0};
-    if (!direct) DN_HIP(hipMemcpyAsync(&res, net->epoch_acc(), sizeof(double) + sizeof(int), hipMemcpyDeviceToHost, net->stream));
-    DN_HIP(hipStreamSynchronize(net->stream));
-    if (direct) res.acc = *(volatile double *)net->result;
     DN_HIP(hipEventElapsedTime(&net->epoch_ms, net->ev_epoch0, net->ev_epoch1));
     collect_times(net);
     if (res.aborted) return DN_ERR_DEVICE;   // a workgroup of the persistent kernel gave up waiting
@@ -1367,7 +1399,7 @@ dn_status dn_set_option(dn_net *net, const char *name, int64_t value)
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->online_twin = (int)value;
     } else if (!strcmp(name, "online_blocks")) {
-        if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
+        if (value < 0 || value > 1 << 20) return DN_ERR_INVALID_ARG;
         net->online_blocks = (int)value;
     } else if (!strcmp(name, "online_wide")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;

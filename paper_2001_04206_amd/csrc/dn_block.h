@@ -214,6 +214,30 @@ __device__ __forceinline__ bool wave_poll(u64 (&v)[N], uint32_t seq, Addr addr, 
     }
 }
 
+// A launch counts only if all of its workgroups are on the device at once, which other work may prevent.  Nobody writes a parameter
+// before the matter is settled, and whoever settles it first settles it for all: the first Gram workgroup, which waits for nobody
+// else, after its products (kPlacePolls polls for those that are missing), or a wave that is about to write or has timed out.
+// patience: polls to wait for the missing ones.  (Looked at in every wait instead, it cost the steps of 784-128-10 3.5 %.)
+constexpr int kPlacePolls = 1 << 16;   // of about a microsecond
+__device__ __forceinline__ bool launch_counts(const BlockPlan &p, int patience)
+{
+    for (int spins = 0;; ++spins) {
+        const int settled = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.settled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (settled != p.launch) return settled == p.launch + 1;
+        const unsigned there = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (spins >= patience || there == p.expected) {
+            int seen = p.launch;
+            const int word = patience > 0 && there == p.expected ? p.launch + 1 : -1 - p.launch;
+            if ((threadIdx.x & 63) == 0)
+                __hip_atomic_compare_exchange_strong(p.settled, &seen, word, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+}
+// Before a wave writes parameters; ok: its own waits have come to their end.  (One that timed out takes the launch back.)
+__device__ __forceinline__ bool may_write(const BlockPlan &p, bool ok) { return launch_counts(p, ok ? kPlacePolls : 0) && ok; }
+
 constexpr int kRecord = 2 * TB * TB;   // words of a block's record: its own inner products, then those with the next block's samples
 constexpr int kFlagWord = TB - 1;      // (own products of sample 0 end one word earlier)
 constexpr int OWN_BAD = 1, NEXT_BAD = 2;
@@ -618,6 +642,7 @@ __device__ __forceinline__ void run_steps(const BlockPlan &p, const ChainLds &l)
     if constexpr (WIDE) __syncthreads();   // the last block's deltas
 
     // ---- epilogue ----
+    if (!WIDE && !may_write(p, *l.abort == 0)) return;
     int n2e = n2;
     asm volatile("" : "+s"(n2e));
 #pragma unroll
@@ -845,6 +870,7 @@ __device__ __forceinline__ void run_rows(const BlockPlan &p, float *lds, lds_int
     }
 
     // ---- epilogue ----
+    if (!may_write(p, ok && *s_abort == 0)) return;
     const int row = row0 + i4;
     if (row >= n1) return;
 #pragma unroll
@@ -863,7 +889,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_abort, s_flags[2];
-    if (threadIdx.x == 0) s_abort = 0;
+    if (threadIdx.x == 0) {
+        s_abort = 0;
+        __hip_atomic_fetch_add(p.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     const int w = (int)blockIdx.x;
     if (w == 0) {
@@ -879,8 +908,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         __syncthreads();
         if ((int)threadIdx.x < 64 * p.chain_waves) run_steps<U, NK, ACT>(p, l);
         else run_fetcher(p, l);
-    } else if (w <= BLOCK_GRAM_GROUPS) run_gram(p, lds, w - 1, BLOCK_GRAM_GROUPS);
-    else run_rows(p, lds, (lds_int *)&s_abort, w - 1 - BLOCK_GRAM_GROUPS);
+    } else if (w <= BLOCK_GRAM_GROUPS) {
+        run_gram(p, lds, w - 1, BLOCK_GRAM_GROUPS);
+        if (w == 1 && threadIdx.x < 64 && !launch_counts(p, kPlacePolls))
+            __hip_atomic_store(p.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (whoever waits need not any longer)
+    } else run_rows(p, lds, (lds_int *)&s_abort, w - 1 - BLOCK_GRAM_GROUPS);
 }
 
 // LDS of the workgroup that runs the steps; the others' partial sums need less.  More than half of a compute unit's: one

@@ -48,6 +48,7 @@ hipError_t block_prepare(const int32_t *n, int act)
 hipError_t launch_block_epoch(const BlockGeom &g, BlockPlan plan, unsigned long long *exchange, hipStream_t stream)
 {
     if (plan.n_samples < 1 || plan.n_samples > BLOCK_LAUNCH_SAMPLES) return hipErrorInvalidValue;
+    if (!plan.arrived || !plan.settled) return hipErrorInvalidValue;
     plan.chain_waves = g.chain_waves;
     plan.d_stride = g.chain_waves * g.units_per_lane * 64;
     plan.z_x = exchange;

@@ -478,6 +478,12 @@ struct BlockPlan {
     unsigned long long *all_x;    // wide hidden layers: parts of the output layer's net inputs
     float lr;
     uint32_t seq0;
+    // Nets of two layers within LDS: the launches of a pass change parameters only from the first on and only as long as all
+    // workgroups of each are there (dn_block.h).  Null for wide hidden layers.
+    unsigned *arrived;            // workgroups so far, over the launches of the pass
+    int *settled;                 // launches that count so far; -1 - k: launch k and those behind it do not
+    int launch;                   // number of this one in the pass
+    unsigned expected;            // *arrived when all of it are there
 };
 
 // False unless the net has two layers of 4 to 1024 inputs, at most 1004 hidden units (512 with more than 16 outputs) and

@@ -4,6 +4,8 @@ CPU checker (fp32 storage, fp64 sums) on the same seeded inputs.
 Tolerance 2e-5 (2-norm, per tensor): a pass of n steps rounds a weight n / 32 times and every step's change a few times, each
 by 6e-8 of itself, and what a step's error does to the later ones stays of that size at these rates; 200 steps of random
 signs come to about 1e-6."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -27,12 +29,13 @@ def dnlib():
     return dn
 
 
-def run(dn, w, passes=(0.0,), shift=0, blocks=True):
+def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1):
     rng = np.random.default_rng(11)
     w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
     net = dn.Net(w.widths, w.acts, w.loss, 1)
     net.set_all(w.W, w.b)
     net.dn_set_option("online_tiny", 0)
+    net.dn_set_option("online_blocks", option)
     o = Oracle("o32", w.widths, w.acts, w.loss)
     o.set_params(w.W, w.b)
     X = torch.zeros(w.X.size + shift, device="cuda:0")[shift:].view(w.X.shape)
@@ -143,6 +146,54 @@ def test_sample_blocks_left_to_other_kernels(dnlib):
     for widths, acts, n in (([64, 128, 10], [RELU, SOFTMAX], 63), ([3, 70, 4], [TANH, SOFTMAX], 96), ([1028, 70, 4], [TANH, SOFTMAX], 96),
                             ([16, 1008, 4], [TANH, SOFTMAX], 96), ([16, 516, 20], [TANH, SOFTMAX], 96), ([16, 70, 65], [TANH, SOFTMAX], 96), ([64, 64, 64], [TANH, SOFTMAX], 96), ([4, 16, 3], [SIG, SOFTMAX], 96)):
         run(dnlib, make(widths, acts, CE, n), blocks=False)
+
+
+# The launch that is taken back is number 0 or 1 of the pass; the samples from it on go to the kernel for one workgroup, to the
+# two-copy kernel and to the general one.
+@pytest.mark.parametrize("launch", [0, 1])
+@pytest.mark.parametrize("widths,acts,n", [([784, 128, 10], [RELU, SOFTMAX], 4096 + 70), ([20, 270, 3], [TANH, SOFTMAX], 4096 + 64),
+                                           ([33, 260, 10], [TANH, SOFTMAX], 2 * 4096 + 100)])
+def test_sample_blocks_taken_back(dnlib, widths, acts, n, launch):
+    """A launch whose workgroups do not all find room on the device changes nothing, and neither do those behind it."""
+    announce("sample blocks: launch %d taken back, widths=%s" % (launch, widths))
+    w = make(widths, acts, CE, n, lr=0.0005)
+    run(dnlib, w, (0.0,), blocks=False, option=2 + launch)
+    run(dnlib, make(widths, acts, CE, 96, lr=0.0005), (0.0, 0.5, 0.0), blocks=launch > 0, option=2 + launch)   # (one launch)
+
+
+def test_sample_blocks_on_four_streams(dnlib):
+    """Four nets of 69 workgroups each at once, more than the device has places for: every pass comes out, and right."""
+    announce("sample blocks: four nets on four streams")
+    w = make([256, 256, 10], [TANH, SOFTMAX], CE, 3000, lr=0.001)
+    o = Oracle("o32", w.widths, w.acts, w.loss)
+    o.set_params(w.W, w.b)
+    ref = [o.train_epoch(w.X, w.labels, 1, w.lr, 0.0)[0] for _ in range(3)]
+    Wr, br = o.get_params()
+    X, y = torch.from_numpy(w.X).to("cuda:0"), torch.from_numpy(w.labels).to("cuda:0")
+    torch.cuda.synchronize()
+    nets = []
+    for _ in range(4):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            nets.append(dnlib.Net(w.widths, w.acts, w.loss, 1))
+            nets[-1].set_all(w.W, w.b)
+    losses = [[] for _ in nets]
+
+    def passes(i):
+        for _ in ref:
+            losses[i].append(nets[i].dn_train_epoch(X, y, 1, w.lr, 0.0))
+
+    threads = [threading.Thread(target=passes, args=(i,)) for i in range(len(nets))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for net, got in zip(nets, losses):
+        assert np.allclose(got, ref, rtol=TOL, atol=0), (got, ref)
+        W, b = net.get_all()
+        for l in range(2):
+            assert_close(W[l], Wr[l], TOL, "W_%d" % (l + 1))
+            assert_close(b[l], br[l], TOL, "b_%d" % (l + 1))
+        net.close()
 
 
 def test_sample_blocks_are_bitwise_reproducible(dnlib):
