@@ -418,7 +418,9 @@ enum {
     DN_SCHED_ONE_WAVE_REGISTERS = 8, /* batch 1, two layers at most 64 wide, no momentum: one wavefront, the net in its registers */
     DN_SCHED_ONE_WORKGROUP = 9,    /* batch 1, two layers, no momentum, W_1 within one compute unit's registers: one workgroup
                                       (the last few samples of a call may run on another batch-1 schedule) */
-    DN_SCHED_SAMPLE_BLOCKS = 10    /* batch 1, two layers, no momentum, enough samples: W_1 read and written once per 32 samples */
+    DN_SCHED_SAMPLE_BLOCKS = 10,   /* batch 1, two layers, no momentum, enough samples: W_1 read and written once per 32 samples */
+    DN_SCHED_WIDE_BLOCKS = 11      /* the same for a hidden layer too wide for LDS (DN_SCHED_WIDE_HIDDEN instead if samples of the
+                                      call had inner products beyond fp32, whose launches that kernel takes) */
 };
 dn_status dn_last_schedule(dn_net *net, int32_t *schedule);
 dn_status dn_kernel_time(dn_net *net, int32_t kernel_class, float *ms_total, int64_t *launches);

@@ -188,6 +188,7 @@ struct dn_net {
     double *hit_acc() const { return (double *)(arena + lo.off_scalars + 16); }   // after epoch_acc and the abort flag
     double *epoch_acc() const { return (double *)(arena + lo.off_scalars); }
     int *abort_flag() const { return (int *)(arena + lo.off_scalars + sizeof(double)); }
+    int *swept() const { return (int *)(arena + lo.off_scalars + 12); }   // see WidePlan
     unsigned *arrived() const { return (unsigned *)(arena + lo.off_scalars + 24); }   // launches of sample blocks: see BlockPlan
     int *settled() const { return (int *)(arena + lo.off_scalars + 28); }
     unsigned long long *exchange() const { return (unsigned long long *)(arena + lo.off_online); }
@@ -512,7 +513,8 @@ dn_status run_wide(dn_net *net, const WideGeom &g, const float *X, const int32_t
     // launched behind and ends at once unless a block's inner products left fp32.
     const bool blocks = mu == 0.f && net->online_blocks && net->wide_block_ready && n_samples >= kBlocksMinSamples &&
                         (reinterpret_cast<uintptr_t>(X) & 15) == 0;   // (it reads the samples in sixteen-byte pieces)
-    if (blocks) net->last_schedule = DN_SCHED_SAMPLE_BLOCKS;
+    if (blocks) net->last_schedule = DN_SCHED_WIDE_BLOCKS;
+    p.swept = net->swept();
     const int64_t chunk = blocks ? BLOCK_LAUNCH_SAMPLES : (int64_t)1 << 30;
     for (int64_t s0 = 0; s0 < n_samples; s0 += chunk) {
         const int64_t n = (n_samples - s0) < chunk ? (n_samples - s0) : chunk;
@@ -1171,7 +1173,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     int64_t first = 0;    // samples that are done
     const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && one_wave(net, momentum, tiny);
     // what the kernels of a whole pass leave beside the parameters: off_scalars
-    struct { double acc; int aborted, pad; double hits; unsigned arrived; int settled; } res{};
+    struct { double acc; int aborted, swept; double hits; unsigned arrived; int settled; } res{};
     static_assert(sizeof(res) == 32, "the scalars of the arena");
     if (!direct) DN_HIP(hipMemsetAsync(net->epoch_acc(), 0, sizeof(res), net->stream));
     DN_HIP(hipEventRecord(net->ev_epoch0, net->stream));
@@ -1216,6 +1218,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         blocks = false;
         DN_HIP(hipMemsetAsync(net->abort_flag(), 0, sizeof(res) - sizeof(double), net->stream));
     }
+    if (res.swept) net->last_schedule = DN_SCHED_WIDE_HIDDEN;   // some or all of the samples were not the block kernel's after all
     DN_HIP(hipEventElapsedTime(&net->epoch_ms, net->ev_epoch0, net->ev_epoch1));
     collect_times(net);
     if (res.aborted) return DN_ERR_DEVICE;   // a workgroup of the persistent kernel gave up waiting

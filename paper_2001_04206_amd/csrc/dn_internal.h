@@ -388,6 +388,7 @@ struct WidePlan {
     int lds_x, lds_a, lds_d, lds_b, lds_z, lds_w2, lds_vb, lds_vw2, lds_zall, lds_out, lds_w1;
     const unsigned long long *gram;   // not null: the launch is only for the case that a block's inner products are not usable (their
     int gram_blocks;                  // records' flags), which the kernel launched before it leaves to this one
+    int *swept;                       // ... set to 1 by a launch that was left its samples
 };
 
 // false if the net does not suit the kernel (not two layers, inputs not a multiple of 4 or above 384,

@@ -282,6 +282,7 @@ __global__ __launch_bounds__(kThreads) void wide_epoch_kernel(WidePlan p)
         for (int b = threadIdx.x; b < p.gram_blocks; b += kThreads)
             bad = bad || (uint32_t)p.gram[(size_t)b * (2 * BLOCK_SAMPLES * BLOCK_SAMPLES) + BLOCK_SAMPLES - 1] != 0;
         if (!__syncthreads_or(bad)) return;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *p.swept = 1;
     }
     const int w = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int sg = lane >> 4, g = lane & 15;

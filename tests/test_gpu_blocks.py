@@ -29,7 +29,7 @@ def dnlib():
     return dn
 
 
-def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1):
+def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1, wide=False):
     rng = np.random.default_rng(11)
     w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
     net = dn.Net(w.widths, w.acts, w.loss, 1)
@@ -43,7 +43,8 @@ def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1):
     y = torch.from_numpy(w.labels).to("cuda:0")
     for mu in passes:
         got = net.dn_train_epoch(X, y, 1, w.lr, mu)
-        assert (net.dn_last_schedule() == dn.DN_SCHED_SAMPLE_BLOCKS) == (blocks and mu == 0.0)
+        ran, own = net.dn_last_schedule(), dn.DN_SCHED_WIDE_BLOCKS if wide else dn.DN_SCHED_SAMPLE_BLOCKS
+        assert ran == own if blocks and mu == 0.0 else ran not in (dn.DN_SCHED_SAMPLE_BLOCKS, dn.DN_SCHED_WIDE_BLOCKS), ran
         ref, _ = o.train_epoch(w.X, w.labels, 1, w.lr, mu)
         assert abs(got - ref) <= TOL * max(abs(ref), 1e-6), (got, ref)
     W, b = net.get_all()
@@ -52,6 +53,18 @@ def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1):
         assert_close(W[l], Wr[l], TOL, "W_%d" % (l + 1))
         assert_close(b[l], br[l], TOL, "b_%d" % (l + 1))
     net.close()
+
+
+def on_device(dn, w, option=1):
+    net = dn.Net(w.widths, w.acts, w.loss, 1)
+    net.set_all(w.W, w.b)
+    net.dn_set_option("online_blocks", option)
+    return net, torch.from_numpy(w.X).to("cuda:0"), torch.from_numpy(w.labels).to("cuda:0")
+
+
+def same_bits(one, other):
+    """... of two (loss, (W, b))."""
+    return one[0] == other[0] and all(np.array_equal(a, b) for a, b in zip(one[1][0] + one[1][1], other[1][0] + other[1][1]))
 
 
 def make(widths, acts, loss, n, lr=0.003):
@@ -130,15 +143,23 @@ WIDE = [
 @pytest.mark.parametrize("widths,acts,loss,n", WIDE)
 def test_sample_blocks_of_wide_hidden_layers_match_checker(dnlib, widths, acts, loss, n):
     announce("sample blocks, wide hidden layer widths=%s n=%d" % (widths, n))
-    run(dnlib, make(widths, acts, loss, n, lr=0.0003), (0.0, 0.5, 0.0))
+    run(dnlib, make(widths, acts, loss, n, lr=0.0003), (0.0, 0.5, 0.0), wide=True)
 
 
 def test_sample_blocks_of_wide_hidden_layers_beyond_fp32(dnlib):
-    """Inner products that overflow: the kernel that sweeps W_1 every step takes the pass."""
+    """Inner products that overflow: the kernel that sweeps W_1 every step takes the pass, with the bits that it has by itself."""
     announce("sample blocks, wide hidden layer: inner products beyond fp32")
     w = make([340, 38000, 10], [TANH, SOFTMAX], CE, 70, lr=0.0003)
-    w.X[[3, 20, 66]] *= np.float32(3e18)
-    run(dnlib, w)
+    w.X[[3, 20, 66]] *= np.float32(1e19)
+    assert np.isfinite(w.X).all() and not np.isfinite(w.X[3] @ w.X[20])
+    run(dnlib, w, blocks=False)
+    outs = []
+    for option in (1, 0):
+        net, X, y = on_device(dnlib, w, option)
+        outs.append((net.dn_train_epoch(X, y, 1, w.lr, 0.0), net.get_all()))
+        assert net.dn_last_schedule() == dnlib.DN_SCHED_WIDE_HIDDEN
+        net.close()
+    assert same_bits(*outs)
 
 
 def test_sample_blocks_left_to_other_kernels(dnlib):
@@ -196,16 +217,14 @@ def test_sample_blocks_on_four_streams(dnlib):
         net.close()
 
 
-def test_sample_blocks_are_bitwise_reproducible(dnlib):
-    announce("sample blocks: determinism")
-    w = make([300, 200, 10], [TANH, SOFTMAX], CE, 500)
+@pytest.mark.parametrize("widths,n", [([300, 200, 10], 500), ([384, 30000, 10], 500)])
+def test_sample_blocks_are_bitwise_reproducible(dnlib, widths, n):
+    announce("sample blocks: determinism %s" % (widths,))
+    w = make(widths, [TANH, SOFTMAX], CE, n, lr=0.0003)
     outs = []
     for _ in range(2):
-        net = dnlib.Net(w.widths, w.acts, w.loss, 1)
-        net.set_all(w.W, w.b)
-        loss = net.dn_train_epoch(torch.from_numpy(w.X).to("cuda:0"), torch.from_numpy(w.labels).to("cuda:0"), 1, w.lr, 0.0)
-        outs.append((loss, net.get_all()))
+        net, X, y = on_device(dnlib, w)
+        outs.append((net.dn_train_epoch(X, y, 1, w.lr, 0.0), net.get_all()))
+        assert net.dn_last_schedule() in (dnlib.DN_SCHED_SAMPLE_BLOCKS, dnlib.DN_SCHED_WIDE_BLOCKS)
         net.close()
-    assert outs[0][0] == outs[1][0]
-    for a, b in zip(outs[0][1][0] + outs[0][1][1], outs[1][1][0] + outs[1][1][1]):
-        assert np.array_equal(a, b)
+    assert same_bits(*outs)

@@ -62,6 +62,13 @@ def test_digits_take_blocks_only_when_they_fit(device):
             assert rows[1][2] == [("block_epoch_kernel", 37)]
 
 
+def test_wide_hidden_layers_report_their_own_schedule(device):
+    rows = device(256, "net:340-38000-3:ce:1", "train:64:1:0", "train:63:1:0", "train:64:1:0.5", "option:online_blocks=0", "train:64:1:0")
+    assert [r[1] for r in rows[1:]] == [dn.DN_SCHED_WIDE_BLOCKS, dn.DN_SCHED_WIDE_HIDDEN, dn.DN_SCHED_WIDE_HIDDEN, dn.DN_SCHED_WIDE_HIDDEN,
+                                        dn.DN_SCHED_WIDE_HIDDEN]
+    assert dn.SCHEDULE_KERNELS[rows[1][1]] in [k for k, _ in rows[1][2]]
+
+
 def test_nets_of_one_wavefront_hold_no_blocks(device):
     """Every layer at most 64 wide: no room in the arena for inner products that nothing forms, whatever runs the passes."""
     products = 4096 // 32 * 2 * 32 * 32 * 8
