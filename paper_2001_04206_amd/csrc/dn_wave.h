@@ -64,11 +64,11 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
-// e^x for x <= 0 (NaN stays): 2^n 2^r with x log2 e = n + r, |r| <= 1/2; log2 e in two parts.
+// e^x for x <= 0 (NaN stays): 2^n 2^r with x log2 e = n + r, |r| <= 1/2; log2 e in two parts.  n is that of x bounded (NaN: to -150),
+// so that it has an integer; the rest of an x below the bound is a power of two that is 0 in fp32.
 __device__ __forceinline__ float exp_below_zero(float x)
 {
-    x = x < -150.f ? -150.f : x;   // 0 in fp32
-    const float n = __builtin_rintf(x * 1.44269502f);
+    const float n = __builtin_rintf(__builtin_amdgcn_fmed3f(x, -150.f, 0.f) * 1.44269502f);
     float r = __builtin_fmaf(x, 1.44269502f, -n);
     r = __builtin_fmaf(x, 1.92596299e-8f, r);
     return __builtin_ldexpf(__builtin_amdgcn_exp2f(r), (int)n);
@@ -81,14 +81,12 @@ __device__ __forceinline__ float inverse(float x)
     return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r);
 }
 
-// 1 / (1 + e^-z) (NaN stays): the same two with the range of z bounded where the result is 0 or 1 in fp32 anyway.
+// 1 / (1 + e^-z) (NaN stays): the same two, n of z bounded where the result is 0 or 1 in fp32 anyway.
 __device__ __forceinline__ float sigmoid_of(float z)
 {
-    float x = z > 150.f ? 150.f : z;
-    x = x < -150.f ? -150.f : x;
-    const float n = __builtin_rintf(x * -1.44269502f);
-    float r = __builtin_fmaf(x, -1.44269502f, -n);
-    r = __builtin_fmaf(x, -1.92596299e-8f, r);
+    const float n = __builtin_rintf(__builtin_amdgcn_fmed3f(z, -150.f, 150.f) * -1.44269502f);
+    float r = __builtin_fmaf(z, -1.44269502f, -n);
+    r = __builtin_fmaf(z, -1.92596299e-8f, r);
     const float d = 1.f + __builtin_ldexpf(__builtin_amdgcn_exp2f(r), (int)n), inv = __builtin_amdgcn_rcpf(d);
     return d < 0x1p100f ? __builtin_fmaf(__builtin_fmaf(-d, inv, 1.f), inv, inv) : inv;
 }
