@@ -29,9 +29,11 @@ def dnlib():
     return dn
 
 
-def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1, wide=False):
+def run(dn, w, passes=(0.0,), shift=0, blocks=True, option=1, wide=False, hidden_bias=None):
     rng = np.random.default_rng(11)
     w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
+    if hidden_bias is not None:
+        w.b[0] = hidden_bias.astype(np.float32)
     net = dn.Net(w.widths, w.acts, w.loss, 1)
     net.set_all(w.W, w.b)
     net.dn_set_option("online_tiny", 0)
@@ -116,12 +118,14 @@ def test_sample_blocks_from_an_odd_address(dnlib):
     run(dnlib, make([128, 70, 10], [TANH, SOFTMAX], CE, 96), shift=1)
 
 
+# hidden units of one to four waves of steps, two and four to a lane; four waves leave none to fetch beside the steps
+@pytest.mark.parametrize("hidden", [70, 200, 300, 500, 600, 1000])
 @pytest.mark.parametrize("large", [[40, 45], [10, 40], [31, 32], [63, 64, 65, 95, 96], [0, 1], list(range(32, 64))])
-def test_sample_blocks_with_inner_products_beyond_fp32(dnlib, large):
+def test_sample_blocks_with_inner_products_beyond_fp32(dnlib, large, hidden):
     """Samples whose inner products overflow (their net inputs do not): within a block, between adjacent blocks, whole
     blocks.  Hidden units are saturated there and W_1 stays as it is for these steps."""
-    announce("sample blocks: inner products beyond fp32, samples %s" % (large,))
-    w = make([40, 70, 5], [TANH, SOFTMAX], CE, 130)
+    announce("sample blocks: inner products beyond fp32, %d hidden units, samples %s" % (hidden, large))
+    w = make([40, hidden, 5], [TANH, SOFTMAX], CE, 130)
     w.X[large] *= np.float32(3e19)
     assert np.isfinite(w.X).all() and not np.isfinite(w.X[large] @ w.X[large].T).all()
     run(dnlib, w, (0.0, 0.5))
@@ -132,8 +136,8 @@ WIDE = [
     # workgroups and blocks, rows that end within a tile
     ([340, 100000, 10], [TANH, SOFTMAX], CE, 65),
     ([384, 60001, 16], [SIG, SIG], MSE, 64),
-    # (no ReLU at these widths: among millions of net inputs one lies within rounding of zero, and whichever side it falls on moves
-    # its row by a step's whole change, 1e-3 of the weights against a bound of 2e-5)
+    # (ReLU below, with net inputs away from zero: among millions one lies within rounding of it, and whichever side it falls on
+    # moves its row by a step's whole change, 1e-3 of the weights against a bound of 2e-5)
     ([340, 38000, 3], [TANH, SOFTMAX], CE, 97),
     ([260, 45003, 11], [TANH, SOFTMAX], CE, 70),
     ([336, 56000, 10], [LIN, SOFTMAX], CE, 96),
@@ -144,6 +148,34 @@ WIDE = [
 def test_sample_blocks_of_wide_hidden_layers_match_checker(dnlib, widths, acts, loss, n):
     announce("sample blocks, wide hidden layer widths=%s n=%d" % (widths, n))
     run(dnlib, make(widths, acts, loss, n, lr=0.0003), (0.0, 0.5, 0.0), wide=True)
+
+
+@pytest.mark.parametrize("widths", [[384, 28000, 10], [340, 38000, 12]])
+def test_sample_blocks_of_wide_hidden_layers_with_relu(dnlib, widths):
+    """Half of the units on, half off, by biases of 1 and -1 beside sums of spread 0.1."""
+    announce("sample blocks, wide hidden layer with ReLU widths=%s" % (widths,))
+    w = make(widths, [RELU, SOFTMAX], CE, 97, lr=0.0001)
+    run(dnlib, w, (0.0, 0.5, 0.0), wide=True, hidden_bias=np.where(np.arange(widths[1]) % 3 < 2, 1.0, -1.0))
+
+
+@pytest.mark.parametrize("large", [[], [4096 + 20, 4096 + 21], [7, 9]])
+def test_sample_blocks_of_wide_hidden_layers_over_two_launches(dnlib, large):
+    """More samples than a launch takes; inner products beyond fp32 in neither, in the second, in the first.  Against the kernel that
+    sweeps W_1 every step (which other tests hold against the checker), a pass with momentum behind it on both."""
+    announce("sample blocks, wide hidden layer: 4096 + 70 samples, large %s" % (large,))
+    w = make([384, 28000, 2], [TANH, SOFTMAX], CE, 4096 + 70, lr=0.0001)
+    w.X[large] *= np.float32(1e19)
+    outs = []
+    for option in (1, 0):
+        net, X, y = on_device(dnlib, w, option)
+        losses = [net.dn_train_epoch(X, y, 1, w.lr, 0.0)]
+        assert net.dn_last_schedule() == (dnlib.DN_SCHED_WIDE_BLOCKS if option and not large else dnlib.DN_SCHED_WIDE_HIDDEN)
+        losses.append(net.dn_train_epoch(X[:50], y[:50], 1, w.lr, 0.5))
+        outs.append((losses, sum(net.get_all(), [])))
+        net.close()
+    assert np.allclose(outs[0][0], outs[1][0], rtol=TOL, atol=0), (outs[0][0], outs[1][0])
+    for got, ref in zip(outs[0][1], outs[1][1]):
+        assert_close(got, ref, 2 * TOL, "parameters")   # (both are off)
 
 
 def test_sample_blocks_of_wide_hidden_layers_beyond_fp32(dnlib):

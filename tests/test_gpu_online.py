@@ -33,7 +33,8 @@ def run_pair(dn, w, n, passes, mode, min_tile=None, tol=1e-4, biases=True, resid
     registers, 2: every pass keeps it in LDS); wide=1 lets two-layer nets with a
     hidden layer beyond LDS run on the kernel that keeps rows of W_1 in LDS and registers (every
     pass must then report that schedule); solo=1 lets plain passes of two-layer nets whose W_1 fits one
-    compute unit's registers run on one workgroup (solo=2: ... but this call has too few samples for it)."""
+    compute unit's registers run on one workgroup (solo=2: ... but this call has too few samples for it).  Samples are never taken in
+    blocks (test_gpu_blocks.py)."""
     if biases:
         rng = np.random.default_rng(11)
         w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
@@ -47,6 +48,7 @@ def run_pair(dn, w, n, passes, mode, min_tile=None, tol=1e-4, biases=True, resid
     net.dn_set_option("online_tiny", tiny)
     net.dn_set_option("online_wide", wide)
     net.dn_set_option("online_solo", 1 if solo else 0)
+    net.dn_set_option("online_blocks", 0)
     o = Oracle("o32", w.widths, w.acts, w.loss)
     o.set_params(w.W, w.b)
     X = torch.from_numpy(w.X[:n]).to("cuda:0")
@@ -311,7 +313,19 @@ def test_persistent_not_available_is_reported(dnlib):
 def test_iris_like_ten_epochs_persistent(dnlib):
     announce("cfg1 4-16-3 B=1, 10 epochs, persistent")
     w = synth.iris_like()
-    run_pair(dnlib, w, w.n_samples, [0.0] * 10, PERSISTENT, tol=1e-3, biases=False)
+    run_pair(dnlib, w, w.n_samples, [0.0] * 10, PERSISTENT, tol=1e-3, biases=False, twin_expected=True)
+
+
+@pytest.mark.parametrize("widths,acts,how", [([784, 128, 10], [TANH, SOFTMAX], dict(solo=1)), ([64, 130, 16], [SIG, SOFTMAX], dict(solo=1)),
+                                             ([128, 300, 12], [TANH, SOFTMAX], dict(twin_expected=True)),
+                                             ([130, 300, 40], [TANH, SOFTMAX], dict(twin=0, twin_expected=False)),
+                                             ([340, 38000, 3], [TANH, SOFTMAX], dict(wide=1))])
+def test_long_passes_without_sample_blocks(dnlib, widths, acts, how):
+    """Passes that would take their samples in blocks, on the kernels that took them before: two plain ones in a row, one with
+    momentum, a plain one that follows it."""
+    announce("online long passes, no sample blocks, widths=%s" % (widths,))
+    w = synth.make("long", widths, acts, CE, n_samples=150, features="normal", init="xavier_uniform", batch=1, lr=0.0005, momentum=0.0, seed=12)
+    run_pair(dnlib, w, 150, [0.0, 0.0, 0.5, 0.0], PERSISTENT, **how)
 
 
 @pytest.mark.parametrize("form", [1, 2], ids=["registers", "lds"])
