@@ -490,7 +490,11 @@ dn_status run_twin(dn_net *net, const TwinGeom &g, const float *X, const int32_t
     return DN_OK;
 }
 
-constexpr int64_t kBlocksMinSamples = 64;   // of a pass, for the samples to be taken in blocks
+// Samples of a pass for them to be taken in blocks.  us a pass of 64, the kernels before / blocks: 65-4-2 146 / 74; 784-4-2 212 / 87;
+// 64-128-10 141 / 89; 784-128-10 378 / 104; 256-256-10 308 / 108; 340-200-40 389 / 153; 1024-512-64 484 / 230; 5-999-2 1649 / 165;
+// 1024-1004-16 347 / 234; hidden layers beyond LDS 340-38000-3 945 / 355, 340-100000-10 1511 / 550, 64-131072-16 1585 / 430.  (The line is
+// where nothing measured lost; it may lie lower.)
+constexpr int64_t kBlocksMinSamples = 64;
 
 // Batch-1 epochs of a two-layer net with a wide hidden layer: most of W_1 stays in LDS and registers.
 dn_status run_wide(dn_net *net, const WideGeom &g, const float *X, const int32_t *labels, int64_t n_samples, float lr,

@@ -12,12 +12,13 @@
 //
 // Roles, one workgroup each, 256 threads (one wave per SIMD: a lane may hold 512 registers):
 //   chain   (workgroup 0) runs the steps.  A lane of the first NW waves keeps U hidden units: their net inputs for the
-//           block's remaining samples (32 registers a unit), their column of W_2 and bias.  The output layer's sums over the units meet by lane swaps and, with
-//           several waves, once through LDS: one barrier a step, none with one wave.
+//           block's remaining samples (32 registers a unit), their column of W_2 and bias.  The output layer's sums over the
+//           units meet by lane swaps and, with several waves, in stamped words in LDS; a step has no barrier, a block has two.
 //   Gram    (workgroups 1 to 4) the blocks' inner products, running ahead of the steps.
 //   rows    (the others) four rows of W_1 each, in registers in the lane layout of v_mfma_f32_4x4x1_16b_f32, which serves
 //           both products: as operand A of W x (lane 4 b + i: row i, columns 4 b .. 4 b + 3 of a group of 64) and as the
 //           accumulator of W - lr delta x.  The four waves split the columns.
+// All of a launch's workgroups have to be on the device at once; launch_counts() below says what happens if they cannot.
 // What crosses workgroups goes in stamped words (dn_persist.h): net inputs from the rows to the chain and deltas back,
 // 32 per unit and block each, and the inner products.
 //
@@ -33,6 +34,8 @@
 // us per step, before (the kernels that sweep W_1 every step) and now: 784-128-10, 4000 samples 3.18 -> 0.72 (one
 // workgroup); 256-256-10 3.5 -> 1.2; 1021-97-16 10.1 -> 1.5 (odd width); 784-500-33 5.8 -> 2.8; 128-1000-16 5.5 -> 2.5;
 // 5-999-2 25.7 -> 2.3; 64-128-10 in passes of 96 samples 2.1 -> 1.3 (about 30 us of each pass are start and end).
+// With four units a lane, or two and more than 32 outputs, a lane's numbers are more than its 512 registers: 7, 43 and 144 of them
+// live in scratch memory for 4, 10 and 16 outputs, 150 for 64 (128-1000-k 1.9, 2.3 and 2.7 us a step, 784-500-64 2.5).
 // Tried on the way: corrections within the block as a register file that moves up by one every step (62 copies a step, 1.48 us);
 // without the look-ahead over the block's end 1.33.
 #pragma once
@@ -931,7 +934,9 @@ hipError_t block_one(const BlockGeom *g, const BlockPlan *plan, hipStream_t stre
 }
 
 // Launches (g == nullptr: raises the LDS limit of) the kernel for a net with one activation function: compiled for 4, 10, 16,
-// 32 and 64 outputs.
+// 32 and 64 outputs, as a step's multiply-adds and lane swaps grow with that number whether the net has as many or not (us a step
+// of 784-128-k 0.66, 0.79, 0.90, 1.03, 1.51; of 784-500-k 1.15, 1.28, 1.42, 1.71, 2.54).  10 rather than 8: the next step up from ten
+// classes would cost 0.11 to 0.41 us, and the library's data sets have three or ten.
 template <int ACT>
 hipError_t block_dispatch(int units, int n2, const BlockGeom *g, const BlockPlan *plan, hipStream_t stream)
 {

@@ -203,8 +203,8 @@ __device__ __forceinline__ LaneQ<Q> lane_read_q(float v, int base)
 
 // What bounds the kernel below: the chain of one sample's operations on one wavefront, so each link is as short as it can be --
 // sigmoid and softmax through exp2 and one Newton step, the output sums in two chains, sample and activations read into scalar
-// registers once.  Iris (4-16-3, 150 samples), us a pass with its launch: 127.7 before these three, 119.3 with them
-// (and 102.8 -> 96.7 later, when the exponentials bounded n alone in one instruction and the loss needed no copy).
+// registers once.  Iris (4-16-3, 150 samples), us a pass with its launch: 127.7 before these three, 119.3 with them; 102.8 once the
+// kernel handed its loss to the host itself; 96.7 with one instruction to bound an exponent.
 __device__ __forceinline__ float short_act(int act, float z) { return act == DN_ACT_SIGMOID ? sigmoid_of(z) : act_fn(act, z); }
 
 template <int N0, int N1, int N2>

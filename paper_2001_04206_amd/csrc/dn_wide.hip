@@ -23,8 +23,8 @@
 // With momentum every row brings its row of velocities along, in the same tier (LDS rows side by side,
 // 48 registers per register row, four of them; streamed rows move 16 bytes per weight and step).
 // At the end of the launch tiers 1 and 2, the biases and the columns of W_2 go back to device memory.
-// (Passes of 64 and more samples without momentum take dn_wide_block.hip instead, which reads and writes W_1 once per 32 samples:
-// 20.2 -> 5.7 us a step.  This kernel keeps shorter ones, momentum, and samples whose inner products leave fp32.)
+// (Passes of 64 and more samples without momentum take dn_wide_block.hip instead, which reads and writes W_1 once per 32 samples,
+// in about a quarter of the time.  This kernel keeps shorter ones, momentum, and samples whose inner products leave fp32.)
 #include <algorithm>
 #include <type_traits>
 

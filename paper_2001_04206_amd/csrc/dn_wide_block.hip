@@ -12,12 +12,14 @@
 // What bounds it: the exchange.  340-100000-10, 256 samples, workgroup 0, cycles per step: activations and own sums 980, exchange
 // 10700 (two hops of 3900 and waiting for the slowest of sixteen workgroups), output layer 690, deltas and corrections 590;
 // a block's sweep is 30 us of matrix instructions beside 180 us of steps.  us per step, a pass with it divided by its samples:
-// 340-100000-10, 256 samples 20.8 -> 5.5 to 6.2 on several cards (a pass 5335 -> 1410 to 1595; one card repeats itself within
-// 0.4 %); 340-60001-10 15.6 -> 6.3 and 384-40000-3 14.3 -> 6.0 in passes of 130 and 96 samples.  Exchanges tried: every workgroup reads
+// 340-100000-10, 256 samples 20.8 -> 5.5 to 6.5 on several cards (a pass 5335 -> 1410 to 1651; one card repeats itself within
+// 0.6 %), 512 samples 5.1 to 5.9; 340-60001-10 15.6 -> 6.3 and 384-40000-3 14.3 -> 6.0 in passes of 130 and 96 samples.  Exchanges tried: every workgroup reads
 // all 2560 words, by workgroup 12.3 us a step, by output (whole lines) 9.0; two levels 7.7, with three looks on their way at a
 // time 8.7 (the looks hold up the words), with eight copies of the upper level 6.9; steps before the sweep (s_setprio) 6.8.
 // The sweep is not what a step waits for: with one long sum instead of one per tile, or without the loads of a tile ahead, a pass
 // takes the same time on one card (6.51, 6.53 and 6.53 in turn).
+// Two waves on a SIMD leave a lane 256 registers: 66 to 68 of its numbers live in scratch memory for up to 10 outputs, 94 for 16
+// (340-100000-k, 512 samples: 5.4 us a step for 3 outputs, 5.6 for 10, 6.2 to 6.8 for 11 to 16).
 #define DN_PERSIST_THREADS 512   // four waves for the steps, four for the sweep
 #include "dn_block.h"
 
