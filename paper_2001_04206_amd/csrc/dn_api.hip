@@ -249,14 +249,16 @@ void refresh_persistent(dn_net *net)
 // 1 and 768 rows 14.3 / 10.7, 21.6 / 18.1; beyond it 4096-16, 1 and 1024 rows 16.1 / 14.7, 33.8 / 40.9, 8192-10, 1 row 17.1 / 18.2,
 // 16384-16, 1 row 19.2 / 38.4, 100000-10, 1 and 1024 rows 45.7 / 289, 389 / 983; 1025 to 2048 rows: 1024-10 22.3 / 20.0, 2048-6 34.1 /
 // 28.6, 512-10 16.1 / 15.3, but 256-16 12.7 / 14.4, 2048-16 1025 rows 24.5 / 24.2, 4096-10 44.6 / 47.3; 4096 rows: 256-10 15.4 /
-// 22.8, 1024-10 31.8 / 35.6.  Squared error, no copy: 1024-10, 1 and 768 rows 10.2 / 8.1, 13.6 / 11.4; 4096-3 14.1 / 9.4; but 64-16
-// 6.9 / 8.8, 256-16, 768 rows 9.0 / 10.5, 1536-16, 768 rows 16.6 / 17.1, 1024-16, 1025 rows 14.9 / 18.5.
+// 22.8, 1024-10 31.8 / 35.6.  Squared error, where the product's launch may be all there is (no copy asked for): 1024-10, 1 and 768
+// rows 10.2 / 8.1, 13.6 / 11.4; 4096-3, 1 row 14.1 / 9.4; 256-10, 1 and 512 rows 8.5 / 8.0, 9.0 / 9.0 (and with the copy 300-10, 64 rows
+// 13.2 / 10.0); but 64-16, 1 row 6.9 / 8.8, 256-16, 768 rows 9.0 / 10.5, 1536-16, 768 rows 16.6 / 17.1, 1024-16, 1025 rows 14.9 / 18.5.
 bool one_launch_forward(const dn_net *net, int rows)
 {
     const int n_out = net->n[net->L], n_in = net->n[net->L - 1];
     if (net->gemm_variant >= 0 || !narrow_layer(n_out)) return false;
     const size_t weights = (size_t)n_out * n_in;
-    if (net->loss != DN_LOSS_CROSS_ENTROPY) return rows <= 768 && n_in >= 1024 && weights <= 16384;
+    if (net->loss != DN_LOSS_CROSS_ENTROPY)
+        return weights <= 16384 && rows <= (n_in >= 1024 ? 768 : n_in >= (n_out <= 10 ? 256 : 512) ? 512 : 0);
     return rows <= 768 ? weights <= 32768 : rows <= 2048 && n_in >= 512 && weights <= 16384;
 }
 

@@ -59,7 +59,7 @@ def test_forward_tail(dnlib, widths, batch, loss, in_place):
 # layer), the largest last layers of one row a workgroup, squared error
 @pytest.mark.parametrize("widths,batch,loss", [([24, 512, 10], 1025, CE), ([20, 1021, 16], 1030, CE), ([20, 1024, 16], 2048, CE), ([520, 7], 1101, CE),
                                                ([24, 511, 10], 1025, CE), ([12, 2048, 16], 768, CE), ([12, 2049, 16], 5, CE), ([8, 10923, 3], 3, CE),
-                                               ([9, 1025, 3], 767, MSE), ([9, 1024, 16], 769, MSE)])
+                                               ([9, 1025, 3], 767, MSE), ([9, 257, 10], 512, MSE), ([9, 255, 10], 64, MSE), ([9, 1024, 16], 769, MSE)])
 def test_forward_tail_lines(dnlib, widths, batch, loss):
     test_forward_tail(dnlib, widths, batch, loss, False)
 

@@ -83,7 +83,8 @@ def test_nets_of_one_wavefront_hold_no_blocks(device):
     ("16-100000-10:ce", 1, False), ("16-100000-10:ce", 1024, False), ("16-16384-16:ce", 64, False), ("16-8193-4:ce", 1, False), ("16-8192-4:ce", 768, True),
     ("16-8192-4:ce", 769, False), ("1024-1024-10:ce", 2048, True), ("1024-1024-10:ce", 2049, False), ("16-1024-16:ce", 2048, True),
     ("16-1025-16:ce", 769, False), ("16-512-16:ce", 769, True), ("16-511-16:ce", 769, False), ("64-96-10:ce", 128, True), ("64-96-17:ce", 128, False),
-    ("16-100000-10:mse", 1, False), ("16-1024-16:mse", 768, True), ("16-1024-16:mse", 769, False), ("16-1023-16:mse", 1, False),
+    ("16-100000-10:mse", 1, False), ("16-1024-16:mse", 768, True), ("16-1024-16:mse", 769, False), ("16-1023-16:mse", 512, True),
+    ("16-1023-16:mse", 513, False), ("16-512-11:mse", 512, True), ("16-511-11:mse", 1, False), ("16-256-10:mse", 64, True), ("16-255-3:mse", 64, False),
     ("16-1025-16:mse", 1, False), ("16-64-16:mse", 1, False)])
 def test_narrow_last_layers_of_predictions(device, net, rows, one):
     status, _, launches = device(256, "net:%s:%d" % (net, rows), "forward:%d" % rows)[1]
