@@ -1374,13 +1374,25 @@ static bool in_pairs(GemmKind kind, const GemmArgs &a, long tiles64)
 // one; below that smaller tiles keep more units busy, for a long k the middle shape, whose k is also split across
 // workgroups.  With 256 tiles or fewer a compute unit has one of them, four waves of it one on each SIMD, and half of such a
 // wave's time is waiting: eight waves (two on a SIMD, half the k each) are faster wherever 64 x 64 was the choice, and for forward
-// and delta products from 129 tiles on and over a long k from 65.  us (eight waves / four / the choice before): forward 256 x
+// and delta products from 129 tiles on, if their 32 x 64 tiles are more than the compute units and their 32 x 32 tiles more than
+// two to each, and over a long k from 65.  us (eight waves / four / the choice before): forward 256 x
 // 4096, k 4096 52 / 60 / 60, k 1024 19.4 / 22.2, k 512 13.8 / 15.3; 768 x 1024, k 1024 17.6 / 21.5; 576 x 1024, k 1024 16.9 / 20.8 /
 // 22.3; 700 x 900, k 300 11.3 / 14.2 / 15.0; 250 x 4001, k 4003 62 / 103; 512 x 1024, k 4096 33.1 / 37.7 / 36.5, k 3072 28.5 / 31.1 /
 // 28.8, k 2048 22.0 / 24.0 / 21.1; 257 x 1021, k 4097 30 / 45 / 42; 384 x 1024, k 4096 30.8 / 35.4 / 32.8; but 256 x 1024 (64 tiles),
 // k 4096 23.8 / 25.3 / 23.0 and 1500 x 1024 (384 tiles), k 1024 33.3 / 28.1.  Gradient (with the launch that forms the output
 // delta) 1024 x 1024, k 2048 37 / 44, k 512 17.8 / 18.4, k 256 13.8 / 13.4; 777 x 1021, k 301 15.1 / 17.1; 1500 x 1500 (576
-// tiles), k 512 41 / 34.5.  Measured, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 62 / 64 / 77; 2048 x 1024, k 1024: 30 / 47 /
+// tiles), k 512 41 / 34.5.
+// With up to 256 tiles of 32 x 64 a compute unit has one of those instead, which is the better by a quarter; with more, but at most
+// 512 of 32 x 32, two of these.  us (eight waves / 32 x 64 / 32 x 32; tiles of each): 330 x 1356 (132, 242, 473), k 280 10.4 / 8.0 / 8.2;
+// 222 x 2112 (132, 231, 462), k 1472 20.8 / 15.4 / 17.9; 641 x 768 (132, 252, 504), k 1628 23.4 / 16.9 / 19.9; 776 x 640 (130, 250, 500),
+// k 4416 47 / 34.6 / 45; 666 x 739 (rows not whole vectors; 132, 252, 504), k 619 15.3 / 11.7 / 13.0; 298 x 1632 (130, 260, 510), k 520
+// 12.3 / 16.4 / 10.5; 401 x 1248 (140, 260, 507), k 622 15.3 / 19.3 / 11.6; 395 x 1248, k 4512 48 / 65 / 45; but 1163 x 418 (133, 259, 518),
+// k 873 18.2 / 23.3 / 18.8.
+// Over a long k from 65 tiles on the same line lies at 128 tiles of 32 x 64, and near 256 of them k has to be longer (eight waves / 32 x
+// 64; tiles of each): 131 x 1376 (66, 110), k 4544 25.2 / 22.2; 73 x 2376 (76, 114), k 3904 24.6 / 23.3; 609 x 416 (70, 140), k 3552 22.7 /
+// 27.0; 1363 x 320 (110, 215), k 3088 24.4 / 23.3; 1034 x 416 (119, 231), k 3360 25.3 / 24.4; 799 x 544 (117, 225), k 4032 29.4 / 31.7;
+// rows that are not whole vectors 33 / 39 to 49.
+// Without the eight-wave tile, us (64x64 / 32x64 / 32x32): forward 256 x 4096, k 4096: 62 / 64 / 77; 2048 x 1024, k 1024: 30 / 47 /
 // 47; 768 x 1024, k 1024: 19.3 / 22.6 / 20.3; 640 x 1024, k 2048: 32 / 35.5 / 32; 512 x 1024, k 2048: 22 / 20 / 24.5; 256 x
 // 1000, k 4096: 24.9 / 21.2 / 23.5; 257 x 1021, k 4097: 45.7 / 42.5 / 43.8; 512 x 1024, k 1024: 15.1 / 13.2 / 14.9; 128 x
 // 1024, k 1024: 13.0 / 10.4 / 8.8; gradient 1024 x 1024, k 512: 15.1 / 19.4 / 19.3.  Operands read through registers
@@ -1395,10 +1407,17 @@ static int pick_variant(GemmKind kind, const GemmArgs &a)
     const long t64 = tiles(64, 64);
     if (in_pairs(kind, a, t64)) {
         if (kind == GEMM_GRAD && large_short_grad(t64, a.K)) return 16;
-        if (t64 <= 256 && (kind == GEMM_GRAD ? t64 >= 128 && a.K > 256 : t64 > 128 || (t64 > 64 && a.K >= 3072))) return 19;
-        if (kind == GEMM_GRAD ? t64 >= 128 : t64 > 256) return 13;
-        if (kind != GEMM_GRAD && a.ws && t64 >= 64 && a.K >= 2048) return 14;
-        return tiles(32, 64) >= 192 && vec_ok(kind, a) ? 14 : 15;
+        const long t32 = tiles(32, 64);
+        const bool vec = vec_ok(kind, a);
+        if (kind == GEMM_GRAD) {
+            if (t64 >= 128) return t64 <= 256 && a.K > 256 ? 19 : 13;
+        } else {
+            if (t64 > 256) return 13;
+            if (t64 > 128 && t32 > 256) return tiles(32, 32) <= 512 ? 15 : 19;
+            if (t64 > 64 && t64 <= 128 && a.K >= 3072 && (!vec || (t32 > 128 && (t32 <= 208 || a.K >= 3584)))) return 19;
+            if (t64 >= 64 && a.ws && a.K >= 2048) return 14;
+        }
+        return t32 >= 192 && vec ? 14 : 15;
     }
     return kind == GEMM_GRAD && large_short_grad(t64, a.K) ? 18 : 17;
 }

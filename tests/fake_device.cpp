@@ -8,7 +8,7 @@
 //     option:online_mode=2
 //     train:96:1:0.9          one epoch: samples, batch, momentum
 //     forward:64              rows
-// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups).
+// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups/template arguments).
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -43,8 +43,11 @@ int log_launch(const void *f, Dim3 grid)
     std::string name = full ? full : names()[f];
     free(full);
     const size_t end = name.find("_kernel"), begin = name.find_last_of(": ", end);   // without namespaces, template arguments and parameters
+    std::string arguments = end == std::string::npos ? "" : name.substr(end + 7, name.rfind('(') - end - 7);
     name = end == std::string::npos ? name : name.substr(begin + 1, end + 7 - begin - 1);
-    launches += " " + name + "/" + std::to_string(grid.x * grid.y * grid.z);
+    launches += " " + name + "/" + std::to_string(grid.x * grid.y * grid.z) + "/";
+    for (char c : arguments)
+        if (c != ' ') launches += c;
     return 0;
 }
 

@@ -23,13 +23,14 @@ def device(tmp_path_factory):
                     "-L" + lib, "-l:libdn.so", "-Wl,--export-dynamic,--allow-shlib-undefined,--disable-new-dtags,-rpath," + lib +
                     ",-rpath,/opt/rocm/lib"], check=True)
 
-    def run(units, *commands):
-        """One (status, schedule, [(kernel, workgroups)]) per command."""
+    def run(units, *commands, arguments=False):
+        """One (status, schedule, [(kernel, workgroups)]) per command; [(kernel, template arguments)] with arguments=True."""
         out = subprocess.run([exe, str(units), *commands], check=True, capture_output=True, text=True, timeout=120).stdout
         rows = []
         for line in out.splitlines():
             status, schedule, *launches = line.split()
-            rows.append((int(status), int(schedule), [(l.split("/")[0], int(l.split("/")[1])) for l in launches]))
+            launches = [l.split("/") for l in launches]
+            rows.append((int(status), int(schedule), [(l[0], l[2] if arguments else int(l[1])) for l in launches]))
         assert len(rows) == len(commands), out
         return rows
 
@@ -89,3 +90,16 @@ def test_nets_of_one_wavefront_hold_no_blocks(device):
 def test_narrow_last_layers_of_predictions(device, net, rows, one):
     status, _, launches = device(256, "net:%s:%d" % (net, rows), "forward:%d" % rows)[1]
     assert status == dn.DN_OK and ("narrow_output_kernel" in [k for k, _ in launches]) == one, launches
+
+
+# rows, terms of a sum, outputs: the tile of the forward product on either side of the lines of the eight-wave tile
+@pytest.mark.parametrize("rows,k,n,tile", [
+    (330, 280, 1356, "32,64,8"), (222, 1472, 2112, "32,64,8"), (641, 1628, 768, "32,64,8"), (776, 4416, 640, "32,64,8"), (666, 619, 739, "32,32,8"),
+    (513, 1000, 960, "32,64,8"), (512, 1000, 1024, "32,64,8"), (513, 1000, 1024, "64,64,8"), (1024, 1000, 1024, "64,64,8"), (1025, 1000, 1024, "64,64,4"),
+    (128, 4544, 2048, "32,64,8"), (131, 4544, 1376, "32,64,8"), (609, 3552, 416, "64,64,8"), (609, 3068, 416, "32,64,8"), (1363, 3088, 320, "32,64,8"),
+    (799, 4032, 544, "64,64,8"), (799, 3580, 544, "32,64,8"), (436, 3073, 999, "64,64,8"), (131, 4545, 1376, "64,64,8"), (298, 520, 1632, "32,32,8"), (395, 4512, 1248, "32,32,8"),
+    (1163, 873, 418, "64,64,8")])
+def test_tiles_of_forward_products(device, rows, k, n, tile):
+    status, _, launches = device(256, "net:%d-%d:mse:%d" % (k, n, rows), "forward:%d" % rows, arguments=True)[1]
+    products = [a for name, a in launches if name == "gemm_kernel"]
+    assert status == dn.DN_OK and len(products) == 1 and products[0].startswith("<dn::SliceTile<%s," % tile), launches
