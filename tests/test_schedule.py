@@ -68,6 +68,9 @@ def test_wide_hidden_layers_report_their_own_schedule(device):
     assert [r[1] for r in rows[1:]] == [dn.DN_SCHED_WIDE_BLOCKS, dn.DN_SCHED_WIDE_HIDDEN, dn.DN_SCHED_WIDE_HIDDEN, dn.DN_SCHED_WIDE_HIDDEN,
                                         dn.DN_SCHED_WIDE_HIDDEN]
     assert dn.SCHEDULE_KERNELS[rows[1][1]] in [k for k, _ in rows[1][2]]
+    # the kernel that sweeps W_1 every step: by itself, and in the form that looks whether it was left the samples
+    rows = device(256, "net:340-38000-3:ce:1", "train:63:1:0", "train:64:1:0", arguments=True)
+    assert [dict(r[2]).get("wide_epoch_kernel") for r in rows[1:]] == ["<12,false,false>", "<12,false,true>"]
 
 
 def test_nets_of_one_wavefront_hold_no_blocks(device):
