@@ -39,9 +39,10 @@
  *     wavefront or one workgroup, made of up to 256 workgroups that wait for one another and fill a compute
  *     unit each, so all of them have to be on the device at once, beside whatever other nets and streams run
  *     there.  Their waits are bounded: an epoch whose workgroups are kept apart for about a second
- *     ends with DN_ERR_DEVICE and undefined parameters.  DN_SCHED_SAMPLE_BLOCKS on hidden layers within LDS
- *     (up to 256 workgroups for nets that one workgroup would train, too) changes nothing before all are
- *     there: such an epoch goes on, after about a tenth of a second, on the other batch-1 schedules.
+ *     ends with DN_ERR_DEVICE and undefined parameters.  DN_SCHED_SAMPLE_BLOCKS, which also takes nets
+ *     that one workgroup would train (with up to 69), changes nothing before all of a launch's
+ *     workgroups are there: a launch that is kept waiting for about a tenth of a second is taken back, and
+ *     the epoch goes on from its samples on the other batch-1 schedules.
  */
 #ifndef DN_H
 #define DN_H
@@ -479,7 +480,7 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    outputs and some layer wider than 64 forms the first layer's products of 32 samples at a time
  *                    and corrects them step by step through the samples' inner products, and so does one over a net that
  *                    "online_wide" takes (of at most 131072 hidden units); 0: such passes take the other batch-1 schedules;
- *                    2 + k, for tests: launch k of such a pass is taken back, as below
+ *                    2 + k, for tests: launch k of such a pass is taken back as if its workgroups had been kept apart
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose
  *                    parameters fit in LDS, twice with momentum) runs on a single wavefront that keeps
  *                    the whole net in LDS -- in its registers, for two layers and momentum 0; 2: the
