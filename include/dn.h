@@ -42,7 +42,8 @@
  *     ends with DN_ERR_DEVICE and undefined parameters.  DN_SCHED_SAMPLE_BLOCKS, which also takes nets
  *     that one workgroup would train (with up to 69), changes nothing before all of a launch's
  *     workgroups are there: a launch that is kept waiting for about a tenth of a second is taken back, and
- *     the epoch goes on from its samples on the other batch-1 schedules.
+ *     the epoch goes on from its samples on the other batch-1 schedules.  So is a launch of the minibatch
+ *     kernel with a tile of every layer per workgroup ("batch_tiles").
  */
 #ifndef DN_H
 #define DN_H
@@ -412,8 +413,8 @@ enum {
     DN_SCHED_LAUNCHES = 1,        /* one launch per product (or per few products) of every step */
     DN_SCHED_PER_SAMPLE = 2,      /* batch 1: the general persistent whole-epoch kernel */
     DN_SCHED_TWO_COPY = 3,        /* batch 1: the persistent kernel with row and column copies of the inner weights */
-    DN_SCHED_MINIBATCH = 4,       /* the persistent minibatch kernel for one- and two-layer nets */
-    DN_SCHED_MINIBATCH_DEEP = 5,  /* the persistent minibatch kernel for deeper nets */
+    DN_SCHED_MINIBATCH = 4,       /* a persistent minibatch kernel, one- or two-layer net ("batch_tiles" says which) */
+    DN_SCHED_MINIBATCH_DEEP = 5,  /* a persistent minibatch kernel, deeper net */
     DN_SCHED_ONE_WAVE = 6,        /* batch 1, every layer at most 64 wide: one wavefront runs the epoch */
     DN_SCHED_WIDE_HIDDEN = 7,     /* batch 1, two layers, a hidden layer too wide for LDS: rows in LDS, registers and memory */
     DN_SCHED_ONE_WAVE_REGISTERS = 8, /* batch 1, two layers at most 64 wide, no momentum: one wavefront, the net in its registers */
@@ -457,6 +458,12 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    multiple of 4, output width <= 128, LDS.  Three to eight layers: momentum 0,
  *                    max_batch <= 64, every width but the last a multiple of 4, output width
  *                    <= 128, LDS)
+ *   "batch_tiles"    1 (default): with "batch_mode" 0 and "online_min_tile" as it comes, minibatches of 2 to 256 samples over nets
+ *                    whose layers are at most 256 square tiles of 32 or of 64 (the last one, if it has at most 64 outputs,
+ *                    not counted; else at most 1024) and fit in LDS that way run on a persistent kernel that keeps a tile of
+ *                    every layer per workgroup, where a step is expected to take less there than on the other schedules; any
+ *                    widths, with or without momentum; 0: never; 2: wherever it fits; 3, for tests: as 2, and the launch is taken
+ *                    back as if its workgroups had been kept apart
  *   "online_min_tile"  weights of one layer a workgroup of the persistent kernel should
  *                    own before the layer is spread over more workgroups (default 4096)
  *   "online_resident"  1 (default): the persistent kernel keeps its weight slices in LDS

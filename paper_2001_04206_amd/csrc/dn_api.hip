@@ -30,6 +30,7 @@ struct Layout {
     size_t off_gemm_ws = 0, off_gemm_counters = 0;   // partial tiles / arrival counters of k-split contractions
     size_t off_batch = 0, batch_bytes = 0;           // exchange buffers of the persistent minibatch kernel
     size_t off_deep = 0, deep_bytes = 0;             // exchange buffers of the persistent minibatch kernel for deeper nets
+    size_t off_tile = 0, tile_bytes = 0;             // exchange buffers of the minibatch kernel whose layers are cut into tiles
     size_t total = 0;
 };
 
@@ -80,6 +81,8 @@ bool compute_layout(const int32_t *widths, int32_t n_widths, int32_t max_batch, 
     lo.off_batch = o; o += align_up(lo.batch_bytes);
     lo.deep_bytes = deep_exchange_bytes_bound(widths, L, max_batch);
     lo.off_deep = o; o += align_up(lo.deep_bytes);
+    lo.tile_bytes = max_batch > 1 ? tile_exchange_bytes(widths, L, max_batch) : 0;
+    lo.off_tile = o; o += align_up(lo.tile_bytes);
     lo.total = o;
     return true;
 }
@@ -163,7 +166,9 @@ struct dn_net {
     // persistent minibatch kernel (one- and two-layer nets)
     bool batch_ok = false, deep_ok = false;
     int batch_mode = 0;
-    uint32_t batch_seq = 0, deep_seq = 0;
+    uint32_t batch_seq = 0, deep_seq = 0, tile_seq = 0;
+    bool tile_ready = false;   // the tiled minibatch kernel's LDS limit is raised
+    int batch_tiles = 1;
     int device_cus = 0;
     // timing
     hipEvent_t ev_epoch0 = nullptr, ev_epoch1 = nullptr;
@@ -194,6 +199,7 @@ struct dn_net {
     unsigned long long *exchange() const { return (unsigned long long *)(arena + lo.off_online); }
     unsigned long long *batch_exchange() const { return (unsigned long long *)(arena + lo.off_batch); }
     char *deep_exchange() const { return arena + lo.off_deep; }
+    unsigned long long *tile_exchange() const { return (unsigned long long *)(arena + lo.off_tile); }
     void split_k(GemmArgs &g) const
     {
         g.ws = split_k_on ? (float *)(arena + lo.off_gemm_ws) : nullptr;
@@ -844,6 +850,67 @@ dn_status run_deep_persistent(dn_net *net, const float *X, const int32_t *labels
     return DN_OK;
 }
 
+// Microseconds a step takes on the schedules that a minibatch pass would run on without tiles: the low side of what was measured, so
+// that tiles are not taken where they could lose.  The kernel for one and two layers (62 nets of 64 and more inputs, 20 %; 28 nets of
+// fewer, which cost it more): with the first layer's rows in few workgroups 784-128-10 batch 128 18.6 and 1288-19-4 batch 4 10.1,
+// but 64-106-3 batch 12 21, 44-424-127 batch 3 72.  Launches, 124 nets, 15 %: 12.7 a layer for the launches themselves, then by flops,
+// parameters read and written, and a launch for a last layer of more than 16 outputs.
+float step_us_without_tiles(const dn_net *net, int batch)
+{
+    const int L = net->L, n0 = net->n[0], nL = net->n[L];
+    if (net->batch_ok && batch_pays(net, batch)) {
+        const int n1 = L == 2 ? net->n[1] : n0, per = std::min(std::min(n1, PB_MAX_ROWS), std::max((n1 + 255) / 256, (4095 + n0) / n0));
+        if (n0 >= 64)
+            return 0.85f * (9.4f + 0.079f * (float)batch + 0.0116f * (float)n1 + 0.146f * (float)nL + 0.0144f * (float)((n1 + per - 1) / per) +
+                            4.27e-5f * (float)batch * (float)n0);
+        return 0.8f * (21.9f + 0.017f * (float)n1 + 0.0184f * (float)(per * nL));
+    }
+    double weights = 0.0;
+    for (int l = 1; l <= L; ++l) weights += (double)net->n[l] * (double)net->n[l - 1];
+    return 0.88f * (11.4f * (float)L + (float)(weights * (6e-8 * batch + 3e-6)) + (nL > 16 ? 3.f : 0.f));
+}
+
+// Whether a minibatch pass runs on the kernel that cuts every layer into tiles.  (A caller that sets "online_min_tile" means the
+// kernels that own rows.)
+bool takes_tiles(const dn_net *net, int64_t n_samples, int batch, TileGeom &g)
+{
+    if (!net->tile_ready || !net->batch_tiles || net->online_min_tile != ON_DEFAULT_MIN_TILE || batch < 2) return false;
+    if ((n_samples + batch - 1) / batch > ((int64_t)1 << 31) / (2 * net->L)) return false;   // (phases are counted in 32 bits)
+    return tile_geometry(net->n.data(), net->L, batch, net->device_cus, g) && g.words * sizeof(unsigned long long) <= net->lo.tile_bytes &&
+           (net->batch_tiles >= 2 || g.step_us < step_us_without_tiles(net, batch));
+}
+
+// A whole minibatch epoch in one launch of that kernel.
+dn_status run_tiles(dn_net *net, const TileGeom &g, const float *X, const int32_t *labels, int64_t n_samples, int batch, float lr,
+                    float mu, bool timing)
+{
+    const int L = net->L;
+    TilePlan p{};
+    for (int l = 1; l <= L; ++l) {
+        TileLayer &y = p.layer[l];
+        y.W = net->W(l); y.b = net->b(l); y.VW = net->VW(l); y.Vb = net->Vb(l);
+        y.n_in = net->n[l - 1]; y.n_out = net->n[l]; y.act = net->act[l];
+    }
+    p.abort_flag = net->abort_flag();
+    p.loss_acc = net->epoch_acc();
+    p.arrived = net->arrived();
+    p.settled = net->settled();
+    p.expected = (unsigned)g.grid + (net->batch_tiles == 3 ? 1u : 0u);   // (3: one more than will come)
+    p.X = X; p.labels = labels; p.n_samples = n_samples; p.batch = batch;
+    p.lr = lr; p.mu = mu; p.loss = net->loss; p.keep_v = 1;
+    const uint64_t phases = (uint64_t)((n_samples + batch - 1) / batch) * (uint64_t)(2 * L - 1) + 1;
+    if ((uint64_t)net->tile_seq + phases + 2 > 0xffffffffull) {   // phase numbers would wrap
+        DN_HIP(hipMemsetAsync(net->tile_exchange(), 0, net->lo.tile_bytes, net->stream));
+        net->tile_seq = 0;
+    }
+    p.seq0 = net->tile_seq;
+    p.ex = net->tile_exchange();
+    ScopedTimer st(net, DN_K_ONLINE, timing);
+    DN_HIP(launch_tile_epoch(g, p, L, net->stream));
+    net->tile_seq += (uint32_t)phases;
+    return DN_OK;
+}
+
 // Launch-per-product path: every step enqueued on the net's stream.
 dn_status run_launches(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, int32_t batch, float lr, float momentum,
                        bool timing)
@@ -981,6 +1048,7 @@ dn_status dn_net_create(const int32_t *widths, int32_t n_widths, const dn_act *a
         net->block_ready = block_exchange_bytes(net->n.data(), L) > 0 && block_prepare(net->n.data(), net->act[1]) == hipSuccess;
         net->batch_prepared = lo.batch_bytes > 0 && batch_prepare() == hipSuccess;
         net->deep_prepared = lo.deep_bytes > 0 && deep_prepare() == hipSuccess;
+        net->tile_ready = lo.tile_bytes > 0 && tile_prepare() == hipSuccess;
         (void)hipGetLastError();
     }
     refresh_persistent(net);
@@ -994,6 +1062,8 @@ dn_status dn_net_create(const int32_t *widths, int32_t n_widths, const dn_act *a
          hipMemsetAsync(net->arena + lo.off_batch, 0, lo.batch_bytes, net->stream) != hipSuccess) ||
         (lo.deep_bytes > 0 &&
          hipMemsetAsync(net->arena + lo.off_deep, 0, lo.deep_bytes, net->stream) != hipSuccess) ||
+        (lo.tile_bytes > 0 &&
+         hipMemsetAsync(net->arena + lo.off_tile, 0, lo.tile_bytes, net->stream) != hipSuccess) ||
         hipEventCreate(&net->ev_epoch0) != hipSuccess || hipEventCreate(&net->ev_epoch1) != hipSuccess ||
         hipStreamSynchronize(net->stream) != hipSuccess) {
         if (net->ev_epoch0) (void)hipEventDestroy(net->ev_epoch0);
@@ -1175,7 +1245,8 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     // 150 samples, us a pass: 119.3 with both, 102.8 without).
     BlockGeom bg;
     TinyPlan tiny;
-    bool blocks = true;   // samples may be taken in blocks
+    TileGeom tg;
+    bool blocks = true, tiles = true;   // samples may be taken in blocks, layers in tiles
     int64_t first = 0;    // samples that are done
     const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && one_wave(net, momentum, tiny);
     // what the kernels of a whole pass leave beside the parameters: off_scalars
@@ -1197,6 +1268,11 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
             dn_status st = run_online(net, X, labels, n, lr, momentum, blocks, timing);
             if (st == DN_ERR_UNSUPPORTED && net->online_mode == 0) persistent = false;
             else if (st != DN_OK) return st;
+        } else if (tiles && net->batch_mode == 0 && takes_tiles(net, n, batch, tg)) {
+            net->last_schedule = net->L <= 2 ? DN_SCHED_MINIBATCH : DN_SCHED_MINIBATCH_DEEP;
+            dn_status st = run_tiles(net, tg, X, labels, n, batch, lr, momentum, timing);
+            if (st != DN_OK) return st;
+            persistent = true;
         } else if (pbatch) {
             net->last_schedule = DN_SCHED_MINIBATCH;
             dn_status st = run_batch_persistent(net, X, labels, n, batch, lr, momentum, timing);
@@ -1218,10 +1294,10 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         DN_HIP(hipStreamSynchronize(net->stream));
         if (direct) res.acc = *(volatile double *)net->result;
         if (res.settled >= 0) break;
-        // A launch of sample blocks whose workgroups did not all find room has changed nothing, nor have those behind it: the
+        // A launch of sample blocks or tiles whose workgroups did not all find room has changed nothing, nor have those behind it: the
         // samples from its first on go to another kernel.
         first += (int64_t)(-1 - res.settled) * BLOCK_LAUNCH_SAMPLES;
-        blocks = false;
+        blocks = tiles = false;
         DN_HIP(hipMemsetAsync(net->abort_flag(), 0, sizeof(res) - sizeof(double), net->stream));
     }
     if (res.swept) net->last_schedule = DN_SCHED_WIDE_HIDDEN;   // some or all of the samples were not the block kernel's after all
@@ -1389,6 +1465,9 @@ dn_status dn_set_option(dn_net *net, const char *name, int64_t value)
     } else if (!strcmp(name, "batch_mode")) {
         if (value < 0 || value > 2) return DN_ERR_INVALID_ARG;
         net->batch_mode = (int)value;
+    } else if (!strcmp(name, "batch_tiles")) {
+        if (value < 0 || value > 3) return DN_ERR_INVALID_ARG;
+        net->batch_tiles = (int)value;
     } else if (!strcmp(name, "merge_launches")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->merge_launches = (int)value;

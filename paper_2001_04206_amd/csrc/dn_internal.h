@@ -304,6 +304,58 @@ size_t deep_exchange_bytes_bound(const int32_t *n, int L, int max_batch);
 hipError_t deep_prepare();
 hipError_t launch_deep_epoch(const DeepGeom &g, const DeepPlan &plan, hipStream_t stream);
 
+// ---- minibatch epochs with every layer cut into square tiles, one per workgroup (dn_tiles.hip) ----
+constexpr int TILE_THREADS = 512;
+constexpr int TILE_MAX_L = 8;
+constexpr int TILE_MAX_WG = 256;
+constexpr int TILE_MAX_BATCH = 256;
+constexpr int TILE_MAX_NL = 1024;
+constexpr size_t TILE_MAX_LDS_BYTES = 152 * 1024;   // (the kernel has 4 KB of its own)
+
+struct TileGeom {
+    int T, grid, rows;                               // side of a tile, workgroups, batch rounded up to 16
+    int tiled, fused;                                // layers in tiles; the last layer is not one of them
+    int R[TILE_MAX_L + 1], C[TILE_MAX_L + 1];        // row and column blocks of W_l
+    int map[TILE_MAX_L + 1];                         // tile (i, j) on workgroup i C + j (0) or j R + i (1)
+    int lds_w[TILE_MAX_L + 1], lds_a[TILE_MAX_L + 1], lds_b[TILE_MAX_L + 1], lds_d, lds_dl, lds_tmp, lds_floats;
+    size_t off_part, off_z, off_dp, off_a[TILE_MAX_L + 1], off_d[TILE_MAX_L + 1], words;   // exchange region, in 64-bit words
+    float step_us;                                   // what a step is expected to take
+};
+
+struct TileLayer {
+    float *W, *b, *VW, *Vb;
+    uint32_t pub_a, pub_d;               // [2][R][rows * T]: blocks of A_l and Delta_l (bytes from ex)
+    int n_in, n_out, act, R, C, map;
+    int lds_w, lds_a, lds_b;             // the tile, its block of A_{l-1}, biases and their velocities
+};
+
+struct TilePlan {
+    int tiled, fused;                    // layers 1..tiled are in tiles; fused: a narrow one follows
+    TileLayer layer[TILE_MAX_L + 1], out;   // out: the last layer
+    unsigned long long *ex;              // exchange region: [TILE_MAX_WG][2] losses, then
+    uint32_t part;                       // [2][grid][rows * T]: partial blocks (bytes from ex)
+    uint32_t zp, dp;                     // fused: [2][rows][n_in / 16][n_out] partial net inputs (n rounded up to 16), [2][rows * T] deltas
+    int *abort_flag;
+    double *loss_acc;
+    const float *X;
+    const int32_t *labels;
+    int64_t n_samples;
+    int batch, grid, rows;
+    float lr, mu;
+    int loss, keep_v;
+    uint32_t seq0;                       // phases seq0 + 1 .. seq0 + steps (2 tiled - 1) + 1 stamp the exchange words
+    int lds_d, lds_dl, lds_tmp;
+    unsigned *arrived;                   // workgroups that have started
+    int *settled;                        // -1: they did not all start, and the launch has changed nothing
+    unsigned expected;                   // *arrived when all are there
+};
+
+// False unless every layer (but for a narrow last one) is at most max_wg tiles and a workgroup's share fits in LDS.
+bool tile_geometry(const int32_t *n, int L, int batch, int max_wg, TileGeom &g);
+size_t tile_exchange_bytes(const int32_t *n, int L, int max_batch);
+hipError_t tile_prepare();
+hipError_t launch_tile_epoch(const TileGeom &g, TilePlan plan, int L, hipStream_t stream);
+
 // ---- persistent batch-1 epoch kernel with two copies of the inner weights (dn_twin.hip) ----
 // Plain gradient descent, two or more layers, everything resident in LDS.  A workgroup owns a
 // block of units of every hidden layer and keeps their rows of W_l (forward, update) and, for

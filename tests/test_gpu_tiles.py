@@ -1,0 +1,135 @@
+"""Minibatch epochs on the kernel that keeps a square tile of every layer per workgroup, against the CPU checker (fp32 storage, fp64
+sums) on the same seeded inputs.
+
+Tolerance 2e-5 (2-norm and largest, per tensor): a step rounds a weight, its velocity and each number of the two products that move it
+by 6e-8 of itself, their sums of up to a few hundred terms by a few times that; the passes here are 2 to 12 steps, and the largest
+error of a tensor is its 2-norm error times a small factor."""
+import numpy as np
+import pytest
+
+from oracle.dn_oracle import Oracle
+from paper_2001_04206_amd import synth
+from parity_util import announce, assert_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+LIN, SIG, TANH, RELU, SOFTMAX = 0, 1, 2, 3, 4
+MSE, CE = 0, 1
+TOL = 2e-5
+ALWAYS, TAKEN_BACK = 2, 3
+
+
+@pytest.fixture(scope="module")
+def dnlib():
+    from paper_2001_04206_amd import dn
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    dn.lib()
+    return dn
+
+
+def workload(widths, acts, loss, batch, n):
+    w = synth.make("tiles", widths, acts, loss, n_samples=n, features="normal", init="xavier_uniform", batch=batch, lr=0.02,
+                   momentum=0.0, seed=6)
+    rng = np.random.default_rng(13)
+    w.b = [rng.standard_normal(k).astype(np.float32) * 0.1 for k in w.widths[1:]]
+    return w
+
+
+def train(dn, w, option, passes, X=None):
+    net = dn.Net(w.widths, w.acts, w.loss, w.batch)
+    net.set_all(w.W, w.b)
+    net.dn_set_option("batch_tiles", option)
+    if X is None:
+        X = torch.from_numpy(w.X).to("cuda:0")
+    y = torch.from_numpy(w.labels).to("cuda:0")
+    losses = [net.dn_train_epoch(X, y, w.batch, w.lr, mu) for mu in passes]
+    schedule, params = net.dn_last_schedule(), net.get_all()
+    net.close()
+    return losses, params, schedule
+
+
+# widths, hidden activation, loss, batch, samples
+NETS = [
+    ([20, 33, 7], TANH, CE, 5, 23),                        # tiles of 32: one column block and two rows, a short last batch
+    ([33, 32, 31, 64], TANH, CE, 17, 60),                  # 64 outputs: two blocks of them
+    ([40, 70, 49], SIG, MSE, 16, 48),                      # 49 to 64 outputs, squared error
+    ([31, 64, 65], TANH, CE, 9, 30),                       # one output more: the last layer is tiles as well
+    ([70, 10], LIN, CE, 16, 40),                           # one layer
+    ([300, 130], LIN, MSE, 100, 230),                      # one layer, wide
+    ([784, 128, 10], TANH, CE, 128, 280),                  # more partial blocks than a lane asks for at once
+    ([64, 96, 80, 10], RELU, CE, 8, 44),
+    ([100, 40, 1000], TANH, CE, 20, 50),                   # the widest output but 24
+    ([24, 16, 1024], TANH, MSE, 3, 9),
+    ([12, 20, 3], TANH, CE, 256, 600),                     # the largest batch on one workgroup: all samples its own
+    ([300, 500, 200, 300], TANH, CE, 33, 100),
+    ([17, 16, 18, 16, 33, 16, 15, 16, 5], TANH, CE, 2, 9), # eight layers, the smallest batch
+    ([1024, 1000, 1021, 10], TANH, CE, 20, 60),            # tiles of 64
+    ([700, 1024, 520, 100], SIG, CE, 37, 111),             # ... with the last layer
+    ([4096, 64, 64, 4], TANH, CE, 32, 96),                 # sixty-four and more partial blocks
+    ([8, 4000, 6], TANH, CE, 40, 80),                      # a column of tiles
+]
+
+
+@pytest.mark.parametrize("widths,act,loss,batch,n", NETS)
+def test_tiles_match_checker(dnlib, widths, act, loss, batch, n):
+    announce("tiles widths=%s batch=%d" % (widths, batch))
+    L = len(widths) - 1
+    w = workload(widths, [act] * (L - 1) + [SOFTMAX if loss == CE else SIG], loss, batch, n)
+    passes = (0.0, 0.7, 0.7)      # plain (leaves the last step's velocity), then momentum on top of it
+    losses, (W, b), schedule = train(dnlib, w, ALWAYS, passes)
+    assert schedule == (dnlib.DN_SCHED_MINIBATCH if L <= 2 else dnlib.DN_SCHED_MINIBATCH_DEEP)
+    o = Oracle("o32", w.widths, w.acts, w.loss)
+    o.set_params(w.W, w.b)
+    for got, mu in zip(losses, passes):
+        ref, _ = o.train_epoch(w.X, w.labels, batch, w.lr, mu)
+        assert abs(got - ref) <= TOL * max(abs(ref), 1e-6), (got, ref)
+    Wr, br = o.get_params()
+    tol = 1e-3 if act == RELU else TOL     # (a net input within rounding of zero may fall on either side)
+    for l in range(L):
+        assert_close(W[l], Wr[l], tol, "W_%d" % (l + 1))
+        assert_close(b[l], br[l], tol, "b_%d" % (l + 1))
+
+
+@pytest.mark.parametrize("widths,batch,n", [([784, 128, 10], 128, 1000), ([1024, 1024, 1024, 1024, 10], 32, 320), ([300, 500, 200, 300], 33, 400)])
+def test_tiles_repeat_bit_for_bit(dnlib, widths, batch, n):
+    announce("tiles determinism widths=%s" % widths)
+    w = workload(widths, [TANH] * (len(widths) - 2) + [SOFTMAX], CE, batch, n)
+    a, b = train(dnlib, w, ALWAYS, (0.0, 0.9)), train(dnlib, w, ALWAYS, (0.0, 0.9))
+    assert a[0] == b[0]
+    for x, y in zip(a[1][0] + a[1][1], b[1][0] + b[1][1]):
+        assert np.array_equal(x, y)
+
+
+def test_features_need_no_alignment(dnlib):
+    """A sample array that begins anywhere gives the same bits."""
+    announce("tiles, misaligned samples")
+    w = workload([101, 70, 10], [TANH, SOFTMAX], CE, 30, 90)
+    buf = torch.zeros(w.X.size + 1, device="cuda:0")
+    shifted = buf[1:].view(w.X.shape)
+    shifted.copy_(torch.from_numpy(w.X))
+    a, b = train(dnlib, w, ALWAYS, (0.9,)), train(dnlib, w, ALWAYS, (0.9,), X=shifted)
+    assert a[0] == b[0] and all(np.array_equal(x, y) for x, y in zip(a[1][0] + a[1][1], b[1][0] + b[1][1]))
+
+
+@pytest.mark.parametrize("widths", [[200, 120, 10], [64, 96, 80, 100]])
+def test_launch_that_is_taken_back_changes_nothing(dnlib, widths):
+    """As if the workgroups had not all found room: the pass runs on the schedule it would have had, to the same bits."""
+    announce("tiles taken back widths=%s" % widths)
+    w = workload(widths, [TANH] * (len(widths) - 2) + [SOFTMAX], CE, 24, 100)
+    a, b = train(dnlib, w, TAKEN_BACK, (0.0, 0.9)), train(dnlib, w, 0, (0.0, 0.9))
+    assert a[0] == b[0] and a[2] == b[2]
+    for x, y in zip(a[1][0] + a[1][1], b[1][0] + b[1][1]):
+        assert np.array_equal(x, y)
+
+
+def test_not_a_number_stays_one(dnlib):
+    """A sample with a NaN: the loss and every weight it reaches are NaN, as one launch per product leaves them."""
+    announce("tiles, NaN")
+    w = workload([40, 50, 33, 12], [TANH, TANH, SOFTMAX], CE, 10, 20)
+    w.X[3, 7] = np.nan
+    got, (W, b), _ = train(dnlib, w, ALWAYS, (0.0,))
+    ref, (Wr, br), _ = train(dnlib, w, 0, (0.0,))
+    assert np.isnan(got[0]) and np.isnan(ref[0])
+    for x, y in zip(W + b, Wr + br):
+        assert np.array_equal(np.isnan(x), np.isnan(y))

@@ -106,3 +106,20 @@ def test_tiles_of_forward_products(device, rows, k, n, tile):
     status, _, launches = device(256, "net:%d-%d:mse:%d" % (k, n, rows), "forward:%d" % rows, arguments=True)[1]
     products = [a for name, a in launches if name == "gemm_kernel"]
     assert status == dn.DN_OK and len(products) == 1 and products[0].startswith("<dn::SliceTile<%s," % tile), launches
+
+
+# net, batch, momentum: whether a pass runs on the kernel that cuts every layer into tiles
+@pytest.mark.parametrize("net,batch,mu,tiles", [
+    ("784-128-10:ce", 128, 0.9, True), ("1024-1024-1024-1024-10:ce", 32, 0, True), ("1024-1024-1024-1024-10:ce", 64, 0, False), ("64-96-80-10:ce", 8, 0.9, True),
+    ("300-500-200-300:ce", 33, 0.9, True), ("48-67-28:ce", 54, 0.9, False), ("1288-19-4:ce", 4, 0, False), ("123-10-55:ce", 147, 0, False),
+    ("1024-1025-1024-10:ce", 16, 0, False), ("100-50-1024:ce", 8, 0, True), ("100-50-1025:ce", 8, 0, False), ("200-120-10:ce", 257, 0, False)])
+def test_passes_on_tiles(device, net, batch, mu, tiles):
+    for units in (256, 100, 8, 1):
+        train = "train:%d:%d:%g" % (3 * batch, batch, mu)
+        rows = device(units, "net:%s:%d" % (net, batch), train, "option:batch_tiles=0", train)
+        assert all(r[0] == dn.DN_OK for r in rows)
+        ran = [grid for kernel, grid in rows[1][2] if kernel == "tile_epoch_kernel"]
+        assert all(grid <= units for grid in ran) and rows[1][2]
+        if units == 256:
+            assert bool(ran) == tiles, rows
+        assert "tile_epoch_kernel" not in [k for k, _ in rows[3][2]]
