@@ -421,8 +421,9 @@ enum {
     DN_SCHED_ONE_WORKGROUP = 9,    /* batch 1, two layers, no momentum, W_1 within one compute unit's registers: one workgroup
                                       (the last few samples of a call may run on another batch-1 schedule) */
     DN_SCHED_SAMPLE_BLOCKS = 10,   /* batch 1, two layers, no momentum, enough samples: W_1 read and written once per 32 samples */
-    DN_SCHED_WIDE_BLOCKS = 11      /* the same for a hidden layer too wide for LDS (DN_SCHED_WIDE_HIDDEN instead if samples of the
+    DN_SCHED_WIDE_BLOCKS = 11,     /* the same for a hidden layer too wide for LDS (DN_SCHED_WIDE_HIDDEN instead if samples of the
                                       call had inner products beyond fp32, whose launches that kernel takes) */
+    DN_SCHED_SLICES = 12           /* batch 1, two to four layers: as few workgroups as hold the net in LDS */
 };
 dn_status dn_last_schedule(dn_net *net, int32_t *schedule);
 dn_status dn_kernel_time(dn_net *net, int32_t kernel_class, float *ms_total, int64_t *launches);
@@ -488,6 +489,10 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    and corrects them step by step through the samples' inner products, and so does one over a net that
  *                    "online_wide" takes (of at most 131072 hidden units); 0: such passes take the other batch-1 schedules;
  *                    2 + k, for tests: launch k of such a pass is taken back as if its workgroups had been kept apart
+ *   "online_slices"  1 (default): with "online_mode" 0, batch 1 on a net of two to four layers of at most 2048 units (the last
+ *                    one 128) runs on as few workgroups as hold it in LDS, where that was measured to be faster: nets that would
+ *                    take the general persistent kernel, and of those that the other options name the ones with more than
+ *                    1024 weights on one wavefront (not in registers) or at most 24576 weights on two copies; 0: never; 2: wherever it fits
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose
  *                    parameters fit in LDS, twice with momentum) runs on a single wavefront that keeps
  *                    the whole net in LDS -- in its registers, for two layers and momentum 0; 2: the

@@ -73,7 +73,7 @@ bool compute_layout(const int32_t *widths, int32_t n_widths, int32_t max_batch, 
     lo.off_scalars = o; o += kAlign;
     lo.online_bytes = std::max({online_exchange_bytes_bound(widths, L), twin_exchange_bytes_bound(widths, L),
                                 wide_exchange_bytes_bound(widths, L), block_exchange_bytes(widths, L),
-                                wide_block_exchange_bytes(widths, L)});
+                                wide_block_exchange_bytes(widths, L), slice_exchange_bytes(widths, L)});
     lo.off_online = o; o += align_up(lo.online_bytes);
     lo.off_gemm_ws = o; o += align_up(GEMM_WS_FLOATS * sizeof(float));
     lo.off_gemm_counters = o; o += align_up(GEMM_COUNTERS * sizeof(unsigned));
@@ -159,6 +159,8 @@ struct dn_net {
     bool wide_ready = false;   // the wide-hidden-layer batch-1 kernel's LDS limit is raised
     bool wide_ok = false;      // ... and the net suits it
     bool wide_block_ready = false;   // ... and the sample-block form of the wide-hidden-layer kernel
+    bool slice_ready = false;  // the few-workgroup batch-1 kernel's LDS limit is raised
+    int online_slices = 1;
     bool block_ready = false;  // the sample-block batch-1 kernel's LDS limit is raised and the net suits it
     int last_schedule = DN_SCHED_NONE;   // how the last dn_train_epoch ran
     double *result = nullptr;   // a slot of result_slots
@@ -629,10 +631,73 @@ bool takes_blocks(const dn_net *net, int64_t n_samples, float mu, BlockGeom &g)
            block_geometry(net->n.data(), net->L, g) && g.grid <= net->device_cus;
 }
 
+// Batch-1 steps of a net on as few workgroups as hold it in LDS.
+dn_status run_slices(dn_net *net, const SliceGeom &g, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
+                     bool timing)
+{
+    const int L = net->L;
+    SlicePlan p{};
+    for (int l = 1; l <= L; ++l) {
+        SliceLayer &y = p.layer[l];
+        y.W = net->W(l); y.b = net->b(l); y.VW = net->VW(l); y.Vb = net->Vb(l);
+        y.n_in = net->n[l - 1]; y.n_out = net->n[l]; y.act = net->act[l];
+    }
+    p.ex = net->exchange();
+    p.abort_flag = net->abort_flag();
+    p.loss_acc = net->epoch_acc();
+    p.lr = lr; p.mu = mu; p.loss = net->loss;
+    const int64_t chunk = (int64_t)1 << 30;
+    for (int64_t s0 = 0; s0 < n_samples; s0 += chunk) {
+        const int64_t n = std::min(n_samples - s0, chunk);
+        if ((uint64_t)net->online_seq + (uint64_t)n + 2 > 0xffffffffull) {   // step numbers would wrap
+            DN_HIP(hipMemsetAsync(net->exchange(), 0, net->lo.online_bytes, net->stream));
+            net->online_seq = 0;
+        }
+        p.X = X + (size_t)s0 * net->n[0];
+        p.labels = labels + s0;
+        p.n_samples = n;
+        p.keep_v = (s0 + n >= n_samples) ? 1 : 0;
+        p.seq0 = net->online_seq;
+        ScopedTimer st(net, DN_K_ONLINE, timing);
+        DN_HIP(launch_slice_epoch(g, p, L, mu != 0.f, net->device_cus, net->stream));
+        net->online_seq += (uint32_t)n;
+    }
+    return DN_OK;
+}
+
+// Whether a batch-1 pass runs on that kernel.  us a step, before / there (100 to 214 samples): against the general kernel, 66 nets of
+// three and four layers, or of two with momentum, on 1 to 128 workgroups, 4-32-643-7 16.4 / 14.6, 96-64-160-440-37 26 / 15, 37-116-21-61
+// 21.8 / 6.6, 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum 19.4 / 7.6: none slower.  Against the kernel with two
+// copies on one workgroup 28-16-32-188-19 16.7 / 9.3, 68-16-676-23 (27 thousand weights) 17.8 / 16.7, but 4-32-736-10 (31 thousand)
+// 13.6 / 15.6, 544-44-224-2 (34 thousand) 10.0 / 10.4, and on two and more workgroups 376-156-32-5 8.2 / 9.5, 868-544-896-640-3 13.8 / 17.8.  Against one wavefront 18-10-21-7-23 (698
+// weights) 7.2 / 7.4, 14-24-4-36-15 (1116) 8.7 / 7.7, 36-54-15-32 13.6 / 5.4.
+bool takes_slices(dn_net *net, float mu, SliceGeom &g)
+{
+    if (!net->slice_ready || !net->online_slices || net->online_mode != 0) return false;
+    const int L = net->L;
+    if (!slice_geometry(net->n.data(), L, mu != 0.f, net->device_cus, g) || g.words * sizeof(unsigned long long) > net->lo.online_bytes) return false;
+    if (net->online_slices == 2) return true;
+    if (L == 2 && mu == 0.f) return false;
+    int64_t weights = 0;
+    for (int l = 1; l <= L; ++l) weights += (int64_t)net->n[l] * net->n[l - 1];
+    TinyPlan tiny;
+    if (one_wave(net, mu, tiny)) return weights > 1024;
+    TwinGeom tg;
+    if (mu == 0.f && net->online_twin && net->twin_ready && twin_geometry(net->n.data(), L, net->online_min_tile, tg) && tg.grid <= net->device_cus)
+        return g.P == 1 && weights <= 24576;
+    WideGeom wg;
+    return !(net->online_wide && net->wide_ok && wide_geometry(net->n.data(), L, net->device_cus, mu != 0.f, wg));
+}
+
 // A whole batch-1 epoch on the persistent kernel that suits the net.
 dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t n_samples, float lr, float mu,
                      bool blocks, bool timing)
 {
+    SliceGeom slices;
+    if (takes_slices(net, mu, slices)) {
+        net->last_schedule = DN_SCHED_SLICES;
+        return run_slices(net, slices, X, labels, n_samples, lr, mu, timing);
+    }
     const int L = net->L;
     TinyPlan tp;
     if (one_wave(net, mu, tp)) return run_tiny(net, tp, X, labels, n_samples, lr, mu, timing);
@@ -1046,6 +1111,7 @@ dn_status dn_net_create(const int32_t *widths, int32_t n_widths, const dn_act *a
         net->wide_block_ready = net->wide_ready && wide_geometry(net->n.data(), L, net->device_cus, false, wg) &&
                                 wide_block_fits(net->n[1], wg.per) && wide_block_prepare(net->n[2], net->act[1]) == hipSuccess;
         net->block_ready = block_exchange_bytes(net->n.data(), L) > 0 && block_prepare(net->n.data(), net->act[1]) == hipSuccess;
+        net->slice_ready = L >= 2 && L <= SLICE_MAX_L && slice_prepare(L) == hipSuccess;
         net->batch_prepared = lo.batch_bytes > 0 && batch_prepare() == hipSuccess;
         net->deep_prepared = lo.deep_bytes > 0 && deep_prepare() == hipSuccess;
         net->tile_ready = lo.tile_bytes > 0 && tile_prepare() == hipSuccess;
@@ -1248,7 +1314,9 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     TileGeom tg;
     bool blocks = true, tiles = true;   // samples may be taken in blocks, layers in tiles
     int64_t first = 0;    // samples that are done
-    const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && one_wave(net, momentum, tiny);
+    SliceGeom slices;
+    const bool few = batch == 1 && takes_slices(net, momentum, slices);
+    const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && !few && one_wave(net, momentum, tiny);
     // what the kernels of a whole pass leave beside the parameters: off_scalars
     struct { double acc; int aborted, swept; double hits; unsigned arrived; int settled; } res{};
     static_assert(sizeof(res) == 32, "the scalars of the arena");
@@ -1258,7 +1326,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         const float *X = X_dev + (size_t)first * net->n[0];
         const int32_t *labels = labels_dev + first;
         const int64_t n = n_samples - first;
-        bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || (blocks && takes_blocks(net, n, momentum, bg)));
+        bool persistent = batch == 1 && net->online_mode != 1 && (online_fit || few || (blocks && takes_blocks(net, n, momentum, bg)));
         // A persistent path that turns out not to fit (its geometry is recomputed for this call's momentum
         // and the current tile option) reports DN_ERR_UNSUPPORTED before it launches anything: in automatic
         // mode the epoch then runs with one launch per product instead.
@@ -1486,6 +1554,9 @@ dn_status dn_set_option(dn_net *net, const char *name, int64_t value)
     } else if (!strcmp(name, "online_twin")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->online_twin = (int)value;
+    } else if (!strcmp(name, "online_slices")) {
+        if (value < 0 || value > 2) return DN_ERR_INVALID_ARG;
+        net->online_slices = (int)value;
     } else if (!strcmp(name, "online_blocks")) {
         if (value < 0 || value > 1 << 20) return DN_ERR_INVALID_ARG;
         net->online_blocks = (int)value;

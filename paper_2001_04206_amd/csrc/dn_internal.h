@@ -450,6 +450,50 @@ size_t wide_exchange_bytes_bound(const int32_t *n, int L);
 hipError_t wide_prepare();
 hipError_t launch_wide_epoch(const WideGeom &g, const WidePlan &plan, hipStream_t stream);
 
+// ---- batch-1 epochs of two to four layers on as few workgroups as hold the net in LDS (dn_slices.hip) ----
+constexpr int SLICE_THREADS = 512;
+constexpr int SLICE_MAX_L = 4;
+constexpr int SLICE_MAX_IN = 2048;       // widths but the last
+constexpr size_t SLICE_MAX_LDS_BYTES = 156 * 1024;
+
+struct SliceGeom {
+    int P, x_pitch;                      // workgroups
+    int per[SLICE_MAX_L + 1], owners[SLICE_MAX_L + 1], fold[SLICE_MAX_L + 1];     // own units of the hidden layers, workgroups that have any,
+                                                                                  // log2 of per, rounded up
+    int pitch[SLICE_MAX_L + 1], shift[SLICE_MAX_L + 1], subs[SLICE_MAX_L + 1];    // of a row of the slice; backward: log2 of its fours, rows at once
+    int lds_w[SLICE_MAX_L + 1], lds_v[SLICE_MAX_L + 1], lds_a[SLICE_MAX_L + 1], lds_d[SLICE_MAX_L + 1], lds_b[SLICE_MAX_L + 1];
+    int lds_x, lds_z, lds_dL, lds_bL, lds_red, lds_floats;
+    size_t act_x[SLICE_MAX_L + 1], part_x[SLICE_MAX_L + 1], z_x, words;           // exchange region, in 64-bit words
+};
+
+struct SliceLayer {
+    float *W, *b, *VW, *Vb;
+    int n_in, n_out, act, per, P, pitch, shift, subs, fold;
+    int lds_w, lds_v, lds_a, lds_d, lds_b;
+    size_t act_x, part_x;                // [2][n_out] activations, [2][P][n_in] partial sums for the layer below (words from ex)
+};
+
+struct SlicePlan {
+    SliceLayer layer[SLICE_MAX_L + 1];
+    unsigned long long *ex;
+    size_t z_x;                          // [2][P][n_L]
+    int *abort_flag;
+    double *loss_acc;
+    const float *X;
+    const int32_t *labels;
+    int64_t n_samples;
+    float lr, mu;
+    int loss, keep_v, P, spread;         // every spread-th workgroup of the launch takes part
+    uint32_t seq0;
+    int lds_x, x_pitch, lds_z, lds_dL, lds_bL, lds_red, lds_floats;
+};
+
+// False unless the net has two to four layers of at most 2048 units (the last one ON_MAX_NL) that max_wg workgroups hold in LDS.
+bool slice_geometry(const int32_t *n, int L, bool momentum, int max_wg, SliceGeom &g);
+size_t slice_exchange_bytes(const int32_t *n, int L);
+hipError_t slice_prepare(int L);
+hipError_t launch_slice_epoch(const SliceGeom &g, SlicePlan plan, int L, bool momentum, int device_cus, hipStream_t stream);
+
 // ---- batch-1 epochs of very small nets on one wavefront (dn_tiny.hip) ----
 // Every width at most 64: lane j is unit j of each layer; parameters, activations and deltas in LDS.
 struct TinyLayer {

@@ -23,14 +23,15 @@ DN_K_FORWARD, DN_K_DELTA, DN_K_GRAD_UPDATE, DN_K_OUTPUT, DN_K_ONLINE = range(5)
 KERNEL_CLASS_NAMES = ["forward", "delta", "grad_update", "output", "online"]
 (DN_SCHED_NONE, DN_SCHED_LAUNCHES, DN_SCHED_PER_SAMPLE, DN_SCHED_TWO_COPY, DN_SCHED_MINIBATCH,
  DN_SCHED_MINIBATCH_DEEP, DN_SCHED_ONE_WAVE, DN_SCHED_WIDE_HIDDEN, DN_SCHED_ONE_WAVE_REGISTERS,
- DN_SCHED_ONE_WORKGROUP, DN_SCHED_SAMPLE_BLOCKS, DN_SCHED_WIDE_BLOCKS) = range(12)
+ DN_SCHED_ONE_WORKGROUP, DN_SCHED_SAMPLE_BLOCKS, DN_SCHED_WIDE_BLOCKS, DN_SCHED_SLICES) = range(13)
 # the kernel behind each persistent schedule (minibatches: the one that the benchmark's nets take; where it does not pay,
 # batch_epoch_kernel and deep_batch_epoch_kernel)
 SCHEDULE_KERNELS = {DN_SCHED_PER_SAMPLE: "online_epoch_kernel", DN_SCHED_TWO_COPY: "twin_epoch_kernel",
                     DN_SCHED_MINIBATCH: "tile_epoch_kernel", DN_SCHED_MINIBATCH_DEEP: "tile_epoch_kernel",
                     DN_SCHED_ONE_WAVE: "tiny_epoch_kernel", DN_SCHED_WIDE_HIDDEN: "wide_epoch_kernel",
                     DN_SCHED_ONE_WAVE_REGISTERS: "tiny_regs_epoch_kernel", DN_SCHED_ONE_WORKGROUP: "solo_epoch_kernel",
-                    DN_SCHED_SAMPLE_BLOCKS: "block_epoch_kernel", DN_SCHED_WIDE_BLOCKS: "wide_block_epoch_kernel"}
+                    DN_SCHED_SAMPLE_BLOCKS: "block_epoch_kernel", DN_SCHED_WIDE_BLOCKS: "wide_block_epoch_kernel",
+                    DN_SCHED_SLICES: "slice_epoch_kernel"}
 
 EXPORTS = [
     "dn_status_string", "dn_net_arena_bytes", "dn_net_create", "dn_net_destroy", "dn_set_params",

@@ -83,7 +83,7 @@ def test_tiles_match_checker(dnlib, widths, act, loss, batch, n):
     o.set_params(w.W, w.b)
     for got, mu in zip(losses, passes):
         ref, _ = o.train_epoch(w.X, w.labels, batch, w.lr, mu)
-        assert abs(got - ref) <= TOL * max(abs(ref), 1e-6), (got, ref)
+        assert abs(got - ref) <= TOL * max(abs(ref), 0.1), (got, ref)   # (a small loss is a difference of net inputs of up to 10, 6e-7 each)
     Wr, br = o.get_params()
     tol = 1e-3 if act == RELU else TOL     # (a net input within rounding of zero may fall on either side)
     for l in range(L):

@@ -123,3 +123,21 @@ def test_passes_on_tiles(device, net, batch, mu, tiles):
         if units == 256:
             assert bool(ran) == tiles, rows
         assert "tile_epoch_kernel" not in [k for k, _ in rows[3][2]]
+
+
+# net, momentum: whether a batch-1 pass runs on as few workgroups as hold it, and on how many
+@pytest.mark.parametrize("net,mu,groups", [
+    ("37-116-21-61:ce", 0, 1), ("37-116-21-61:ce", 0.9, 1), ("96-64-160-440-37:ce", 0, 3), ("192-68-7:ce", 0.9, 1), ("192-68-7:ce", 0, None),
+    ("1024-1024-1024-1024-10:ce", 0, None), ("28-16-32-188-19:ce", 0, 1), ("544-44-224-2:ce", 0, None), ("4-32-736-10:ce", 0, None), ("376-156-32-5:ce", 0, None),
+    ("18-10-21-7-23:ce", 0.9, None), ("14-24-4-36-15:ce", 0.9, 1), ("4-16-3:ce", 0.9, None), ("340-100000-10:ce", 0.9, None),
+    ("20-30-20-30-20-5:ce", 0, None), ("100-70-60-129:ce", 0, None)])
+def test_passes_on_few_workgroups(device, net, mu, groups):
+    for units in (256, 8, 1):
+        rows = device(units, "net:%s:1" % net, "train:32:1:%g" % mu, "option:online_slices=0", "train:32:1:%g" % mu, "option:online_mode=1",
+                      "option:online_slices=2", "train:32:1:%g" % mu)
+        assert all(r[0] == dn.DN_OK for r in rows), rows
+        ran = [grid for kernel, grid in rows[1][2] if kernel == "slice_epoch_kernel"]
+        assert all(grid <= units for grid in ran) and (rows[1][1] == dn.DN_SCHED_SLICES) == bool(ran)
+        if units == 256:
+            assert ran == ([] if groups is None else [groups if groups == 1 else 8 * groups]), rows
+        assert not [1 for r in (rows[3], rows[6]) for kernel, _ in r[2] if kernel == "slice_epoch_kernel"]
