@@ -525,7 +525,7 @@ __global__ __launch_bounds__(ON_THREADS) void online_epoch_kernel(OnlinePlan p)
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_abort;
-    const int w = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int w = owner_index(), tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int L = p.L;
     const int n0 = p.layer[1].n_in;
     const int nL = p.layer[L].n_out;
@@ -1488,7 +1488,7 @@ __global__ __launch_bounds__(ON_THREADS) void deep_batch_epoch_kernel(DeepPlan p
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_abort;
-    const int w = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int w = owner_index(), tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int L = p.L, nL = p.layer[L].n_out, nL1 = nL + 1, maxB = p.max_batch, n0 = p.layer[1].n_in;
     const DeepLayer &last = p.layer[L];
     const int perL = p.layer[L - 1].per;                 // own units of layer L-1 = own columns of W_L

@@ -57,6 +57,16 @@ __device__ __forceinline__ float act_deriv(int act, float a)
     }
 }
 
+// Which part of a net a workgroup owns.  By the usual round-robin placement workgroups blockIdx.x, blockIdx.x + 8, .. share an XCD;
+// neighbours in ownership share one, so that a line of exchange words has one XCD's writers.  Only speed depends on it, us a step in
+// blockIdx order / this one: 1024-1024-1024-1024-10 in dn_twin.hip 13.7 / 12.7, on the general kernel with momentum 26.7 / 25.4, at batch 8
+// in deep_batch_epoch_kernel 39.1 / 38.5; but wide_epoch_kernel 12.8 / 13.2 and batch_epoch_kernel 19.4 / 19.7, which keep theirs.
+__device__ __forceinline__ int owner_index()
+{
+    const int w = blockIdx.x, n = gridDim.x;
+    return n % 8 == 0 ? (w & 7) * (n >> 3) + (w >> 3) : w;
+}
+
 // dW = mu dW - g ; w += dW, with g already scaled by the learning rate.
 __device__ __forceinline__ float apply_update(float w, float g, float &v, float mu, int mode)
 {

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_abort;
     if (blockIdx.x % p.spread != 0) return;   // (the others are one XCD's, by the usual round-robin placement)
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, w = blockIdx.x / p.spread, P = p.P;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, w = p.spread > 1 ? (int)blockIdx.x / p.spread : owner_index(), P = p.P;
     const int nL = p.layer[L].n_out, n0 = p.layer[1].n_in;
     float *const red = lds + p.lds_red, *const z = lds + p.lds_z, *const dL = lds + p.lds_dL, *const bL = lds + p.lds_bL;
     int row0[L + 1], nr[L + 1];   // own units of the hidden layers

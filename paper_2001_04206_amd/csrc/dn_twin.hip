@@ -91,7 +91,7 @@ __global__ __launch_bounds__(ON_THREADS) void twin_epoch_kernel(TwinPlan p)
 {
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_abort;
-    const int w = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int w = owner_index(), tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     constexpr int L = LT;
     const int n0 = p.layer[1].n_in;
     const TwinLayer &last = p.layer[L];
