@@ -12,10 +12,16 @@
 // workgroup adds up its own units' P numbers.  2L - 3 exchanges a step.  Words {value, step number}, two copies by step parity, as
 // in dn_online.hip.
 //
+// A word is written again two steps later, and by then everyone has read it: every workgroup of the P has units of some hidden layer,
+// so each step it publishes either activations that all workgroups wait for (layers 1 to L-2) or a share of the outputs' net inputs
+// that all wait for (layer L-1), and does so after it has read all it needs of the step before.  So nobody gets two steps ahead of
+// anybody.  (A workgroup without units would publish nothing, be waited for by nobody and find its words overwritten: geometry_of
+// counts none, and what a launch has beyond the P ends at once.)
+//
 // What bounds it: the chain of phases, each 0.5 to 1 us for its reads of LDS (80 to 150 cycles each, so several rows and pieces of
 // a row are in flight together) and some hundred instructions of one wave, and the exchanges.  us a step, the kernels above / this one:
 // 37-116-21-61 21.8 / 6.6, 96-64-160-440-37 26 / 15 (three workgroups), 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum
-// 19.4 / 7.6 (64).  Four waves instead of eight: 8.2 for the first net; sums over the parts of a column without reads in flight
+// 19.4 / 7.6 (63).  Four waves instead of eight: 8.2 for the first net; sums over the parts of a column without reads in flight
 // together: 1 us more.  Where two copies of the inner weights fit (dn_twin.hip) and one workgroup does not, that kernel stays:
 // 1024-1024-1024-1024-10 13.6 there, 19.3 here.
 #include "dn_persist.h"
@@ -165,6 +171,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
     __shared__ int s_abort;
     if (blockIdx.x % p.spread != 0) return;   // (the others are one XCD's, by the usual round-robin placement)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, w = p.spread > 1 ? (int)blockIdx.x / p.spread : owner_index(), P = p.P;
+    if (w >= P) return;
     const int nL = p.layer[L].n_out, n0 = p.layer[1].n_in;
     float *const red = lds + p.lds_red, *const z = lds + p.lds_z, *const dL = lds + p.lds_dL, *const bL = lds + p.lds_bL;
     int row0[L + 1], nr[L + 1];   // own units of the hidden layers
@@ -428,7 +435,7 @@ int log2_up(int n)
 bool geometry_of(const int32_t *n, int L, bool momentum, int P, SliceGeom &g)
 {
     g = SliceGeom{};
-    g.P = P;
+    g.P = 1;   // workgroups with units (1000 units on 64 are 16 each for 63 of them)
     auto four = [](int k) { return (k + 3) & ~3; };
     int at = 0;
     auto take = [&](int k) { const int here = at; at += four(k); return here; };
@@ -437,6 +444,7 @@ bool geometry_of(const int32_t *n, int L, bool momentum, int P, SliceGeom &g)
     for (int l = 1; l < L; ++l) {
         g.per[l] = (n[l] + P - 1) / P;
         g.owners[l] = (n[l] + g.per[l] - 1) / g.per[l];
+        if (g.owners[l] > g.P) g.P = g.owners[l];
         g.lds_a[l] = take(l < L - 1 ? n[l] : g.per[l]);
         g.lds_d[l] = take(g.per[l]);
         g.lds_b[l] = take(2 * g.per[l]);
@@ -451,7 +459,7 @@ bool geometry_of(const int32_t *n, int L, bool momentum, int P, SliceGeom &g)
         g.pitch[l] = four(cols);
         const int groups = g.pitch[l] / 4;
         g.shift[l] = log2_up(groups);
-        if ((1 << g.shift[l]) > SLICE_THREADS || (l < L && g.per[l] > SLICE_THREADS && P > 1)) return false;
+        if ((1 << g.shift[l]) > SLICE_THREADS || (l < L && g.per[l] > SLICE_THREADS && g.P > 1)) return false;
         g.subs[l] = SLICE_THREADS >> g.shift[l];
         if (g.subs[l] > 8) g.subs[l] = 8;
         if ((size_t)rows * g.pitch[l] > (size_t)1 << 20) return false;
@@ -461,17 +469,17 @@ bool geometry_of(const int32_t *n, int L, bool momentum, int P, SliceGeom &g)
     }
     g.lds_floats = at;
     size_t words = 0;
-    if (P > 1) {
+    if (g.P > 1) {
         for (int l = 1; l < L - 1; ++l) {
             g.act_x[l] = words;
             words += (size_t)2 * n[l];
         }
         for (int l = 2; l < L; ++l) {
             g.part_x[l] = words;
-            words += (size_t)2 * P * n[l - 1];
+            words += (size_t)2 * g.P * n[l - 1];
         }
         g.z_x = words;
-        words += (size_t)2 * P * n[L];
+        words += (size_t)2 * g.P * n[L];
     }
     g.words = words;
     return true;
@@ -534,10 +542,11 @@ hipError_t launch_slice_epoch(const SliceGeom &g, SlicePlan plan, int L, bool mo
         y.lds_w = g.lds_w[l]; y.lds_v = g.lds_v[l]; y.lds_a = g.lds_a[l]; y.lds_d = g.lds_d[l]; y.lds_b = g.lds_b[l];
         y.act_x = g.act_x[l]; y.part_x = g.part_x[l];
     }
-    // Up to 32 workgroups go to one XCD: every eighth one, the others end at once.
+    // Up to 32 workgroups go to one XCD: every eighth one, the others end at once.  More: a multiple of eight, for owner_index.
     plan.spread = g.P > 1 && g.P <= 32 && 8 * g.P <= device_cus ? 8 : 1;
     const size_t bytes = (size_t)g.lds_floats * sizeof(float);
-    const int grid = g.P * plan.spread;
+    const int eights = (g.P + 7) / 8 * 8;
+    const int grid = plan.spread > 1 ? g.P * plan.spread : g.P > 1 && eights <= device_cus ? eights : g.P;
     switch (L) {
     case 2: return launch<2>(plan, momentum, grid, bytes, stream);
     case 3: return launch<3>(plan, momentum, grid, bytes, stream);

@@ -8,7 +8,8 @@
 //     option:online_mode=2
 //     train:96:1:0.9          one epoch: samples, batch, momentum
 //     forward:64              rows
-// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups/template arguments).
+// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups/template arguments/what
+// fake_plans.cpp reads in the kernel's parameters).
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -21,6 +22,8 @@
 #include <unistd.h>
 
 #include "dn.h"
+
+std::string plan_of(const std::string &kernel, void **parameters);   // fake_plans.cpp
 
 namespace {
 
@@ -36,7 +39,7 @@ std::map<const void *, std::string> &names()   // (the library registers its ker
     return m;
 }
 
-int log_launch(const void *f, Dim3 grid)
+int log_launch(const void *f, Dim3 grid, void **parameters)
 {
     int status;
     char *full = abi::__cxa_demangle(names()[f].c_str(), nullptr, nullptr, &status);
@@ -48,6 +51,7 @@ int log_launch(const void *f, Dim3 grid)
     launches += " " + name + "/" + std::to_string(grid.x * grid.y * grid.z) + "/";
     for (char c : arguments)
         if (c != ' ') launches += c;
+    launches += "/" + plan_of(name, parameters);
     return 0;
 }
 
@@ -75,8 +79,8 @@ int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shared, void **st
     *grid = call.grid; *block = call.block; *shared = call.shared; *stream = call.stream;
     return 0;
 }
-int hipLaunchKernel(const void *f, Dim3 grid, Dim3, void **, size_t, void *) { return log_launch(f, grid); }
-int hipExtLaunchKernel(const void *f, Dim3 grid, Dim3, void **, size_t, void *, void *, void *, int) { return log_launch(f, grid); }
+int hipLaunchKernel(const void *f, Dim3 grid, Dim3, void **parameters, size_t, void *) { return log_launch(f, grid, parameters); }
+int hipExtLaunchKernel(const void *f, Dim3 grid, Dim3, void **parameters, size_t, void *, void *, void *, int) { return log_launch(f, grid, parameters); }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 1; return 0; }
 int hipFuncSetAttribute(const void *, int, int) { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }

@@ -1,12 +1,14 @@
 """Which kernels the library launches, on devices of made-up sizes: tests/fake_device.cpp stands in for the HIP runtime, so the
 library's own host code decides and nothing runs.  No launch of workgroups that wait for one another may be larger than the
 device, and a pass that no such kernel can take runs launch by launch."""
+import math
 import os
+import random
 import subprocess
 
 import pytest
 
-from paper_2001_04206_amd import dn
+from paper_2001_04206_amd import build, dn
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,22 +17,25 @@ ROOT = os.path.dirname(HERE)
 @pytest.fixture(scope="module")
 def device(tmp_path_factory):
     if not os.path.exists(dn.LIB_PATH):
-        from paper_2001_04206_amd import build
         build.build()
     exe = str(tmp_path_factory.mktemp("fake_device") / "fake_device")
     lib = os.path.dirname(dn.LIB_PATH)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "fake_device.cpp"), "-o", exe,
+    plans = exe + "_plans.o"
+    subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-fPIC", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(lib, "csrc"), "-c",
+                    os.path.join(HERE, "fake_plans.cpp"), "-o", plans], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "fake_device.cpp"), plans, "-o", exe,
                     "-L" + lib, "-l:libdn.so", "-Wl,--export-dynamic,--allow-shlib-undefined,--disable-new-dtags,-rpath," + lib +
                     ",-rpath,/opt/rocm/lib"], check=True)
 
-    def run(units, *commands, arguments=False):
-        """One (status, schedule, [(kernel, workgroups)]) per command; [(kernel, template arguments)] with arguments=True."""
+    def run(units, *commands, arguments=False, plans=False):
+        """One (status, schedule, [(kernel, workgroups)]) per command; [(kernel, template arguments)] with arguments=True,
+        [(kernel, what its parameters say)] with plans=True."""
         out = subprocess.run([exe, str(units), *commands], check=True, capture_output=True, text=True, timeout=120).stdout
         rows = []
         for line in out.splitlines():
             status, schedule, *launches = line.split()
             launches = [l.split("/") for l in launches]
-            rows.append((int(status), int(schedule), [(l[0], l[2] if arguments else int(l[1])) for l in launches]))
+            rows.append((int(status), int(schedule), [(l[0], l[3] if plans else l[2] if arguments else int(l[1])) for l in launches]))
         assert len(rows) == len(commands), out
         return rows
 
@@ -141,3 +146,23 @@ def test_passes_on_few_workgroups(device, net, mu, groups):
         if units == 256:
             assert ran == ([] if groups is None else [groups if groups == 1 else 8 * groups]), rows
         assert not [1 for r in (rows[3], rows[6]) for kernel, _ in r[2] if kernel == "slice_epoch_kernel"]
+
+
+def test_workgroups_that_wait_are_waited_for(device):
+    """A workgroup of the few that hold a net has units of some hidden layer, or nobody would wait for it and its words would be
+    overwritten before it reads them."""
+    rng = random.Random(4)
+    width = lambda: int(math.exp(rng.uniform(math.log(2), math.log(2049))))
+    nets = ["1000-1000-33:ce", "868-544-896-640-3:ce", "900-805-210-3:ce", "920-873-8:ce", "768-704-28-10:ce", "2048-85-4:ce"]
+    nets += ["%s-%d:ce" % ("-".join(str(width()) for _ in range(rng.choice([2, 3, 4]))), rng.randint(1, 128)) for _ in range(120)]
+    took = 0
+    for units in (256, 32):
+        commands = [c for net in nets for c in ("net:%s:1" % net, "option:online_slices=2", "train:32:1:0", "train:32:1:0.9")]
+        for status, _, launches in device(units, *commands, plans=True):
+            assert status == dn.DN_OK
+            for kernel, plan in launches:
+                if kernel == "slice_epoch_kernel":
+                    groups, owning = map(int, plan.split("of"))
+                    assert groups == owning
+                    took += groups > 1
+    assert took > 100
