@@ -15,8 +15,9 @@ namespace {
 // Numbers are kept as three bf16 parts, each the leading 16 bits of what is left (v = h + m + l exactly): six products, hh hm mh mm
 // hl lh, leave out terms of 2^-23 of the product and less.  Three parts need no scale and no test of what fits beside the largest
 // (two f16 parts would take three products, but deltas span more than their range).  What is not finite spoils the sum it enters,
-// and a number below 2^-109 has a subnormal part, which the instruction takes for zero: a workgroup that has found either when it
-// has finished goes through its pixels again with fp32 operands on the fp32 instruction.
+// and a number below 2^-110 may have a last bit below 2^-133, bf16's smallest number (the instruction keeps subnormal numbers: 2^-133 times
+// 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found either when it has finished goes through its pixels again
+// with fp32 operands on the fp32 instruction.
 // The bf16 instruction rounds its sums downwards (measured: every element of dW 5e-7 of the root mean square too low over 128
 // images of 32 x 32).  So pixels 4..7 and 12..15 of a row enter with their sign turned and their sums are subtracted: 2.2e-7 from
 // 64 bits there, without a common sign; the fp32 instruction 3.5e-7.
@@ -49,7 +50,7 @@ __device__ __forceinline__ float leading16(float v) { return __uint_as_float(__f
 
 // eight numbers of one channel and pixel into LDS: as three bf16 parts or (FP32) as two 16-byte words; least: twice the bits of the
 // smallest magnitude that is not zero, less one
-constexpr unsigned DWI_LEAST = (18u << 24) - 1u;   // of 2^-109: a smaller one's last part is subnormal and counts as zero
+constexpr unsigned DWI_LEAST = (18u << 24) - 1u;   // of 2^-109: a smaller one's last bits may be less than bf16 holds
 template <bool FP32>
 __device__ __forceinline__ void dwi_store(const float (&v)[8], char *at, int part, unsigned &least)
 {

@@ -81,6 +81,18 @@ def test_numbers_of_all_sizes(scale_x, scale_d):
     check(X, delta, 0, *run(X, delta, 0))
 
 
+@pytest.mark.parametrize("exponent,last_bits", [(-109, 63), (-107, 15), (-106, 7), (-104, 1)])
+@pytest.mark.parametrize("small", ["delta", "X"])
+def test_numbers_whose_last_bits_are_subnormal(exponent, last_bits, small):
+    """2^exponent (1 + last_bits 2^-23): the last bits by themselves are below 2^-126.  Taken for zero, they would make every product,
+    all of one sign, 2^-17 too small at 2^-109, 2^-19 at 2^-107, 2^-20 at 2^-106."""
+    announce("conv dW, %s of 2^%d" % (small, exponent))
+    X, delta = (t.abs() + 0.5 for t in make(57, 31, 30, 30, 63, 0))
+    tiny = 2.0 ** exponent * (1 + last_bits * 2.0 ** -23)
+    X, delta = (X * 2.0 ** 70, torch.full_like(delta, tiny)) if small == "delta" else (torch.full_like(X, tiny), delta * 2.0 ** 70)
+    check(X, delta, 0, *run(X, delta, 0))
+
+
 def test_not_finite():
     """A number that is not finite reaches the filters it meets, as it does on the fp32 instruction, and no other."""
     announce("conv dW not finite")
