@@ -1487,18 +1487,20 @@ struct DwPlan {
 };
 
 // Whether conv_dw_images_kernel takes the filter gradient that conv_dw_mfma_kernel would run as `groups` workgroups of `blocks`
-// pixel blocks and `tiles` column tiles (3 x 3 filters).  The difference of the two calls' times over 133 layers (8 to 128 -> 32 to
-// 128 channels, 12 to 48 pixels an edge, batches of 8 to 256; up to 3e9 multiply-adds) is, fitted, 1.17 us for each tile of a
-// pixel block on the way of a slot of three workgroups per CU, 0.02 us for each pixel block of the device, less 5.35 us for each
-// row of the longest chunk here and 5.3 us.  Taken from an expected gain of 6 us on: 86 of the 133, 1.02 to 2.24 times as fast, none
-// slower (at 0 us three of 101 lose); few rows a workgroup, or mostly padding (11 of 32 channels, 8 of 9 images), lose up to 1.4
-// times and keep the old form.  Forward and backward call of 150 other layers: 62 faster, 1.17 times in the mean.
+// pixel blocks and `tiles` column tiles (3 x 3 filters).  The difference of the two calls' times over 328 layers (8 to 128 -> 32 to
+// 128 channels, 12 to 48 pixels an edge, batches of 8 to 256; 3e7 to 3e9 multiply-adds) is, fitted for its low side, 0.61 us for each tile
+// of a pixel block on the way of a slot of three workgroups per CU, 0.02 us for each pixel block of the device, less 5.9 us for each row
+// of the longest chunk here and 5.5 us.  Taken where the expected gain is 5 us and a seventh of what the rows take: of the 328 136, 1.0 to
+// 2.43 times as fast, 1.37 in the mean, none slower (at 3 us two lose, one of them 13 %); 50 of the others would gain 3 to 25 %.  Of 88
+// larger ones 86, 1.01 to 2.45 times as fast; without the seventh 256 images of 64 x 64, 16 -> 32 channels, three quarters of whose tile is
+// padding, take 277 us for 266.  Few rows a workgroup, or mostly padding (11 of 32 channels, 8 of 9 images), lose up to 1.2 times.
 bool takes_images(const ConvShape &s, long groups, long blocks, int tiles, int rows, int chunks)
 {
     const double slots = groups > 768 ? groups / 768.0 : 1.0;
-    const double gain = 1.17 * blocks * tiles * slots + 0.02 * groups * blocks - 5.35 * ((rows + chunks - 1) / chunks) - 5.3;
+    const double here = 5.9 * ((rows + chunks - 1) / chunks);
+    const double gain = 0.61 * blocks * tiles * slots + 0.02 * groups * blocks - here - 5.5;
     const size_t image = 4 * std::max((size_t)s.Cin * s.H * s.W, (size_t)s.Cout * s.Ho * s.Wo);   // its offsets take 32 bits
-    return gain > 6.0 && image < (size_t)1 << 31;
+    return gain > std::max(5.0, 0.15 * here) && image < (size_t)1 << 31;
 }
 
 DwPlan dw_plan(const ConvShape &s)

@@ -12,15 +12,17 @@ namespace {
 // (k) are the same pixel of eight images, and its lower and upper half of the lanes hold two neighbouring pixels: a tap then moves a
 // lane's address by whole 16-byte words, and no operand is ever read across a word.
 //
-// Numbers are kept as three bf16 parts, each the leading 16 bits of what is left (v = h + m + l exactly): six products, hh hm mh mm
-// hl lh, leave out terms of 2^-23 of the product and less.  Three parts need no scale and no test of what fits beside the largest
-// (two f16 parts would take three products, but deltas span more than their range).  What is not finite spoils the sum it enters,
-// and a number below 2^-110 may have a last bit below 2^-133, bf16's smallest number (the instruction keeps subnormal numbers: 2^-133 times
-// 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found either when it has finished goes through its pixels again
-// with fp32 operands on the fp32 instruction.
-// The bf16 instruction rounds its sums downwards (measured: every element of dW 5e-7 of the root mean square too low over 128
-// images of 32 x 32).  So pixels 4..7 and 12..15 of a row enter with their sign turned and their sums are subtracted: 2.2e-7 from
-// 64 bits there, without a common sign; the fp32 instruction 3.5e-7.
+// Numbers are kept as three bf16 parts, each what is left rounded to nearest (v = h + m + l exactly): six products, hh hm mh mm hl lh,
+// leave out terms of 2^-25 of the product and less, of either sign.  Three parts need no scale and no test of what fits beside the largest
+// (two f16 parts would take three products, but deltas span more than their range).  What is not finite, or rounds to infinity, spoils the
+// sum it enters, and a number below 2^-110 may have a last bit below 2^-133, bf16's smallest number (the instruction keeps subnormal numbers:
+// 2^-133 times 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found either when it has finished goes through its
+// pixels again with fp32 operands on the fp32 instruction.
+// The bf16 instruction rounds its sums downwards.  So no long sum is formed on it: sixteen products at a time (six instructions, the
+// small terms first) begin at zero and are added to the long sum on the vector unit, to nearest; and pixels 4..7 and 12..15 of a row
+// enter with their sign turned and their sums are subtracted.  Errors of dW against 64 bits (1e-8; fp32 instruction / long sums on the
+// bf16 instruction, parts cut off / this): 128 images of 32 x 32, 32 -> 64 channels, normal numbers 35 / 21 / 14, with ReLU on the input
+// 27 / 21 / 14, all positive 6.4 / 7.2 / 5.9; 256 images of 48 x 24, 64 -> 128 81 / 60 / 20, 58 / 59 / 20, 8.2 / 82 / 5.5.
 //
 // A workgroup of eight waves owns 64 output x 32 input channels, all nine taps, and a run of the rows [8 images][16 columns]
 // (rows in the order image group, strip of columns, row).  LDS holds the row's delta and three rows of the input (the next input
@@ -28,11 +30,11 @@ namespace {
 // nine accumulator tiles, 108 matrix instructions for 51 reads of 16 bytes a row.  The four q are added through LDS at the end.
 // The slot of channel c at pixel p is (c + p) mod 32 (64): writes, whose lanes run over pixels, and reads, whose lanes run over
 // channels, both spread over all banks.
-// Bound: the matrix unit half of the time.  128 images 32 x 32 x 32 -> 64: 39 us (52 to 66 on the fp32 instruction, by what runs
-// before it); a row takes 12.5 thousand cycles of which the two waves of a unit need 6.9 thousand for their products, storing the
-// parts 2.7 and requesting the next row 1.4, in which all waves move together; adding the four q and writing the sums 14 thousand
-// once.  Requests between the products spill (17 registers, slower); one sum per row added to the long one: more exact by itself,
-// 66 for 61 us with the delta pass.
+// Bound: the matrix unit half of the time; storing the parts and requesting the next row, in which all waves move together; 16 additions
+// for six matrix instructions, beside the other wave's.  128 images 32 x 32 x 32 -> 64: 44 us (52 to 66 on the fp32 instruction, by what
+// runs before it; 39 with the long sums on the bf16 instruction).  With the delta pass: 60 (82; 55); requests between the products spill (17 registers,
+// slower); sums of both pixel pairs of a tap before they are added: 20 reloads a row, 64; two short sums at a time, one added while the other
+// is formed: 18 to 39 reloads, 63 to 77.
 constexpr int DWI_THREADS = 512, DWI_TW = 16, DWI_XW = DWI_TW + 2, DWI_IMAGES = 8, DWI_OC = 64, DWI_IC = 32;
 constexpr int DWI_XROW = DWI_XW * DWI_IC * 16, DWI_XPART = 3 * DWI_XROW, DWI_DPART = DWI_TW * DWI_OC * 16;   // bytes
 constexpr int DWI_STAGE = 3 * (DWI_XPART + DWI_DPART), DWI_SUMS = 4 * 9 * 16 * 64 * 4;
@@ -42,11 +44,11 @@ typedef __bf16 v8b_t __attribute__((ext_vector_type(8)));
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 typedef float v4s_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ unsigned upper_halves(float lo, float hi)
+__device__ __forceinline__ unsigned two_bf16(float lo, float hi)   // rounded to nearest
 {
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+    typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, v2b{(__bf16)lo, (__bf16)hi});
 }
-__device__ __forceinline__ float leading16(float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); }
 
 // eight numbers of one channel and pixel into LDS: as three bf16 parts or (FP32) as two 16-byte words; least: twice the bits of the
 // smallest magnitude that is not zero, less one
@@ -62,10 +64,10 @@ __device__ __forceinline__ void dwi_store(const float (&v)[8], char *at, int par
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float a = v[2 * j], b = v[2 * j + 1];
-            const float a1 = a - leading16(a), b1 = b - leading16(b), a2 = a1 - leading16(a1), b2 = b1 - leading16(b1);
-            p[0][j] = upper_halves(a, b);
-            p[1][j] = upper_halves(a1, b1);
-            p[2][j] = upper_halves(a2, b2);
+            p[0][j] = two_bf16(a, b);
+            const float a1 = a - __uint_as_float(p[0][j] << 16), b1 = b - __uint_as_float(p[0][j] & 0xffff0000u);
+            p[1][j] = two_bf16(a1, b1);
+            p[2][j] = two_bf16(a1 - __uint_as_float(p[1][j] << 16), b1 - __uint_as_float(p[1][j] & 0xffff0000u));
             least = min(least, min((__float_as_uint(a) << 1) - 1u, (__float_as_uint(b) << 1) - 1u));
         }
 #pragma unroll
@@ -192,42 +194,38 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
 #pragma unroll
             for (int k = 0; k < 3; ++k) fetch(r, k);
         }
-        v4u_t a[2][PARTS];
+// step e = 9 k + 3 ky + kx: pixels 2 k + h, whose input pixels for tap kx are kx + 2 k + h
+        v4u_t a[PARTS], b[2][PARTS];
+        auto b_load = [&](int e) {
+            const int d = e % 3 + 2 * (e / 9);
+            const char *b_at = b_from + (y + e / 3 % 3) % 3 * DWI_XROW + d * (DWI_IC * 16) + ((b_slot + d) & 31) * 16;
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+            for (int w = 0; w < PARTS; ++w) b[e & 1][w] = *reinterpret_cast<const v4u_t *>(b_at + w * DWI_XPART);
+        };
+        b_load(0);
 #pragma unroll
-            for (int w = 0; w < PARTS; ++w) a[k][w] = *reinterpret_cast<const v4u_t *>(a_from[k] + w * DWI_DPART);
+        for (int e = 0; e < 18; ++e) {
+            if (e % 9 == 0) {
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-            const int from = (y + ky) % 3 * DWI_XROW;
-            // tap kx of pixels 2 k + h is input pixel kx + 2 k + h: two sums at a time, so that neither waits for itself
-#pragma unroll
-            for (int g = 0; g < 3; ++g) {
-                const int d0 = g == 0 ? 0 : (g == 1 ? 2 : 3), d1 = g == 0 ? 1 : (g == 1 ? 2 : 4);
-                v4u_t b[2][PARTS];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int d = e == 0 ? d0 : d1;
-                    const char *b_at = b_from + from + d * (DWI_IC * 16) + ((b_slot + d) & 31) * 16;
-#pragma unroll
-                    for (int w = 0; w < PARTS; ++w) b[e][w] = e == 1 && d1 == d0 ? b[0][w] : *reinterpret_cast<const v4u_t *>(b_at + w * DWI_XPART);
-                }
-                const int k0 = g == 2, k1 = g > 0;
-                v16f_t &c0 = acc[3 * ky + d0 - 2 * k0], &c1 = acc[3 * ky + d1 - 2 * k1];
-                if constexpr (FP32) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[k0][j >> 2][j & 3]), __uint_as_float(b[0][j >> 2][j & 3]), c0, 0, 0, 0);
-                        c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[k1][j >> 2][j & 3]), __uint_as_float(b[1][j >> 2][j & 3]), c1, 0, 0, 0);
-                    }
-                } else {
-                    auto mul = [&](int u, int v) {
-                        c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b_t, a[k0][u]), __builtin_bit_cast(v8b_t, b[0][v]), c0, 0, 0, 0);
-                        c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b_t, a[k1][u]), __builtin_bit_cast(v8b_t, b[1][v]), c1, 0, 0, 0);
-                    };
-                    mul(2, 0); mul(0, 2); mul(1, 1); mul(1, 0); mul(0, 1); mul(0, 0);
-                }
+                for (int w = 0; w < PARTS; ++w) a[w] = *reinterpret_cast<const v4u_t *>(a_from[e / 9] + w * DWI_DPART);
             }
+            if (e < 17) b_load(e + 1);
+            v16f_t &c = acc[e % 9];
+            if constexpr (FP32) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[j >> 2][j & 3]), __uint_as_float(b[e & 1][j >> 2][j & 3]), c, 0, 0, 0);
+            } else {
+                v16f_t t = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                auto mul = [&](int u, int v) {
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b_t, a[u]), __builtin_bit_cast(v8b_t, b[e & 1][v]), t, 0, 0, 0);
+                };
+                mul(2, 0); mul(0, 2); mul(1, 1); mul(1, 0); mul(0, 1); mul(0, 0);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) c[i] += t[i];
+                asm volatile("" : "+v"(c));   // (stays where it is: without this the allocator moves and spills the nine)
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 }

@@ -8,6 +8,7 @@
 //     option:online_mode=2
 //     train:96:1:0.9          one epoch: samples, batch, momentum
 //     forward:64              rows
+//     convback:128:32:32:32:64:3:1:1   dn_conv_backward: batch, channels, height, width, output channels, filter edge, stride, padding
 // One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups/template arguments/what
 // fake_plans.cpp reads in the kernel's parameters).
 #include <cstdint>
@@ -131,6 +132,12 @@ int main(int argc, char **argv)
             status = dn_train_epoch(net, X, (const int32_t *)X, atoi(c[1].c_str()), atoi(c[2].c_str()), 0.01f, (float)atof(c[3].c_str()), &loss);
         } else if (c[0] == "forward") {
             status = dn_forward(net, X, atoi(c[1].c_str()), (float *)somewhere);
+        } else if (c[0] == "convback") {
+            int32_t v[8];
+            for (int k = 0; k < 8; ++k) v[k] = atoi(c[k + 1].c_str());
+            const size_t bytes = dn_conv_backward_workspace_bytes(v[0], v[1], v[2], v[3], v[4], v[5], v[5], v[6], v[7]);
+            float *Y = (float *)somewhere;
+            status = dn_conv_backward(X, X, Y, Y, Y, nullptr, Y, Y, somewhere, bytes, v[0], v[1], v[2], v[3], v[4], v[5], v[5], v[6], v[7], DN_ACT_TANH, nullptr);
         }
         int32_t schedule = -1;
         if (net) dn_last_schedule(net, &schedule);

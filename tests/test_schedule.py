@@ -166,3 +166,14 @@ def test_workgroups_that_wait_are_waited_for(device):
                     assert groups == owning
                     took += groups > 1
     assert took > 100
+
+
+def test_layers_on_eight_images_a_lane(device):
+    """The layers by which tests/test_gpu_conv_dw.py tests conv_dw_images_kernel are ones that take it; narrow or padded ones do not."""
+    from test_gpu_conv_dw import LONG, ODD, SHAPES
+    others = [(8, 8, 14, 14, 32, 1), (256, 16, 64, 64, 32, 1), (57, 31, 30, 30, 63, 0)]
+    shapes = SHAPES + [LONG, ODD] + others
+    rows = device(256, *["convback:%d:%d:%d:%d:%d:3:1:%d" % s for s in shapes], "convback:128:32:32:32:64:5:1:2", "convback:128:32:32:32:64:3:2:1")
+    assert all(r[0] == dn.DN_OK for r in rows)
+    took = ["conv_dw_images_kernel" in [k for k, _ in r[2]] for r in rows]
+    assert took == [True] * (len(SHAPES) + 2) + [False] * (len(others) + 2)
