@@ -462,7 +462,7 @@ struct SliceGeom {
                                                                                   // log2 of per, rounded up
     int pitch[SLICE_MAX_L + 1], shift[SLICE_MAX_L + 1], subs[SLICE_MAX_L + 1];    // of a row of the slice; backward: log2 of its fours, rows at once
     int lds_w[SLICE_MAX_L + 1], lds_v[SLICE_MAX_L + 1], lds_a[SLICE_MAX_L + 1], lds_d[SLICE_MAX_L + 1], lds_b[SLICE_MAX_L + 1];
-    int lds_x, lds_z, lds_dL, lds_bL, lds_red, lds_floats;
+    int lds_x, lds_z, lds_dL, lds_bL, lds_red, lds_zero, lds_floats;
     size_t act_x[SLICE_MAX_L + 1], part_x[SLICE_MAX_L + 1], z_x, words;           // exchange region, in 64-bit words
 };
 
@@ -485,7 +485,7 @@ struct SlicePlan {
     float lr, mu;
     int loss, keep_v, P, spread;         // every spread-th workgroup of the launch takes part
     uint32_t seq0;
-    int lds_x, x_pitch, lds_z, lds_dL, lds_bL, lds_red, lds_floats;
+    int lds_x, x_pitch, lds_z, lds_dL, lds_bL, lds_red, lds_zero, lds_floats;
 };
 
 // False unless the net has two to four layers of at most 2048 units (the last one ON_MAX_NL) that max_wg workgroups hold in LDS.

@@ -20,7 +20,7 @@
 //
 // What bounds it: the chain of phases, each 0.5 to 1 us for its reads of LDS (80 to 150 cycles each, so several rows and pieces of
 // a row are in flight together) and some hundred instructions of one wave, and the exchanges.  us a step, the kernels above / this one:
-// 37-116-21-61 21.8 / 6.6, 96-64-160-440-37 26 / 15 (three workgroups), 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum
+// 37-116-21-61 21.8 / 6.7, 96-64-160-440-37 26 / 15 (three workgroups), 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum
 // 19.4 / 7.6 (63).  Four waves instead of eight: 8.2 for the first net; sums over the parts of a column without reads in flight
 // together: 1 us more.  Where two copies of the inner weights fit (dn_twin.hip) and one workgroup does not, that kernel stays:
 // 1024-1024-1024-1024-10 13.6 there, 19.3 here.
@@ -56,9 +56,9 @@ __device__ __forceinline__ float whole_wave_sum(float v)
 
 // LANES (sixteen or sixty-four) a row, RU rows and CU pieces of a row in flight together (a phase is a few such rounds, and a round
 // takes as long as its slowest read of LDS): fin(row, sum) on one lane per row.  Rows of `pitch` floats (a multiple of four, padding
-// zero, as is x's).
+// zero, as is x's).  zero: four zeros, which pieces beyond a row's end take in place of numbers of both (an infinity times zero is none).
 template <int LANES, int RU, int CU, class Fin>
-__device__ __forceinline__ void rows_times_n(const float *W, int rows, int pitch, const float *x, Fin fin)
+__device__ __forceinline__ void rows_times_n(const float *W, int rows, int pitch, const float *x, const float *zero, Fin fin)
 {
     constexpr int kAtOnce = kThreads / LANES;   // rows side by side
     const int lane = threadIdx.x & (LANES - 1), first = threadIdx.x / LANES;
@@ -74,17 +74,16 @@ __device__ __forceinline__ void rows_times_n(const float *W, int rows, int pitch
             v4f xv[CU], a[RU][CU];
 #pragma unroll
             for (int k = 0; k < CU; ++k) {
-                const int c = c0 + 4 * (lane + LANES * k), cc = min(c, pitch - 4);
-                xv[k] = *(const v4f *)(x + cc);
+                const int c = c0 + 4 * (lane + LANES * k);
+                const bool in = c < pitch;
+                xv[k] = *(const v4f *)(in ? x + c : zero);
 #pragma unroll
-                for (int u = 0; u < RU; ++u) a[u][k] = *(const v4f *)(w[u] + cc);
+                for (int u = 0; u < RU; ++u) a[u][k] = *(const v4f *)(in ? w[u] + c : zero);
             }
 #pragma unroll
-            for (int k = 0; k < CU; ++k) {
-                if (c0 + 4 * (lane + LANES * k) >= pitch) xv[k] = (v4f){0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < CU; ++k)
 #pragma unroll
                 for (int u = 0; u < RU; ++u) s[u] += a[u][k] * xv[k];
-            }
         }
         float v = 0.f;
 #pragma unroll
@@ -98,19 +97,19 @@ __device__ __forceinline__ void rows_times_n(const float *W, int rows, int pitch
     }
 }
 template <class Fin>
-__device__ __forceinline__ void rows_times(const float *W, int rows, int pitch, const float *x, Fin fin)
+__device__ __forceinline__ void rows_times(const float *W, int rows, int pitch, const float *x, const float *zero, Fin fin)
 {
-    if (rows > 64) rows_times_n<16, 4, 2>(W, rows, pitch, x, fin);
-    else if (rows > 16) rows_times_n<16, 2, 4>(W, rows, pitch, x, fin);
-    else if (pitch > 128) rows_times_n<64, 2, 4>(W, rows, pitch, x, fin);
-    else rows_times_n<16, 1, 2>(W, rows, pitch, x, fin);
+    if (rows > 64) rows_times_n<16, 4, 2>(W, rows, pitch, x, zero, fin);
+    else if (rows > 16) rows_times_n<16, 2, 4>(W, rows, pitch, x, zero, fin);
+    else if (pitch > 128) rows_times_n<64, 2, 4>(W, rows, pitch, x, zero, fin);
+    else rows_times_n<16, 1, 2>(W, rows, pitch, x, zero, fin);
 }
 
 // One pass over a slice: W[r][c] -= (lr d[r]) a[c] by the rule of MOM, and with SUM s[c] = sum over the rows of d[r] W[r][c] from the
 // weights before: red holds `subs` parts of it afterwards, part k at red + k * 4 * groups (a barrier must follow).  Four rows in
-// flight together.
+// flight together.  Padding, columns `cols` to pitch - 1, stays zero beside infinities too.
 template <bool MOM, bool SUM>
-__device__ __forceinline__ void rank_one(float *W, float *V, int rows, int pitch, const float *d, const float *a, float lr, float mu,
+__device__ __forceinline__ void rank_one(float *W, float *V, int rows, int cols, int pitch, const float *d, const float *a, float lr, float mu,
                                          float *red, int shift, int subs)
 {
     constexpr int RU = 4;
@@ -120,6 +119,7 @@ __device__ __forceinline__ void rank_one(float *W, float *V, int rows, int pitch
     if (4 * g < pitch) {
         const int c = 4 * g;
         const v4f av = *(const v4f *)(a + c);
+        float no_number = 0.f;   // NaN once a delta is not finite
         for (int r0 = sub; r0 < rows; r0 += RU * subs) {
             float *w[RU];
             v4f wv[RU], vv[RU];
@@ -136,7 +136,10 @@ __device__ __forceinline__ void rank_one(float *W, float *V, int rows, int pitch
             for (int u = 0; u < RU; ++u) {
                 const bool on = r0 + u * subs < rows;
                 const float gv = lr * dv[u];
-                if (SUM) s += (on ? dv[u] : 0.f) * wv[u];
+                no_number = fmaf(gv, 0.f, no_number);
+                if (SUM)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) s[k] = on ? fmaf(dv[u], wv[u][k], s[k]) : s[k];
                 if (MOM) {
                     const v4f v = mu * vv[u] - gv * av;
                     if (on) {
@@ -148,6 +151,12 @@ __device__ __forceinline__ void rank_one(float *W, float *V, int rows, int pitch
                 }
             }
         }
+        if (no_number != 0.f && c + 4 > cols)
+            for (int r = sub; r < rows; r += subs)
+                for (int k = max(c, cols); k < c + 4; ++k) {
+                    W[r * pitch + k] = 0.f;
+                    if (MOM) V[r * pitch + k] = 0.f;
+                }
     }
     if (SUM) *(v4f *)(red + (sub << shift) * 4 + 4 * g) = s;
 }
@@ -173,6 +182,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, w = p.spread > 1 ? (int)blockIdx.x / p.spread : owner_index(), P = p.P;
     if (w >= P) return;
     const int nL = p.layer[L].n_out, n0 = p.layer[1].n_in;
+    const float *const zero = lds + p.lds_zero;
     float *const red = lds + p.lds_red, *const z = lds + p.lds_z, *const dL = lds + p.lds_dL, *const bL = lds + p.lds_bL;
     int row0[L + 1], nr[L + 1];   // own units of the hidden layers
 #pragma unroll
@@ -236,7 +246,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
             const float *b = lds + y.lds_b;
             u64 *ax = p.ex + y.act_x + (size_t)par * y.n_out + row0[l];
             const bool publish = l < L - 1 && P > 1;
-            rows_times(lds + y.lds_w, nr[l], y.pitch, in, [&](int r, float s) {
+            rows_times(lds + y.lds_w, nr[l], y.pitch, in, zero, [&](int r, float s) {
                 const float a = act_fn(y.act, s + b[r]);
                 out[r] = a;
                 if (publish) ll_store(ax + r, a, seq);
@@ -259,7 +269,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
         {
             const SliceLayer &y = p.layer[L];
             u64 *zx = p.ex + p.z_x + ((size_t)par * P + w) * nL;
-            rows_times(lds + y.lds_w, nL, y.pitch, lds + p.layer[L - 1].lds_a, [&](int r, float s) {
+            rows_times(lds + y.lds_w, nL, y.pitch, lds + p.layer[L - 1].lds_a, zero, [&](int r, float s) {
                 if (P == 1) z[r] = s + bL[r];
                 else if (nr[L - 1] > 0) ll_store(zx + r, s, seq);
             });
@@ -313,7 +323,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
             // ---- backward through the last layer ----
-            rank_one<MOM, true>(lds + y.lds_w, lds + y.lds_v, nL, y.pitch, dL, lds + p.layer[L - 1].lds_a, p.lr, p.mu, red, y.shift, y.subs);
+            rank_one<MOM, true>(lds + y.lds_w, lds + y.lds_v, nL, nr[L - 1], y.pitch, dL, lds + p.layer[L - 1].lds_a, p.lr, p.mu, red, y.shift, y.subs);
             __syncthreads();
             const SliceLayer &h = p.layer[L - 1];
             for (int r = tid; r < nr[L - 1]; r += kThreads) {
@@ -331,7 +341,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
         for (int l = L - 1; l >= 2; --l) {
             const SliceLayer &y = p.layer[l], &h = p.layer[l - 1];
             const float *a = lds + h.lds_a;
-            rank_one<MOM, true>(lds + y.lds_w, lds + y.lds_v, nr[l], y.pitch, lds + y.lds_d, a, p.lr, p.mu, red, y.shift, y.subs);
+            rank_one<MOM, true>(lds + y.lds_w, lds + y.lds_v, nr[l], y.n_in, y.pitch, lds + y.lds_d, a, p.lr, p.mu, red, y.shift, y.subs);
             __syncthreads();
             u64 *px = p.ex + y.part_x + ((size_t)par * P + w) * y.n_in;
             for (int c = tid; c < y.n_in; c += kThreads) {
@@ -383,7 +393,7 @@ __global__ __launch_bounds__(SLICE_THREADS) void slice_epoch_kernel(SlicePlan p)
         if (P > 1 && s_abort) break;
 
         // ---- layer 1 ----
-        rank_one<MOM, false>(lds + p.layer[1].lds_w, lds + p.layer[1].lds_v, nr[1], p.layer[1].pitch, lds + p.layer[1].lds_d, x, p.lr, p.mu, red,
+        rank_one<MOM, false>(lds + p.layer[1].lds_w, lds + p.layer[1].lds_v, nr[1], n0, p.layer[1].pitch, lds + p.layer[1].lds_d, x, p.lr, p.mu, red,
                              p.layer[1].shift, p.layer[1].subs);
         if (step + 1 < p.n_samples) {
             float *xn = lds + p.lds_x + (buf ^ 1) * p.x_pitch;
@@ -454,6 +464,7 @@ bool geometry_of(const int32_t *n, int L, bool momentum, int P, SliceGeom &g)
     g.lds_dL = take(ON_MAX_NL);
     g.lds_bL = take(2 * ON_MAX_NL);
     g.lds_red = take(4 * SLICE_THREADS);
+    g.lds_zero = take(4);
     for (int l = 1; l <= L; ++l) {
         const int rows = l < L ? g.per[l] : n[L], cols = l < L ? n[l - 1] : g.per[L - 1];
         g.pitch[l] = four(cols);
@@ -534,7 +545,7 @@ hipError_t launch_slice_epoch(const SliceGeom &g, SlicePlan plan, int L, bool mo
 {
     plan.P = g.P;
     plan.lds_x = g.lds_x; plan.x_pitch = g.x_pitch; plan.lds_z = g.lds_z; plan.lds_dL = g.lds_dL; plan.lds_bL = g.lds_bL;
-    plan.lds_red = g.lds_red; plan.lds_floats = g.lds_floats;
+    plan.lds_red = g.lds_red; plan.lds_zero = g.lds_zero; plan.lds_floats = g.lds_floats;
     plan.z_x = g.z_x;
     for (int l = 1; l <= L; ++l) {
         SliceLayer &y = plan.layer[l];

@@ -104,3 +104,30 @@ def test_not_a_number_stays_one(dnlib):
     assert schedule != dnlib.DN_SCHED_SLICES and np.isnan(got[0]) and np.isnan(ref[0])
     for x, y in zip(W + b, Wr + br):
         assert np.array_equal(np.isnan(x), np.isnan(y))
+
+
+@pytest.mark.parametrize("widths", [[5, 6, 2], [1021, 501, 2]])
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+def test_infinite_deltas(dnlib, widths, mu):
+    """Rows of no multiple of four.  The first sample's first output is infinite, and so is its delta, which makes all weights below it and
+    their row of the last layer -inf.  The second sample's net inputs are then -inf in the hidden layer and, through weights of one sign, infinite
+    in the second output, whose row of the last layer becomes infinite: a NaN in the padding of a row, or from a weight beside the padding,
+    would show there."""
+    announce("slices, infinite deltas widths=%s mu=%g" % (widths, mu))
+    w = synth.make("slices", widths, [LIN, LIN], MSE, n_samples=2, features="normal", init="xavier_uniform", batch=1, lr=0.0001, momentum=0.0, seed=6)
+    w.X = np.abs(w.X) + np.float32(0.1)
+    w.W = [np.abs(W) + np.float32(0.1) for W in w.W]
+    w.W[-1][0], w.W[-1][1] = 3e38, -1.0
+    w.b = [np.full(k, 0.1, np.float32) for k in widths[1:]]
+    losses, (W, b), schedule = train(dnlib, w, (mu,))
+    assert schedule == dnlib.DN_SCHED_SLICES
+    ref = dnlib.Net(w.widths, w.acts, w.loss, 1)
+    ref.set_all(w.W, w.b)
+    ref.dn_set_option("online_mode", 1)
+    ref.dn_train_epoch(torch.from_numpy(w.X).to("cuda:0"), torch.from_numpy(w.labels).to("cuda:0"), 1, w.lr, mu)
+    Wr, br = ref.get_all()
+    ref.close()
+    assert np.isinf(W[1][1]).all()
+    for got, want in zip(W + b, Wr + br):
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(kind(got), kind(want))
