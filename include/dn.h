@@ -413,8 +413,8 @@ enum {
     DN_SCHED_LAUNCHES = 1,        /* one launch per product (or per few products) of every step */
     DN_SCHED_PER_SAMPLE = 2,      /* batch 1: the general persistent whole-epoch kernel */
     DN_SCHED_TWO_COPY = 3,        /* batch 1: the persistent kernel with row and column copies of the inner weights */
-    DN_SCHED_MINIBATCH = 4,       /* a persistent minibatch kernel, one- or two-layer net ("batch_tiles" says which) */
-    DN_SCHED_MINIBATCH_DEEP = 5,  /* a persistent minibatch kernel, deeper net */
+    DN_SCHED_MINIBATCH = 4,       /* a persistent minibatch kernel, one- or two-layer net (there are two: dn_last_kernel) */
+    DN_SCHED_MINIBATCH_DEEP = 5,  /* a persistent minibatch kernel, deeper net (likewise) */
     DN_SCHED_ONE_WAVE = 6,        /* batch 1, every layer at most 64 wide: one wavefront runs the epoch */
     DN_SCHED_WIDE_HIDDEN = 7,     /* batch 1, two layers, a hidden layer too wide for LDS: rows in LDS, registers and memory */
     DN_SCHED_ONE_WAVE_REGISTERS = 8, /* batch 1, two layers at most 64 wide, no momentum: one wavefront, the net in its registers */
@@ -426,6 +426,9 @@ enum {
     DN_SCHED_SLICES = 12           /* batch 1, two to four layers: as few workgroups as hold the net in LDS */
 };
 dn_status dn_last_schedule(dn_net *net, int32_t *schedule);
+/* The persistent kernel behind that schedule, by the name a profiler's kernel trace shows ("tile_epoch_kernel"); "" where there was
+ * none.  The string is the library's and stays. */
+dn_status dn_last_kernel(dn_net *net, const char **name);
 dn_status dn_kernel_time(dn_net *net, int32_t kernel_class, float *ms_total, int64_t *launches);
 /* Algorithmic floating-point operations (2 x rows x columns x contraction length per product)
  * of the timed launches of one class of the last dn_train_epoch; 0 for the classes that are not

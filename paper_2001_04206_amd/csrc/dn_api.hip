@@ -171,6 +171,7 @@ struct dn_net {
     uint32_t batch_seq = 0, deep_seq = 0, tile_seq = 0;
     bool tile_ready = false;   // the tiled minibatch kernel's LDS limit is raised
     int batch_tiles = 1;
+    bool last_tiles = false;   // it ran the last dn_train_epoch
     int device_cus = 0;
     // timing
     hipEvent_t ev_epoch0 = nullptr, ev_epoch1 = nullptr;
@@ -1331,6 +1332,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         // and the current tile option) reports DN_ERR_UNSUPPORTED before it launches anything: in automatic
         // mode the epoch then runs with one launch per product instead.
         net->last_schedule = DN_SCHED_LAUNCHES;
+        net->last_tiles = false;
         if (persistent) {
             net->last_schedule = DN_SCHED_PER_SAMPLE;   // run_online changes it if another kernel takes the pass
             dn_status st = run_online(net, X, labels, n, lr, momentum, blocks, timing);
@@ -1338,6 +1340,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
             else if (st != DN_OK) return st;
         } else if (tiles && net->batch_mode == 0 && takes_tiles(net, n, batch, tg)) {
             net->last_schedule = net->L <= 2 ? DN_SCHED_MINIBATCH : DN_SCHED_MINIBATCH_DEEP;
+            net->last_tiles = true;
             dn_status st = run_tiles(net, tg, X, labels, n, batch, lr, momentum, timing);
             if (st != DN_OK) return st;
             persistent = true;
@@ -1492,6 +1495,26 @@ dn_status dn_last_schedule(dn_net *net, int32_t *schedule)
 {
     if (!net || !schedule) return DN_ERR_INVALID_ARG;
     *schedule = net->last_schedule;
+    return DN_OK;
+}
+
+dn_status dn_last_kernel(dn_net *net, const char **name)
+{
+    if (!net || !name) return DN_ERR_INVALID_ARG;
+    switch (net->last_schedule) {
+    case DN_SCHED_PER_SAMPLE: *name = "online_epoch_kernel"; break;
+    case DN_SCHED_TWO_COPY: *name = "twin_epoch_kernel"; break;
+    case DN_SCHED_MINIBATCH: *name = net->last_tiles ? "tile_epoch_kernel" : "batch_epoch_kernel"; break;
+    case DN_SCHED_MINIBATCH_DEEP: *name = net->last_tiles ? "tile_epoch_kernel" : "deep_batch_epoch_kernel"; break;
+    case DN_SCHED_ONE_WAVE: *name = "tiny_epoch_kernel"; break;
+    case DN_SCHED_WIDE_HIDDEN: *name = "wide_epoch_kernel"; break;
+    case DN_SCHED_ONE_WAVE_REGISTERS: *name = "tiny_regs_epoch_kernel"; break;
+    case DN_SCHED_ONE_WORKGROUP: *name = "solo_epoch_kernel"; break;
+    case DN_SCHED_SAMPLE_BLOCKS: *name = "block_epoch_kernel"; break;
+    case DN_SCHED_WIDE_BLOCKS: *name = "wide_block_epoch_kernel"; break;
+    case DN_SCHED_SLICES: *name = "slice_epoch_kernel"; break;
+    default: *name = ""; break;
+    }
     return DN_OK;
 }
 

@@ -24,10 +24,9 @@ KERNEL_CLASS_NAMES = ["forward", "delta", "grad_update", "output", "online"]
 (DN_SCHED_NONE, DN_SCHED_LAUNCHES, DN_SCHED_PER_SAMPLE, DN_SCHED_TWO_COPY, DN_SCHED_MINIBATCH,
  DN_SCHED_MINIBATCH_DEEP, DN_SCHED_ONE_WAVE, DN_SCHED_WIDE_HIDDEN, DN_SCHED_ONE_WAVE_REGISTERS,
  DN_SCHED_ONE_WORKGROUP, DN_SCHED_SAMPLE_BLOCKS, DN_SCHED_WIDE_BLOCKS, DN_SCHED_SLICES) = range(13)
-# the kernel behind each persistent schedule (minibatches: the one that the benchmark's nets take; where it does not pay,
-# batch_epoch_kernel and deep_batch_epoch_kernel)
+# the kernel behind each persistent schedule (minibatches: or tile_epoch_kernel, dn_last_kernel says)
 SCHEDULE_KERNELS = {DN_SCHED_PER_SAMPLE: "online_epoch_kernel", DN_SCHED_TWO_COPY: "twin_epoch_kernel",
-                    DN_SCHED_MINIBATCH: "tile_epoch_kernel", DN_SCHED_MINIBATCH_DEEP: "tile_epoch_kernel",
+                    DN_SCHED_MINIBATCH: "batch_epoch_kernel", DN_SCHED_MINIBATCH_DEEP: "deep_batch_epoch_kernel",
                     DN_SCHED_ONE_WAVE: "tiny_epoch_kernel", DN_SCHED_WIDE_HIDDEN: "wide_epoch_kernel",
                     DN_SCHED_ONE_WAVE_REGISTERS: "tiny_regs_epoch_kernel", DN_SCHED_ONE_WORKGROUP: "solo_epoch_kernel",
                     DN_SCHED_SAMPLE_BLOCKS: "block_epoch_kernel", DN_SCHED_WIDE_BLOCKS: "wide_block_epoch_kernel",
@@ -37,7 +36,7 @@ EXPORTS = [
     "dn_status_string", "dn_net_arena_bytes", "dn_net_create", "dn_net_destroy", "dn_set_params",
     "dn_get_params", "dn_get_grads", "dn_forward", "dn_backward", "dn_update", "dn_train_epoch",
     "dn_train", "dn_evaluate", "dn_layer_backward_workspace_bytes", "dn_layer_backward_host",
-    "dn_last_epoch_ms", "dn_last_schedule", "dn_kernel_time", "dn_kernel_flops", "dn_set_option",
+    "dn_last_epoch_ms", "dn_last_schedule", "dn_last_kernel", "dn_kernel_time", "dn_kernel_flops", "dn_set_option",
     "dn_conv_forward", "dn_conv_backward_workspace_bytes", "dn_conv_backward", "dn_maxpool_forward",
     "dn_maxpool_backward", "dn_input_gradient", "dn_sgd_step",
     "dn_conv_backward_static", "dn_conv_backward_static_limit",
@@ -88,6 +87,7 @@ def lib():
                                              C.POINTER(f32), C.POINTER(f32), C.POINTER(f32)]
         l.dn_last_epoch_ms.argtypes = [vp, C.POINTER(f32)]
         l.dn_last_schedule.argtypes = [vp, C.POINTER(i32)]
+        l.dn_last_kernel.argtypes = [vp, C.POINTER(C.c_char_p)]
         l.dn_kernel_time.argtypes = [vp, i32, C.POINTER(f32), C.POINTER(i64)]
         l.dn_kernel_flops.argtypes = [vp, i32, C.POINTER(C.c_double)]
         l.dn_set_option.argtypes = [vp, C.c_char_p, i64]
@@ -448,6 +448,11 @@ class Net:
         v = C.c_int32(0)
         _check(lib().dn_last_schedule(self._h, C.byref(v)), "dn_last_schedule")
         return int(v.value)
+
+    def dn_last_kernel(self) -> str:
+        v = C.c_char_p()
+        _check(lib().dn_last_kernel(self._h, C.byref(v)), "dn_last_kernel")
+        return v.value.decode()
 
     def dn_kernel_time(self, kernel_class: int) -> Tuple[float, int]:
         ms, n = C.c_float(0.0), C.c_int64(0)

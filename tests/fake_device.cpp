@@ -9,7 +9,7 @@
 //     train:96:1:0.9          one epoch: samples, batch, momentum
 //     forward:64              rows
 //     convback:128:32:32:32:64:3:1:1   dn_conv_backward: batch, channels, height, width, output channels, filter edge, stride, padding
-// One line per command: its status, the schedule of the last epoch and the launches it made (name/workgroups/template arguments/what
+// One line per command: its status, the schedule of the last epoch and its kernel, and the launches it made (name/workgroups/template arguments/what
 // fake_plans.cpp reads in the kernel's parameters).
 #include <cstdint>
 #include <cstdio>
@@ -140,8 +140,10 @@ int main(int argc, char **argv)
             status = dn_conv_backward(X, X, Y, Y, Y, nullptr, Y, Y, somewhere, bytes, v[0], v[1], v[2], v[3], v[4], v[5], v[5], v[6], v[7], DN_ACT_TANH, nullptr);
         }
         int32_t schedule = -1;
+        const char *kernel = "";
         if (net) dn_last_schedule(net, &schedule);
-        printf("%d %d%s\n", status, schedule, launches.c_str());
+        if (net) dn_last_kernel(net, &kernel);
+        printf("%d %d=%s%s\n", status, schedule, kernel, launches.c_str());
         fflush(stdout);
     }
     _exit(0);

@@ -4,9 +4,17 @@
 
 #include "dn_internal.h"
 
-// slice_epoch_kernel: workgroups that take part, and how many of them have units of some hidden layer
+// slice_epoch_kernel: workgroups that take part, and how many of them have units of some hidden layer.  tile_epoch_kernel: whether all the
+// workgroups it waits for will come; if not, it says so as it would on a device.
 std::string plan_of(const std::string &kernel, void **parameters)
 {
+    if (kernel == "tile_epoch_kernel") {
+        const dn::TilePlan &p = *static_cast<const dn::TilePlan *>(parameters[0]);
+        if (p.expected == (unsigned)p.grid) return "all";
+        *p.settled = -1;
+        *p.abort_flag = 1;
+        return "kept-apart";
+    }
     if (kernel != "slice_epoch_kernel") return "";
     const dn::SlicePlan &p = *static_cast<const dn::SlicePlan *>(parameters[0]);
     int L = 0, owning = 0;

@@ -490,10 +490,12 @@ def test_tile_option_refits_the_minibatch_kernel(dnlib):
     for tile in (None, 1 << 22):
         net = dnlib.Net(w.widths, w.acts, w.loss, 8)
         net.set_all(w.W, w.b)
+        net.dn_set_option("batch_tiles", 0)
         if tile is not None:
             net.dn_set_option("online_min_tile", tile)
         loss = net.dn_train_epoch(X, y, 8, w.lr, w.momentum)
         assert net.dn_last_schedule() == (dnlib.DN_SCHED_MINIBATCH if tile is None else dnlib.DN_SCHED_LAUNCHES)
+        assert net.dn_last_kernel() == ("batch_epoch_kernel" if tile is None else "")
         outs.append((loss, net.get_all()))
         if tile is not None:
             net.dn_set_option("batch_mode", 2)
@@ -633,4 +635,5 @@ def test_every_benchmark_workload_takes_its_intended_schedule(dnlib):
                                   w.lr, w.momentum)
         assert np.isfinite(loss), w.name
         assert net.dn_last_schedule() == want, (w.name, net.dn_last_schedule(), want)
+        assert (net.dn_last_kernel() == "tile_epoch_kernel") == (want in (S.DN_SCHED_MINIBATCH, S.DN_SCHED_MINIBATCH_DEEP)), (w.name, net.dn_last_kernel())
         net.close()

@@ -45,11 +45,12 @@ def train(dn, w, option, passes, X=None):
     y = torch.from_numpy(w.labels).to("cuda:0")
     losses = [net.dn_train_epoch(X, y, w.batch, w.lr, mu) for mu in passes]
     schedule, params = net.dn_last_schedule(), net.get_all()
+    assert (net.dn_last_kernel() == "tile_epoch_kernel") == (option == ALWAYS)
     net.close()
     return losses, params, schedule
 
 
-# widths, hidden activation, loss, batch, samples
+# widths, hidden activation, loss, batch, samples (tests/test_schedule.py sees to it that they fit)
 NETS = [
     ([20, 33, 7], TANH, CE, 5, 23),                        # tiles of 32: one column block and two rows, a short last batch
     ([33, 32, 31, 64], TANH, CE, 17, 60),                  # 64 outputs: two blocks of them
@@ -61,7 +62,8 @@ NETS = [
     ([64, 96, 80, 10], RELU, CE, 8, 44),
     ([100, 40, 1000], TANH, CE, 20, 50),                   # the widest output but 24
     ([24, 16, 1024], TANH, MSE, 3, 9),
-    ([12, 20, 3], TANH, CE, 256, 600),                     # the largest batch on one workgroup: all samples its own
+    ([12, 20, 3], TANH, CE, 224, 500),                     # the largest batch on one workgroup: all samples its own
+    ([30, 70], LIN, MSE, 256, 600),                        # the largest of all
     ([300, 500, 200, 300], TANH, CE, 33, 100),
     ([17, 16, 18, 16, 33, 16, 15, 16, 5], TANH, CE, 2, 9), # eight layers, the smallest batch
     ([1024, 1000, 1021, 10], TANH, CE, 20, 60),            # tiles of 64

@@ -27,15 +27,16 @@ def device(tmp_path_factory):
                     "-L" + lib, "-l:libdn.so", "-Wl,--export-dynamic,--allow-shlib-undefined,--disable-new-dtags,-rpath," + lib +
                     ",-rpath,/opt/rocm/lib"], check=True)
 
-    def run(units, *commands, arguments=False, plans=False):
+    def run(units, *commands, arguments=False, plans=False, names=False):
         """One (status, schedule, [(kernel, workgroups)]) per command; [(kernel, template arguments)] with arguments=True,
-        [(kernel, what its parameters say)] with plans=True."""
+        [(kernel, what its parameters say)] with plans=True; the schedule's kernel (dn_last_kernel) in its place with names=True."""
         out = subprocess.run([exe, str(units), *commands], check=True, capture_output=True, text=True, timeout=120).stdout
         rows = []
         for line in out.splitlines():
             status, schedule, *launches = line.split()
+            schedule, kernel = schedule.split("=")
             launches = [l.split("/") for l in launches]
-            rows.append((int(status), int(schedule), [(l[0], l[3] if plans else l[2] if arguments else int(l[1])) for l in launches]))
+            rows.append((int(status), kernel if names else int(schedule), [(l[0], l[3] if plans else l[2] if arguments else int(l[1])) for l in launches]))
         assert len(rows) == len(commands), out
         return rows
 
@@ -177,3 +178,45 @@ def test_layers_on_eight_images_a_lane(device):
     assert all(r[0] == dn.DN_OK for r in rows)
     took = ["conv_dw_images_kernel" in [k for k, _ in r[2]] for r in rows]
     assert took == [True] * (len(SHAPES) + 2) + [False] * (len(others) + 2)
+
+
+# net, largest batch, pass, options: every schedule
+PASSES = [("4-16-3:ce", 1, "64:1:0", ()), ("4-16-3:ce", 1, "64:1:0.9", ()), ("784-128-10:ce", 1, "64:1:0", ()), ("784-128-10:ce", 1, "63:1:0", ()),
+          ("1024-1024-1024-1024-10:ce", 1, "8:1:0", ()), ("1024-1024-1024-1024-10:ce", 1, "8:1:0.9", ("online_slices=0",)),
+          ("37-116-21-61:ce", 1, "8:1:0", ()), ("340-100000-10:ce", 1, "63:1:0", ()), ("340-100000-10:ce", 1, "64:1:0", ()),
+          ("784-128-10:ce", 128, "256:128:0.9", ()), ("784-128-10:ce", 128, "256:128:0.9", ("batch_tiles=0",)), ("784-512-10:ce", 64, "128:64:0.9", ()),
+          ("784-512-10:ce", 64, "128:64:0.9", ("batch_tiles=2",)), ("1024-1024-1024-1024-10:ce", 8, "16:8:0", ("batch_mode=2",)),
+          ("1024-1024-1024-1024-10:ce", 32, "64:32:0", ()), ("4096-4096-4096-1000:ce", 256, "512:256:0.9", ()), ("784-128-10:ce", 1, "8:1:0", ("online_mode=1",))]
+
+
+def test_the_kernel_of_a_pass_is_known_by_name(device):
+    """dn_last_kernel names a kernel that the pass launched, and none where it went launch by launch."""
+    seen = set()
+    for net, batch, run, options in PASSES:
+        commands = ["net:%s:%d" % (net, batch)] + ["option:" + o for o in options] + ["train:" + run]
+        schedule, kernel = device(256, *commands)[-1][1], device(256, *commands, names=True)[-1][1]
+        launched = [k for k, _ in device(256, *commands)[-1][2]]
+        assert kernel in launched if kernel else schedule == dn.DN_SCHED_LAUNCHES, (net, options, kernel, launched)
+        assert kernel in ("", "tile_epoch_kernel", dn.SCHEDULE_KERNELS.get(schedule)), (net, kernel)
+        seen.add((schedule, kernel))
+    assert len(seen) == 14
+    assert device(256, "net:4-16-3:ce:1", names=True)[0][1] == ""
+
+
+@pytest.mark.parametrize("net,batch,after", [("200-120-10:ce", 24, "batch_epoch_kernel"), ("64-96-80-100:ce", 24, None)])
+def test_a_launch_of_tiles_that_is_kept_apart(device, net, batch, after):
+    """The pass begins on tiles and ends on the schedule it has without them."""
+    train = "train:%d:%d:0.9" % (4 * batch, batch)
+    commands = ("net:%s:%d" % (net, batch), "option:batch_tiles=3", train, "option:batch_tiles=0", train)
+    rows, plans = device(256, *commands), device(256, *commands, plans=True)
+    assert all(r[0] == dn.DN_OK for r in rows)
+    assert plans[2][2][0] == ("tile_epoch_kernel", "kept-apart") and rows[2][2][1:] == rows[4][2]
+    assert rows[2][1] == rows[4][1] and (after is None or rows[2][2][1][0] == after)
+
+
+def test_nets_by_which_tiles_are_tested(device):
+    from test_gpu_tiles import CE, NETS
+    for widths, _, loss, batch, n in NETS + [([12, 20, 3], 0, CE, 225, 500), ([30, 70], 0, CE, 257, 600)]:
+        net = "net:%s:%s:%d" % ("-".join(map(str, widths)), "ce" if loss == CE else "mse", batch)
+        took = device(256, net, "option:batch_tiles=2", "train:%d:%d:0.7" % (n, batch), names=True)[2][1] == "tile_epoch_kernel"
+        assert took == (batch not in (225, 257)), (widths, batch)
