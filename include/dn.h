@@ -467,7 +467,8 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    not counted; else at most 1024) and fit in LDS that way run on a persistent kernel that keeps a tile of
  *                    every layer per workgroup, where a step is expected to take less there than on the other schedules; any
  *                    widths, with or without momentum; 0: never; 2: wherever it fits; 3, for tests: as 2, and the launch is taken
- *                    back as if its workgroups had been kept apart
+ *                    back as if its workgroups had been kept apart.  After a launch that was taken back the net's next 8
+ *                    minibatch passes do without (16 if the next launch is taken back too, up to 1024; setting the option ends that)
  *   "online_min_tile"  weights of one layer a workgroup of the persistent kernel should
  *                    own before the layer is spread over more workgroups (default 4096)
  *   "online_resident"  1 (default): the persistent kernel keeps its weight slices in LDS

@@ -172,6 +172,7 @@ struct dn_net {
     bool tile_ready = false;   // the tiled minibatch kernel's LDS limit is raised
     int batch_tiles = 1;
     bool last_tiles = false;   // it ran the last dn_train_epoch
+    int tile_pause = 0, tile_rest = 0;   // passes without it after a launch that was taken back; how many of them are left
     int device_cus = 0;
     // timing
     hipEvent_t ev_epoch0 = nullptr, ev_epoch1 = nullptr;
@@ -1313,7 +1314,10 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     BlockGeom bg;
     TinyPlan tiny;
     TileGeom tg;
-    bool blocks = true, tiles = true;   // samples may be taken in blocks, layers in tiles
+    // Samples may be taken in blocks, layers in tiles.  A launch of tiles that is taken back has cost a tenth of a second, some fifty times a
+    // small pass: whatever kept its workgroups apart is given 8 passes to go away, then 16, up to 1024.
+    bool blocks = true, tiles = batch > 1 && net->tile_rest == 0;
+    if (batch > 1 && net->tile_rest > 0) --net->tile_rest;
     int64_t first = 0;    // samples that are done
     SliceGeom slices;
     const bool few = batch == 1 && takes_slices(net, momentum, slices);
@@ -1364,11 +1368,15 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
         if (!direct) DN_HIP(hipMemcpyAsync(&res, net->epoch_acc(), sizeof(res), hipMemcpyDeviceToHost, net->stream));
         DN_HIP(hipStreamSynchronize(net->stream));
         if (direct) res.acc = *(volatile double *)net->result;
-        if (res.settled >= 0) break;
+        if (res.settled >= 0) {
+            if (net->last_tiles) net->tile_pause = 0;
+            break;
+        }
         // A launch of sample blocks or tiles whose workgroups did not all find room has changed nothing, nor have those behind it: the
         // samples from its first on go to another kernel.
         first += (int64_t)(-1 - res.settled) * BLOCK_LAUNCH_SAMPLES;
         blocks = tiles = false;
+        if (net->last_tiles) net->tile_rest = net->tile_pause = std::min(std::max(8, 2 * net->tile_pause), 1024);
         DN_HIP(hipMemsetAsync(net->abort_flag(), 0, sizeof(res) - sizeof(double), net->stream));
     }
     if (res.swept) net->last_schedule = DN_SCHED_WIDE_HIDDEN;   // some or all of the samples were not the block kernel's after all
@@ -1559,6 +1567,7 @@ dn_status dn_set_option(dn_net *net, const char *name, int64_t value)
     } else if (!strcmp(name, "batch_tiles")) {
         if (value < 0 || value > 3) return DN_ERR_INVALID_ARG;
         net->batch_tiles = (int)value;
+        net->tile_pause = net->tile_rest = 0;
     } else if (!strcmp(name, "merge_launches")) {
         if (value != 0 && value != 1) return DN_ERR_INVALID_ARG;
         net->merge_launches = (int)value;

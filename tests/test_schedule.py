@@ -220,3 +220,14 @@ def test_nets_by_which_tiles_are_tested(device):
         net = "net:%s:%s:%d" % ("-".join(map(str, widths)), "ce" if loss == CE else "mse", batch)
         took = device(256, net, "option:batch_tiles=2", "train:%d:%d:0.7" % (n, batch), names=True)[2][1] == "tile_epoch_kernel"
         assert took == (batch not in (225, 257)), (widths, batch)
+
+
+def test_tiles_rest_after_a_launch_that_was_kept_apart(device):
+    """8 passes, 16 after the next such launch, and so on; setting the option begins anew."""
+    tried = lambda rows: ["tile_epoch_kernel" in [k for k, _ in r[2]] for r in rows]
+    train = "train:96:24:0.9"
+    rows = device(256, "net:200-120-10:ce:24", "option:batch_tiles=3", *[train] * 60, "option:batch_tiles=2", train, train)
+    assert [i for i, t in enumerate(tried(rows[2:62])) if t] == [0, 9, 26, 59]
+    assert tried(rows[-2:]) == [True, True]
+    rows = device(256, "net:200-120-10:ce:24", "option:batch_tiles=3", *[train] * 2000)
+    assert [i for i, t in enumerate(tried(rows[2:])) if t] == [0, 9, 26, 59, 124, 253, 510, 1023]
