@@ -496,7 +496,8 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *   "online_slices"  1 (default): with "online_mode" 0, batch 1 on a net of two to four layers of at most 2048 units (the last
  *                    one 128) runs on as few workgroups as hold it in LDS, where that was measured to be faster: nets that would
  *                    take the general persistent kernel, and of those that the other options name the ones with more than
- *                    1024 weights on one wavefront (not in registers) or at most 24576 weights on two copies; 0: never; 2: wherever it fits
+ *                    1024 weights on one wavefront (not in registers) or at most 24576 weights on two copies; not where "online_min_tile"
+ *                    or "online_resident" has been set, which mean the general kernel; 0: never; 2: wherever it fits
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose
  *                    parameters fit in LDS, twice with momentum) runs on a single wavefront that keeps
  *                    the whole net in LDS -- in its registers, for two layers and momentum 0; 2: the

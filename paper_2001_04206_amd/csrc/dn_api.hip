@@ -680,6 +680,8 @@ bool takes_slices(dn_net *net, float mu, SliceGeom &g)
     if (!slice_geometry(net->n.data(), L, mu != 0.f, net->device_cus, g) || g.words * sizeof(unsigned long long) > net->lo.online_bytes) return false;
     if (net->online_slices == 2) return true;
     if (L == 2 && mu == 0.f) return false;
+    // (a caller that sets one of these means the general kernel)
+    if (net->online_min_tile != ON_DEFAULT_MIN_TILE || net->online_resident == 0) return false;
     int64_t weights = 0;
     for (int l = 1; l <= L; ++l) weights += (int64_t)net->n[l] * net->n[l - 1];
     TinyPlan tiny;

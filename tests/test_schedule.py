@@ -231,3 +231,13 @@ def test_tiles_rest_after_a_launch_that_was_kept_apart(device):
     assert tried(rows[-2:]) == [True, True]
     rows = device(256, "net:200-120-10:ce:24", "option:batch_tiles=3", *[train] * 2000)
     assert [i for i, t in enumerate(tried(rows[2:])) if t] == [0, 9, 26, 59, 124, 253, 510, 1023]
+
+
+@pytest.mark.parametrize("net,mu", [("37-116-21-61:ce", 0), ("838-953-33-75-87:ce", 0.9), ("1000-1000-33:ce", 0.9), ("28-16-32-188-19:ce", 0), ("36-54-15-32:ce", 0)])
+def test_options_of_the_general_kernel_leave_it_the_pass(device, net, mu):
+    """"online_min_tile" and "online_resident" say how the kernels that own rows run: the few workgroups do not take the pass then."""
+    train = "train:32:1:%g" % mu
+    rows = device(256, "net:%s:1" % net, train, "option:online_min_tile=64", train, "option:online_min_tile=4096", train, "option:online_resident=0", train,
+                  "option:online_slices=2", train, "option:online_slices=0", train, names=True)
+    ran = [r[1] for r in rows if r[2]]
+    assert [k == "slice_epoch_kernel" for k in ran] == [True, False, True, False, True, False] and ran[3] == ran[5]
