@@ -682,6 +682,8 @@ bool takes_slices(dn_net *net, float mu, SliceGeom &g)
     if (L == 2 && mu == 0.f) return false;
     // (a caller that sets one of these means the general kernel)
     if (net->online_min_tile != ON_DEFAULT_MIN_TILE || net->online_resident == 0) return false;
+    // (on a device of few compute units a net may fit no other persistent kernel: its passes stay launches, which wait for nobody)
+    if (g.P > 1 && !net->online_ok) return false;
     int64_t weights = 0;
     for (int l = 1; l <= L; ++l) weights += (int64_t)net->n[l] * net->n[l - 1];
     TinyPlan tiny;

@@ -241,3 +241,13 @@ def test_options_of_the_general_kernel_leave_it_the_pass(device, net, mu):
                   "option:online_slices=2", train, "option:online_slices=0", train, names=True)
     ran = [r[1] for r in rows if r[2]]
     assert [k == "slice_epoch_kernel" for k in ran] == [True, False, True, False, True, False] and ran[3] == ran[5]
+
+
+@pytest.mark.parametrize("units", [8, 32, 64])
+def test_passes_that_waited_for_nobody_still_do_not(device, units):
+    """A net that fits no kernel whose workgroups wait for one another but the few workgroups' one runs launch by launch; on one workgroup
+    it may run there."""
+    for net, mu in (("838-953-33-75-87:ce", 0.9), ("140-225-1480-3:ce", 0), ("567-79-8-1-63:ce", 0.9), ("37-116-21-61:ce", 0), ("192-68-7:ce", 0.9), ("128-96-40-10:ce", 0)):
+        rows = device(units, "net:%s:1" % net, "train:8:1:%g" % mu, "option:online_slices=0", "train:8:1:%g" % mu)
+        if rows[3][1] == dn.DN_SCHED_LAUNCHES:
+            assert [k for k in rows[1][2] if k[0].endswith("epoch_kernel")] in ([], [("slice_epoch_kernel", 1)]), (net, rows[1])
