@@ -667,12 +667,12 @@ dn_status run_slices(dn_net *net, const SliceGeom &g, const float *X, const int3
     return DN_OK;
 }
 
-// Whether a batch-1 pass runs on that kernel.  us a step, before / there (100 to 214 samples): against the general kernel, 66 nets of
-// three and four layers, or of two with momentum, on 1 to 128 workgroups, 4-32-643-7 16.4 / 14.6, 96-64-160-440-37 26 / 15, 37-116-21-61
-// 21.8 / 6.6, 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum 19.4 / 7.6: none slower.  Against the kernel with two
-// copies on one workgroup 28-16-32-188-19 16.7 / 9.3, 68-16-676-23 (27 thousand weights) 17.8 / 16.7, but 4-32-736-10 (31 thousand)
-// 13.6 / 15.6, 544-44-224-2 (34 thousand) 10.0 / 10.4, and on two and more workgroups 376-156-32-5 8.2 / 9.5, 868-544-896-640-3 13.8 / 17.8.  Against one wavefront 18-10-21-7-23 (698
-// weights) 7.2 / 7.4, 14-24-4-36-15 (1116) 8.7 / 7.7, 36-54-15-32 13.6 / 5.4.
+// Whether a batch-1 pass runs on that kernel.  us a step, before / there (200 and 214 samples): against the general kernel, 4-32-643-7 16.2 /
+// 14.6, 96-64-160-440-37 26 / 16, 37-116-21-61 21.5 / 6.8, with momentum 192-68-7 8.6 / 4.6, 1000-1000-33 19.0 / 7.2 and 1024-1024-1024-1024-10
+// 25.4 / 22.7.  Against the kernel with two copies on one workgroup 28-16-32-188-19 15.9 / 9.5, 532-44-20-9 (24468 weights) 7.6 / 7.6,
+// 68-16-676-23 (27 thousand) 17.8 / 15.8, but 4-32-736-10 (31 thousand) 13.5 / 15.8, 544-44-224-2 (34 thousand) 10.0 / 10.4, and on two and
+// more workgroups 376-156-32-5 8.1 / 9.6, 868-544-896-640-3 12.9 / 17.9.  Against one wavefront 18-10-21-7-23 (698 weights) 6.8 / 6.8,
+// 8-33-10-19-14 with momentum (1050) 8.1 / 7.8, 36-54-15-32 13.6 / 5.8.  560 nets drawn at random: none of the 419 taken is slower.
 bool takes_slices(dn_net *net, float mu, SliceGeom &g)
 {
     if (!net->slice_ready || !net->online_slices || net->online_mode != 0) return false;

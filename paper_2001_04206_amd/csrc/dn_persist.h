@@ -75,6 +75,30 @@ __device__ __forceinline__ float apply_update(float w, float g, float &v, float 
     return w + v;
 }
 
+// One more fruitless poll: true if this workgroup or another has given up.
+__device__ __forceinline__ bool give_up(int spins, int *abort_flag, volatile int *s_abort)
+{
+    if (spins > kSpinLimit) {
+        __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_abort = 1;
+        return true;
+    }
+    if ((spins & 255) == 0 && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+        *s_abort = 1;
+        return true;
+    }
+    return false;
+}
+
+// Sums over the rows of sixteen lanes of a wave; every lane gets its column's.
+__device__ __forceinline__ float add_rows(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
 // Polls `total` exchange words; word q lives at addr(q) and its value goes to sink(q, value).
 // Each thread keeps kPollBatch loads in flight and re-reads only the words that are not
 // yet stamped with `seq`.  On a timeout (or when another workgroup has already given up)
@@ -110,17 +134,7 @@ __device__ __forceinline__ void poll_words(int total, uint32_t seq, Addr addr, S
                 }
             }
             if (all) break;
-            ++spins;
-            if (spins > kSpinLimit) {
-                __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                *s_abort = 1;
-                break;
-            }
-            if ((spins & 255) == 0 &&
-                __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                *s_abort = 1;
-                break;
-            }
+            if (give_up(++spins, abort_flag, s_abort)) break;
         }
 #pragma unroll
         for (int u = 0; u < kPollBatch; ++u) {

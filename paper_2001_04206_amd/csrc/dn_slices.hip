@@ -20,39 +20,17 @@
 //
 // What bounds it: the chain of phases, each 0.5 to 1 us for its reads of LDS (80 to 150 cycles each, so several rows and pieces of
 // a row are in flight together) and some hundred instructions of one wave, and the exchanges.  us a step, the kernels above / this one:
-// 37-116-21-61 21.8 / 6.7, 96-64-160-440-37 26 / 15 (three workgroups), 192-68-7 with momentum 8.9 / 4.6, 1000-1000-33 with momentum
-// 19.4 / 7.6 (63).  Four waves instead of eight: 8.2 for the first net; sums over the parts of a column without reads in flight
+// 37-116-21-61 21.5 / 6.8, 96-64-160-440-37 26 / 16 (three workgroups), 192-68-7 with momentum 8.6 / 4.6, 1000-1000-33 with momentum
+// 19.0 / 7.2 (63).  Four waves instead of eight: 8.2 for the first net; sums over the parts of a column without reads in flight
 // together: 1 us more.  Where two copies of the inner weights fit (dn_twin.hip) and one workgroup does not, that kernel stays:
-// 1024-1024-1024-1024-10 13.6 there, 19.3 here.
+// 1024-1024-1024-1024-10 12.7 there, 19.7 here.
 #include "dn_persist.h"
 
 namespace dn {
 namespace {
 
-// One more fruitless poll: true if this workgroup or another has given up.
-__device__ __forceinline__ bool give_up(int spins, int *abort_flag, volatile int *s_abort)
-{
-    if (spins > kSpinLimit) {
-        __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *s_abort = 1;
-        return true;
-    }
-    if ((spins & 255) == 0 && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-        *s_abort = 1;
-        return true;
-    }
-    return false;
-}
-
 // Sum over the wave, in every lane.
-__device__ __forceinline__ float whole_wave_sum(float v)
-{
-    v = row16_sum(v);
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
-}
+__device__ __forceinline__ float whole_wave_sum(float v) { return add_rows(row16_sum(v)); }
 
 // LANES (sixteen or sixty-four) a row, RU rows and CU pieces of a row in flight together (a phase is a few such rounds, and a round
 // takes as long as its slowest read of LDS): fin(row, sum) on one lane per row.  Rows of `pitch` floats (a multiple of four, padding

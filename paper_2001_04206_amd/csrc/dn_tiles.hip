@@ -57,15 +57,6 @@ __device__ __forceinline__ int at(int m, int c)
 
 __device__ __forceinline__ v4f mfma(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// Sums over the rows of sixteen lanes of a wave; every lane gets its column's.
-__device__ __forceinline__ float add_rows(float v)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
-}
-
 __device__ __forceinline__ void put(u64 *ex, uint32_t byte, float v, uint32_t seq) { ll_store((u64 *)((char *)ex + byte), v, seq); }
 
 // Waits until all words whose bit in `need` is set carry `seq`, asking for all again until they do.  False: this or another
