@@ -16,8 +16,9 @@ namespace {
 // leave out terms of 2^-25 of the product and less, of either sign.  Three parts need no scale and no test of what fits beside the largest
 // (two f16 parts would take three products, but deltas span more than their range).  What is not finite, or rounds to infinity, spoils the
 // sum it enters, and a number below 2^-110 may have a last bit below 2^-133, bf16's smallest number (the instruction keeps subnormal numbers:
-// 2^-133 times 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found either when it has finished goes through its
-// pixels again with fp32 operands on the fp32 instruction.
+// 2^-133 times 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found the first when it has finished, or meets the
+// second on its way, goes through its pixels with fp32 operands on the fp32 instruction instead.  (The layer pair below 150 us, with one
+// such small number an image 191, 214 with the first pass finished, some 160 all in fp32.)
 // The bf16 instruction rounds its sums downwards.  So no long sum is formed on it: sixteen products at a time (six instructions, the
 // small terms first) begin at zero and are added to the long sum on the vector unit, to nearest; and pixels 4..7 and 12..15 of a row
 // enter with their sign turned and their sums are subtracted.  Errors of dW against 64 bits (1e-8; fp32 instruction / long sums on the
@@ -38,7 +39,7 @@ namespace {
 constexpr int DWI_THREADS = 512, DWI_TW = 16, DWI_XW = DWI_TW + 2, DWI_IMAGES = 8, DWI_OC = 64, DWI_IC = 32;
 constexpr int DWI_XROW = DWI_XW * DWI_IC * 16, DWI_XPART = 3 * DWI_XROW, DWI_DPART = DWI_TW * DWI_OC * 16;   // bytes
 constexpr int DWI_STAGE = 3 * (DWI_XPART + DWI_DPART), DWI_SUMS = 4 * 9 * 16 * 64 * 4;
-constexpr int DWI_LDS = DWI_SUMS > DWI_STAGE ? DWI_SUMS : DWI_STAGE;
+constexpr int DWI_LDS = DWI_SUMS > DWI_STAGE + 16 ? DWI_SUMS : DWI_STAGE + 16;
 
 typedef __bf16 v8b_t __attribute__((ext_vector_type(8)));
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
@@ -75,15 +76,18 @@ __device__ __forceinline__ void dwi_store(const float (&v)[8], char *at, int par
     }
 }
 
-// One workgroup's rows lo .. hi - 1: accumulators (added to) and the sums of the delta values this thread stages (set).
+// One workgroup's rows lo .. hi - 1: accumulators (added to) and the sums of the delta values this thread stages (set).  False, for
+// all threads: a row has a number too small for its parts, and it and the rows behind it have been left.
 template <bool FP32>
-__device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__restrict__ X, const float *__restrict__ delta, int ic0,
-                                         int oc0, int lo, int hi, int strips, char *lds, v16f_t (&acc)[9], float (&bsum)[2], unsigned &least)
+__device__ __forceinline__ bool dwi_rows(const ConvShape &s, const float *__restrict__ X, const float *__restrict__ delta, int ic0,
+                                         int oc0, int lo, int hi, int strips, char *lds, v16f_t (&acc)[9], float (&bsum)[2])
 {
     constexpr int PARTS = FP32 ? 2 : 3;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, idx = lane & 31, h = lane >> 5;
     const int o = wave & 1, q = wave >> 1;
     char *xs = lds, *ds = lds + 3 * DWI_XPART;
+    volatile int *too_small = reinterpret_cast<volatile int *>(lds + DWI_STAGE);
+    if (!FP32 && tid == 0) *too_small = 0;   // (read behind two barriers)
     const unsigned pix = (unsigned)(s.Ho * s.Wo), in = (unsigned)(s.H * s.W);
     // what this thread stages: delta of two output channels and the input of one channel at one column; the first wave also the two
     // last columns of the input
@@ -145,7 +149,7 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
             if (halo) load(x_base, x_off(h_at, r.y + 2, r.x0 + hp), hv);
         }
     };
-    auto put_x = [&](const Row &r, int y, float (&a)[8], float (&b)[8]) {
+    auto put_x = [&](const Row &r, int y, float (&a)[8], float (&b)[8], unsigned &least) {
         const bool row_on = y >= s.pad && y - s.pad < s.H;
         const int images = s.B - r.first, to = y % 3 * DWI_XROW;
         auto col_on = [&](int col) { return col >= s.pad && col - s.pad < s.W; };
@@ -159,6 +163,7 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
 
     Row r = row_of(lo);
     for (int n = lo; n < hi; ++n) {
+        unsigned least = ~0u;
         const bool fresh = n == lo || r.y == 0;   // the two upper tap rows are not in LDS, and nothing has been requested
         if (fresh) {
             images_from(r.first);
@@ -171,12 +176,12 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
         }
         __syncthreads();   // the previous row has been used
         if (fresh) {
-            put_x(r, r.y, dv[0], xv);
-            put_x(r, r.y + 1, dv[1], hv);
+            put_x(r, r.y, dv[0], xv, least);
+            put_x(r, r.y + 1, dv[1], hv, least);
 #pragma unroll
             for (int k = 0; k < 3; ++k) fetch(r, k);
         }
-        put_x(r, r.y + 2, xv, hv);
+        put_x(r, r.y + 2, xv, hv, least);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             blank(dv[k], d_on[k] && r.x0 + sp < s.Wo, s.B - r.first);
@@ -187,7 +192,9 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
             }
             dwi_store<FP32>(dv[k], d_to[k], DWI_DPART, least);
         }
+        if (!FP32 && least < DWI_LEAST) *too_small = 1;
         __syncthreads();
+        if (!FP32 && *too_small) return false;   // (set again behind the next barrier at the earliest)
         const int y = r.y;
         r = row_of(n + 1);
         if (n + 1 < hi && r.y > 0) {
@@ -228,6 +235,7 @@ __device__ __forceinline__ void dwi_rows(const ConvShape &s, const float *__rest
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    return true;
 }
 
 // grid: (input groups of 32 x output groups of 64, chunks).  part[chunk]: filter sums as [tap][oc][ic], then the bias sums.
@@ -242,7 +250,6 @@ __global__ __launch_bounds__(DWI_THREADS, 2) void conv_dw_images_kernel(ConvShap
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, idx = lane & 31, h = lane >> 5, o = wave & 1, q = wave >> 1;
     v16f_t acc[9];
     float bsum[2];
-    unsigned least = ~0u;
     // (0 + 2) - (1 + 3) of the four q: the upper two leave theirs in LDS, then q 0 and 1 exchange what the other one finishes
     auto at = [&](int w, int t, int i) { return reinterpret_cast<v4s_t *>(lds + (((w * 9 + t) * 4 + i) * 64 + lane) * 16); };
     auto put = [&](int w, int t) {
@@ -263,7 +270,7 @@ __global__ __launch_bounds__(DWI_THREADS, 2) void conv_dw_images_kernel(ConvShap
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
     };
-    auto merge = [&] {   // whether all sums are finite, and no number was too small for its parts
+    auto merge = [&] {   // whether all sums are finite
         __syncthreads();
         if (q >= 2) {
 #pragma unroll
@@ -288,13 +295,12 @@ __global__ __launch_bounds__(DWI_THREADS, 2) void conv_dw_images_kernel(ConvShap
                 for (int i = 0; i < 16; ++i) zero = fmaf(acc[t][i], 0.f, zero);   // NaN where a sum is not finite
             }
         }
-        return !__syncthreads_or(!(zero == 0.f) || least < DWI_LEAST);
+        return !__syncthreads_or(!(zero == 0.f));
     };
     clear();
-    dwi_rows<false>(s, X, delta, ic0, oc0, lo, hi, strips, lds, acc, bsum, least);
-    if (!merge()) {
+    if (!dwi_rows<false>(s, X, delta, ic0, oc0, lo, hi, strips, lds, acc, bsum) || !merge()) {
         clear();
-        dwi_rows<true>(s, X, delta, ic0, oc0, lo, hi, strips, lds, acc, bsum, least);
+        dwi_rows<true>(s, X, delta, ic0, oc0, lo, hi, strips, lds, acc, bsum);
         merge();
     }
     const size_t plane = (size_t)s.Cout * s.Cin, filt = 9 * plane;

@@ -110,6 +110,18 @@ def test_numbers_whose_last_bits_are_subnormal(exponent, last_bits, small):
     check(X, delta, 0, *run(X, delta, 0))
 
 
+@pytest.mark.parametrize("image,y,small", [(0, 0, "delta"), (60, 13, "X"), (120, 27, "delta"), (120, 29, "X")])
+def test_one_number_too_small(image, y, small):
+    """The workgroup that meets it begins again, wherever in its rows that is; all others keep their sums."""
+    announce("conv dW, image %d row %d of %s too small" % (image, y, small))
+    X, delta = make(*ODD)
+    (delta if small == "delta" else X)[image, 5, y, 7] = 2.0 ** -115
+    dW, db = run(X, delta, 0)
+    check(X, delta, 0, dW, db)
+    again = run(X, delta, 0)
+    assert torch.equal(dW, again[0]) and torch.equal(db, again[1])
+
+
 def test_not_finite():
     """A number that is not finite reaches the filters it meets, as it does on the fp32 instruction, and no other."""
     announce("conv dW not finite")
