@@ -84,7 +84,9 @@ const char *dn_status_string(dn_status s);
 
 /*
  * Bytes of device arena a net of these widths needs for batches up to
- * max_batch.  Returns 0 if the arguments are invalid (NULL, n_widths < 2, a
+ * max_batch: parameters, activations and the exchange regions of every kernel it could train on, whatever
+ * the options (of the tiled minibatch kernel 7 MB for 784-128-10 at max_batch 128, 18 MB for
+ * 1024-1024-1024-1024-10 at 2048).  Returns 0 if the arguments are invalid (NULL, n_widths < 2, a
  * width <= 0, max_batch <= 0, or sizes that overflow).
  */
 size_t dn_net_arena_bytes(const int32_t *widths, int32_t n_widths, int32_t max_batch);

@@ -17,8 +17,8 @@ namespace {
 // (two f16 parts would take three products, but deltas span more than their range).  What is not finite, or rounds to infinity, spoils the
 // sum it enters, and a number below 2^-110 may have a last bit below 2^-133, bf16's smallest number (the instruction keeps subnormal numbers:
 // 2^-133 times 2^97 is 2^-36, and a product of 2^-133 is one): a workgroup that has found the first when it has finished, or meets the
-// second on its way, goes through its pixels with fp32 operands on the fp32 instruction instead.  (The layer pair below 150 us, with one
-// such small number an image 191, 214 with the first pass finished, some 160 all in fp32.)
+// second on its way, goes through its pixels with fp32 operands on the fp32 instruction instead.  (The layer pair below 150 us; with one
+// such small number an image 191, 214 with the first pass finished, 181 all in fp32; deltas of 1e-35 195, 225 and 196.)
 // The bf16 instruction rounds its sums downwards.  So no long sum is formed on it: sixteen products at a time (six instructions, the
 // small terms first) begin at zero and are added to the long sum on the vector unit, to nearest; and pixels 4..7 and 12..15 of a row
 // enter with their sign turned and their sums are subtracted.  Errors of dW against 64 bits (1e-8; fp32 instruction / long sums on the
