@@ -496,8 +496,8 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *                    "online_wide" takes (of at most 131072 hidden units); 0: such passes take the other batch-1 schedules;
  *                    2 + k, for tests: launch k of such a pass is taken back as if its workgroups had been kept apart
  *   "online_slices"  1 (default): with "online_mode" 0, batch 1 on a net of two to four layers of at most 2048 units (the last
- *                    one 128) runs on as few workgroups as hold it in LDS, where that was measured to be faster: nets that would
- *                    take the general persistent kernel, and of those that the other options name the ones with more than
+ *                    one 128) runs on as few workgroups as hold it in LDS, where a pass of so many samples is expected to take less
+ *                    there: nets that would take the general persistent kernel, and of those that the other options name the ones with more than
  *                    1024 weights on one wavefront (not in registers) or at most 24576 weights on two copies; not where "online_min_tile"
  *                    or "online_resident" has been set, which mean the general kernel; 0: never; 2: wherever it fits
  *   "online_tiny"    1 (default): batch 1 on a net whose layers are all at most 64 wide (and whose

@@ -667,13 +667,56 @@ dn_status run_slices(dn_net *net, const SliceGeom &g, const float *X, const int3
     return DN_OK;
 }
 
+// Whether n_samples samples take less there than on the kernel that would run them otherwise.  Both take what a step costs and, once,
+// what a call costs; a call costs more here the more rows a workgroup has to load (34 us, and 0.035 a row), so short passes stay where they
+// were: one sample of 9-16-64-3 30 there / 44 here, of 124-748-476-504-10 67 / 84, of 40-8-1384-4 67 / 117.  Steps are estimated, the other kernel
+// on the low side, by what was measured on 450 nets (1 to 192 samples; the estimates fit to 8 % in the mean): a step on the general kernel
+// grows with the units of its busiest workgroups and, from three layers on, with the partial sums these add up (3-1322-410-38 with momentum
+// 246, 16-832-3 12.9), here with the rows of a workgroup (13 and 16.9).  On nets that the estimates had not seen, 1 to 120 samples: of
+// 2611 passes taken five are slower than 0.97 times the other kernel's, the slowest 0.94.
+bool slices_pay(const dn_net *net, const SliceGeom &g, int64_t n_samples, bool two_copies)
+{
+    const int L = net->L;
+    const int32_t *n = net->n.data();
+    double rows = 0, runs = 0;              // of a workgroup here: rows of the hidden layers, runs of 64 weights in them
+    double units = 0, far = 0, partial = 0; // there: units of a workgroup, the same by the 256 inputs, partial sums it adds up
+    bool many = false;                      // there: several workgroups
+    int owned_below = 0;
+    for (int l = 1; l < L; ++l) {
+        rows += g.per[l];
+        runs += (double)g.per[l] * ((n[l - 1] + 63) / 64);
+        const int owned = std::min(n[l], std::max((n[l] + 255) / 256, (4095 + n[l - 1]) / n[l - 1])), owners = (n[l] + owned - 1) / owned;
+        units += owned;
+        far += (double)owned * ((n[l - 1] + 255) / 256);
+        partial += (double)owners * owned_below;
+        many = many || owners > 1;
+        owned_below = owned;
+    }
+    const double outputs = n[L], deep = L - 3, spread = g.P > 1;
+    double there, here, call;
+    if (two_copies) {
+        there = 0.88 * (4.3 + 2.9 * deep + (many ? 2.0 : 0.0) + 0.04 * units + 0.036 * outputs);
+        here = 4.2 + 1.5 * deep + 0.014 * rows + 0.0086 * outputs + 0.0039 * n[0];
+        call = 0.5 + 0.028 * runs;
+    } else if (L == 2) {
+        there = 0.9 * (5.0 + (many ? 1.9 : 0.0) + 0.0285 * far + 0.166 * outputs);
+        here = 3.4 + 1.1 * spread + 0.0157 * rows + 0.027 * outputs;
+        call = 0.039 * runs - 5.3;
+    } else {
+        there = 0.9 * (11.5 + 6.3 * deep + 0.031 * far + 0.0012 * partial + 0.12 * outputs);
+        here = 5.3 + 1.1 * deep + 4.5 * spread * (L - 2) + 0.012 * rows + 0.012 * outputs;
+        call = 0.039 * runs - 5.3;
+    }
+    return (double)n_samples * (there - here) > call;
+}
+
 // Whether a batch-1 pass runs on that kernel.  us a step, before / there (200 and 214 samples): against the general kernel, 4-32-643-7 16.2 /
 // 14.6, 96-64-160-440-37 26 / 16, 37-116-21-61 21.5 / 6.8, with momentum 192-68-7 8.6 / 4.6, 1000-1000-33 19.0 / 7.2 and 1024-1024-1024-1024-10
 // 25.4 / 22.7.  Against the kernel with two copies on one workgroup 28-16-32-188-19 15.9 / 9.5, 532-44-20-9 (24468 weights) 7.6 / 7.6,
 // 68-16-676-23 (27 thousand) 17.8 / 15.8, but 4-32-736-10 (31 thousand) 13.5 / 15.8, 544-44-224-2 (34 thousand) 10.0 / 10.4, and on two and
 // more workgroups 376-156-32-5 8.1 / 9.6, 868-544-896-640-3 12.9 / 17.9.  Against one wavefront 18-10-21-7-23 (698 weights) 6.8 / 6.8,
-// 8-33-10-19-14 with momentum (1050) 8.1 / 7.8, 36-54-15-32 13.6 / 5.8.  560 nets drawn at random: none of the 419 taken is slower.
-bool takes_slices(dn_net *net, float mu, SliceGeom &g)
+// 8-33-10-19-14 with momentum (1050) 8.1 / 7.8, 36-54-15-32 13.6 / 5.8.
+bool takes_slices(dn_net *net, float mu, int64_t n_samples, SliceGeom &g)
 {
     if (!net->slice_ready || !net->online_slices || net->online_mode != 0) return false;
     const int L = net->L;
@@ -686,13 +729,16 @@ bool takes_slices(dn_net *net, float mu, SliceGeom &g)
     if (g.P > 1 && !net->online_ok) return false;
     int64_t weights = 0;
     for (int l = 1; l <= L; ++l) weights += (int64_t)net->n[l] * net->n[l - 1];
+    // One wavefront: a step gains by the net's size, a call costs up to 16 us more (54 nets of 1050 to 7200 weights, the first faster
+    // pass: 1050 64 samples, 1350 8, 2000 6, 2400 3 or 4, 2800 2 or 3, 3600 one).
     TinyPlan tiny;
-    if (one_wave(net, mu, tiny)) return weights > 1024;
+    if (one_wave(net, mu, tiny)) return weights > 1024 && ((double)n_samples + 1.2) * (double)(weights - 900) > 6300.0;
     TwinGeom tg;
     if (mu == 0.f && net->online_twin && net->twin_ready && twin_geometry(net->n.data(), L, net->online_min_tile, tg) && tg.grid <= net->device_cus)
-        return g.P == 1 && weights <= 24576;
+        return g.P == 1 && weights <= 24576 && slices_pay(net, g, n_samples, true);
     WideGeom wg;
-    return !(net->online_wide && net->wide_ok && wide_geometry(net->n.data(), L, net->device_cus, mu != 0.f, wg));
+    if (net->online_wide && net->wide_ok && wide_geometry(net->n.data(), L, net->device_cus, mu != 0.f, wg)) return false;
+    return !net->online_ok || slices_pay(net, g, n_samples, false);
 }
 
 // A whole batch-1 epoch on the persistent kernel that suits the net.
@@ -700,7 +746,7 @@ dn_status run_online(dn_net *net, const float *X, const int32_t *labels, int64_t
                      bool blocks, bool timing)
 {
     SliceGeom slices;
-    if (takes_slices(net, mu, slices)) {
+    if (takes_slices(net, mu, n_samples, slices)) {
         net->last_schedule = DN_SCHED_SLICES;
         return run_slices(net, slices, X, labels, n_samples, lr, mu, timing);
     }
@@ -1324,7 +1370,7 @@ dn_status dn_train_epoch(dn_net *net, const float *X_dev, const int32_t *labels_
     if (batch > 1 && net->tile_rest > 0) --net->tile_rest;
     int64_t first = 0;    // samples that are done
     SliceGeom slices;
-    const bool few = batch == 1 && takes_slices(net, momentum, slices);
+    const bool few = batch == 1 && takes_slices(net, momentum, n_samples, slices);
     const bool direct = batch == 1 && net->online_mode != 1 && online_fit && net->result && !few && one_wave(net, momentum, tiny);
     // what the kernels of a whole pass leave beside the parameters: off_scalars
     struct { double acc; int aborted, swept; double hits; unsigned arrived; int settled; } res{};

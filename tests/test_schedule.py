@@ -243,6 +243,17 @@ def test_options_of_the_general_kernel_leave_it_the_pass(device, net, mu):
     assert [k == "slice_epoch_kernel" for k in ran] == [True, False, True, False, True, False] and ran[3] == ran[5]
 
 
+# net, momentum, samples: passes of few samples, whose time is what a call costs, and nets whose steps the other kernel takes faster
+@pytest.mark.parametrize("net,mu,n,few", [
+    ("9-16-64-3:ce", 0, 1, False), ("9-16-64-3:ce", 0, 200, True), ("36-54-15-32:ce", 0, 1, False), ("36-54-15-32:ce", 0, 2, True),
+    ("124-748-476-504-10:ce", 0, 1, False), ("124-748-476-504-10:ce", 0, 8, True), ("3-1322-410-38:ce", 0.9, 1, True), ("4-32-643-7:ce", 0, 4, False),
+    ("40-8-1384-4:ce", 0, 40, False), ("4-932-16-8:ce", 0, 1, False), ("4-932-16-8:ce", 0, 40, True), ("16-832-3:ce", 0.9, 10000, False),
+    ("192-68-7:ce", 0.9, 1, True), ("4-1952-3:ce", 0.9, 10000, False)])
+def test_short_passes_stay_where_they_were(device, net, mu, n, few):
+    row = device(256, "net:%s:1" % net, "train:%d:1:%g" % (n, mu))[1]
+    assert row[0] == dn.DN_OK and (row[1] == dn.DN_SCHED_SLICES) == few, row
+
+
 @pytest.mark.parametrize("units", [8, 32, 64])
 def test_passes_that_waited_for_nobody_still_do_not(device, units):
     """A net that fits no kernel whose workgroups wait for one another but the few workgroups' one runs launch by launch; on one workgroup
