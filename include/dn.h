@@ -467,7 +467,7 @@ dn_status dn_kernel_flops(dn_net *net, int32_t kernel_class, double *flops);
  *   "batch_tiles"    1 (default): with "batch_mode" 0 and "online_min_tile" as it comes, minibatches of 2 to 256 samples over nets
  *                    whose layers are at most 256 square tiles of 32 or of 64 (the last one, if it has at most 64 outputs,
  *                    not counted; else at most 1024) and fit in LDS that way run on a persistent kernel that keeps a tile of
- *                    every layer per workgroup, where a step is expected to take less there than on the other schedules; any
+ *                    every layer per workgroup, where the pass is expected to take less there than on the other schedules; any
  *                    widths, with or without momentum; 0: never; 2: wherever it fits; 3, for tests: as 2, and the launch is taken
  *                    back as if its workgroups had been kept apart.  After a launch that was taken back the net's next 8
  *                    minibatch passes do without (16 if the next launch is taken back too, up to 1024; setting the option ends that)

@@ -968,8 +968,8 @@ dn_status run_deep_persistent(dn_net *net, const float *X, const int32_t *labels
 }
 
 // Microseconds a step takes on the schedules that a minibatch pass would run on without tiles: the low side of what was measured, so
-// that tiles are not taken where they could lose.  The kernel for one and two layers (62 nets of 64 and more inputs, 20 %; 28 nets of
-// fewer, which cost it more): with the first layer's rows in few workgroups 784-128-10 batch 128 18.6 and 1288-19-4 batch 4 10.1,
+// that tiles are not taken where they could lose.  The kernel for one and two layers (62 nets of 64 and more inputs, 20 %; 61 nets of
+// fewer, which cost it more, the fewer the more: 24-888-4 batch 43 22, 8-512-6 batch 109 44): with the first layer's rows in few workgroups 784-128-10 batch 128 18.6 and 1288-19-4 batch 4 10.1,
 // but 64-106-3 batch 12 21, 44-424-127 batch 3 72.  Launches, 124 nets, 15 %: 12.7 a layer for the launches themselves, then by flops,
 // parameters read and written, and a launch for a last layer of more than 16 outputs.
 float step_us_without_tiles(const dn_net *net, int batch)
@@ -980,21 +980,42 @@ float step_us_without_tiles(const dn_net *net, int batch)
         if (n0 >= 64)
             return 0.85f * (9.4f + 0.079f * (float)batch + 0.0116f * (float)n1 + 0.146f * (float)nL + 0.0144f * (float)((n1 + per - 1) / per) +
                             4.27e-5f * (float)batch * (float)n0);
-        return 0.8f * (21.9f + 0.017f * (float)n1 + 0.0184f * (float)(per * nL));
+        return (n0 < 20 ? 0.8f : 0.62f) * (21.9f + 0.017f * (float)n1 + 0.0184f * (float)(per * nL));
     }
     double weights = 0.0;
     for (int l = 1; l <= L; ++l) weights += (double)net->n[l] * (double)net->n[l - 1];
     return 0.88f * (11.4f * (float)L + (float)(weights * (6e-8 * batch + 3e-6)) + (nL > 16 ? 3.f : 0.f));
 }
 
+// A net of one layer: microseconds that a step on tiles takes less than on batch_epoch_kernel, the low side.  There it has no exchange
+// but the outputs', here the workgroups of a row of tiles wait for one another and share the samples among them: nets of few inputs and
+// outputs lose (us a step, batch_epoch_kernel / tiles: 16-21 batch 234 14 / 78, 304-3 batch 157 7.2 / 10.9, 12-3 batch 19 5.8 / 9.3), many
+// outputs gain (392-112 batch 19 37 / 6.7, 480-27 batch 12 10 / 6.0).  121 nets, both estimates to 12 and 5 % in the mean.
+float one_layer_gain(const dn_net *net, int batch, const TileGeom &g)
+{
+    auto up = [](int a, int b) { return (a + b - 1) / b; };
+    const int n0 = net->n[0], nL = net->n[1], samples = up(batch, g.grid), out16 = up(nL, 16);
+    const float there = 4.9f + 0.0212f * (float)batch + 0.0856f * (float)nL + 0.00086f * (float)batch * (float)nL + 1.27e-4f * (float)n0 * (float)nL;
+    const float here = 3.3f + 1.3f * (float)up(samples, 8) + 0.92f * (float)(up(samples * out16, 16) * up(up(g.C[1], 4), 4)) +
+                       0.48f * (float)(g.rows / 16) * (float)g.T / 32.f;
+    return 0.83f * there - here;
+}
+
 // Whether a minibatch pass runs on the kernel that cuts every layer into tiles.  (A caller that sets "online_min_tile" means the
-// kernels that own rows.)
+// kernels that own rows.)  A call there costs 3 to 7 us more than one on batch_epoch_kernel, so a pass of few steps may stay on that: us a
+// call of 1, 2, 4 and 8 steps, batch_epoch_kernel / tiles: 784-128-10 batch 128 53.7 / 58.5, 72.4 / 75.3, 109 / 107, 186 / 172.
+// (Launches and the kernel for deeper nets lose with one step already: 32 samples of 1024-1024-1024-1024-10 at batch 32 115 / 95.)
 bool takes_tiles(const dn_net *net, int64_t n_samples, int batch, TileGeom &g)
 {
     if (!net->tile_ready || !net->batch_tiles || net->online_min_tile != ON_DEFAULT_MIN_TILE || batch < 2) return false;
     if ((n_samples + batch - 1) / batch > ((int64_t)1 << 31) / (2 * net->L)) return false;   // (phases are counted in 32 bits)
-    return tile_geometry(net->n.data(), net->L, batch, net->device_cus, g) && g.words * sizeof(unsigned long long) <= net->lo.tile_bytes &&
-           (net->batch_tiles >= 2 || g.step_us < step_us_without_tiles(net, batch));
+    if (!tile_geometry(net->n.data(), net->L, batch, net->device_cus, g) || g.words * sizeof(unsigned long long) > net->lo.tile_bytes) return false;
+    if (net->batch_tiles >= 2) return true;
+    const float steps = (float)((n_samples + batch - 1) / batch);
+    const bool rows = net->batch_ok && batch_pays(net, batch);   // batch_epoch_kernel runs the pass without tiles
+    if (rows && net->L == 1) return one_layer_gain(net, batch, g) * steps > 3.f;
+    const float without = step_us_without_tiles(net, batch);
+    return g.step_us < without && (!rows || (1.18f * without - g.step_us) * steps > 8.f);
 }
 
 // A whole minibatch epoch in one launch of that kernel.

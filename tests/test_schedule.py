@@ -254,6 +254,14 @@ def test_short_passes_stay_where_they_were(device, net, mu, n, few):
     assert row[0] == dn.DN_OK and (row[1] == dn.DN_SCHED_SLICES) == few, row
 
 
+@pytest.mark.parametrize("net,batch,steps,tiles", [
+    ("784-128-10:ce", 128, 1, False), ("784-128-10:ce", 128, 8, True), ("1024-1024-1024-1024-10:ce", 32, 1, True), ("16-21:ce", 234, 100, False),
+    ("304-3:ce", 157, 100, False), ("12-3:ce", 19, 100, False), ("392-112:ce", 19, 4, True), ("24-888-4:ce", 43, 100, False), ("24-416-11:ce", 10, 4, True)])
+def test_few_steps_and_narrow_nets_without_tiles(device, net, batch, steps, tiles):
+    row = device(256, "net:%s:%d" % (net, batch), "train:%d:%d:0.9" % (steps * batch, batch), names=True)[1]
+    assert row[0] == dn.DN_OK and (row[1] == "tile_epoch_kernel") == tiles, row
+
+
 @pytest.mark.parametrize("units", [8, 32, 64])
 def test_passes_that_waited_for_nobody_still_do_not(device, units):
     """A net that fits no kernel whose workgroups wait for one another but the few workgroups' one runs launch by launch; on one workgroup
